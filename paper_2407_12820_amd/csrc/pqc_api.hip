@@ -831,8 +831,15 @@ int pqc_block_stats(const pqc_config* cfg, const int32_t* idx, int64_t n_idx, in
   if (!idx || !counts || n_idx < 0 || block_tokens < 1 || block_tokens >= kCountBins) return PQC_EINVAL;
   const int nb = (p.s.N + block_tokens - 1) / block_tokens;
   if (k_cache < 0 || k_cache > nb || (k_cache > 0 && !blocks)) return PQC_EINVAL;
-  hipLaunchKernelGGL(block_stats_kernel, dim3((unsigned)(p.s.B * p.s.Hkv)), dim3(1024), 0, static_cast<hipStream_t>(stream),
-                     idx, (long long)n_idx, p.s.N, (int)block_tokens, nb, (int)k_cache, counts, blocks);
+  const unsigned long long inv_bt = ((1ull << kBlockShift) + (unsigned)block_tokens - 1) / (unsigned)block_tokens;
+  const dim3 grid((unsigned)(p.s.B * p.s.Hkv));
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (nb <= kLdsBlocks)
+    hipLaunchKernelGGL(block_stats_kernel<true>, grid, dim3(1024), (size_t)nb * sizeof(int), st, idx, (long long)n_idx, p.s.N, inv_bt, nb,
+                       (int)k_cache, counts, blocks);
+  else
+    hipLaunchKernelGGL(block_stats_kernel<false>, grid, dim3(1024), 0, st, idx, (long long)n_idx, p.s.N, inv_bt, nb, (int)k_cache, counts,
+                       blocks);
   return hipGetLastError() == hipSuccess ? PQC_OK : PQC_EHIP;
 }
 

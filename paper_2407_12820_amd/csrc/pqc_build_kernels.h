@@ -375,29 +375,47 @@ __global__ __launch_bounds__(256) void pq_mean_kernel(BuildShape s, const unsign
 
 // ------------------------------------------------------------ block statistics
 // Section 3.4: the block-level cache is refreshed with the k_cache blocks that hold the
-// most retrieved tokens.  One workgroup per unit: counts per block (global atomics, read
-// back through the L2 with returning atomics), a histogram of the count values (a count
-// never exceeds the block size when the listed tokens are distinct), the cut c* and the
-// number of blocks to admit at the cut, then the blocks in the order in which the cache
-// refresh serves them: fullest first, the lower block number first among equal counts.  A
-// block's place is (blocks with a larger count) + (blocks before it with the same count);
-// the second term comes from a counter per count value that the waves of a chunk of 1024
-// blocks advance one after the other, lanes with equal counts being ranked inside a wave
-// by ballots.
+// most retrieved tokens.  One workgroup per unit: counts per block, a histogram of the
+// count values (a count never exceeds the block size when the listed tokens are distinct),
+// the cut c* and the number of blocks to admit at the cut, then the blocks in the order in
+// which the cache refresh serves them: fullest first, the lower block number first among
+// equal counts.
+//
+// What bounds it: latency (13175 listed tokens of a unit are 52 KB).  The list is read eight
+// entries per thread at a time; lists are mostly ascending, so the entries of a block sit in
+// neighbouring lanes and only the first lane of a run of equal blocks adds, the run's length:
+// an LDS atomic takes about a clock per lane when the lanes meet in one address.  With
+// LDS_COUNTS (up to kLdsBlocks blocks) the counts live in LDS; beyond that they are counted in
+// the output array with global atomics and read back through the L2, as was done for every
+// size before: 120 us at 131072 tokens in blocks of 128, 13175 listed (8 units), against
+// 8.2 us now.
+// The blocks above the cut are few (fewer than k_cache): up to kRankBlocks of them are ranked by
+// counting larger (count, lower block number) keys; beyond that a block's place is (blocks with
+// a larger count) + (blocks before it with the same count), the second term coming from a counter
+// per count value that the waves of a chunk of 1024 blocks advance one after the other, lanes
+// with equal counts being ranked inside a wave by ballots (quadratic ranking would take longer).
 constexpr int kCountBins = 2048;
-__global__ __launch_bounds__(1024) void block_stats_kernel(const int* __restrict__ idx, long long n_idx, int N, int bt,
+constexpr int kLdsBlocks = 16384;  // 64 KB of counts beside the 25 KB the selection needs
+constexpr int kRankBlocks = 256;   // four keys per step and wave: 64 steps
+constexpr int kBlockShift = 40;    // token / block size as a product: exact for tokens < 2^22 and block sizes < 2^11
+template <bool LDS_COUNTS>
+__global__ __launch_bounds__(1024) void block_stats_kernel(const int* __restrict__ idx, long long n_idx, int N,
+                                                           unsigned long long inv_bt /* ceil(2^kBlockShift / block size) */,
                                                            int nb, int k_cache, int* __restrict__ counts,
                                                            int* __restrict__ blocks) {
-  constexpr int NT = 1024, NW = NT / 64;
+  constexpr int NT = 1024, NW = NT / 64, U = 8;
+  extern __shared__ int lcnt[];  // [nb] with LDS_COUNTS
   __shared__ unsigned hist[kCountBins];
   __shared__ int above[kCountBins];  // blocks with a larger count
   __shared__ int run[kCountBins];    // blocks with this count placed so far
+  __shared__ unsigned long long keys[kRankBlocks];  // (count, inverted block number): larger is served first
   __shared__ int scan_sm[2 * NW + 1];
-  __shared__ int res[2];
+  __shared__ int res[3];
   __shared__ int any_sm;
   const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   int* cu = counts + (size_t)u * nb;
-  for (int i = tid; i < nb; i += NT) cu[i] = 0;
+  int* cnt = LDS_COUNTS ? lcnt : cu;
+  for (int i = tid; i < nb; i += NT) cnt[i] = 0;
   for (int i = tid; i < kCountBins; i += NT) {
     hist[i] = 0u;
     run[i] = 0;
@@ -405,17 +423,40 @@ __global__ __launch_bounds__(1024) void block_stats_kernel(const int* __restrict
   if (tid == 0) {
     res[0] = kCountBins;  // cut (no block reaches it when k_cache == 0)
     res[1] = 0;           // blocks above the cut
+    res[2] = 0;           // of them collected so far
   }
-  __threadfence();
+  if constexpr (!LDS_COUNTS) __threadfence();
   __syncthreads();
   const int* lst = idx + (size_t)u * n_idx;
-  for (long long i = tid; i < n_idx; i += NT) {
-    const int t = lst[i];
-    if (t >= 0 && t < N) atomicAdd(&cu[t / bt], 1);
+  for (long long i0 = 0; i0 < n_idx; i0 += (long long)U * NT) {
+    int t[U];
+#pragma unroll
+    for (int x = 0; x < U; ++x) {
+      const long long i = i0 + x * NT + tid;
+      t[x] = lst[i < n_idx ? i : n_idx - 1];
+    }
+    PQC_LOADS_ISSUED();
+#pragma unroll
+    for (int x = 0; x < U; ++x) {
+      const bool ok = i0 + x * NT + tid < n_idx && t[x] >= 0 && t[x] < N;
+      const int blk = ok ? (int)(((unsigned long long)(unsigned)t[x] * inv_bt) >> kBlockShift) : -1;
+      const int prev = dpp_i<0x138>(-2, blk);  // the lane below (wave_shr:1)
+      const unsigned long long heads = __ballot(blk != prev);
+      if (blk >= 0 && blk != prev) {
+        const unsigned long long next = (heads >> lane) >> 1;
+        atomicAdd(&cnt[blk], next ? __ffsll((long long)next) : 64 - lane);
+      }
+    }
   }
-  __threadfence();
+  if constexpr (!LDS_COUNTS) __threadfence();
   __syncthreads();
-  for (int i = tid; i < nb; i += NT) atomicAdd(&hist[min(atomicAdd(&cu[i], 0), kCountBins - 1)], 1u);
+  auto count_of = [&](int i) -> int { return LDS_COUNTS ? lcnt[i] : atomicAdd(&cu[i], 0); };
+  for (int i = tid; i < nb; i += NT) {
+    const int c = count_of(i);
+    if constexpr (LDS_COUNTS) cu[i] = c;
+    if (k_cache > 0) atomicAdd(&hist[min(c, kCountBins - 1)], 1u);
+  }
+  if (k_cache == 0) return;  // uniform
   __syncthreads();
   // thread tid owns count values kCountBins-1-2*tid and kCountBins-2-2*tid (descending)
   const int h0 = (int)hist[kCountBins - 1 - 2 * tid], h1 = (int)hist[kCountBins - 2 - 2 * tid];
@@ -423,26 +464,33 @@ __global__ __launch_bounds__(1024) void block_stats_kernel(const int* __restrict
   int cum = block_exclusive_scan<NT>(h0 + h1, &total, scan_sm);
   above[kCountBins - 1 - 2 * tid] = cum;
   above[kCountBins - 2 - 2 * tid] = cum + h0;
-  if (k_cache > 0 && cum < k_cache && cum + h0 >= k_cache) {
+  if (cum < k_cache && cum + h0 >= k_cache) {
     res[0] = kCountBins - 1 - 2 * tid;
     res[1] = cum;
-  } else if (k_cache > 0 && cum + h0 < k_cache && cum + h0 + h1 >= k_cache) {
+  } else if (cum + h0 < k_cache && cum + h0 + h1 >= k_cache) {
     res[0] = kCountBins - 2 - 2 * tid;
     res[1] = cum + h0;
   }
   __syncthreads();
   const int cut = res[0], n_above = res[1], need = k_cache - n_above;
+  const bool ranked = n_above <= kRankBlocks;  // uniform
   int* out = blocks + (size_t)u * k_cache;
   int carry_t = 0;
-  for (int i0 = 0; i0 < (k_cache > 0 ? nb : 0); i0 += NT) {
+  for (int i0 = 0; i0 < nb; i0 += NT) {
     const int i = i0 + tid;
-    const int c = i < nb ? min(atomicAdd(&cu[i], 0), kCountBins - 1) : -1;
+    const int c = i < nb ? min(count_of(i), kCountBins - 1) : -1;
     const bool a = c > cut;
     // blocks at the cut: the lowest-numbered `need` of them, behind all blocks above the cut
-    int tt;
-    const int pt = block_exclusive_scan<NT>(c == cut ? 1 : 0, &tt, scan_sm);
-    if (c == cut && carry_t + pt < need) out[n_above + carry_t + pt] = i;
-    carry_t += tt;
+    if (carry_t < need) {  // uniform
+      int tt;
+      const int pt = block_exclusive_scan<NT>(c == cut ? 1 : 0, &tt, scan_sm);
+      if (c == cut && carry_t + pt < need) out[n_above + carry_t + pt] = i;
+      carry_t += tt;
+    }
+    if (ranked) {
+      if (a) keys[atomicAdd(&res[2], 1)] = ((unsigned long long)c << 32) | (0xffffffffu - (unsigned)i);
+      continue;
+    }
     // blocks above the cut (chunks without any skip the ordered part)
     if (tid == 0) any_sm = 0;
     __syncthreads();
@@ -475,6 +523,21 @@ __global__ __launch_bounds__(1024) void block_stats_kernel(const int* __restrict
         __syncthreads();
       }
       if (a) out[above[c] + base + rank_w] = i;
+    }
+  }
+  if (ranked) {
+    __syncthreads();
+    if (tid < n_above) {
+      const unsigned long long mine = keys[tid];
+      int rank = 0;
+      for (int j0 = 0; j0 < n_above; j0 += 4) {
+        unsigned long long o[4];
+#pragma unroll
+        for (int y = 0; y < 4; ++y) o[y] = keys[min(j0 + y, n_above - 1)];
+#pragma unroll
+        for (int y = 0; y < 4; ++y) rank += (j0 + y < n_above && o[y] > mine) ? 1 : 0;
+      }
+      out[rank] = (int)(0xffffffffu - (unsigned)mine);
     }
   }
 }

@@ -253,6 +253,33 @@ def test_block_stats_match_oracle(pqc, block, k_cache):
     np.testing.assert_array_equal(blocks.cpu().numpy(), want_b)  # same blocks in the same order: fullest first, lower index on ties
 
 
+# the edges of the count kernel: blocks whose counts still fit LDS and one more, more blocks above the cut than are ranked by
+# counting, an unsorted list (no runs of equal blocks), a list with entries that are no tokens
+@pytest.mark.parametrize("n,n_idx,block,k_cache,order", [
+    (16384, 3000, 1, 2900, "sorted"), (16385, 3000, 1, 2900, "sorted"), (16385, 3000, 1, 17, "shuffled"), (40000, 20000, 64, 300, "shuffled"),
+    (40000, 20000, 64, 200, "sorted"), (40000, 1, 64, 3, "sorted"), (5000, 4999, 2047, 3, "shuffled"), (9000, 1025, 7, 100, "foreign"),
+])
+def test_block_stats_edges(pqc, n, n_idx, block, k_cache, order):
+    w = wl.Workload(name="blocks", batch=1, n_q_heads=4, n_kv_heads=2, head_dim=128, n_tokens=n, pq_m=2, pq_centroids=16,
+                    topk=100, n_init=4, n_local=64, dtype="bf16", kmeans_iters=1, recipe="plain")
+    print(f"[case] block stats n={n} n_idx={n_idx} block={block} k_cache={k_cache} {order}", flush=True)
+    rng = np.random.default_rng(n + n_idx + block)
+    rows = []
+    for _ in range(2):  # counts grow towards the end of the range, so that many differ
+        r = rng.choice(n, size=n_idx, replace=False, p=(np.arange(n) + 1.0) / (n * (n + 1.0) / 2.0))
+        rows.append(r if order == "shuffled" else np.sort(r))
+    idx = np.stack(rows).reshape(1, 2, -1).astype(np.int32)
+    given = idx.copy()
+    if order == "foreign":
+        given[0, :, ::5] = np.where(np.arange(given[0, :, ::5].shape[-1]) % 2, -3, n + 2)
+        idx = np.delete(idx, np.s_[::5], axis=-1)
+    counts, blocks = pqc.block_stats(w, torch.from_numpy(given).to(DEV), block, k_cache)
+    torch.cuda.synchronize()
+    want_c = oracle.block_counts(np.ascontiguousarray(idx), n, block)
+    np.testing.assert_array_equal(counts.cpu().numpy(), want_c)
+    np.testing.assert_array_equal(blocks.cpu().numpy(), oracle.block_topk(want_c, k_cache))
+
+
 @pytest.mark.parametrize("policy", ["lru", "lfu"])
 @pytest.mark.parametrize("n_slots,k_cache,block", [(32, 32, 128), (1, 1, 128), (5, 3, 64), (4, 9, 256), (16, 0, 128),
                                                    (1024, 200, 16), (100, 1024, 4)])
