@@ -108,6 +108,29 @@ def make_config(w: Workload, softmax_scale: float = 0.0, capacity: int = 0) -> C
                   w.n_init, w.n_local, PQC_F32 if w.dtype == "f32" else PQC_BF16, softmax_scale, capacity)
 
 
+# What a call costs before its first launch is host time, and the small steps and the block cache's two calls are shorter
+# than it: configurations are kept with their (immutable) workload, and the current stream is asked for as a number.
+_configs = {}  # (id of the workload, capacity) -> (the workload, byref of its configuration); emptied when it has grown
+
+
+def _config(w: Workload, capacity: int = 0):
+    """byref of the workload's configuration with the default softmax scale; never changed afterwards."""
+    kept = _configs.get((id(w), capacity))
+    if kept is None or kept[0] is not w:
+        if len(_configs) >= 256:
+            _configs.clear()
+        kept = _configs[(id(w), capacity)] = (w, C.byref(make_config(w, capacity=capacity)))
+    return kept[1]
+
+
+def _stream_of(stream, device: torch.device) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    if device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
 class PQCacheError(RuntimeError):
     def __init__(self, status: int, what: str, hip: int = 0):
         self.status = status
@@ -135,12 +158,31 @@ class PQCache:
         if rc != 0:
             raise PQCacheError(rc, "pqc_create")
         self.kv_torch = torch.float32 if w.dtype == "f32" else torch.bfloat16
+        self._lay_out()
+
+    def _lay_out(self) -> None:
+        """Shapes of the current length, and (dtype, shape) of the tensors of a decode call in the order of its arguments."""
+        w = self.w
+        self._shapes = {
+            "q": (w.batch, w.n_q_heads, w.head_dim),
+            "centroids": (w.batch, w.n_kv_heads, w.pq_m, w.pq_centroids, w.sub_dim),
+            "codes": (w.batch, w.n_kv_heads, self.capacity, w.pq_m),
+            "kv": (w.batch, w.n_kv_heads, self.capacity, w.head_dim),
+            "idx": (w.batch, w.n_kv_heads, w.n_selected),
+            "out": (w.batch, w.n_q_heads, w.head_dim),
+            "table": (w.batch, w.n_kv_heads, w.pq_m, w.pq_centroids),
+            "scores": (w.batch, w.n_kv_heads, w.n_tokens),
+        }
+        sh, kv = self._shapes, self.kv_torch
+        self._decode_specs = ((kv, sh["q"]), (torch.float32, sh["centroids"]), (torch.uint8, sh["codes"]), (kv, sh["kv"]),
+                              (kv, sh["kv"]), (torch.int32, sh["idx"]), (torch.float32, sh["out"]))
 
     def set_length(self, n_tokens: int, topk: int) -> None:
         """The cache now holds n_tokens tokens (<= capacity) and topk of the middle ones are retrieved."""
         self._check(self.lib.pqc_set_length(self.handle, n_tokens, topk), "pqc_set_length")
         self.w = dataclasses.replace(self.w, n_tokens=n_tokens, topk=topk)
         self.cfg.n_tokens, self.cfg.topk = n_tokens, topk
+        self._lay_out()
 
     def close(self) -> None:
         if getattr(self, "handle", None) is not None and self.handle.value:
@@ -155,15 +197,14 @@ class PQCache:
 
     # -- marshalling helpers
     def _ptr(self, t: torch.Tensor, dtype, shape) -> int:
+        if t.dtype is dtype and t.shape == shape and t.is_contiguous() and t.device == self.device:
+            return t.data_ptr()
         if t.device != self.device or not t.is_contiguous():
             raise ValueError("tensor must be contiguous and on the context's device")
-        if t.dtype != dtype or tuple(t.shape) != tuple(shape):
-            raise ValueError(f"expected {dtype} {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
-        return t.data_ptr()
+        raise ValueError(f"expected {dtype} {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
 
     def _stream(self, stream) -> int:
-        s = stream if stream is not None else torch.cuda.current_stream(self.device)
-        return s.cuda_stream
+        return _stream_of(stream, self.device)
 
     def _check(self, rc: int, what: str) -> None:
         if rc != 0:
@@ -172,52 +213,35 @@ class PQCache:
     # -- shapes
     @property
     def shapes(self):
-        w = self.w
-        return {
-            "q": (w.batch, w.n_q_heads, w.head_dim),
-            "centroids": (w.batch, w.n_kv_heads, w.pq_m, w.pq_centroids, w.sub_dim),
-            "codes": (w.batch, w.n_kv_heads, self.capacity, w.pq_m),
-            "kv": (w.batch, w.n_kv_heads, self.capacity, w.head_dim),
-            "idx": (w.batch, w.n_kv_heads, w.n_selected),
-            "out": (w.batch, w.n_q_heads, w.head_dim),
-            "table": (w.batch, w.n_kv_heads, w.pq_m, w.pq_centroids),
-            "scores": (w.batch, w.n_kv_heads, w.n_tokens),
-        }
+        return dict(self._shapes)
 
     def empty_outputs(self) -> Tuple[torch.Tensor, torch.Tensor]:
-        sh = self.shapes
+        sh = self._shapes
         return (torch.empty(sh["idx"], dtype=torch.int32, device=self.device),
                 torch.empty(sh["out"], dtype=torch.float32, device=self.device))
 
     # -- entry points (same names as the C ABI)
     def decode(self, q, centroids, codes, k_cache, v_cache, out_idx=None, out_attn=None, stream=None):
-        sh = self.shapes
         if out_idx is None or out_attn is None:
             out_idx, out_attn = self.empty_outputs()
-        rc = self.lib.pqc_decode(self.handle, self._ptr(q, self.kv_torch, sh["q"]),
-                                 self._ptr(centroids, torch.float32, sh["centroids"]),
-                                 self._ptr(codes, torch.uint8, sh["codes"]),
-                                 self._ptr(k_cache, self.kv_torch, sh["kv"]), self._ptr(v_cache, self.kv_torch, sh["kv"]),
-                                 self._ptr(out_idx, torch.int32, sh["idx"]), self._ptr(out_attn, torch.float32, sh["out"]),
-                                 self._stream(stream))
-        self._check(rc, "pqc_decode")
+        rc = self.lib.pqc_decode(self.handle, *self.marshal_decode_args(q, centroids, codes, k_cache, v_cache, out_idx, out_attn),
+                                 _stream_of(stream, self.device))
+        if rc != 0:
+            self._check(rc, "pqc_decode")
         return out_idx, out_attn
 
     def decode_append(self, q, centroids, codes, k_cache, v_cache, new_key, position: int, out_idx=None, out_attn=None,
                       stream=None):
         """pqc_decode plus the code of the token at `position` (its key: new_key [B,Hkv,D]), in the same launches."""
-        sh = self.shapes
         if out_idx is None or out_attn is None:
             out_idx, out_attn = self.empty_outputs()
         w = self.w
-        rc = self.lib.pqc_decode_append(self.handle, self._ptr(q, self.kv_torch, sh["q"]),
-                                        self._ptr(centroids, torch.float32, sh["centroids"]),
-                                        self._ptr(codes, torch.uint8, sh["codes"]),
-                                        self._ptr(k_cache, self.kv_torch, sh["kv"]), self._ptr(v_cache, self.kv_torch, sh["kv"]),
+        qp, cp, cdp, kp, vp_, oi, oa = self.marshal_decode_args(q, centroids, codes, k_cache, v_cache, out_idx, out_attn)
+        rc = self.lib.pqc_decode_append(self.handle, qp, cp, cdp, kp, vp_,
                                         self._ptr(new_key, self.kv_torch, (w.batch, w.n_kv_heads, w.head_dim)), position,
-                                        self._ptr(out_idx, torch.int32, sh["idx"]), self._ptr(out_attn, torch.float32, sh["out"]),
-                                        self._stream(stream))
-        self._check(rc, "pqc_decode_append")
+                                        oi, oa, _stream_of(stream, self.device))
+        if rc != 0:
+            self._check(rc, "pqc_decode_append")
         return out_idx, out_attn
 
     def decode_indexed_append(self, q, centroids, codes, pair_counts, k_cache, v_cache, new_key, position: int, out_idx=None,
@@ -236,11 +260,12 @@ class PQCache:
     def marshal_decode_args(self, q, centroids, codes, k_cache, v_cache, out_idx, out_attn):
         """Checks the seven tensors of a decode call once and returns their device addresses, for
         callers that repeat the same call and want the per-call Python cost out of the way."""
-        sh = self.shapes
-        return (self._ptr(q, self.kv_torch, sh["q"]), self._ptr(centroids, torch.float32, sh["centroids"]),
-                self._ptr(codes, torch.uint8, sh["codes"]), self._ptr(k_cache, self.kv_torch, sh["kv"]),
-                self._ptr(v_cache, self.kv_torch, sh["kv"]), self._ptr(out_idx, torch.int32, sh["idx"]),
-                self._ptr(out_attn, torch.float32, sh["out"]))
+        dev, out = self.device, []
+        for t, (dtype, shape) in zip((q, centroids, codes, k_cache, v_cache, out_idx, out_attn), self._decode_specs):
+            if t.dtype is not dtype or t.shape != shape or not t.is_contiguous() or t.device != dev:
+                self._ptr(t, dtype, shape)  # says what is wrong
+            out.append(t.data_ptr())
+        return tuple(out)
 
     def decode_marshalled(self, args, stream_handle: int) -> None:
         self._check(self.lib.pqc_decode(self.handle, *args, stream_handle), "pqc_decode")
@@ -271,7 +296,7 @@ class PQCache:
                                      self._stream(stream))
 
     def lut(self, q, centroids, table=None, stream=None):
-        sh = self.shapes
+        sh = self._shapes
         if table is None:
             table = torch.empty(sh["table"], dtype=torch.float32, device=self.device)
         rc = self.lib.pqc_lut(self.handle, self._ptr(q, self.kv_torch, sh["q"]),
@@ -281,7 +306,7 @@ class PQCache:
         return table
 
     def scan(self, table, codes, scores=None, stream=None):
-        sh = self.shapes
+        sh = self._shapes
         if scores is None:
             scores = torch.empty(sh["scores"], dtype=torch.float32, device=self.device)
         rc = self.lib.pqc_scan(self.handle, self._ptr(table, torch.float32, sh["table"]),
@@ -291,7 +316,7 @@ class PQCache:
         return scores
 
     def topk(self, scores, out_idx=None, stream=None):
-        sh = self.shapes
+        sh = self._shapes
         if out_idx is None:
             out_idx = torch.empty(sh["idx"], dtype=torch.int32, device=self.device)
         rc = self.lib.pqc_topk(self.handle, self._ptr(scores, torch.float32, sh["scores"]),
@@ -300,7 +325,7 @@ class PQCache:
         return out_idx
 
     def gather_attn(self, q, k_cache, v_cache, idx, out_attn=None, stream=None):
-        sh = self.shapes
+        sh = self._shapes
         if out_attn is None:
             out_attn = torch.empty(sh["out"], dtype=torch.float32, device=self.device)
         rc = self.lib.pqc_gather_attn(self.handle, self._ptr(q, self.kv_torch, sh["q"]),
@@ -316,7 +341,7 @@ def _kv_dtype(w: Workload):
 
 
 def _need(t: torch.Tensor, dtype, shape, what: str) -> int:
-    if not t.is_cuda or not t.is_contiguous() or t.dtype != dtype or tuple(t.shape) != tuple(shape):
+    if not t.is_cuda or not t.is_contiguous() or t.dtype is not dtype or t.shape != shape:
         raise ValueError(f"{what}: expected contiguous device {dtype} {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
     return t.data_ptr()
 
@@ -328,7 +353,7 @@ def decode_static(w: Workload, q, centroids, codes, k_cache, v_cache, out_idx, o
     cfg = make_config(w, softmax_scale, capacity)
     ntok = capacity or w.n_tokens
     kvt = _kv_dtype(w)
-    st = (stream if stream is not None else torch.cuda.current_stream(q.device)).cuda_stream
+    st = _stream_of(stream, q.device)
     rc = lib.pqc_decode_static(
         C.byref(cfg), _need(q, kvt, (w.batch, w.n_q_heads, w.head_dim), "q"),
         _need(centroids, torch.float32, (w.batch, w.n_kv_heads, w.pq_m, w.pq_centroids, w.sub_dim), "centroids"),
@@ -347,18 +372,18 @@ def pq_build(w: Workload, keys: torch.Tensor, init_idx: torch.Tensor, iters: Opt
 
     capacity (here and below): token room of `keys` and `codes` per head when it exceeds w.n_tokens."""
     lib = load()
-    cfg = make_config(w, capacity=capacity)
+    cfg = _config(w, capacity)
     ntok = capacity or w.n_tokens
     dev = keys.device
     iters = w.kmeans_iters if iters is None else iters
-    nbytes = lib.pqc_pq_build_workspace_bytes(C.byref(cfg))
+    nbytes = lib.pqc_pq_build_workspace_bytes(cfg)
     if nbytes == 0:
         raise PQCacheError(-1, "pqc_pq_build_workspace_bytes")
     ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
     cent = torch.empty((w.batch, w.n_kv_heads, w.pq_m, w.pq_centroids, w.sub_dim), dtype=torch.float32, device=dev)
     codes = torch.zeros((w.batch, w.n_kv_heads, ntok, w.pq_m), dtype=torch.uint8, device=dev)
-    st = (stream if stream is not None else torch.cuda.current_stream(dev)).cuda_stream
-    rc = lib.pqc_pq_build(C.byref(cfg), _need(keys, _kv_dtype(w), (w.batch, w.n_kv_heads, ntok, w.head_dim), "keys"),
+    st = _stream_of(stream, dev)
+    rc = lib.pqc_pq_build(cfg, _need(keys, _kv_dtype(w), (w.batch, w.n_kv_heads, ntok, w.head_dim), "keys"),
                           _need(init_idx, torch.int32, (w.batch, w.n_kv_heads, w.pq_m, w.pq_centroids), "init_idx"),
                           iters, cent.data_ptr(), codes.data_ptr(), ws.data_ptr(), nbytes, st)
     if rc != 0:
@@ -368,12 +393,12 @@ def pq_build(w: Workload, keys: torch.Tensor, init_idx: torch.Tensor, iters: Opt
 
 def pq_assign(w: Workload, keys: torch.Tensor, centroids: torch.Tensor, stream=None, capacity: int = 0) -> torch.Tensor:
     lib = load()
-    cfg = make_config(w, capacity=capacity)
+    cfg = _config(w, capacity)
     ntok = capacity or w.n_tokens
     dev = keys.device
     codes = torch.zeros((w.batch, w.n_kv_heads, ntok, w.pq_m), dtype=torch.uint8, device=dev)
-    st = (stream if stream is not None else torch.cuda.current_stream(dev)).cuda_stream
-    rc = lib.pqc_pq_assign(C.byref(cfg), _need(keys, _kv_dtype(w), (w.batch, w.n_kv_heads, ntok, w.head_dim), "keys"),
+    st = _stream_of(stream, dev)
+    rc = lib.pqc_pq_assign(cfg, _need(keys, _kv_dtype(w), (w.batch, w.n_kv_heads, ntok, w.head_dim), "keys"),
                            _need(centroids, torch.float32, (w.batch, w.n_kv_heads, w.pq_m, w.pq_centroids, w.sub_dim), "centroids"),
                            codes.data_ptr(), st)
     if rc != 0:
@@ -385,9 +410,9 @@ def pq_encode_token(w: Workload, key: torch.Tensor, centroids: torch.Tensor, cod
                     stream=None, capacity: int = 0) -> None:
     """Write the nearest-centroid codes of one new key per (sequence, KV head) at `position` of `codes`."""
     lib = load()
-    cfg = make_config(w, capacity=capacity)
-    st = (stream if stream is not None else torch.cuda.current_stream(key.device)).cuda_stream
-    rc = lib.pqc_pq_encode_token(C.byref(cfg), _need(key, _kv_dtype(w), (w.batch, w.n_kv_heads, w.head_dim), "key"),
+    cfg = _config(w, capacity)
+    st = _stream_of(stream, key.device)
+    rc = lib.pqc_pq_encode_token(cfg, _need(key, _kv_dtype(w), (w.batch, w.n_kv_heads, w.head_dim), "key"),
                                  _need(centroids, torch.float32, (w.batch, w.n_kv_heads, w.pq_m, w.pq_centroids, w.sub_dim), "centroids"),
                                  _need(codes, torch.uint8, (w.batch, w.n_kv_heads, capacity or w.n_tokens, w.pq_m), "codes"),
                                  position, st)
@@ -398,11 +423,11 @@ def pq_encode_token(w: Workload, key: torch.Tensor, centroids: torch.Tensor, cod
 def pair_counts(w: Workload, codes: torch.Tensor, stream=None, capacity: int = 0) -> torch.Tensor:
     """Tokens per pair of codes, [B][Hkv][C*C] (uint32 values in an int32 tensor); two partitions only."""
     lib = load()
-    cfg = make_config(w, capacity=capacity)
+    cfg = _config(w, capacity)
     _need(codes, torch.uint8, (w.batch, w.n_kv_heads, capacity or w.n_tokens, w.pq_m), "codes")
     out = torch.empty((w.batch, w.n_kv_heads, w.pq_centroids * w.pq_centroids), dtype=torch.int32, device=codes.device)
-    st = (stream if stream is not None else torch.cuda.current_stream(codes.device)).cuda_stream
-    rc = lib.pqc_pair_counts(C.byref(cfg), codes.data_ptr(), out.data_ptr(), st)
+    st = _stream_of(stream, codes.device)
+    rc = lib.pqc_pair_counts(cfg, codes.data_ptr(), out.data_ptr(), st)
     if rc != 0:
         raise PQCacheError(rc, "pqc_pair_counts")
     return out
@@ -411,9 +436,9 @@ def pair_counts(w: Workload, codes: torch.Tensor, stream=None, capacity: int = 0
 def pair_counts_add(w: Workload, codes: torch.Tensor, position: int, counts: torch.Tensor, stream=None,
                     capacity: int = 0) -> None:
     lib = load()
-    cfg = make_config(w, capacity=capacity)
-    st = (stream if stream is not None else torch.cuda.current_stream(codes.device)).cuda_stream
-    rc = lib.pqc_pair_counts_add(C.byref(cfg), codes.data_ptr(), position, counts.data_ptr(), st)
+    cfg = _config(w, capacity)
+    st = _stream_of(stream, codes.device)
+    rc = lib.pqc_pair_counts_add(cfg, codes.data_ptr(), position, counts.data_ptr(), st)
     if rc != 0:
         raise PQCacheError(rc, "pqc_pair_counts_add")
 
@@ -421,14 +446,14 @@ def pair_counts_add(w: Workload, codes: torch.Tensor, position: int, counts: tor
 def block_stats(w: Workload, idx: torch.Tensor, block_tokens: int, k_cache: int, stream=None):
     """Listed tokens per block and the k_cache fullest blocks -> (counts [B][Hkv][nb], blocks [B][Hkv][k_cache])."""
     lib = load()
-    cfg = make_config(w)
+    cfg = _config(w)
     if idx.dtype != torch.int32 or idx.dim() != 3 or tuple(idx.shape[:2]) != (w.batch, w.n_kv_heads) or not idx.is_contiguous():
         raise ValueError("idx must be a contiguous int32 tensor [B][Hkv][n_idx]")
     nb = (w.n_tokens + block_tokens - 1) // block_tokens
     counts = torch.empty((w.batch, w.n_kv_heads, nb), dtype=torch.int32, device=idx.device)
     blocks = torch.empty((w.batch, w.n_kv_heads, k_cache), dtype=torch.int32, device=idx.device)
-    st = (stream if stream is not None else torch.cuda.current_stream(idx.device)).cuda_stream
-    rc = lib.pqc_block_stats(C.byref(cfg), idx.data_ptr(), idx.shape[2], block_tokens, k_cache, counts.data_ptr(),
+    st = _stream_of(stream, idx.device)
+    rc = lib.pqc_block_stats(cfg, idx.data_ptr(), idx.shape[2], block_tokens, k_cache, counts.data_ptr(),
                              blocks.data_ptr() if k_cache > 0 else None, st)
     if rc != 0:
         raise PQCacheError(rc, "pqc_block_stats")
@@ -448,7 +473,7 @@ def block_cache_update(w: Workload, block_tokens: int, policy: str, step: int, c
                        slot_block: torch.Tensor, slot_stamp: torch.Tensor, slot_uses: torch.Tensor, stream=None) -> torch.Tensor:
     """One look-up and refresh of the block cache state (updated in place) -> stats [B,Hkv,4] int32."""
     lib = load()
-    cfg = make_config(w)
+    cfg = _config(w)
     nb = (w.n_tokens + block_tokens - 1) // block_tokens
     n_slots, k_cache = slot_block.shape[-1], blocks.shape[-1]
     _need(counts, torch.int32, (w.batch, w.n_kv_heads, nb), "counts")
@@ -456,8 +481,8 @@ def block_cache_update(w: Workload, block_tokens: int, policy: str, step: int, c
     for t, name in ((slot_block, "slot_block"), (slot_stamp, "slot_stamp"), (slot_uses, "slot_uses")):
         _need(t, torch.int32, (w.batch, w.n_kv_heads, n_slots), name)
     stats = torch.empty((w.batch, w.n_kv_heads, 4), dtype=torch.int32, device=counts.device)
-    st = (stream if stream is not None else torch.cuda.current_stream(counts.device)).cuda_stream
-    rc = lib.pqc_block_cache_update(C.byref(cfg), block_tokens, n_slots, {"lru": 0, "lfu": 1}[policy], step, counts.data_ptr(),
+    st = _stream_of(stream, counts.device)
+    rc = lib.pqc_block_cache_update(cfg, block_tokens, n_slots, {"lru": 0, "lfu": 1}[policy], step, counts.data_ptr(),
                                     blocks.data_ptr() if k_cache else None, k_cache, slot_block.data_ptr(),
                                     slot_stamp.data_ptr(), slot_uses.data_ptr(), stats.data_ptr(), st)
     if rc != 0:
