@@ -366,6 +366,12 @@ def decode_static(w: Workload, q, centroids, codes, k_cache, v_cache, out_idx, o
         raise PQCacheError(rc, "pqc_decode_static")
 
 
+def _new_codes(w: Workload, ntok: int, dev) -> torch.Tensor:
+    """The code tensor of a call that writes the first n_tokens codes of every head; entries beyond them are zero."""
+    new = torch.empty if ntok == w.n_tokens else torch.zeros
+    return new((w.batch, w.n_kv_heads, ntok, w.pq_m), dtype=torch.uint8, device=dev)
+
+
 def pq_build(w: Workload, keys: torch.Tensor, init_idx: torch.Tensor, iters: Optional[int] = None, stream=None,
              capacity: int = 0):
     """K-Means PQ construction on the GPU -> (centroids [B,Hkv,M,C,Dm] f32, codes [B,Hkv,N,M] u8).
@@ -381,7 +387,7 @@ def pq_build(w: Workload, keys: torch.Tensor, init_idx: torch.Tensor, iters: Opt
         raise PQCacheError(-1, "pqc_pq_build_workspace_bytes")
     ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
     cent = torch.empty((w.batch, w.n_kv_heads, w.pq_m, w.pq_centroids, w.sub_dim), dtype=torch.float32, device=dev)
-    codes = torch.zeros((w.batch, w.n_kv_heads, ntok, w.pq_m), dtype=torch.uint8, device=dev)
+    codes = _new_codes(w, ntok, dev)
     st = _stream_of(stream, dev)
     rc = lib.pqc_pq_build(cfg, _need(keys, _kv_dtype(w), (w.batch, w.n_kv_heads, ntok, w.head_dim), "keys"),
                           _need(init_idx, torch.int32, (w.batch, w.n_kv_heads, w.pq_m, w.pq_centroids), "init_idx"),
@@ -396,7 +402,7 @@ def pq_assign(w: Workload, keys: torch.Tensor, centroids: torch.Tensor, stream=N
     cfg = _config(w, capacity)
     ntok = capacity or w.n_tokens
     dev = keys.device
-    codes = torch.zeros((w.batch, w.n_kv_heads, ntok, w.pq_m), dtype=torch.uint8, device=dev)
+    codes = _new_codes(w, ntok, dev)
     st = _stream_of(stream, dev)
     rc = lib.pqc_pq_assign(cfg, _need(keys, _kv_dtype(w), (w.batch, w.n_kv_heads, ntok, w.head_dim), "keys"),
                            _need(centroids, torch.float32, (w.batch, w.n_kv_heads, w.pq_m, w.pq_centroids, w.sub_dim), "centroids"),

@@ -695,44 +695,90 @@ namespace {
 
 struct BuildPlan {
   BuildShape s;
+  RoundGrid round;    // a K-Means round: assignment and sums in one pass
+  RoundGrid assign;   // the assignment alone
+  bool fused;         // the accumulators of a round fit into LDS beside the centroids
+  bool mfma;
   size_t off_sums, off_counts, total;
 };
+
+constexpr size_t kRoundLds = 156 * 1024;  // of the compute unit's 160 KB
+
+// Token ranges per (unit, partition).  One workgroup fills a compute unit, so the time of a launch is that of its rounds of
+// 256 workgroups; each pays for staging the centroids and writing the sums what about 1024 tokens cost.
+RoundGrid round_grid(const BuildShape& s, int staged) {
+  RoundGrid r{1, (s.N + 15) / 16 * 16, staged};
+  double best = 1e30;
+  for (int p = 1; p <= 128; ++p) {
+    const int tokens = ((s.N + p - 1) / p + 15) / 16 * 16;
+    const int ranges = (s.N + tokens - 1) / tokens;
+    const double rounds = std::ceil((double)s.units * s.M * ranges / 256.0);
+    const double cost = rounds * (tokens + 1024.0);
+    if (cost < best * 0.999) {
+      best = cost;
+      r.ranges = ranges;
+      r.tokens = tokens;
+    }
+  }
+  return r;
+}
 
 int make_build_plan(const pqc_config* cfg, BuildPlan* bp) {
   Plan p;
   const int rc = make_plan(cfg, &p);
   if (rc != PQC_OK) return rc;
-  bp->s.units = p.s.B * p.s.Hkv;
-  bp->s.N = p.s.N; bp->s.M = p.s.M; bp->s.C = p.s.C; bp->s.Dm = p.s.Dm; bp->s.cap = p.s.cap;
-  const size_t n = (size_t)bp->s.units * p.s.M * p.s.C;
+  BuildShape& s = bp->s;
+  s.units = p.s.B * p.s.Hkv;
+  s.N = p.s.N; s.M = p.s.M; s.C = p.s.C; s.Dm = p.s.Dm; s.cap = p.s.cap;
+  bp->mfma = cfg->kv_dtype == PQC_BF16 && s.Dm >= 32;
+  auto stage_bytes = [&](int n) { return bp->mfma ? mfma_stage_bytes(n, s.Dm) : vector_stage_bytes(n, s.Dm); };
+  int staged = s.C;
+  while (stage_bytes(staged) > kRoundLds) staged = (staged / 2 + 15) / 16 * 16;
+  bp->assign = round_grid(s, staged);
+  bp->fused = stage_bytes(s.C) + round_sum_bytes(s.C, s.Dm) <= kRoundLds;
+  bp->round = bp->assign;
+  const size_t n = (size_t)s.units * s.M * s.C * (bp->fused ? bp->round.ranges : 1);
   bp->off_sums = 0;
-  bp->off_counts = align_up(sizeof(unsigned long long) * n * p.s.Dm);
+  bp->off_counts = align_up(sizeof(unsigned long long) * n * s.Dm);
   bp->total = align_up(bp->off_counts + sizeof(unsigned) * n);
   return PQC_OK;
 }
 
+// One launch over all token ranges: with sums a K-Means round, without it the assignment (codes written).
+template <typename T, int DM, bool ACCUM>
+void launch_round_d(const BuildPlan& bp, const T* keys, const float* cent, uint8_t* codes, unsigned long long* sums, unsigned* counts,
+                    hipStream_t st) {
+  const BuildShape& s = bp.s;
+  const RoundGrid& r = ACCUM ? bp.round : bp.assign;
+  const dim3 grid((unsigned)(s.units * s.M * r.ranges));
+  const size_t acc = ACCUM ? round_sum_bytes(s.C, s.Dm) : 0;
+  if constexpr (sizeof(T) == 2 && DM >= 32) {
+    const size_t lds = mfma_stage_bytes(r.staged, DM) + acc;
+    // eight tiles per wave read each staged centroid once for 128 tokens (as many as the registers of four waves per SIMD hold
+    // with longer sub-vectors); short ranges take two, so that more than a few of the sixteen waves have tokens
+    constexpr int kTiles = DM >= 128 ? 4 : DM == 64 ? 6 : 8;
+    if (r.tokens >= 16 * 16 * kTiles)
+      hipLaunchKernelGGL((pq_round_mfma_kernel<DM, kTiles, ACCUM>), grid, dim3(1024), lds, st, s, r, keys, cent, codes, sums, counts);
+    else
+      hipLaunchKernelGGL((pq_round_mfma_kernel<DM, 2, ACCUM>), grid, dim3(1024), lds, st, s, r, keys, cent, codes, sums, counts);
+  } else {
+    hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, ACCUM>), grid, dim3(round_vector_threads<DM>()), vector_stage_bytes(r.staged, DM) + acc,
+                       st, s, r, keys, cent, codes, sums, counts);
+  }
+}
+template <typename T, bool ACCUM>
+void launch_round(const BuildPlan& bp, const T* keys, const float* cent, uint8_t* codes, unsigned long long* sums, unsigned* counts,
+                  hipStream_t st) {
+  switch (bp.s.Dm) {
+    case 16: launch_round_d<T, 16, ACCUM>(bp, keys, cent, codes, sums, counts, st); break;
+    case 32: launch_round_d<T, 32, ACCUM>(bp, keys, cent, codes, sums, counts, st); break;
+    case 64: launch_round_d<T, 64, ACCUM>(bp, keys, cent, codes, sums, counts, st); break;
+    default: launch_round_d<T, 128, ACCUM>(bp, keys, cent, codes, sums, counts, st); break;
+  }
+}
 template <typename T>
-void launch_assign(const BuildShape& s, const T* keys, int64_t unit_stride, int n_tokens, int pos0, const float* cent,
-                   uint8_t* codes, hipStream_t st) {
-  if constexpr (sizeof(T) == 2) {
-    if (s.Dm >= 32) {  // bf16 keys: the matrix-core kernel
-      const dim3 mgrid((n_tokens + kAssignMfmaTok - 1) / kAssignMfmaTok, (unsigned)(s.units * s.M));
-      const bf16_t* kb = reinterpret_cast<const bf16_t*>(keys);
-      switch (s.Dm) {
-        case 32: hipLaunchKernelGGL((pq_assign_mfma_kernel<32>), mgrid, dim3(256), 0, st, s, kb, unit_stride, n_tokens, pos0, cent, codes); break;
-        case 64: hipLaunchKernelGGL((pq_assign_mfma_kernel<64>), mgrid, dim3(256), 0, st, s, kb, unit_stride, n_tokens, pos0, cent, codes); break;
-        default: hipLaunchKernelGGL((pq_assign_mfma_kernel<128>), mgrid, dim3(256), 0, st, s, kb, unit_stride, n_tokens, pos0, cent, codes); break;
-      }
-      return;
-    }
-  }
-  const dim3 grid((n_tokens + kAssignTok - 1) / kAssignTok, (unsigned)(s.units * s.M));
-  switch (s.Dm) {
-    case 16: hipLaunchKernelGGL((pq_assign_kernel<T, 16>), grid, dim3(256), 0, st, s, keys, unit_stride, n_tokens, pos0, cent, codes); break;
-    case 32: hipLaunchKernelGGL((pq_assign_kernel<T, 32>), grid, dim3(256), 0, st, s, keys, unit_stride, n_tokens, pos0, cent, codes); break;
-    case 64: hipLaunchKernelGGL((pq_assign_kernel<T, 64>), grid, dim3(256), 0, st, s, keys, unit_stride, n_tokens, pos0, cent, codes); break;
-    default: hipLaunchKernelGGL((pq_assign_kernel<T, 128>), grid, dim3(256), 0, st, s, keys, unit_stride, n_tokens, pos0, cent, codes); break;
-  }
+void launch_assign(const BuildPlan& bp, const T* keys, const float* cent, uint8_t* codes, hipStream_t st) {
+  launch_round<T, false>(bp, keys, cent, codes, nullptr, nullptr, st);
 }
 
 template <typename T>
@@ -742,13 +788,15 @@ int pq_build_t(const BuildPlan& bp, const T* keys, const int32_t* init_idx, int 
   unsigned long long* sums = reinterpret_cast<unsigned long long*>(wsp + bp.off_sums);
   unsigned* counts = reinterpret_cast<unsigned*>(wsp + bp.off_counts);
   const unsigned uj = (unsigned)(s.units * s.M);
-  const size_t nacc = bp.total / sizeof(unsigned long long);  // sums and counts, zeroed together
-  const size_t ncent = (size_t)uj * s.C * s.Dm;
-  hipLaunchKernelGGL((pq_init_kernel<T>), dim3(1, uj), dim3(256), 0, st, s, keys, init_idx, cent);
+  const dim3 per_cent((unsigned)((s.C * s.Dm + 255) / 256), uj);
+  hipLaunchKernelGGL((pq_init_kernel<T>), per_cent, dim3(256), 0, st, s, keys, init_idx, cent);
   for (int it = 0; it < iters; ++it) {
-    launch_assign<T>(s, keys, (int64_t)s.cap * kD, s.N, 0, cent, codes, st);
-    hipLaunchKernelGGL(pq_zero_kernel, dim3((unsigned)((nacc + 255) / 256)), dim3(256), 0, st, sums, nacc);
-    {
+    if (bp.fused) {
+      launch_round<T, true>(bp, keys, cent, codes, sums, counts, st);
+    } else {  // the accumulators are too large for LDS: codes first, then the sums of the members of each code
+      launch_assign<T>(bp, keys, cent, codes, st);
+      const size_t nacc = bp.total / sizeof(unsigned long long);  // sums and counts, zeroed together
+      hipLaunchKernelGGL(pq_zero_kernel, dim3((unsigned)((nacc + 255) / 256)), dim3(256), 0, st, sums, nacc);
       const int tpw = accum_tokens_per_wg(s.C);
       const dim3 grid((s.N + tpw - 1) / tpw, uj);
       const size_t lds = (size_t)tpw * sizeof(unsigned short);
@@ -759,9 +807,9 @@ int pq_build_t(const BuildPlan& bp, const T* keys, const int32_t* init_idx, int 
         default: hipLaunchKernelGGL((pq_accum_kernel<T, 128>), grid, dim3(256), lds, st, s, keys, codes, sums, counts); break;
       }
     }
-    hipLaunchKernelGGL(pq_mean_kernel, dim3((unsigned)((ncent + 255) / 256)), dim3(256), 0, st, s, sums, counts, cent);
+    hipLaunchKernelGGL(pq_mean_kernel, per_cent, dim3(256), 0, st, s, bp.fused ? bp.round.ranges : 1, sums, counts, cent);
   }
-  launch_assign<T>(s, keys, (int64_t)s.cap * kD, s.N, 0, cent, codes, st);
+  launch_assign<T>(bp, keys, cent, codes, st);
   return hipGetLastError() == hipSuccess ? PQC_OK : PQC_EHIP;
 }
 
@@ -796,11 +844,10 @@ int pqc_pq_assign(const pqc_config* cfg, const void* keys, const float* centroid
   if (!keys || !centroids || !codes) return PQC_EINVAL;
   if (!aligned16(keys) || !aligned16(centroids) || !aligned16(codes)) return PQC_EINVAL;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const BuildShape& s = bp.s;
   if (cfg->kv_dtype == PQC_F32)
-    launch_assign<float>(s, static_cast<const float*>(keys), (int64_t)s.cap * kD, s.N, 0, centroids, codes, st);
+    launch_assign<float>(bp, static_cast<const float*>(keys), centroids, codes, st);
   else
-    launch_assign<bf16_t>(s, static_cast<const bf16_t*>(keys), (int64_t)s.cap * kD, s.N, 0, centroids, codes, st);
+    launch_assign<bf16_t>(bp, static_cast<const bf16_t*>(keys), centroids, codes, st);
   return hipGetLastError() == hipSuccess ? PQC_OK : PQC_EHIP;
 }
 

@@ -3,18 +3,16 @@
 // and the nearest-centroid code of a token that leaves the local window (Section 3.1,
 // last paragraph; Algorithm 2 "PQArgNearest").
 //
-// Grid layout: blockIdx.y = unit * M + partition j, blockIdx.x = token chunk.
-// Distances are evaluated in fp32 as sum_e (x_e - c_e)^2, e ascending; the lowest
-// centroid index wins ties.  Centroid sums are accumulated in 64-bit fixed point
-// (2^-20 resolution), which makes the update independent of summation order and
-// therefore reproducible; an empty cluster keeps its centroid.
+// Distances are compared in fp32; the lowest centroid index wins ties.  Centroid sums
+// are accumulated in 64-bit fixed point (2^-20 resolution), which makes the update
+// independent of summation order and therefore reproducible; an empty cluster keeps its
+// centroid.
 #pragma once
 #include "pqc_device.h"
 
 namespace pqc {
 
 constexpr int kFixShift = 20;
-constexpr int kAssignTok = 256;   // tokens per workgroup of the assignment kernel
 
 struct BuildShape {
   int units, N, M, C, Dm;
@@ -26,54 +24,12 @@ template <typename T>
 __global__ __launch_bounds__(256) void pq_init_kernel(BuildShape s, const T* __restrict__ keys,
                                                       const int* __restrict__ init_idx, float* __restrict__ cent) {
   const int uj = blockIdx.y, u = uj / s.M, j = uj % s.M;
-  for (int i = threadIdx.x; i < s.C * s.Dm; i += 256) {
-    const int c = i / s.Dm, e = i % s.Dm;
-    int t = init_idx[(size_t)uj * s.C + c];
-    t = max(0, min(s.N - 1, t));
-    cent[(size_t)uj * s.C * s.Dm + i] = load_as_float<T>(keys, ((size_t)u * s.cap + t) * kD + j * s.Dm + e);
-  }
-}
-
-// codes[u][t][j] = argmin_c || keys[u][t][j*Dm..] - cent[u][j][c] ||^2
-// One thread per token; centroids staged through LDS 32 at a time.
-template <typename T, int DM>
-__global__ __launch_bounds__(256) void pq_assign_kernel(BuildShape s, const T* __restrict__ keys, int64_t key_unit_stride,
-                                                        int n_tokens, int code_pos0, const float* __restrict__ cent,
-                                                        uint8_t* __restrict__ codes) {
-  constexpr int CG = 32;
-  __shared__ float cs[CG * DM];
-  const int uj = blockIdx.y, u = uj / s.M, j = uj % s.M;
-  const int t = blockIdx.x * kAssignTok + threadIdx.x;
-  const bool live = t < n_tokens;
-  float x[DM];
-  if (live) {
-#pragma unroll
-    for (int e = 0; e < DM; ++e) x[e] = load_as_float<T>(keys, (size_t)u * key_unit_stride + (size_t)t * kD + j * DM + e);
-  } else {
-#pragma unroll
-    for (int e = 0; e < DM; ++e) x[e] = 0.0f;
-  }
-  float best = INFINITY;
-  int arg = 0;
-  for (int c0 = 0; c0 < s.C; c0 += CG) {
-    const int nc = min(CG, s.C - c0);
-    __syncthreads();
-    for (int i = threadIdx.x; i < nc * DM; i += 256) cs[i] = cent[((size_t)uj * s.C + c0) * DM + i];
-    __syncthreads();
-    for (int c = 0; c < nc; ++c) {
-      float d2 = 0.0f;
-#pragma unroll
-      for (int e = 0; e < DM; ++e) {
-        const float df = x[e] - cs[c * DM + e];
-        d2 = fmaf(df, df, d2);
-      }
-      if (d2 < best) {
-        best = d2;
-        arg = c0 + c;
-      }
-    }
-  }
-  if (live) codes[((size_t)u * s.cap + code_pos0 + t) * s.M + j] = (uint8_t)arg;
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= s.C * s.Dm) return;
+  const int c = i / s.Dm, e = i % s.Dm;
+  int t = init_idx[(size_t)uj * s.C + c];
+  t = max(0, min(s.N - 1, t));
+  cent[(size_t)uj * s.C * s.Dm + i] = load_as_float<T>(keys, ((size_t)u * s.cap + t) * kD + j * s.Dm + e);
 }
 
 // One token per unit (the code of an appended token): one thread per centroid, the same distance chain
@@ -107,141 +63,365 @@ __global__ __launch_bounds__(256) void pq_encode_kernel(BuildShape s, const T* _
   if (c == 0) codes[((size_t)u * s.cap + position) * s.M + j] = (uint8_t)(best & 0xffu);
 }
 
-// The same assignment on the matrix cores, for bf16 keys and sub-vectors of 32, 64 or 128
-// dimensions: this step is a dense contraction (tokens x dimensions by dimensions x
-// centroids).  The nearest centroid minimises |c|^2 - 2 x.c.  Keys are bf16 already; an fp32
-// centroid is split into three bf16 terms that add up to it exactly, so the products are
-// exact and only the fp32 accumulation rounds.  Per wave: 16-token tiles as the A operand
-// (kept in registers), 16-centroid tiles as the B operand (from LDS), D[token][centroid];
-// each lane keeps the best centroid of its column per token, the columns are merged with DPP
-// row operations at the end (equal values: lower centroid index).
-constexpr int kAssignTiles = 8;                          // 16-token tiles per wave and batch
-constexpr int kAssignBatchTok = 4 * 16 * kAssignTiles;   // tokens per workgroup and batch
-constexpr int kAssignBatches = 4;                        // batches per workgroup (the staged centroids are reused)
-constexpr int kAssignMfmaTok = kAssignBatchTok * kAssignBatches;
-template <int DM>
-__global__ __launch_bounds__(256) void pq_assign_mfma_kernel(BuildShape s, const bf16_t* __restrict__ keys,
-                                                             int64_t key_unit_stride, int n_tokens, int code_pos0,
-                                                             const float* __restrict__ cent, uint8_t* __restrict__ codes) {
-  constexpr int KK = DM / 32;            // k steps of 32 dimensions
-  constexpr int CG = 8192 / DM;          // centroids staged at a time (48 KB of bf16 terms)
-  constexpr int RS = DM + 8;             // LDS row stride in bf16 (16 bytes of padding)
-  __shared__ __attribute__((aligned(16))) unsigned short ct[3][CG * RS];  // hi, mid, lo terms
-  __shared__ float cn[CG];
-  const int uj = blockIdx.y, u = uj / s.M, j = uj % s.M, tid = threadIdx.x;
+// ------------------------------------------------------------- one K-Means round
+// Assignment of every token to its nearest centroid and, in the same pass over the keys, the sums of the new
+// centroids' members.  A workgroup owns one range of tokens of one (unit, partition): it stages the centroids in LDS
+// once, streams its keys through registers, and adds each key to an LDS accumulator of its centroid; at the end the
+// accumulators go to the workspace as they are (no atomics, nothing to clear), one set per range, and pq_mean_kernel
+// adds the ranges up.  With ACCUM = false the kernel is the assignment alone and writes codes.
+//
+// Sums are 64-bit integers of the values in fixed point (2^-20, round to nearest even), so the result does not depend
+// on the order of tokens, waves or workgroups.  The conversion is one addition in double precision: x + 1.5 * 2^32 has
+// its last bit at 2^-20, so its bit pattern is the pattern of 1.5 * 2^32 plus the fixed-point integer; the constant is
+// taken out again count times when the accumulators are written.  (|x| >= 2^30 takes a conversion of its own.)
+struct RoundGrid {
+  int ranges;   // token ranges per (unit, partition)
+  int tokens;   // tokens per range, a multiple of 16
+  int staged;   // centroids staged at a time (all of them when they fit; always all with ACCUM)
+};
+constexpr double kFixBias = 6442450944.0;  // 1.5 * 2^32
+constexpr long long kFixBiasBits = 0x41f8000000000000ll;
+__device__ __forceinline__ unsigned long long fix_biased(float x) { return (unsigned long long)__double_as_longlong((double)x + kFixBias); }
+__device__ __forceinline__ unsigned long long fix_biased_large(float x) {
+  return (unsigned long long)__float2ll_rn(x * (float)(1 << kFixShift)) + (unsigned long long)kFixBiasBits;
+}
+
+// LDS of a round: the staged centroids, then the accumulators ([C][Dm + 1]: an odd row length spreads the rows of the
+// centroids that a wave adds to over the banks) and the member counts.
+__host__ __device__ constexpr size_t round_sum_bytes(int C, int Dm) { return (size_t)C * (Dm + 1) * 8 + ((size_t)C * 4 + 15) / 16 * 16; }
+__host__ __device__ constexpr int mfma_term_stride(int Dm) { return Dm + 8; }  // bf16 values; 16 bytes of padding
+__host__ __device__ constexpr size_t mfma_stage_bytes(int staged, int Dm) {
+  return (size_t)((staged + 15) / 16 * 16) * (3 * mfma_term_stride(Dm) * 2 + 4);
+}
+__host__ __device__ constexpr size_t vector_stage_bytes(int staged, int Dm) { return (size_t)staged * (Dm + 4) * 4; }
+
+// Workgroups go to the eight XCDs round-robin.  The M partitions of a token range read interleaved pieces of the same
+// rows (64 or 128 bytes each), so they are placed on one XCD, next to each other, and share the lines in its L2.
+__device__ __forceinline__ void round_place(const BuildShape& s, int ranges, int& u, int& j, int& p) {
+  const int items = s.units * ranges, lin = blockIdx.x, full = items / 8 * 8;
+  int item;
+  if (lin < full * s.M) {
+    const int i = lin % (8 * s.M);
+    item = lin / (8 * s.M) * 8 + (i & 7);
+    j = i >> 3;
+  } else {
+    const int i = lin - full * s.M, left = items - full;
+    item = full + i % left;
+    j = i / left;
+  }
+  u = item / ranges;
+  p = item % ranges;
+}
+
+__device__ __forceinline__ void round_flush(const BuildShape& s, int slot, const unsigned long long* sums, const unsigned* cnt,
+                                            unsigned long long* __restrict__ part_sums, unsigned* __restrict__ part_counts) {
+  const int n = s.C * s.Dm;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const int c = i / s.Dm, e = i - c * s.Dm;
+    part_sums[(size_t)slot * n + i] = sums[c * (s.Dm + 1) + e] - (unsigned long long)cnt[c] * (unsigned long long)kFixBiasBits;
+  }
+  for (int i = threadIdx.x; i < s.C; i += blockDim.x) part_counts[(size_t)slot * s.C + i] = cnt[i];
+}
+
+// bf16 keys and sub-vectors of 32, 64 or 128 dimensions: the assignment is a dense contraction (tokens x dimensions by
+// dimensions x centroids) and runs on the matrix cores.  The nearest centroid minimises |c|^2 - 2 x.c.  Keys are bf16
+// already; an fp32 centroid is split into three bf16 terms that add up to it exactly, so the products are exact and
+// only the fp32 accumulation rounds.  Per wave: TT tiles of 16 tokens as the B operand (kept in registers), 16-centroid
+// tiles as the A operand (from LDS), D[centroid 4*quad+i][token col]: a lane keeps the best of its four centroid rows
+// for one token per tile, so that the index costs one register per tile and only the four quads are merged at the end
+// (with the operands the other way round, sixteen columns of four tokens each had to be merged).
+template <int DM, int TT, bool ACCUM>
+__global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, RoundGrid r, const bf16_t* __restrict__ keys,
+                                                             const float* __restrict__ cent, uint8_t* __restrict__ codes,
+                                                             unsigned long long* __restrict__ part_sums,
+                                                             unsigned* __restrict__ part_counts) {
+  constexpr int NT = 1024, NW = NT / 64, KK = DM / 32, RS = mfma_term_stride(DM);
+  extern __shared__ __attribute__((aligned(16))) unsigned char round_lds[];
+  const int rows = (r.staged + 15) / 16 * 16;
+  unsigned short* ct = reinterpret_cast<unsigned short*>(round_lds);  // [3][rows * RS]: hi, mid, lo terms
+  float* cn = reinterpret_cast<float*>(round_lds + (size_t)rows * RS * 6);
+  unsigned long long* sums = reinterpret_cast<unsigned long long*>(round_lds + mfma_stage_bytes(r.staged, DM));
+  unsigned* cnt = reinterpret_cast<unsigned*>(sums + s.C * (DM + 1));
+  int u, j, p;
+  round_place(s, r.ranges, u, j, p);
+  const int uj = u * s.M + j, tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6, col = lane & 15, quad = lane >> 4;
-  const bool one_group = s.C <= CG;  // then the centroids are staged once for all batches
-  for (int batch = 0; batch < kAssignBatches; ++batch) {
-    const int tok0 = (blockIdx.x * kAssignBatches + batch) * kAssignBatchTok + w * 16 * kAssignTiles;
-    if (blockIdx.x * kAssignMfmaTok + batch * kAssignBatchTok >= n_tokens) break;  // workgroup-uniform
-    // this wave's keys: tile tt, row col, dims 32*kk + 8*quad .. +7
-    bf16x8_t a[kAssignTiles][KK];
+  const int t_begin = p * r.tokens, t_end = min(s.N, t_begin + r.tokens);
+  const bool one_group = s.C <= r.staged;  // then the centroids are staged once
+  auto stage = [&](int c0) {
+    const int nc = min(r.staged, s.C - c0);
+    for (int i = tid; i < nc * DM; i += NT) {  // every value as three bf16 terms that add up to it exactly
+      const float v = cent[((size_t)uj * s.C + c0) * DM + i];
+      const unsigned h = bf16_round_bits(v);
+      const float r1 = v - __uint_as_float(h << 16);
+      const unsigned m = bf16_round_bits(r1);
+      const float r2 = r1 - __uint_as_float(m << 16);
+      const unsigned l = bf16_round_bits(r2);
+      const int o = (i / DM) * RS + (i % DM);
+      ct[o] = (unsigned short)h;
+      ct[rows * RS + o] = (unsigned short)m;
+      ct[2 * rows * RS + o] = (unsigned short)l;
+    }
+    // squared norms: four threads per centroid, a quarter of the dimensions each; rows that hold no centroid lose always
+    for (int cb = 0; cb < rows; cb += NT / 4) {
+      const int c = cb + (tid >> 2), seg = tid & 3;
+      const float4* cr = reinterpret_cast<const float4*>(cent + ((size_t)uj * s.C + c0 + min(c, nc - 1)) * DM + seg * (DM / 4));
+      float n2 = 0.0f;
 #pragma unroll
-    for (int tt = 0; tt < kAssignTiles; ++tt) {
-      const int t = min(tok0 + tt * 16 + col, n_tokens - 1);
-      const uint4* kp =
-          reinterpret_cast<const uint4*>(keys + (size_t)u * key_unit_stride + (size_t)t * kD + j * DM + 8 * quad);
+      for (int e = 0; e < DM / 16; ++e) {
+        const float4 v = cr[e];
+        n2 = fmaf(v.x, v.x, n2);
+        n2 = fmaf(v.y, v.y, n2);
+        n2 = fmaf(v.z, v.z, n2);
+        n2 = fmaf(v.w, v.w, n2);
+      }
+      n2 += dpp_f<0xB1>(0.0f, n2);
+      n2 += dpp_f<0x4E>(0.0f, n2);
+      if (seg == 0 && c < rows) cn[c] = c < nc ? n2 : INFINITY;
+    }
+    for (int i = tid; i < (rows - nc) * DM; i += NT) {  // (zero, so that no stale bits of LDS reach the products)
+      const int o = (nc + i / DM) * RS + (i % DM);
+      ct[o] = ct[rows * RS + o] = ct[2 * rows * RS + o] = 0;
+    }
+  };
+  if (one_group) stage(0);
+  if constexpr (ACCUM) {
+    for (int i = tid; i < s.C * (DM + 1); i += NT) sums[i] = 0ull;
+    for (int i = tid; i < s.C; i += NT) cnt[i] = 0u;
+  }
+  if (one_group) __syncthreads();
+  for (int b0 = t_begin; b0 < t_end; b0 += NW * 16 * TT) {  // workgroup-uniform
+    const int tok0 = b0 + w * 16 * TT;
+    const bool live = tok0 < t_end;  // wave-uniform
+    bf16x8_t x[TT][KK];              // tile tt: token col, dims 32*kk + 8*quad .. +7
+    float best[TT];
+    int bidx[TT];
+    if (live) {
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) {
-        const uint4 raw = kp[4 * kk];
-        __builtin_memcpy(&a[tt][kk], &raw, 16);
+      for (int tt = 0; tt < TT; ++tt) {
+        const int t = min(tok0 + tt * 16 + col, s.N - 1);
+        const uint4* kp = reinterpret_cast<const uint4*>(keys + ((size_t)u * s.cap + t) * kD + j * DM + 8 * quad);
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+          const uint4 raw = kp[4 * kk];
+          __builtin_memcpy(&x[tt][kk], &raw, 16);
+        }
       }
     }
-    float best[kAssignTiles][4];
-    int bidx[kAssignTiles][4];
 #pragma unroll
-    for (int tt = 0; tt < kAssignTiles; ++tt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        best[tt][i] = INFINITY;
-        bidx[tt][i] = 0;
-      }
-    for (int c0 = 0; c0 < s.C; c0 += CG) {
-      const int nc = min(CG, s.C - c0);
-      if (!(one_group && batch > 0)) {
+    for (int tt = 0; tt < TT; ++tt) {
+      best[tt] = INFINITY;
+      bidx[tt] = 0;
+    }
+    for (int c0 = 0; c0 < s.C; c0 += r.staged) {
+      if (!one_group) {
         __syncthreads();
-        // stage: split every centroid value into three bf16 terms that add up to it exactly
-        for (int i = tid; i < nc * DM; i += 256) {
-          const float v = cent[((size_t)uj * s.C + c0) * DM + i];
-          const unsigned h = bf16_round_bits(v);
-          const float r1 = v - __uint_as_float(h << 16);
-          const unsigned m = bf16_round_bits(r1);
-          const float r2 = r1 - __uint_as_float(m << 16);
-          const unsigned l = bf16_round_bits(r2);
-          const int o = (i / DM) * RS + (i % DM);
-          ct[0][o] = (unsigned short)h;
-          ct[1][o] = (unsigned short)m;
-          ct[2][o] = (unsigned short)l;
-        }
-        // squared norms: four threads per centroid, a quarter of the dimensions each
-        for (int cb = 0; cb < nc; cb += 64) {
-          const int c = cb + (tid >> 2), seg = tid & 3;
-          const float4* cr = reinterpret_cast<const float4*>(cent + ((size_t)uj * s.C + c0 + min(c, nc - 1)) * DM + seg * (DM / 4));
-          float n2 = 0.0f;
-#pragma unroll
-          for (int e = 0; e < DM / 16; ++e) {
-            const float4 v = cr[e];
-            n2 = fmaf(v.x, v.x, n2);
-            n2 = fmaf(v.y, v.y, n2);
-            n2 = fmaf(v.z, v.z, n2);
-            n2 = fmaf(v.w, v.w, n2);
-          }
-          n2 += dpp_f<0xB1>(0.0f, n2);
-          n2 += dpp_f<0x4E>(0.0f, n2);
-          if (seg == 0 && c < nc) cn[c] = n2;
-        }
+        stage(c0);
         __syncthreads();
       }
+      if (!live) continue;
+      const int nc = min(r.staged, s.C - c0);
       for (int nt = 0; nt * 16 < nc; ++nt) {
-        const int c = nt * 16 + col;  // this lane's centroid column
-        const bool live = c < nc;
-        bf16x8_t b[3][KK];
+        bf16x8_t a[3][KK];  // centroid row nt*16 + col
 #pragma unroll
         for (int term = 0; term < 3; ++term)
 #pragma unroll
           for (int kk = 0; kk < KK; ++kk) {
-            const uint4 raw = *reinterpret_cast<const uint4*>(&ct[term][min(c, nc - 1) * RS + 32 * kk + 8 * quad]);
-            __builtin_memcpy(&b[term][kk], &raw, 16);
+            const uint4 raw = *reinterpret_cast<const uint4*>(&ct[(term * rows + nt * 16 + col) * RS + 32 * kk + 8 * quad]);
+            __builtin_memcpy(&a[term][kk], &raw, 16);
           }
-        const float cnv = live ? cn[c] : INFINITY;
+        const f32x4_t cnv = *reinterpret_cast<const f32x4_t*>(&cn[nt * 16 + 4 * quad]);
+        const int c = c0 + nt * 16 + 4 * quad;
 #pragma unroll
-        for (int tt = 0; tt < kAssignTiles; ++tt) {
+        for (int tt = 0; tt < TT; ++tt) {
           f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
             for (int term = 2; term >= 0; --term)  // small terms first
-              acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[tt][kk], b[term][kk], acc, 0, 0, 0);
+              acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[term][kk], x[tt][kk], acc, 0, 0, 0);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {  // token 4*quad + i of the tile against centroid c
-            const float sc = fmaf(-2.0f, acc[i], cnv);
-            if (sc < best[tt][i]) {  // strict: an earlier (lower) centroid of this lane keeps a tie
-              best[tt][i] = sc;
-              bidx[tt][i] = c0 + c;
+          for (int i = 0; i < 4; ++i) {
+            const float sc = fmaf(-2.0f, acc[i], cnv[i]);
+            if (sc < best[tt]) {  // strict: an earlier (lower) centroid of this lane keeps a tie
+              best[tt] = sc;
+              bidx[tt] = c + i;
             }
           }
         }
       }
     }
-    // merge the 16 columns of a row of lanes; equal values: lower centroid index
+    if (!live) continue;
+    // merge the four quads; equal values: lower centroid index
 #pragma unroll
-    for (int tt = 0; tt < kAssignTiles; ++tt)
+    for (int tt = 0; tt < TT; ++tt) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float v = best[tt][i];
-        int x = bidx[tt][i];
-        auto take = [&](float ov, int ox) {
-          const bool t = ov < v || (ov == v && ox < x);
-          v = t ? ov : v;
-          x = t ? ox : x;
-        };
-        take(dpp_f<0xB1>(v, v), dpp_i<0xB1>(x, x));
-        take(dpp_f<0x4E>(v, v), dpp_i<0x4E>(x, x));
-        take(dpp_f<0x141>(v, v), dpp_i<0x141>(x, x));
-        take(dpp_f<0x140>(v, v), dpp_i<0x140>(x, x));
-        const int t = tok0 + tt * 16 + 4 * quad + i;
-        if (col == 0 && t < n_tokens) codes[((size_t)u * s.cap + code_pos0 + t) * s.M + j] = (uint8_t)x;
+      for (int o = 16; o <= 32; o <<= 1) {
+        const float ov = __shfl_xor(best[tt], o);
+        const int oi = __shfl_xor(bidx[tt], o);
+        const bool take = ov < best[tt] || (ov == best[tt] && oi < bidx[tt]);
+        best[tt] = take ? ov : best[tt];
+        bidx[tt] = take ? oi : bidx[tt];
       }
+    }
+    if constexpr (ACCUM) {
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) {
+        if (tok0 + tt * 16 + col < t_end) {
+          unsigned long long* row = sums + bidx[tt] * (DM + 1) + 8 * quad;
+          if (quad == 0) atomicAdd(&cnt[bidx[tt]], 1u);
+#pragma unroll
+          for (int kk = 0; kk < KK; ++kk) {
+            unsigned rw[4];
+            __builtin_memcpy(rw, &x[tt][kk], 16);
+            float f[8], top = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              f[2 * e] = __uint_as_float(rw[e] << 16);
+              f[2 * e + 1] = __uint_as_float(rw[e] & 0xffff0000u);
+              top = fmaxf(fmaxf(fabsf(f[2 * e]), fabsf(f[2 * e + 1])), top);
+            }
+            if (__builtin_expect(!(top < 1073741824.0f), 0)) {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) atomicAdd(&row[32 * kk + e], fix_biased_large(f[e]));
+            } else {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) atomicAdd(&row[32 * kk + e], fix_biased(f[e]));
+            }
+          }
+        }
+      }
+    } else {
+      // lane (quad, col) writes the code of token col of tile 4*k + quad: one store for four tiles
+      uint8_t* cp = codes + ((size_t)u * s.cap) * s.M + j;
+#pragma unroll
+      for (int k = 0; k < TT; k += 4) {
+        int code = bidx[k];
+#pragma unroll
+        for (int y = 1; y < 4; ++y)
+          if (k + y < TT) code = quad == y ? bidx[k + y < TT ? k + y : 0] : code;
+        const int t = tok0 + (k + quad) * 16 + col;
+        if (k + quad < TT && t < t_end) cp[(size_t)t * s.M] = (uint8_t)code;
+      }
+    }
+  }
+  if constexpr (ACCUM) {
+    __syncthreads();
+    round_flush(s, uj * r.ranges + p, sums, cnt, part_sums, part_counts);
+  }
+}
+
+// fp32 keys, and sub-vectors of 16 dimensions: on the vector ALU, distances as sum_e (x_e - c_e)^2, e ascending.  Four
+// lanes share a token (lane = 16*quad + token): quad q runs the chains of centroids q, q+4, ..., so that short caches
+// still occupy the chip (a single fp32 head of 10007 tokens is 157 waves at one token per lane), and adds the
+// dimensions q, q+4, ... of the key to the sums.
+template <int DM>
+constexpr int round_vector_threads() { return DM >= 128 ? 512 : 1024; }
+template <typename T, int DM, bool ACCUM>
+__global__ __launch_bounds__(round_vector_threads<DM>()) void pq_round_vector_kernel(BuildShape s, RoundGrid r, const T* __restrict__ keys,
+                                                                                     const float* __restrict__ cent,
+                                                                                     uint8_t* __restrict__ codes,
+                                                                                     unsigned long long* __restrict__ part_sums,
+                                                                                     unsigned* __restrict__ part_counts) {
+  constexpr int NT = round_vector_threads<DM>(), NW = NT / 64, RS = DM + 4;
+  extern __shared__ __attribute__((aligned(16))) unsigned char round_lds[];
+  float* cs = reinterpret_cast<float*>(round_lds);  // [staged][RS]
+  unsigned long long* sums = reinterpret_cast<unsigned long long*>(round_lds + vector_stage_bytes(r.staged, DM));
+  unsigned* cnt = reinterpret_cast<unsigned*>(sums + s.C * (DM + 1));
+  int u, j, p;
+  round_place(s, r.ranges, u, j, p);
+  const int uj = u * s.M + j, tid = threadIdx.x;
+  const int lane = tid & 63, w = tid >> 6, col = lane & 15, quad = lane >> 4;
+  const int t_begin = p * r.tokens, t_end = min(s.N, t_begin + r.tokens);
+  const bool one_group = s.C <= r.staged;
+  auto stage = [&](int c0) {
+    const int nc = min(r.staged, s.C - c0);
+    const f32x4_t* src = reinterpret_cast<const f32x4_t*>(cent + ((size_t)uj * s.C + c0) * DM);
+    for (int i = tid; i < nc * (DM / 4); i += NT) *reinterpret_cast<f32x4_t*>(&cs[(i / (DM / 4)) * RS + 4 * (i % (DM / 4))]) = src[i];
+  };
+  if (one_group) stage(0);
+  if constexpr (ACCUM) {
+    for (int i = tid; i < s.C * (DM + 1); i += NT) sums[i] = 0ull;
+    for (int i = tid; i < s.C; i += NT) cnt[i] = 0u;
+  }
+  if (one_group) __syncthreads();
+  for (int b0 = t_begin; b0 < t_end; b0 += NW * 16) {  // workgroup-uniform
+    const int tok0 = b0 + w * 16;
+    const bool live = tok0 < t_end;  // wave-uniform
+    float x[DM];
+    if (live) {
+      const T* kp = keys + ((size_t)u * s.cap + min(tok0 + col, s.N - 1)) * kD + j * DM;
+      constexpr int EPV = 16 / (int)sizeof(T);
+#pragma unroll
+      for (int v = 0; v < DM / EPV; ++v) {
+        const uint4 raw = reinterpret_cast<const uint4*>(kp)[v];
+        const unsigned rw[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if constexpr (sizeof(T) == 2) {
+            x[v * EPV + 2 * e] = __uint_as_float(rw[e] << 16);
+            x[v * EPV + 2 * e + 1] = __uint_as_float(rw[e] & 0xffff0000u);
+          } else {
+            x[v * EPV + e] = __uint_as_float(rw[e]);
+          }
+        }
+      }
+    }
+    float best = INFINITY;
+    int arg = 0;
+    for (int c0 = 0; c0 < s.C; c0 += r.staged) {
+      if (!one_group) {
+        __syncthreads();
+        stage(c0);
+        __syncthreads();
+      }
+      if (!live) continue;
+      const int nc = min(r.staged, s.C - c0);
+      for (int c = quad; c < nc; c += 4) {
+        const f32x4_t* cr = reinterpret_cast<const f32x4_t*>(&cs[c * RS]);
+        float d2 = 0.0f;
+#pragma unroll
+        for (int e = 0; e < DM / 4; ++e) {
+          const f32x4_t cv = cr[e];
+#pragma unroll
+          for (int y = 0; y < 4; ++y) {
+            const float df = x[4 * e + y] - cv[y];
+            d2 = fmaf(df, df, d2);
+          }
+        }
+        if (d2 < best) {
+          best = d2;
+          arg = c0 + c;
+        }
+      }
+    }
+    if (!live) continue;
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {  // equal values: lower centroid index
+      const float ov = __shfl_xor(best, o);
+      const int oi = __shfl_xor(arg, o);
+      const bool take = ov < best || (ov == best && oi < arg);
+      best = take ? ov : best;
+      arg = take ? oi : arg;
+    }
+    const int t = tok0 + col;
+    if constexpr (ACCUM) {
+      if (t < t_end) {
+        unsigned long long* row = sums + arg * (DM + 1) + quad;
+        if (quad == 0) atomicAdd(&cnt[arg], 1u);
+#pragma unroll
+        for (int e = 0; e < DM / 4; ++e) {
+          const float v = quad == 0 ? x[4 * e] : quad == 1 ? x[4 * e + 1] : quad == 2 ? x[4 * e + 2] : x[4 * e + 3];
+          atomicAdd(&row[4 * e], __builtin_expect(!(fabsf(v) < 1073741824.0f), 0) ? fix_biased_large(v) : fix_biased(v));
+        }
+      }
+    } else {
+      if (quad == 0 && t < t_end) codes[((size_t)u * s.cap + t) * s.M + j] = (uint8_t)arg;
+    }
+  }
+  if constexpr (ACCUM) {
+    __syncthreads();
+    round_flush(s, uj * r.ranges + p, sums, cnt, part_sums, part_counts);
   }
 }
 
@@ -363,14 +543,34 @@ __global__ __launch_bounds__(256) void pq_accum_kernel(BuildShape s, const T* __
   }
 }
 
-// cent = sums / counts where counts > 0
-__global__ __launch_bounds__(256) void pq_mean_kernel(BuildShape s, const unsigned long long* __restrict__ sums,
+// cent = sums / counts where counts > 0, the sums and counts of a (unit, partition)'s token ranges added up
+__global__ __launch_bounds__(256) void pq_mean_kernel(BuildShape s, int ranges, const unsigned long long* __restrict__ sums,
                                                       const unsigned* __restrict__ counts, float* __restrict__ cent) {
-  const size_t i = blockIdx.x * (size_t)256 + threadIdx.x;
-  const size_t n = (size_t)s.units * s.M * s.C * s.Dm;
+  constexpr int U = 8;
+  const int n = s.C * s.Dm, i = blockIdx.x * 256 + threadIdx.x;
+  const size_t uj = blockIdx.y;
   if (i >= n) return;
-  const unsigned k = counts[i / s.Dm];
-  if (k) cent[i] = (float)((double)(long long)sums[i] * (1.0 / (double)(1 << kFixShift)) / (double)k);
+  const int c = i / s.Dm;
+  unsigned long long tot = 0ull;
+  unsigned k = 0u;
+  for (int p0 = 0; p0 < ranges; p0 += U) {
+    unsigned long long v[U];
+    unsigned m[U];
+#pragma unroll
+    for (int x = 0; x < U; ++x) {
+      const size_t slot = uj * ranges + min(p0 + x, ranges - 1);
+      v[x] = sums[slot * n + i];
+      m[x] = counts[slot * s.C + c];
+    }
+    PQC_LOADS_ISSUED();
+#pragma unroll
+    for (int x = 0; x < U; ++x)
+      if (p0 + x < ranges) {
+        tot += v[x];
+        k += m[x];
+      }
+  }
+  if (k) cent[uj * n + i] = (float)((double)(long long)tot * (1.0 / (double)(1 << kFixShift)) / (double)k);
 }
 
 // ------------------------------------------------------------ block statistics
