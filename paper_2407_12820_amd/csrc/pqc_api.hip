@@ -746,7 +746,7 @@ int make_build_plan(const pqc_config* cfg, BuildPlan* bp) {
 
 // One launch over all token ranges: with sums a K-Means round, without it the assignment (codes written).
 template <typename T, int DM, bool ACCUM>
-void launch_round_d(const BuildPlan& bp, const T* keys, const float* cent, uint8_t* codes, unsigned long long* sums, unsigned* counts,
+void launch_round_d(const BuildPlan& bp, const T* keys, float* cent, uint8_t* codes, unsigned long long* sums, unsigned* counts,
                     hipStream_t st) {
   const BuildShape& s = bp.s;
   const RoundGrid& r = ACCUM ? bp.round : bp.assign;
@@ -767,7 +767,7 @@ void launch_round_d(const BuildPlan& bp, const T* keys, const float* cent, uint8
   }
 }
 template <typename T, bool ACCUM>
-void launch_round(const BuildPlan& bp, const T* keys, const float* cent, uint8_t* codes, unsigned long long* sums, unsigned* counts,
+void launch_round(const BuildPlan& bp, const T* keys, float* cent, uint8_t* codes, unsigned long long* sums, unsigned* counts,
                   hipStream_t st) {
   switch (bp.s.Dm) {
     case 16: launch_round_d<T, 16, ACCUM>(bp, keys, cent, codes, sums, counts, st); break;
@@ -778,7 +778,7 @@ void launch_round(const BuildPlan& bp, const T* keys, const float* cent, uint8_t
 }
 template <typename T>
 void launch_assign(const BuildPlan& bp, const T* keys, const float* cent, uint8_t* codes, hipStream_t st) {
-  launch_round<T, false>(bp, keys, cent, codes, nullptr, nullptr, st);
+  launch_round<T, false>(bp, keys, const_cast<float*>(cent), codes, nullptr, nullptr, st);  // read only without sums
 }
 
 template <typename T>
@@ -807,7 +807,8 @@ int pq_build_t(const BuildPlan& bp, const T* keys, const int32_t* init_idx, int 
         default: hipLaunchKernelGGL((pq_accum_kernel<T, 128>), grid, dim3(256), lds, st, s, keys, codes, sums, counts); break;
       }
     }
-    hipLaunchKernelGGL(pq_mean_kernel, per_cent, dim3(256), 0, st, s, bp.fused ? bp.round.ranges : 1, sums, counts, cent);
+    if (!bp.fused || bp.round.ranges > 1)  // (one range: the round has written the means)
+      hipLaunchKernelGGL(pq_mean_kernel, per_cent, dim3(256), 0, st, s, bp.fused ? bp.round.ranges : 1, sums, counts, cent);
   }
   launch_assign<T>(bp, keys, cent, codes, st);
   return hipGetLastError() == hipSuccess ? PQC_OK : PQC_EHIP;

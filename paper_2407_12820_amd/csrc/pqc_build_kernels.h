@@ -113,14 +113,26 @@ __device__ __forceinline__ void round_place(const BuildShape& s, int ranges, int
   p = item % ranges;
 }
 
-__device__ __forceinline__ void round_flush(const BuildShape& s, int slot, const unsigned long long* sums, const unsigned* cnt,
-                                            unsigned long long* __restrict__ part_sums, unsigned* __restrict__ part_counts) {
-  const int n = s.C * s.Dm;
+__device__ __forceinline__ float fixed_mean(unsigned long long sum, unsigned count) {
+  return (float)((double)(long long)sum * (1.0 / (double)(1 << kFixShift)) / (double)count);
+}
+
+// The accumulators to the workspace; a workgroup that owns all tokens of its (unit, partition) writes the new centroids
+// itself (nobody else reads them in this launch, and it has staged the old ones).
+__device__ __forceinline__ void round_flush(const BuildShape& s, int ranges, int uj, int p, const unsigned long long* sums,
+                                            const unsigned* cnt, float* __restrict__ cent, unsigned long long* __restrict__ part_sums,
+                                            unsigned* __restrict__ part_counts) {
+  const int n = s.C * s.Dm, slot = uj * ranges + p;
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
     const int c = i / s.Dm, e = i - c * s.Dm;
-    part_sums[(size_t)slot * n + i] = sums[c * (s.Dm + 1) + e] - (unsigned long long)cnt[c] * (unsigned long long)kFixBiasBits;
+    const unsigned long long v = sums[c * (s.Dm + 1) + e] - (unsigned long long)cnt[c] * (unsigned long long)kFixBiasBits;
+    if (ranges > 1)
+      part_sums[(size_t)slot * n + i] = v;
+    else if (cnt[c])
+      cent[(size_t)uj * n + i] = fixed_mean(v, cnt[c]);
   }
-  for (int i = threadIdx.x; i < s.C; i += blockDim.x) part_counts[(size_t)slot * s.C + i] = cnt[i];
+  if (ranges > 1)
+    for (int i = threadIdx.x; i < s.C; i += blockDim.x) part_counts[(size_t)slot * s.C + i] = cnt[i];
 }
 
 // bf16 keys and sub-vectors of 32, 64 or 128 dimensions: the assignment is a dense contraction (tokens x dimensions by
@@ -132,10 +144,14 @@ __device__ __forceinline__ void round_flush(const BuildShape& s, int slot, const
 // (with the operands the other way round, sixteen columns of four tokens each had to be merged).
 template <int DM, int TT, bool ACCUM>
 __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, RoundGrid r, const bf16_t* __restrict__ keys,
-                                                             const float* __restrict__ cent, uint8_t* __restrict__ codes,
+                                                             float* cent, uint8_t* __restrict__ codes,
                                                              unsigned long long* __restrict__ part_sums,
                                                              unsigned* __restrict__ part_counts) {
   constexpr int NT = 1024, NW = NT / 64, KK = DM / 32, RS = mfma_term_stride(DM);
+  // With short sub-vectors the comparisons, not the matrix products, bound the kernel: then the four scores of the best
+  // tile are kept (12 instructions for four scores instead of 16) and which of them it was is found at the end; with
+  // longer ones the products hide them and the registers hold keys.
+  constexpr bool KEEP = DM == 32;
   extern __shared__ __attribute__((aligned(16))) unsigned char round_lds[];
   const int rows = (r.staged + 15) / 16 * 16;
   unsigned short* ct = reinterpret_cast<unsigned short*>(round_lds);  // [3][rows * RS]: hi, mid, lo terms
@@ -194,8 +210,9 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
     const int tok0 = b0 + w * 16 * TT;
     const bool live = tok0 < t_end;  // wave-uniform
     bf16x8_t x[TT][KK];              // tile tt: token col, dims 32*kk + 8*quad .. +7
-    float best[TT];
-    int bidx[TT];
+    float best[TT];    // smallest score of this lane's centroid rows for the token
+    f32x4_t kept[TT];  // KEEP: the four scores of the tile of centroids that holds it
+    int bidx[TT];      // its centroid (KEEP: the first of those four)
     if (live) {
 #pragma unroll
       for (int tt = 0; tt < TT; ++tt) {
@@ -211,6 +228,7 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
       best[tt] = INFINITY;
+      kept[tt] = f32x4_t{INFINITY, INFINITY, INFINITY, INFINITY};
       bidx[tt] = 0;
     }
     for (int c0 = 0; c0 < s.C; c0 += r.staged) {
@@ -241,11 +259,21 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
             for (int term = 2; term >= 0; --term)  // small terms first
               acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[term][kk], x[tt][kk], acc, 0, 0, 0);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float sc = fmaf(-2.0f, acc[i], cnv[i]);
-            if (sc < best[tt]) {  // strict: an earlier (lower) centroid of this lane keeps a tie
-              best[tt] = sc;
-              bidx[tt] = c + i;
+          for (int i = 0; i < 4; ++i) acc[i] = fmaf(-2.0f, acc[i], cnv[i]);
+          // strict comparisons: an earlier (lower) centroid of this lane keeps a tie
+          if constexpr (KEEP) {
+            const float low = fminf(fminf(fminf(fminf(best[tt], acc[0]), acc[1]), acc[2]), acc[3]);
+            const bool lower = low < best[tt];
+            best[tt] = low;
+            bidx[tt] = lower ? c : bidx[tt];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) kept[tt][i] = lower ? acc[i] : kept[tt][i];
+          } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const bool lower = acc[i] < best[tt];
+              best[tt] = lower ? acc[i] : best[tt];
+              bidx[tt] = lower ? c + i : bidx[tt];
             }
           }
         }
@@ -255,6 +283,7 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
     // merge the four quads; equal values: lower centroid index
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
+      if constexpr (KEEP) bidx[tt] += kept[tt][0] == best[tt] ? 0 : kept[tt][1] == best[tt] ? 1 : kept[tt][2] == best[tt] ? 2 : 3;
 #pragma unroll
       for (int o = 16; o <= 32; o <<= 1) {
         const float ov = __shfl_xor(best[tt], o);
@@ -307,7 +336,7 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
   }
   if constexpr (ACCUM) {
     __syncthreads();
-    round_flush(s, uj * r.ranges + p, sums, cnt, part_sums, part_counts);
+    round_flush(s, r.ranges, uj, p, sums, cnt, cent, part_sums, part_counts);
   }
 }
 
@@ -319,7 +348,7 @@ template <int DM>
 constexpr int round_vector_threads() { return DM >= 128 ? 512 : 1024; }
 template <typename T, int DM, bool ACCUM>
 __global__ __launch_bounds__(round_vector_threads<DM>()) void pq_round_vector_kernel(BuildShape s, RoundGrid r, const T* __restrict__ keys,
-                                                                                     const float* __restrict__ cent,
+                                                                                     float* cent,
                                                                                      uint8_t* __restrict__ codes,
                                                                                      unsigned long long* __restrict__ part_sums,
                                                                                      unsigned* __restrict__ part_counts) {
@@ -421,7 +450,7 @@ __global__ __launch_bounds__(round_vector_threads<DM>()) void pq_round_vector_ke
   }
   if constexpr (ACCUM) {
     __syncthreads();
-    round_flush(s, uj * r.ranges + p, sums, cnt, part_sums, part_counts);
+    round_flush(s, r.ranges, uj, p, sums, cnt, cent, part_sums, part_counts);
   }
 }
 
@@ -570,7 +599,7 @@ __global__ __launch_bounds__(256) void pq_mean_kernel(BuildShape s, int ranges, 
         k += m[x];
       }
   }
-  if (k) cent[uj * n + i] = (float)((double)(long long)tot * (1.0 / (double)(1 << kFixShift)) / (double)k);
+  if (k) cent[uj * n + i] = fixed_mean(tot, k);
 }
 
 // ------------------------------------------------------------ block statistics
