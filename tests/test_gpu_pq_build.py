@@ -193,6 +193,56 @@ def test_build_at_full_length_matches_oracle(pqc, name, T):
     print(f"[result] {name}: {near} near-tie codes of {cd_ref.size}", flush=True)
 
 
+# One round and the assignment at the edges of the kernels' tiles and ranges: fewer tokens than a 16-token tile, one more than a
+# tile, one more than a wave's and a workgroup's batch, one range and several per (unit, partition), accumulators that do not fit
+# LDS (two partitions of 256), centroids staged in groups (one partition of 256), 16-dimensional sub-vectors, centroid counts
+# that are not a multiple of 16, fp32 keys of every sub-vector length; "huge": keys beyond 2^30, which are converted another way.
+@pytest.mark.parametrize("dtype,m,c,n,units,kind", [
+    ("bf16", 2, 64, 1, 1, ""), ("bf16", 2, 64, 17, 3, ""), ("bf16", 4, 256, 2049, 2, ""), ("bf16", 4, 7, 129, 2, ""),
+    ("bf16", 4, 256, 300, 96, ""), ("bf16", 2, 256, 1000, 2, ""), ("bf16", 1, 256, 700, 2, ""), ("bf16", 1, 20, 2100, 1, ""),
+    ("bf16", 8, 200, 500, 2, ""), ("f32", 8, 33, 257, 2, ""), ("f32", 4, 256, 1000, 1, ""), ("f32", 2, 64, 15, 2, ""),
+    ("f32", 1, 256, 600, 1, ""), ("f32", 1, 9, 513, 2, ""), ("bf16", 2, 48, 1600, 2, "huge"), ("f32", 4, 16, 400, 2, "huge"),
+    ("bf16", 4, 32, 900, 2, "twins"), ("bf16", 2, 32, 900, 2, "twins"), ("f32", 2, 32, 900, 2, "twins"),
+])
+def test_round_edges(pqc, dtype, m, c, n, units, kind):
+    w = wl.Workload(name="round", batch=units, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=n, pq_m=m, pq_centroids=c,
+                    topk=1 if n < 80 else n // 4, n_init=0, n_local=0, dtype=dtype, kmeans_iters=1, recipe="plain")
+    print(f"[case] round edges {dtype} m={m} c={c} n={n} units={units} {kind}", flush=True)
+    d = wl.generate(w, seed=n + c)
+    rng = np.random.default_rng(n)
+    kf = wl.to_f32(d["k"], dtype).copy()
+    if kind == "huge":
+        kf[rng.random(kf.shape[:3]) < 0.05] *= 3.0e9
+    keys_h = kf if dtype == "f32" else wl.f32_to_bf16_bits(kf)
+    kf = wl.to_f32(keys_h, dtype)
+    init = wl.kmeans_init_indices(w, seed=3)
+    if kind == "twins":  # every centroid twice: the lower index must take all members
+        init[..., 1::2] = init[..., 0::2]
+    keys, init_d = pqc.to_device(keys_h, dtype, DEV), torch.from_numpy(init).to(DEV)
+    c0, cd0 = pqc.pq_build(w, keys, init_d, iters=0)
+    c1, cd1 = pqc.pq_build(w, keys, init_d, iters=1)
+    torch.cuda.synchronize()
+    c0, cd0, c1, cd1 = c0.cpu().numpy(), cd0.cpu().numpy(), c1.cpu().numpy(), cd1.cpu().numpy()
+    c0_ref, cd0_ref, _ = oracle.pq_build(keys_h, dtype, m, c, 0, init)
+    np.testing.assert_array_equal(c0, c0_ref)
+    if kind == "twins":
+        assert np.all(cd0 % 2 == 0)
+    if kind != "huge":  # (|c|^2 - 2 x.c of magnitudes far apart: the comparison rule of near-ties does not fit)
+        assert _codes_agree(kf, c0_ref, cd0, cd0_ref, m) <= 1 + 1e-3 * cd0.size
+        want = np.stack([oracle.nearest_codes(np.ascontiguousarray(keys_h[:, :, t]), dtype, c1) for t in range(n)], axis=2)
+        assert _codes_agree(kf, c1, cd1, want, m) <= 1 + 1e-3 * cd1.size
+    Dm = 128 // m
+    for u in range(units):
+        for j in range(m):
+            x = kf[u, 0, :, j * Dm:(j + 1) * Dm].astype(np.float64)
+            for k in range(c):
+                members = cd0[u, 0, :, j] == k
+                want = x[members].mean(0) if members.any() else c0[u, 0, j, k].astype(np.float64)
+                # 2^-20 per key and one fp32 rounding; the mean of keys of both signs may cancel
+                tol = 2e-6 * (1.0 + np.abs(want)) + (2.0 ** -20 if kind != "huge" else np.abs(x[members]).max(initial=1.0) * 2.0 ** -24)
+                assert np.all(np.abs(c1[u, 0, j, k] - want) <= tol), (u, j, k)
+
+
 def test_encode_token_writes_nearest_codes_in_place(pqc):
     w = wl.get("batch8_32k", batch=3, n_tokens=700)
     d = wl.generate(w, seed=13)
