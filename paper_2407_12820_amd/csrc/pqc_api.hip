@@ -3,7 +3,6 @@
 // nothing synchronises the host: every entry point only enqueues kernels.
 #include "../../include/pqcache.h"
 
-#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -20,13 +19,9 @@ using namespace pqc;
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
-constexpr size_t kCleared = kHistCopies * kNB + 2;  // words per unit that a call finds zero: histogram replicas, ticket, slot counter;
-                                                    // behind those of all units, two words per select workgroup
-constexpr int kWorkgroups = 256;                    // of the histogram and select kernels over all units: one per compute unit
-
 struct Plan {
   Shape s;
-  size_t off_ctl, off_lut, off_range, off_hist, off_bins, off_crec, off_ctok, off_part, off_trace, total;
+  size_t off_ctl, off_lut, off_range, off_hist, off_bins, off_crec, off_stage, off_cnt, off_part, off_trace, total;
   int rec_stride;
 };
 
@@ -45,27 +40,24 @@ int env_int(const char* name, int fallback) {
 }
 
 // Offsets of the workspace regions for the given per-unit sizes.
-void lay_out(Plan* p, size_t positions_per_unit, size_t workgroups_per_unit, size_t partials_per_unit) {
+void lay_out(Plan* p, size_t bins_per_unit, size_t stage_words_per_unit, size_t counts_per_unit, size_t partials_per_unit) {
   const Shape& s = p->s;
   const size_t units = (size_t)s.B * s.Hkv;
   size_t off = 0;
   p->off_ctl = off;   off = align_up(off + sizeof(BinParams) * units);
   p->off_lut = off;   off = align_up(off + sizeof(float) * units * s.M * s.C);
   p->off_range = off; off = align_up(off + sizeof(float2) * units);
-  p->off_hist = off;  off = align_up(off + sizeof(unsigned) * units * kCleared + sizeof(unsigned long long) * units * workgroups_per_unit);
-  p->off_bins = off;  off = align_up(off + sizeof(unsigned short) * units * positions_per_unit);
+  p->off_hist = off;  off = align_up(off + sizeof(unsigned) * units * (kHistCopies * kNB + 1));  // + record counters
+  p->off_bins = off;  off = align_up(off + sizeof(unsigned short) * units * bins_per_unit);
   p->off_crec = off;  off = align_up(off + (size_t)p->rec_stride * units);
-  p->off_ctok = off;  off = align_up(off + sizeof(int) * units * positions_per_unit);
+  p->off_stage = off; off = align_up(off + sizeof(unsigned long long) * units * stage_words_per_unit);
+  p->off_cnt = off;   off = align_up(off + sizeof(int2) * units * counts_per_unit);
   p->off_part = off;  off = align_up(off + sizeof(float) * units * partials_per_unit * s.G * (kD + 2));
 #ifdef PQC_TRACE
   p->off_trace = off; off = align_up(off + sizeof(unsigned long long) * 3 * kTraceWgs * kTraceSlots);
 #endif
   p->total = off;
 }
-
-// Most tokens per workgroup: kMaxVecA chunks of 16 codes per thread in the histogram kernel, kMaxVecC groups of 8 tokens per
-// lane in the select kernel.
-int max_tokens(int M) { return std::min(kMaxVecA * 1024 * (16 / M), kMaxVecC * kSelThreads * 8); }
 
 int make_plan(const pqc_config* c, Plan* p) {
   if (!c) return PQC_EINVAL;
@@ -94,31 +86,39 @@ int make_plan(const pqc_config* c, Plan* p) {
   s.scale_log2e = scale * 1.4426950408889634f;
   const long long units = (long long)s.B * s.Hkv;
 
-  // A unit's codes start at byte u*cap*M; when that is not always 16-byte aligned the first chunk of a unit begins with up to
-  // 15 phantom tokens that the grids must cover as well.
+  // A unit's codes start at byte u*cap*M; when that is not always 16-byte aligned the first
+  // chunk of a unit begins with up to 15 phantom tokens that the grids must cover as well.
   const int lead = ((long long)s.cap * s.M) % 16 == 0 ? 0 : 15;
-  // Both kernels give a workgroup the same tokens.  Both fill a compute unit with one workgroup (the histogram kernel builds
-  // the unit's whole table in every one, so few, large workgroups; the select kernel leaves one partial state each for the
-  // unit's last one to fold), so a unit gets its share of 256 workgroups; multiples of 256 tokens, at least 512.
-  int tok = env_int("PQC_TOK", 0);
-  if (!tok) {
-    const int share = units < kWorkgroups ? (int)(kWorkgroups / units) : 1;
-    tok = ((s.N + lead + share - 1) / share + 255) / 256 * 256;
-    if (tok < 512) tok = 512;
-    const int most = max_tokens(s.M);
-    if (tok > most) tok = most;
+  // histogram kernel: about one 1024-thread workgroup per compute unit over all units
+  const int maxA = 4096 * (16 / s.M) < 16384 ? 4096 * (16 / s.M) : 16384;  // kMaxVecA chunks per thread
+  int tokA = env_int("PQC_TOK_A", 0);
+  if (!tokA) {
+    // every workgroup builds the unit's whole table first, so few, large workgroups: 4096 tokens measured best
+    // from 32K to 128K tokens per unit (at 32K: 27.6 us per step against 28.3 with 1024)
+    tokA = 4096;
+    while (tokA < maxA && units * ((s.N + lead + tokA - 1) / tokA) > 320) tokA *= 2;
   }
-  if (tok % 256 || tok > max_tokens(s.M)) return PQC_EINVAL;
-  s.tok = tok;
-  s.nblk = (s.N + lead + tok - 1) / tok;
-#ifdef PQC_TRACE
-  s.forceLate = env_int("PQC_FORCE_LATE", 0);
-#endif
-  s.histCopies = s.nblk <= 32 ? 1 : s.nblk <= 64 ? 2 : kHistCopies;
+  if (tokA % 1024 || tokA > maxA) return PQC_EINVAL;
+  s.tokA = tokA; s.nblkA = (s.N + lead + tokA - 1) / tokA;
+  s.histCopies = s.nblkA <= 32 ? 1 : s.nblkA <= 64 ? 2 : kHistCopies;
+  // select kernel: 256-thread workgroups, two resident per compute unit
+  int tokC = env_int("PQC_TOK_C", 0);
+  if (!tokC) {
+    tokC = 512;
+    while (tokC < 8192 && units * ((s.N + tokC - 1) / tokC) > 512) tokC *= 2;
+  }
+  if (tokC != 512 && tokC != 1024 && tokC != 2048 && tokC != 4096 && tokC != 8192) return PQC_EINVAL;
+  s.tokC = tokC; s.nblkC = (s.N + tokC - 1) / tokC;
+  s.binStride = s.nblkC * s.tokC;
+  s.stageStride = s.tokC + 40;
   s.rowsP = env_int("PQC_ROWS_P", 256);
   s.nblkP = (s.Ktot + s.rowsP - 1) / s.rowsP;
-  s.npart = s.nblk > s.nblkP ? s.nblk : s.nblkP;
+  s.npart = s.nblkC > s.nblkP ? s.nblkC : s.nblkP;
   p->rec_stride = (int)cand_unit_bytes(G, c->kv_dtype == PQC_F32 ? 4 : 2);
+  // finalize kernel: as many workgroups per query head (each with its share of the output dimensions) as keep the
+  // grid within about two workgroups per compute unit
+  s.slices = 1;
+  while (s.slices < kMaxSlices && units * (2 * s.slices * G + kCopyWgs) <= 512) s.slices *= 2;
   // sample ranks that bracket the K-th largest score by 5 standard errors (+2)
   const int nmid = s.N - s.I - s.L;
   s.sampleN = nmid < 1024 ? (nmid > 0 ? nmid : 1) : 1024;
@@ -131,7 +131,7 @@ int make_plan(const pqc_config* c, Plan* p) {
     if (s.rankHi < 1) s.rankHi = 0;
   }
 
-  lay_out(p, (size_t)s.nblk * s.tok, (size_t)s.nblk, (size_t)s.npart);
+  lay_out(p, (size_t)s.binStride, (size_t)s.nblkC * s.stageStride, (size_t)s.nblkC, (size_t)s.npart);
   return PQC_OK;
 }
 
@@ -144,12 +144,15 @@ size_t workspace_bound(const pqc_config* c) {
   const Shape& s = p.s;
   if (s.cap == s.N) return p.total;
   const size_t units = (size_t)s.B * s.Hkv, cap = (size_t)s.cap;
-  // a unit has at most its share of the workgroups, or as many as the largest number of tokens per workgroup leaves
-  const size_t tok_most = env_int("PQC_TOK", 0) ? (size_t)env_int("PQC_TOK", 0) : (size_t)max_tokens(s.M);
-  const size_t nb = std::max(std::max((size_t)kWorkgroups / units, (size_t)1), (cap + 15 + tok_most - 1) / tok_most);
-  const size_t npart = std::max((cap + s.rowsP - 1) / s.rowsP, nb);
-  // positions: a workgroup's share is rounded up to 256, and the last workgroup is rounded up to its share
-  lay_out(&p, cap + 15 + 256 * nb + std::min((size_t)max_tokens(s.M), (cap + 15) / nb + 512), nb, npart);
+  // select kernel grid: tokens per workgroup double until the grid has at most 512 workgroups or
+  // they reach 8192 (an override by environment may pin them as low as 512)
+  const size_t tok_min = env_int("PQC_TOK_C", 0) ? (size_t)env_int("PQC_TOK_C", 0) : 8192;
+  size_t nb = 512 / units;
+  if (nb < (cap + tok_min - 1) / tok_min) nb = (cap + tok_min - 1) / tok_min;
+  if (nb < 1) nb = 1;
+  size_t npart = (cap + s.rowsP - 1) / s.rowsP;
+  if (npart < nb) npart = nb;
+  lay_out(&p, cap + 8192, cap + 8192 + 40 * nb, nb, npart);
   return p.total;
 }
 
@@ -181,7 +184,7 @@ int check_launch(pqc_ctx* ctx) {
   return PQC_OK;
 }
 
-// Histograms, tickets and slot counters must be zero when a call starts; the select kernel leaves them
+// Histograms and record counters must be zero when a call starts; finalize_kernel leaves them
 // so, which makes a completed call stateless (and a captured one replayable).
 int ensure_clean_hist(pqc_ctx* ctx, hipStream_t st) {
   if (ctx->next_phase != 0) {  // a step begun phase by phase (pqc_decode_phase) was left unfinished: its histogram is stale
@@ -190,7 +193,7 @@ int ensure_clean_hist(pqc_ctx* ctx, hipStream_t st) {
   }
   if (ctx->hist_clean) return PQC_OK;
   const Shape& s = ctx->plan.s;
-  const size_t na = (size_t)s.B * s.Hkv * kCleared + 2 * (size_t)s.B * s.Hkv * s.nblk;
+  const size_t na = (size_t)s.B * s.Hkv * (kHistCopies * kNB + 1);  // histograms and the record counters behind them
   hipLaunchKernelGGL(reset_kernel, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, st, ctx->ws.hist, na);
   return check_launch(ctx);
 }
@@ -200,8 +203,8 @@ int ensure_clean_hist(pqc_ctx* ctx, hipStream_t st) {
 // unit's M*C*Dm floats over 1024 threads) and of the codes or scores (VA: the workgroup's tokA tokens).
 template <typename T, class SRC, int VW>
 void launch_hist_w(const Shape& s, const Workspace& ws, const T* q, const float* cent, const void* src, size_t lds, hipStream_t st) {
-  const dim3 grid(s.nblk, (unsigned)(s.B * s.Hkv));
-  const int chunks = s.tok / SRC::P, va = (chunks + 1023) / 1024;
+  const dim3 grid(s.nblkA, (unsigned)(s.B * s.Hkv));
+  const int chunks = s.tokA / SRC::P, va = (chunks + 1023) / 1024;
   if (va <= 1)
     hipLaunchKernelGGL((hist_kernel<T, SRC, VW, 1>), grid, dim3(1024), lds, st, s, ws, q, cent, src);
   else if (va <= 2)
@@ -222,30 +225,37 @@ void launch_hist(const Shape& s, const Workspace& ws, const T* q, const float* c
   }
 }
 
-template <typename T, int G, class SRC, bool ATTN, int MODE>
-void launch_select(pqc_ctx* ctx, const T* q, const T* k, const T* v, const void* src, const float* cent, const unsigned* pair_counts,
-                   int32_t* out_idx, float* out_attn, hipStream_t st) {
+template <typename T, int G>
+void launch_finalize(pqc_ctx* ctx, const T* qt, const T* kt, const T* vt, int32_t* out_idx, float* out_attn, hipStream_t st) {
   const Shape& s = ctx->plan.s;
-  const AppendArgs& ap = ctx->append;
-  // the appended token's code: one more workgroup per unit, except with pair counts, which every workgroup reads
-  const dim3 grid(s.nblk + (ap.key && MODE == kFromHist ? 1 : 0), (unsigned)(s.B * s.Hkv));
-  const bool mfma = ATTN && sizeof(T) == 2 && kMatrixCoreAttention;
-  const SelectLds o = select_lds(G, sizeof(T), ATTN, mfma, MODE == kFromPairs, s.tok, s.nblk);
-  hipLaunchKernelGGL((select_kernel<T, G, SRC, ATTN, MODE>), grid, dim3(kSelThreads), (size_t)o.bytes, st, s, ctx->ws, q, k, v, src, cent,
-                     pair_counts, out_idx, out_attn, ap);
+  const dim3 grid(G * s.slices + kCopyWgs + (ctx->append.key ? 1 : 0), (unsigned)(s.B * s.Hkv));
+  // Tokens that share all their codes share a score: with few distinct code words the tie class at the threshold is
+  // large (131072 tokens over 64 x 64 code pairs: up to 70 candidates), and the kernel requests more records up front.
+  double words = 1.0;
+  for (int j = 0; j < s.M; ++j) words *= s.C;
+  if (s.slices == kMaxSlices && s.N >= 16.0 * words)
+    hipLaunchKernelGGL((finalize_kernel<T, G, true, true>), grid, dim3(256), finalize_lds_bytes(s, true), st, s, ctx->ws, qt, kt, vt,
+                       out_idx, out_attn, ctx->append);
+  else
+    hipLaunchKernelGGL((finalize_kernel<T, G, true, false>), grid, dim3(256), finalize_lds_bytes(s, true), st, s, ctx->ws, qt, kt, vt,
+                       out_idx, out_attn, ctx->append);
 }
 
-// phases: bit k set = phase k of the decode path (0 histogram, 1 select, attention and output; phase 2 has no launch)
+// phases: bit k set = launch kernel k of the decode path (0 histogram, 1 select + attention, 2 finalize)
 template <typename T, int G, int M>
 void launch_decode_tgm(pqc_ctx* ctx, const void* q, const float* cent, const uint8_t* codes, const void* k,
                        const void* v, int32_t* out_idx, float* out_attn, hipStream_t st, unsigned phases) {
   const Shape& s = ctx->plan.s;
+  const unsigned units = (unsigned)(s.B * s.Hkv);
   const T* qt = static_cast<const T*>(q);
-  const void* src = static_cast<const void*>(codes);
-  if (phases & 1u) launch_hist<T, CodeChunks<M>>(s, ctx->ws, qt, cent, src, sizeof(float) * lut_tile_floats(1024, M, s.C), st);
+  const T* kt = static_cast<const T*>(k);
+  const T* vt = static_cast<const T*>(v);
+  if (phases & 1u) launch_hist<T, CodeChunks<M>>(s, ctx->ws, qt, cent, static_cast<const void*>(codes), sizeof(float) * lut_tile_floats(1024, M, s.C), st);
   if (phases & 2u)
-    launch_select<T, G, CodeChunks<M>, true, kFromHist>(ctx, qt, static_cast<const T*>(k), static_cast<const T*>(v), src, nullptr, nullptr,
-                                                        out_idx, out_attn, st);
+    hipLaunchKernelGGL((select_kernel<T, G, CodeChunks<M>, true>), dim3(s.nblkC, units), dim3(256),
+                       s.tokC * sizeof(unsigned short), st, s, ctx->ws, qt, kt, vt, static_cast<const void*>(codes));
+  if (phases & 4u)
+    launch_finalize<T, G>(ctx, qt, kt, vt, out_idx, out_attn, st);
 }
 
 template <typename T, int G>
@@ -270,12 +280,19 @@ void launch_decode_t(pqc_ctx* ctx, const void* q, const float* cent, const uint8
   }
 }
 
-// decode with the threshold taken from code-pair counts (M = 2): no histogram kernel
+// decode with the threshold taken from code-pair counts (M = 2): select + finalize, no histogram kernel
 template <typename T, int G>
 void launch_indexed_tg(pqc_ctx* ctx, const void* q, const float* cent, const uint8_t* codes, const unsigned* pair_counts,
                        const void* k, const void* v, int32_t* out_idx, float* out_attn, hipStream_t st) {
-  launch_select<T, G, CodeChunks<2>, true, kFromPairs>(ctx, static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
-                                                       static_cast<const void*>(codes), cent, pair_counts, out_idx, out_attn, st);
+  const Shape& s = ctx->plan.s;
+  const unsigned units = (unsigned)(s.B * s.Hkv);
+  const T* qt = static_cast<const T*>(q);
+  const T* kt = static_cast<const T*>(k);
+  const T* vt = static_cast<const T*>(v);
+  hipLaunchKernelGGL((select_kernel<T, G, CodeChunks<2>, true, true>), dim3(s.nblkC, units), dim3(256),
+                     s.tokC * sizeof(unsigned short), st, s, ctx->ws, qt, kt, vt, static_cast<const void*>(codes), cent,
+                     pair_counts, ctx->append.key ? ctx->append.position : -1);
+  launch_finalize<T, G>(ctx, qt, kt, vt, out_idx, out_attn, st);
 }
 
 template <typename T>
@@ -368,14 +385,13 @@ void bind_workspace(pqc_ctx* ctx) {
   ctx->ws.ctl = reinterpret_cast<BinParams*>(base + p.off_ctl);
   ctx->ws.lut = reinterpret_cast<float*>(base + p.off_lut);
   ctx->ws.hist = reinterpret_cast<unsigned*>(base + p.off_hist);
-  ctx->ws.ticket = ctx->ws.hist + (size_t)p.s.B * p.s.Hkv * kHistCopies * kNB;
-  ctx->ws.cand_count = ctx->ws.ticket + (size_t)p.s.B * p.s.Hkv;
-  ctx->ws.counts = reinterpret_cast<unsigned long long*>(ctx->ws.cand_count + (size_t)p.s.B * p.s.Hkv);
+  ctx->ws.cand_count = ctx->ws.hist + (size_t)p.s.B * p.s.Hkv * kHistCopies * kNB;
   ctx->ws.range = reinterpret_cast<float2*>(base + p.off_range);
   ctx->ws.bins = reinterpret_cast<unsigned short*>(base + p.off_bins);
   ctx->ws.cand_rec = reinterpret_cast<unsigned char*>(base + p.off_crec);
   ctx->ws.rec_stride = p.rec_stride;
-  ctx->ws.cand_tok = reinterpret_cast<int*>(base + p.off_ctok);
+  ctx->ws.stage = reinterpret_cast<unsigned long long*>(base + p.off_stage);
+  ctx->ws.stage_cnt = reinterpret_cast<int2*>(base + p.off_cnt);
   ctx->ws.partials = reinterpret_cast<float*>(base + p.off_part);
 #ifdef PQC_TRACE
   ctx->ws.trace = reinterpret_cast<unsigned long long*>(base + p.off_trace);
@@ -415,9 +431,7 @@ int pqc_set_length(pqc_ctx* ctx, int32_t n_tokens, int32_t topk) {
   const int rc = make_plan(&c, &p);  // rejects a length beyond the capacity
   if (rc != PQC_OK) return rc;
   if (p.total > ctx->workspace_bytes) return PQC_EWORKSPACE;
-  // The cleared region does not move and stays clean, except that more workgroups per unit than before take words at its end
-  // that another region has used.
-  if (p.s.nblk > ctx->plan.s.nblk) ctx->hist_clean = false;
+  // The histogram region does not move and a clean one is all zero, whatever the length: it stays clean.
   ctx->cfg = c;
   ctx->plan = p;
   bind_workspace(ctx);
@@ -447,7 +461,7 @@ static int decode_impl(pqc_ctx* ctx, const void* q, const float* centroids, cons
     launch_decode_t<bf16_t>(ctx, q, centroids, codes, k_cache, v_cache, out_idx, out_attn, st, phases);
   rc = check_launch(ctx);
   if (rc == PQC_OK && (phases & 4u)) {
-    ctx->hist_clean = true;  // the select kernel zeroed them again
+    ctx->hist_clean = true;  // finalize_kernel zeroed them again
   }
   return rc;
 }
@@ -584,8 +598,10 @@ int pqc_topk(pqc_ctx* ctx, const float* scores, int32_t* out_idx, void* stream) 
   const float* nof = nullptr;
   hipLaunchKernelGGL(score_range_kernel, dim3(1, units), dim3(1024), 0, st, s, scores, ctx->ws.range);
   launch_hist<float, ScoreChunks>(s, ctx->ws, nof, nof, static_cast<const void*>(scores), 0, st);
-  launch_select<float, 1, ScoreChunks, false, kFromHist>(ctx, nof, nof, nof, static_cast<const void*>(scores), nof, nullptr, out_idx,
-                                                         nullptr, st);
+  hipLaunchKernelGGL((select_kernel<float, 1, ScoreChunks, false>), dim3(s.nblkC, units), dim3(256), s.tokC * sizeof(unsigned short), st,
+                     s, ctx->ws, nof, nof, nof, static_cast<const void*>(scores));
+  hipLaunchKernelGGL((finalize_kernel<float, 1, false>), dim3(1 + kCopyWgs, units), dim3(256), finalize_lds_bytes(s, false), st, s,
+                     ctx->ws, nof, nof, nof, out_idx, static_cast<float*>(nullptr), AppendArgs{nullptr, nullptr, nullptr, 0, nullptr});
   rc = check_launch(ctx);
   if (rc == PQC_OK) {
     ctx->hist_clean = true;

@@ -15,8 +15,7 @@ constexpr int kNB = 2048;        // score bins of the one-pass threshold search
 constexpr int kHistCopies = 4;   // histogram replica slots per unit; Shape::histCopies of them are in use
 constexpr int kD = 128;          // head dimension
 constexpr int kLutRow = 256;     // LDS stride of one partition's table (max centroids)
-constexpr int kCandRec = 1024;   // boundary-bin candidates per unit that are ranked against each other inside LDS
-constexpr int kCandRows = 128;   // of them, those whose logits and V rows are recorded
+constexpr int kCandRec = 1024;   // boundary-bin candidate records per unit (ranked inside LDS by the finalize kernel)
 constexpr float kNegBig = -1.0e30f;
 
 struct bf16_t {
@@ -31,37 +30,39 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 struct Shape {
   int B, Hq, Hkv, G, N, M, C, Dm, K, I, L, Ktot;
   int cap;          // tokens the K/V caches and the code tensor hold per unit (>= N): their stride between units
-  int tok, nblk;    // histogram and select kernels: tokens per workgroup (a multiple of 256), workgroups per unit
+  int tokA, nblkA;  // histogram kernel: tokens per workgroup, workgroups per unit
+  int tokC, nblkC;  // select kernel: tokens per workgroup, workgroups per unit
   int rowsP, nblkP; // list-attention kernel: rows per workgroup, workgroups per unit
   int npart;        // partial slots per unit
+  int slices;       // finalize kernel: workgroups per query head (1, 2 or 4), each producing kD/slices output dimensions
+  int binStride;    // stored bins per unit (nblkC * tokC)
+  int stageStride;  // 8-byte words between the staging slots of consecutive select workgroups: tokC plus a pad, so that
+                    // the slots do not all start on the same memory channels
   int histCopies;   // histogram replicas in use (1, 2 or 4): spreads the flush atomics of units with many workgroups
   int sampleN;      // tokens sampled per unit to place the fine bins (<= 1024)
   int rankHi, rankLo;  // sample ranks (from the top) that bracket the K-th largest score
   float scale_log2e;
-#ifdef PQC_TRACE
-  int forceLate;  // debug builds: treat every list as late
-#endif
 };
 
-// What a select workgroup leaves behind for every boundary-bin candidate, enough for the unit's last workgroup to rank
-// it and, if admitted, to add it to the attention output without touching the K/V cache again.  Per unit, as arrays over
-// the candidates, so that what the last workgroup reads of them is dense:
-//   composite  [kCandRec]       uint64   (score key, ~token): larger ranks first
-//   logit      [G][kCandRows]   float    q_h . k for the group's heads (raw, unscaled)
-//   v          [kCandRows][kD]  T        the V row
+// What a select workgroup leaves behind for every boundary-bin candidate, enough for the finalize kernel to rank it
+// and, if admitted, to add it to the attention output without touching the K/V cache again.  Per unit, as arrays
+// over the candidates in order of arrival (at most kCandRec), so that what a finalize workgroup reads of them is dense:
+//   composite  [kCandRec]      uint64   (score key, ~token): larger ranks first
+//   logit      [G][kCandRec]   float    q_h . k for the group's heads (raw, unscaled)
+//   v          [kCandRec][kD]  T        the V row
 struct CandView {
   unsigned long long* composite;
   float* logit;
   unsigned char* v;
 };
 __host__ __device__ constexpr size_t cand_unit_bytes(int G, int elem_bytes) {
-  return ((size_t)kCandRec * 8 + (size_t)G * kCandRows * 4 + (size_t)kCandRows * kD * elem_bytes + 255) / 256 * 256;
+  return ((size_t)kCandRec * 8 + (size_t)G * kCandRec * 4 + (size_t)kCandRec * kD * elem_bytes + 255) / 256 * 256;
 }
 __device__ __forceinline__ CandView cand_view(unsigned char* unit_base, int G) {
   CandView c;
   c.composite = reinterpret_cast<unsigned long long*>(unit_base);
   c.logit = reinterpret_cast<float*>(unit_base + (size_t)kCandRec * 8);
-  c.v = unit_base + (size_t)kCandRec * 8 + (size_t)G * kCandRows * 4;
+  c.v = unit_base + (size_t)kCandRec * 8 + (size_t)G * kCandRec * 4;
   return c;
 }
 
@@ -71,41 +72,18 @@ struct Workspace {
   BinParams* ctl;              // [units]                       score -> bin map of the unit
   float* lut;                  // [units][M][C]
   float2* range;               // [units]                       (min, max) score, stand-alone top-k only
-  unsigned* hist;              // [units][histCopies][kNB]      zero between calls (room for kHistCopies replicas)
-  unsigned* ticket;            // [units]   select workgroups of the unit that are done; zero between calls (directly behind hist)
-  unsigned* cand_count;        // [units]   candidate slots handed out; zero between calls (behind ticket)
-  unsigned long long* counts;  // [units][nblk]   what each select workgroup has found (kCountsHere, kListLate); zero between calls
-  unsigned short* bins;        // [units][nblk * tok]  per token (behind the unit's phantom tokens): bin + 1, kBinWindow inside
-                               //   the two windows, 0 where there is no token; a select workgroup whose list is late leaves it
-                               //   in the place of its tokens' bins
+  unsigned* hist;              // [2][units][histCopies][kNB]   zero between uses (room for kHistCopies replicas)
+  unsigned* cand_count;        // [2][units]   records handed out so far (directly behind hist, zeroed with it)
+  unsigned short* bins;        // [units][binStride]  per token: bin + 1, or kBinWindow inside the two windows
   unsigned char* cand_rec;     // [units] blocks of rec_stride bytes: the candidates' composites, logits and V rows (CandView)
-  int* cand_tok;               // [units][nblk * tok]  candidates of each select workgroup, ascending, from its first slot on
-  float* partials;             // [units][npart][G][kD] accumulators, then [units][G][npart] (m, l) pairs
+  unsigned long long* stage;   // [units][nblkC][stageStride]: selected ids (front, int32) / candidate composites (ending at word tokC)
+  int2* stage_cnt;             // [units][nblkC]     (selected, candidates)
+  float* partials;             // [units][npart][G][kD+2]
   int rec_stride;
 #ifdef PQC_TRACE
   unsigned long long* trace;   // [3 kernels][kTraceWgs][kTraceSlots] time stamps (debug builds only)
 #endif
 };
-
-// Data that workgroups of one kernel hand to each other (the partial states and candidates of a unit, read by the
-// workgroup of the unit that finishes last): stores go through to where every XCD sees them and loads do not look
-// at what this XCD's L2 may hold.  A fence would write back the whole L2 instead.
-__device__ __forceinline__ void put32(void* p, unsigned v) { __hip_atomic_store(static_cast<unsigned*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void put64(void* p, unsigned long long v) {
-  __hip_atomic_store(static_cast<unsigned long long*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned get32(const void* p) {
-  return __hip_atomic_load(static_cast<const unsigned*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long get64(const void* p) {
-  return __hip_atomic_load(static_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long pack2(float a, float b) {
-  return ((unsigned long long)__float_as_uint(b) << 32) | __float_as_uint(a);
-}
-__device__ __forceinline__ float2 unpack2(unsigned long long v) {
-  return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
-}
 
 // Phase time stamps for debug builds (-DPQC_TRACE); compiled out otherwise.
 #ifdef PQC_TRACE
@@ -290,13 +268,6 @@ __device__ __forceinline__ float load_as_float<float>(const float* p, int i) {
 template <>
 __device__ __forceinline__ float load_as_float<bf16_t>(const bf16_t* p, int i) {
   return __uint_as_float((unsigned)p[i].bits << 16);
-}
-
-// Two neighbouring values, at an even index.
-__device__ __forceinline__ float2 load_pair(const float* p) { return *reinterpret_cast<const float2*>(p); }
-__device__ __forceinline__ float2 load_pair(const bf16_t* p) {
-  const unsigned v = *reinterpret_cast<const unsigned*>(p);
-  return make_float2(__uint_as_float(v << 16), __uint_as_float(v & 0xffff0000u));
 }
 
 // Centroids travel global -> registers (coalesced, all loads in flight at once) -> a
@@ -722,7 +693,7 @@ __device__ __forceinline__ PairThreshold pair_threshold(const Shape& s, const T*
                                                         const uint8_t* __restrict__ codes_u /* [N][2] of the unit */,
                                                         PairLds& L, int* scan_sm /* [2*(NT/64)+1] */, MarkFn mark,
                                                         int uncounted /* a window token the counts do not hold yet, or -1 */) {
-  static_assert(NT >= 256, "one thread per digit of the radix search");
+  static_assert(NT == 256, "written for 256 threads");
   constexpr int Dm = kD / 2, PPT = kPairSlots / NT, BPT = kNB / NT;
   const int tid = threadIdx.x, C = s.C, np = C * C;
   // ---- loads: one table entry's centroid per thread (2C threads), query, counts, window codes
@@ -879,7 +850,7 @@ __device__ __forceinline__ PairThreshold pair_threshold(const Shape& s, const T*
     unsigned prefix = 0u;
     long long w = want;
     for (int shift = 24; shift >= 0; shift -= 8) {
-      if (tid < 256) L.hist[tid] = 0u;  // one per digit
+      L.hist[tid] = 0u;  // 256 digits
       __syncthreads();
 #pragma unroll
       for (int x = 0; x < PPT; ++x)
@@ -920,6 +891,9 @@ struct RowRaw<bf16_t> {
   __device__ __forceinline__ void load(const bf16_t* base, int t, int sub) {
     a = *reinterpret_cast<const uint4*>(base + (size_t)t * kD + sub * 8);
   }
+  __device__ __forceinline__ void load_row(const void* row, int sub) {
+    a = *reinterpret_cast<const uint4*>(static_cast<const unsigned char*>(row) + sub * 16);
+  }
   __device__ __forceinline__ void zero() { a = make_uint4(0, 0, 0, 0); }
   __device__ __forceinline__ void unpack(float (&f)[8]) const {
     f[0] = __uint_as_float(a.x << 16);
@@ -931,10 +905,7 @@ struct RowRaw<bf16_t> {
     f[6] = __uint_as_float(a.w << 16);
     f[7] = __uint_as_float(a.w & 0xffff0000u);
   }
-  __device__ __forceinline__ void put(unsigned char* dst, int sub) const {
-    put64(dst + sub * 16, ((unsigned long long)a.y << 32) | a.x);
-    put64(dst + sub * 16 + 8, ((unsigned long long)a.w << 32) | a.z);
-  }
+  __device__ __forceinline__ void store(unsigned char* dst, int sub) const { *reinterpret_cast<uint4*>(dst + sub * 16) = a; }
 };
 template <>
 struct RowRaw<float> {
@@ -942,6 +913,10 @@ struct RowRaw<float> {
   __device__ __forceinline__ void load(const float* base, int t, int sub) {
     a = *reinterpret_cast<const float4*>(base + (size_t)t * kD + sub * 4);
     b = *reinterpret_cast<const float4*>(base + (size_t)t * kD + 64 + sub * 4);
+  }
+  __device__ __forceinline__ void load_row(const void* row, int sub) {
+    a = *reinterpret_cast<const float4*>(static_cast<const unsigned char*>(row) + sub * 16);
+    b = *reinterpret_cast<const float4*>(static_cast<const unsigned char*>(row) + 256 + sub * 16);
   }
   __device__ __forceinline__ void zero() {
     a = make_float4(0, 0, 0, 0);
@@ -951,11 +926,9 @@ struct RowRaw<float> {
     f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w;
     f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
   }
-  __device__ __forceinline__ void put(unsigned char* dst, int sub) const {
-    put64(dst + sub * 16, pack2(a.x, a.y));
-    put64(dst + sub * 16 + 8, pack2(a.z, a.w));
-    put64(dst + 256 + sub * 16, pack2(b.x, b.y));
-    put64(dst + 256 + sub * 16 + 8, pack2(b.z, b.w));
+  __device__ __forceinline__ void store(unsigned char* dst, int sub) const {
+    *reinterpret_cast<float4*>(dst + sub * 16) = a;
+    *reinterpret_cast<float4*>(dst + 256 + sub * 16) = b;
   }
 };
 
@@ -996,17 +969,13 @@ __device__ __forceinline__ void load_query(const T* __restrict__ q /* [G][kD] */
 
 // Attend the rows list(p), p in [first, count) stepping by `stride`, where every
 // wave-iteration covers 4*R consecutive list positions.  list(p) must be valid
-// for p < count; tokens are clamped into [0, N).  once(): called one time, after the first rows.
-struct DoNothing {
-  __device__ __forceinline__ void operator()() const {}
-};
-template <typename T, int G, int R, class ListFn, class OnceFn = DoNothing>
+// for p < count; tokens are clamped into [0, N).
+template <typename T, int G, int R, class ListFn>
 __device__ __forceinline__ void attend_rows(const T* __restrict__ kbase, const T* __restrict__ vbase, int N,
                                             ListFn list, int count, int first, int stride,
-                                            const float (&qr)[G][8], AttnState<G>& st, OnceFn once = OnceFn()) {
+                                            const float (&qr)[G][8], AttnState<G>& st) {
   const int lane = threadIdx.x & 63;
   const int sub = lane & 15, slot = lane >> 4;
-  if (first >= count) once();
   for (int base = first; base < count; base += stride) {
     RowRaw<T> kr[R], vr[R];
     bool ok[R];
@@ -1065,7 +1034,6 @@ __device__ __forceinline__ void attend_rows(const T* __restrict__ kbase, const T
 #pragma unroll
         for (int e = 0; e < 8; ++e) st.acc[h][e] = fmaf(pw[r][h], vf[e], st.acc[h][e]);
     }
-    if (base == first) once();
   }
 }
 
@@ -1298,15 +1266,12 @@ __device__ __forceinline__ void mfma_consume(const MfmaStage& g, int count, int 
 }
 
 // Rows list(first), list(first+1), ... in stages of 16*kMfmaTiles positions, `stride` apart.
-template <class ListFn, class OnceFn = DoNothing>
+template <class ListFn>
 __device__ __forceinline__ void mfma_attend(const bf16_t* __restrict__ kbase, const bf16_t* __restrict__ vbase, int N,
                                             ListFn list, int count, int first, int stride, float scale_log2e,
                                             const bf16x8_t (&qf)[4], unsigned char* vt /* wave-private LDS [kVTileBytes] */,
-                                            MfmaState& st, OnceFn once = OnceFn() /* called one time, after the first stage */) {
-  if (first >= count) {  // wave-uniform
-    once();
-    return;
-  }
+                                            MfmaState& st) {
+  if (first >= count) return;  // wave-uniform
   MfmaStage ga, gb;
   int base = first;
   mfma_issue(kbase, vbase, N, list, count, base, ga);
@@ -1314,7 +1279,6 @@ __device__ __forceinline__ void mfma_attend(const bf16_t* __restrict__ kbase, co
     mfma_issue(kbase, vbase, N, list, count, base + stride, gb);
     PQC_LOADS_ISSUED();
     mfma_consume(ga, count, base, scale_log2e, qf, vt, st);
-    if (base == first) once();
     base += stride;
     if (base >= count) break;
     mfma_issue(kbase, vbase, N, list, count, base + stride, ga);
