@@ -33,7 +33,7 @@ __global__ __launch_bounds__(256) void pq_init_kernel(BuildShape s, const T* __r
 }
 
 // One token per unit (the code of an appended token): one thread per centroid, the same distance chain
-// as pq_assign_kernel, the smallest (distance, centroid) pair through a 64-bit LDS minimum.
+// as pq_round_vector_kernel, the smallest (distance, centroid) pair through a 64-bit LDS minimum.
 template <typename T>
 __global__ __launch_bounds__(256) void pq_encode_kernel(BuildShape s, const T* __restrict__ key /* [units][kD] */, int position,
                                                         const float* __restrict__ cent, uint8_t* __restrict__ codes) {
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
             for (int e = 0; e < 4; ++e) {
               f[2 * e] = __uint_as_float(rw[e] << 16);
               f[2 * e + 1] = __uint_as_float(rw[e] & 0xffff0000u);
-              top = fmaxf(fmaxf(fabsf(f[2 * e]), fabsf(f[2 * e + 1])), top);
+              top = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(f[2 * e]), fabsf(f[2 * e + 1])), top);  // NaN stays
             }
             if (__builtin_expect(!(top < 1073741824.0f), 0)) {
 #pragma unroll

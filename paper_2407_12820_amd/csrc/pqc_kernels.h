@@ -704,7 +704,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(Shape s, Workspace ws, co
   const int SL = ATTN ? s.slices : 1;  // head workgroups per head
   if ((int)blockIdx.x == heads * SL + kCopyWgs) {
     // -------------------------------------------------------------- append workgroup
-    // one thread per centroid, the distance chain of pq_assign_kernel, the smallest (distance, centroid) pair
+    // one thread per centroid, the distance chain of pq_round_vector_kernel, the smallest (distance, centroid) pair
     // of each partition through a 64-bit LDS minimum
     __shared__ float ax[kD];
     __shared__ unsigned long long abest[8];

@@ -243,6 +243,33 @@ def test_round_edges(pqc, dtype, m, c, n, units, kind):
                 assert np.all(np.abs(c1[u, 0, j, k] - want) <= tol), (u, j, k)
 
 
+# A key value that is not a number adds nothing to the sum of its centroid (its token still counts as a member) and leaves
+# every other dimension alone, whichever conversion the kernel takes for the values around it.
+@pytest.mark.parametrize("dtype,m,c", [("bf16", 4, 16), ("bf16", 2, 64), ("bf16", 1, 32), ("bf16", 1, 256), ("f32", 2, 16)])
+def test_round_passes_over_what_is_not_a_number(pqc, dtype, m, c):
+    n, Dm = 700, 128 // m
+    w = wl.Workload(name="round", batch=1, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=n, pq_m=m, pq_centroids=c,
+                    topk=n // 4, n_init=0, n_local=0, dtype=dtype, kmeans_iters=1, recipe="plain")
+    print(f"[case] not a number {dtype} m={m} c={c}", flush=True)
+    d = wl.generate(w, seed=c)
+    init = wl.kmeans_init_indices(w, seed=3)
+    kf = wl.to_f32(d["k"], dtype).copy()
+    bad = np.setdiff1d(np.arange(n), init.ravel())[::37]
+    kf[0, 0, bad, (5 * bad) % 128] = np.nan
+    keys = pqc.to_device(kf if dtype == "f32" else wl.f32_to_bf16_bits(kf), dtype, DEV)
+    init_d = torch.from_numpy(init).to(DEV)
+    _, cd0 = pqc.pq_build(w, keys, init_d, iters=0)
+    c1, _ = pqc.pq_build(w, keys, init_d, iters=1)
+    torch.cuda.synchronize()
+    cd0, c1 = cd0.cpu().numpy(), c1.cpu().numpy()
+    x = np.nan_to_num(keys.float().cpu().numpy()[0, 0].astype(np.float64), nan=0.0)
+    for j in range(m):
+        for k in np.unique(cd0[0, 0, :, j]):
+            want = x[cd0[0, 0, :, j] == k, j * Dm:(j + 1) * Dm].mean(0)
+            # 2^-20 per key and one fp32 rounding
+            assert np.all(np.abs(c1[0, 0, j, k] - want) <= 2.0 ** -20 + 2e-6 * (1.0 + np.abs(want))), (j, k)
+
+
 def test_encode_token_writes_nearest_codes_in_place(pqc):
     w = wl.get("batch8_32k", batch=3, n_tokens=700)
     d = wl.generate(w, seed=13)
