@@ -755,8 +755,9 @@ void launch_round_d(const BuildPlan& bp, const T* keys, float* cent, uint8_t* co
   if constexpr (sizeof(T) == 2 && DM >= 32) {
     const size_t lds = mfma_stage_bytes(r.staged, DM) + acc;
     // eight tiles per wave read each staged centroid once for 128 tokens (as many as the registers of four waves per SIMD hold
-    // with longer sub-vectors); short ranges take two, so that more than a few of the sixteen waves have tokens
-    constexpr int kTiles = DM >= 128 ? 4 : DM == 64 ? 6 : 8;
+    // with longer sub-vectors: six of 64 dimensions spill and take 1197 us for the eight rounds that five do in 770 us, four in
+    // 777 us); short ranges take two, so that more than a few of the sixteen waves have tokens
+    constexpr int kTiles = DM >= 128 ? 3 : DM == 64 ? 5 : 8;
     if (r.tokens >= 16 * 16 * kTiles)
       hipLaunchKernelGGL((pq_round_mfma_kernel<DM, kTiles, ACCUM>), grid, dim3(1024), lds, st, s, r, keys, cent, codes, sums, counts);
     else

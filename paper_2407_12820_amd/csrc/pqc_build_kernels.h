@@ -86,8 +86,11 @@ __device__ __forceinline__ unsigned long long fix_biased_large(float x) {
   return (unsigned long long)__float2ll_rn(x * (float)(1 << kFixShift)) + (unsigned long long)kFixBiasBits;
 }
 
-// LDS of a round: the staged centroids, then the accumulators ([C][Dm + 1]: an odd row length spreads the rows of the
-// centroids that a wave adds to over the banks) and the member counts.
+// LDS of a round: the staged centroids, then the accumulators and the member counts.  Rows of Dm + 1 sums
+// (an odd row length spreads the rows of the centroids that a wave adds to over the banks), or, matrix-core kernel with 64 and
+// 128 dimensions, rows of Dm sums, so that the bank of a sum depends on its dimension alone, in the order of sum_place: every
+// second 32 dimensions are turned by 16, which lets the sixteen lanes of a quad add to sixteen different sums modulo 32.
+__host__ __device__ constexpr int sum_place(int e) { return e ^ ((e >> 1) & 16); }
 __host__ __device__ constexpr size_t round_sum_bytes(int C, int Dm) { return (size_t)C * (Dm + 1) * 8 + ((size_t)C * 4 + 15) / 16 * 16; }
 __host__ __device__ constexpr int mfma_term_stride(int Dm) { return Dm + 8; }  // bf16 values; 16 bytes of padding
 __host__ __device__ constexpr size_t mfma_stage_bytes(int staged, int Dm) {
@@ -117,15 +120,21 @@ __device__ __forceinline__ float fixed_mean(unsigned long long sum, unsigned cou
   return (float)((double)(long long)sum * (1.0 / (double)(1 << kFixShift)) / (double)count);
 }
 
+template <bool TURNED>  // rows of Dm sums in the order of sum_place, or rows of Dm + 1 sums as they are
+__device__ __forceinline__ int sum_index(const BuildShape& s, int c, int e) {
+  return TURNED ? c * s.Dm + sum_place(e) : c * (s.Dm + 1) + e;
+}
+
 // The accumulators to the workspace; a workgroup that owns all tokens of its (unit, partition) writes the new centroids
 // itself (nobody else reads them in this launch, and it has staged the old ones).
+template <bool TURNED>
 __device__ __forceinline__ void round_flush(const BuildShape& s, int ranges, int uj, int p, const unsigned long long* sums,
                                             const unsigned* cnt, float* __restrict__ cent, unsigned long long* __restrict__ part_sums,
                                             unsigned* __restrict__ part_counts) {
   const int n = s.C * s.Dm, slot = uj * ranges + p;
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
     const int c = i / s.Dm, e = i - c * s.Dm;
-    const unsigned long long v = sums[c * (s.Dm + 1) + e] - (unsigned long long)cnt[c] * (unsigned long long)kFixBiasBits;
+    const unsigned long long v = sums[sum_index<TURNED>(s, c, e)] - (unsigned long long)cnt[c] * (unsigned long long)kFixBiasBits;
     if (ranges > 1)
       part_sums[(size_t)slot * n + i] = v;
     else if (cnt[c])
@@ -133,6 +142,14 @@ __device__ __forceinline__ void round_flush(const BuildShape& s, int ranges, int
   }
   if (ranges > 1)
     for (int i = threadIdx.x; i < s.C; i += blockDim.x) part_counts[(size_t)slot * s.C + i] = cnt[i];
+}
+
+// Eight bf16 values turned: value e becomes the one that was value (e + n) modulo 8, n < 8.
+__device__ __forceinline__ void turn_left(unsigned (&v)[4], int n) {
+  const unsigned a[4] = {n & 2 ? v[1] : v[0], n & 2 ? v[2] : v[1], n & 2 ? v[3] : v[2], n & 2 ? v[0] : v[3]};
+  const unsigned b[4] = {n & 4 ? a[2] : a[0], n & 4 ? a[3] : a[1], n & 4 ? a[0] : a[2], n & 4 ? a[1] : a[3]};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_alignbit(b[(i + 1) & 3], b[i], (n & 1) * 16);
 }
 
 // bf16 keys and sub-vectors of 32, 64 or 128 dimensions: the assignment is a dense contraction (tokens x dimensions by
@@ -152,12 +169,16 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
   // tile are kept (12 instructions for four scores instead of 16) and which of them it was is found at the end; with
   // longer ones the products hide them and the registers hold keys.
   constexpr bool KEEP = DM == 32;
+  // 64 and 128 dimensions: sums turned (see sum_place; 131072 tokens x 8 heads, 2x64, eight rounds 900 -> 770 us).  With 32 the
+  // turning costs more than the banks give back, as the matrix products and comparisons take longer than the additions.
+  constexpr bool TURNED = KK > 1;
+  constexpr int SR = TURNED ? DM : DM + 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char round_lds[];
   const int rows = (r.staged + 15) / 16 * 16;
   unsigned short* ct = reinterpret_cast<unsigned short*>(round_lds);  // [3][rows * RS]: hi, mid, lo terms
   float* cn = reinterpret_cast<float*>(round_lds + (size_t)rows * RS * 6);
   unsigned long long* sums = reinterpret_cast<unsigned long long*>(round_lds + mfma_stage_bytes(r.staged, DM));
-  unsigned* cnt = reinterpret_cast<unsigned*>(sums + s.C * (DM + 1));
+  unsigned* cnt = reinterpret_cast<unsigned*>(sums + s.C * SR);
   int u, j, p;
   round_place(s, r.ranges, u, j, p);
   const int uj = u * s.M + j, tid = threadIdx.x;
@@ -200,9 +221,11 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
       ct[o] = ct[rows * RS + o] = ct[2 * rows * RS + o] = 0;
     }
   };
+  const int turn = col & 7;      // where a lane starts in the eight dimensions it holds, so that the lanes of a quad spread
+  const bool upper = col >= 8;
   if (one_group) stage(0);
   if constexpr (ACCUM) {
-    for (int i = tid; i < s.C * (DM + 1); i += NT) sums[i] = 0ull;
+    for (int i = tid; i < s.C * SR; i += NT) sums[i] = 0ull;
     for (int i = tid; i < s.C; i += NT) cnt[i] = 0u;
   }
   if (one_group) __syncthreads();
@@ -297,25 +320,40 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
 #pragma unroll
       for (int tt = 0; tt < TT; ++tt) {
         if (tok0 + tt * 16 + col < t_end) {
-          unsigned long long* row = sums + bidx[tt] * (DM + 1) + 8 * quad;
+          unsigned long long* row = sums + bidx[tt] * SR;
           if (quad == 0) atomicAdd(&cnt[bidx[tt]], 1u);
 #pragma unroll
-          for (int kk = 0; kk < KK; ++kk) {
-            unsigned rw[4];
-            __builtin_memcpy(rw, &x[tt][kk], 16);
-            float f[8], top = 0.0f;
+          for (int k0 = 0; k0 < KK; k0 += 2) {
+            unsigned rw[2][4];
+            __builtin_memcpy(rw[0], &x[tt][k0], 16);
+            __builtin_memcpy(rw[1], &x[tt][k0 + 1 < KK ? k0 + 1 : k0], 16);
+            if constexpr (KK > 1) {  // the upper eight lanes of a quad take the other 32 dimensions first
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              f[2 * e] = __uint_as_float(rw[e] << 16);
-              f[2 * e + 1] = __uint_as_float(rw[e] & 0xffff0000u);
-              top = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(f[2 * e]), fabsf(f[2 * e + 1])), top);  // NaN stays
+              for (int i = 0; i < 4; ++i) {
+                const unsigned lo = rw[0][i];
+                rw[0][i] = upper ? rw[1][i] : lo;
+                rw[1][i] = upper ? lo : rw[1][i];
+              }
             }
-            if (__builtin_expect(!(top < 1073741824.0f), 0)) {
 #pragma unroll
-              for (int e = 0; e < 8; ++e) atomicAdd(&row[32 * kk + e], fix_biased_large(f[e]));
-            } else {
+            for (int h = 0; h < (KK > 1 ? 2 : 1); ++h) {
+              // dimensions of 32 * kk + 8 * quad + {turn, turn + 1, ... modulo 8}
+              unsigned long long* part = row + 32 * k0 + (KK > 1 && (h == 1) != upper ? sum_place(32 + 8 * quad) : 8 * quad);
+              float f[8], top = 0.0f;
+              if constexpr (TURNED) turn_left(rw[h], turn);
 #pragma unroll
-              for (int e = 0; e < 8; ++e) atomicAdd(&row[32 * kk + e], fix_biased(f[e]));
+              for (int e = 0; e < 4; ++e) {
+                f[2 * e] = __uint_as_float(rw[h][e] << 16);
+                f[2 * e + 1] = __uint_as_float(rw[h][e] & 0xffff0000u);
+                top = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(f[2 * e]), fabsf(f[2 * e + 1])), top);  // NaN stays
+              }
+              if (__builtin_expect(!(top < 1073741824.0f), 0)) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) atomicAdd(&part[TURNED ? (turn + e) & 7 : e], fix_biased_large(f[e]));
+              } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) atomicAdd(&part[TURNED ? (turn + e) & 7 : e], fix_biased(f[e]));
+              }
             }
           }
         }
@@ -336,7 +374,7 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
   }
   if constexpr (ACCUM) {
     __syncthreads();
-    round_flush(s, r.ranges, uj, p, sums, cnt, cent, part_sums, part_counts);
+    round_flush<TURNED>(s, r.ranges, uj, p, sums, cnt, cent, part_sums, part_counts);
   }
 }
 
@@ -450,7 +488,7 @@ __global__ __launch_bounds__(round_vector_threads<DM>()) void pq_round_vector_ke
   }
   if constexpr (ACCUM) {
     __syncthreads();
-    round_flush(s, r.ranges, uj, p, sums, cnt, cent, part_sums, part_counts);
+    round_flush<false>(s, r.ranges, uj, p, sums, cnt, cent, part_sums, part_counts);
   }
 }
 
