@@ -699,7 +699,6 @@ struct BuildPlan {
   RoundGrid assign;   // the assignment alone
   bool fused;         // the accumulators of a round fit into LDS beside the centroids
   bool mfma;
-  size_t off_sums, off_counts, total;
 };
 
 constexpr size_t kRoundLds = 156 * 1024;  // of the compute unit's 160 KB
@@ -707,7 +706,7 @@ constexpr size_t kRoundLds = 156 * 1024;  // of the compute unit's 160 KB
 // Token ranges per (unit, partition).  One workgroup fills a compute unit, so the time of a launch is that of its rounds of
 // 256 workgroups; each pays for staging the centroids and writing the sums what about 1024 tokens cost.
 RoundGrid round_grid(const BuildShape& s, int staged) {
-  RoundGrid r{1, (s.N + 15) / 16 * 16, staged};
+  RoundGrid r{1, 1, (s.N + 15) / 16 * 16, staged};
   double best = 1e30;
   for (int p = 1; p <= 128; ++p) {
     const int tokens = ((s.N + p - 1) / p + 15) / 16 * 16;
@@ -737,11 +736,22 @@ int make_build_plan(const pqc_config* cfg, BuildPlan* bp) {
   bp->assign = round_grid(s, staged);
   bp->fused = stage_bytes(s.C) + round_sum_bytes(s.C, s.Dm) <= kRoundLds;
   bp->round = bp->assign;
-  const size_t n = (size_t)s.units * s.M * s.C * (bp->fused ? bp->round.ranges : 1);
-  bp->off_sums = 0;
-  bp->off_counts = align_up(sizeof(unsigned long long) * n * s.Dm);
-  bp->total = align_up(bp->off_counts + sizeof(unsigned) * n);
   return PQC_OK;
+}
+
+// The workspace holds sets of sums and counts.  Neither the least a build runs in nor the most it makes use of depends on
+// n_tokens, so that one workspace serves every length of a cache: one set per (unit, partition), and as many as short of
+// one workgroup per compute unit can fill.
+struct BuildWorkspace {
+  size_t off_counts, total;
+};
+BuildWorkspace build_workspace(const BuildShape& s, int sets) {
+  const size_t n = (size_t)s.units * s.M * s.C * sets;
+  const size_t off = align_up(sizeof(unsigned long long) * n * s.Dm);
+  return {off, align_up(off + sizeof(unsigned) * n)};
+}
+int most_sum_sets(const BuildPlan& bp) {
+  return bp.fused ? std::max(1, std::min(kSumSets, 256 / (bp.s.units * bp.s.M))) : 1;
 }
 
 // One launch over all token ranges: with sums a K-Means round, without it the assignment (codes written).
@@ -786,18 +796,19 @@ template <typename T>
 int pq_build_t(const BuildPlan& bp, const T* keys, const int32_t* init_idx, int iters, float* cent, uint8_t* codes,
                char* wsp, hipStream_t st) {
   const BuildShape& s = bp.s;
-  unsigned long long* sums = reinterpret_cast<unsigned long long*>(wsp + bp.off_sums);
-  unsigned* counts = reinterpret_cast<unsigned*>(wsp + bp.off_counts);
+  const int sets = bp.fused ? bp.round.sets : 1;
+  unsigned long long* sums = reinterpret_cast<unsigned long long*>(wsp);
+  unsigned* counts = reinterpret_cast<unsigned*>(wsp + build_workspace(s, sets).off_counts);
   const unsigned uj = (unsigned)(s.units * s.M);
   const dim3 per_cent((unsigned)((s.C * s.Dm + 255) / 256), uj);
-  hipLaunchKernelGGL((pq_init_kernel<T>), per_cent, dim3(256), 0, st, s, keys, init_idx, cent);
+  const bool means = !bp.fused || bp.round.ranges > 1;  // else a round writes them itself
+  hipLaunchKernelGGL((pq_init_kernel<T>), per_cent, dim3(256), 0, st, s, keys, init_idx, cent,
+                     means && sets == 1 ? sums : nullptr, counts);
   for (int it = 0; it < iters; ++it) {
     if (bp.fused) {
       launch_round<T, true>(bp, keys, cent, codes, sums, counts, st);
     } else {  // the accumulators are too large for LDS: codes first, then the sums of the members of each code
       launch_assign<T>(bp, keys, cent, codes, st);
-      const size_t nacc = bp.total / sizeof(unsigned long long);  // sums and counts, zeroed together
-      hipLaunchKernelGGL(pq_zero_kernel, dim3((unsigned)((nacc + 255) / 256)), dim3(256), 0, st, sums, nacc);
       const int tpw = accum_tokens_per_wg(s.C);
       const dim3 grid((s.N + tpw - 1) / tpw, uj);
       const size_t lds = (size_t)tpw * sizeof(unsigned short);
@@ -808,8 +819,7 @@ int pq_build_t(const BuildPlan& bp, const T* keys, const int32_t* init_idx, int 
         default: hipLaunchKernelGGL((pq_accum_kernel<T, 128>), grid, dim3(256), lds, st, s, keys, codes, sums, counts); break;
       }
     }
-    if (!bp.fused || bp.round.ranges > 1)  // (one range: the round has written the means)
-      hipLaunchKernelGGL(pq_mean_kernel, per_cent, dim3(256), 0, st, s, bp.fused ? bp.round.ranges : 1, sums, counts, cent);
+    if (means) hipLaunchKernelGGL(pq_mean_kernel, per_cent, dim3(256), 0, st, s, sets, sums, counts, cent);
   }
   launch_assign<T>(bp, keys, cent, codes, st);
   return hipGetLastError() == hipSuccess ? PQC_OK : PQC_EHIP;
@@ -822,7 +832,7 @@ extern "C" {
 size_t pqc_pq_build_workspace_bytes(const pqc_config* cfg) {
   BuildPlan bp;
   if (make_build_plan(cfg, &bp) != PQC_OK) return 0;
-  return bp.total;
+  return build_workspace(bp.s, most_sum_sets(bp)).total;
 }
 
 int pqc_pq_build(const pqc_config* cfg, const void* keys, const int32_t* init_idx, int32_t iters, float* centroids,
@@ -832,7 +842,10 @@ int pqc_pq_build(const pqc_config* cfg, const void* keys, const int32_t* init_id
   if (rc != PQC_OK) return rc;
   if (!keys || !init_idx || !centroids || !codes || iters < 0) return PQC_EINVAL;
   if (!aligned16(keys) || !aligned16(init_idx) || !aligned16(centroids) || !aligned16(codes)) return PQC_EINVAL;
-  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kAlign) || workspace_bytes < bp.total) return PQC_EWORKSPACE;
+  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kAlign) || workspace_bytes < build_workspace(bp.s, 1).total)
+    return PQC_EWORKSPACE;
+  if (bp.round.ranges <= most_sum_sets(bp) && workspace_bytes >= build_workspace(bp.s, bp.round.ranges).total)
+    bp.round.sets = bp.round.ranges;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* wsp = static_cast<char*>(workspace);
   if (cfg->kv_dtype == PQC_F32) return pq_build_t<float>(bp, static_cast<const float*>(keys), init_idx, iters, centroids, codes, wsp, st);

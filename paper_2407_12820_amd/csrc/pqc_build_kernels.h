@@ -19,10 +19,11 @@ struct BuildShape {
   int cap;  // tokens the key and code tensors hold per unit (>= N): their stride between units
 };
 
-// centroids[u][j][c][:] = keys[u][init_idx[u][j][c]][j*Dm : (j+1)*Dm]
+// centroids[u][j][c][:] = keys[u][init_idx[u][j][c]][j*Dm : (j+1)*Dm]; member sums and counts of the first round cleared
 template <typename T>
 __global__ __launch_bounds__(256) void pq_init_kernel(BuildShape s, const T* __restrict__ keys,
-                                                      const int* __restrict__ init_idx, float* __restrict__ cent) {
+                                                      const int* __restrict__ init_idx, float* __restrict__ cent,
+                                                      unsigned long long* __restrict__ sums, unsigned* __restrict__ counts) {
   const int uj = blockIdx.y, u = uj / s.M, j = uj % s.M;
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= s.C * s.Dm) return;
@@ -30,6 +31,9 @@ __global__ __launch_bounds__(256) void pq_init_kernel(BuildShape s, const T* __r
   int t = init_idx[(size_t)uj * s.C + c];
   t = max(0, min(s.N - 1, t));
   cent[(size_t)uj * s.C * s.Dm + i] = load_as_float<T>(keys, ((size_t)u * s.cap + t) * kD + j * s.Dm + e);
+  if (!sums) return;  // no round adds to them
+  sums[(size_t)uj * s.C * s.Dm + i] = 0ull;
+  if (e == 0) counts[(size_t)uj * s.C + c] = 0u;
 }
 
 // One token per unit (the code of an appended token): one thread per centroid, the same distance chain
@@ -67,15 +71,24 @@ __global__ __launch_bounds__(256) void pq_encode_kernel(BuildShape s, const T* _
 // Assignment of every token to its nearest centroid and, in the same pass over the keys, the sums of the new
 // centroids' members.  A workgroup owns one range of tokens of one (unit, partition): it stages the centroids in LDS
 // once, streams its keys through registers, and adds each key to an LDS accumulator of its centroid; at the end the
-// accumulators go to the workspace as they are (no atomics, nothing to clear), one set per range, and pq_mean_kernel
-// adds the ranges up.  With ACCUM = false the kernel is the assignment alone and writes codes.
+// accumulators go to the workspace and pq_mean_kernel takes the means.  Up to kSumSets ranges of a (unit, partition) write
+// a set of sums each, as they are; more of them, or where the workspace holds one set only, add to one set with atomics
+// (integers: the same sums), which the start and every mean clear.  With ACCUM = false the kernel is the assignment alone
+// and writes codes.
+//
+// Why the line lies there (four rounds, sets against atomics): 8192 tokens x 8 heads, 4x256, 8 ranges 141 against 156 us;
+// 16384 tokens x 8 heads, 2x64, 16 ranges 102 against 107 us; 8192 tokens x 2 heads, 4x256, 32 ranges 106 against 92 us;
+// 2048 tokens of one head, 2x64, 128 ranges 102 against 57 us.  Atomics cost about 0.3 ns each, however many ranges there are; the
+// mean's walk over the sets grows with their number.
 //
 // Sums are 64-bit integers of the values in fixed point (2^-20, round to nearest even), so the result does not depend
 // on the order of tokens, waves or workgroups.  The conversion is one addition in double precision: x + 1.5 * 2^32 has
 // its last bit at 2^-20, so its bit pattern is the pattern of 1.5 * 2^32 plus the fixed-point integer; the constant is
 // taken out again count times when the accumulators are written.  (|x| >= 2^30 takes a conversion of its own.)
+constexpr int kSumSets = 16;  // most sets of sums per (unit, partition)
 struct RoundGrid {
   int ranges;   // token ranges per (unit, partition)
+  int sets;     // sets of sums per (unit, partition) in the workspace: ranges (a set each) or 1
   int tokens;   // tokens per range, a multiple of 16
   int staged;   // centroids staged at a time (all of them when they fit; always all with ACCUM)
 };
@@ -128,20 +141,33 @@ __device__ __forceinline__ int sum_index(const BuildShape& s, int c, int e) {
 // The accumulators to the workspace; a workgroup that owns all tokens of its (unit, partition) writes the new centroids
 // itself (nobody else reads them in this launch, and it has staged the old ones).
 template <bool TURNED>
-__device__ __forceinline__ void round_flush(const BuildShape& s, int ranges, int uj, int p, const unsigned long long* sums,
+__device__ __forceinline__ void round_flush(const BuildShape& s, const RoundGrid& r, int uj, int p, const unsigned long long* sums,
                                             const unsigned* cnt, float* __restrict__ cent, unsigned long long* __restrict__ part_sums,
                                             unsigned* __restrict__ part_counts) {
-  const int n = s.C * s.Dm, slot = uj * ranges + p;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+  const int n = s.C * s.Dm;
+  const bool shared = r.sets < r.ranges;
+  const size_t set = (size_t)uj * r.sets + (shared ? 0 : p);
+  // ranges that add to one set start at different places of it: they finish at about the same time
+  const int first = shared ? (int)((long long)n * p / r.ranges) & ~63 : 0;
+  for (int i0 = threadIdx.x; i0 < n; i0 += blockDim.x) {
+    const int i = i0 + first < n ? i0 + first : i0 + first - n;
     const int c = i / s.Dm, e = i - c * s.Dm;
     const unsigned long long v = sums[sum_index<TURNED>(s, c, e)] - (unsigned long long)cnt[c] * (unsigned long long)kFixBiasBits;
-    if (ranges > 1)
-      part_sums[(size_t)slot * n + i] = v;
-    else if (cnt[c])
-      cent[(size_t)uj * n + i] = fixed_mean(v, cnt[c]);
+    if (r.ranges == 1) {
+      if (cnt[c]) cent[(size_t)uj * n + i] = fixed_mean(v, cnt[c]);
+    } else if (!shared) {
+      part_sums[set * n + i] = v;
+    } else if (cnt[c]) {
+      atomicAdd(&part_sums[set * n + i], v);
+    }
   }
-  if (ranges > 1)
-    for (int i = threadIdx.x; i < s.C; i += blockDim.x) part_counts[(size_t)slot * s.C + i] = cnt[i];
+  if (r.ranges > 1)
+    for (int i = threadIdx.x; i < s.C; i += blockDim.x) {
+      if (!shared)
+        part_counts[set * s.C + i] = cnt[i];
+      else if (cnt[i])
+        atomicAdd(&part_counts[set * s.C + i], cnt[i]);
+    }
 }
 
 // Eight bf16 values turned: value e becomes the one that was value (e + n) modulo 8, n < 8.
@@ -374,7 +400,7 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
   }
   if constexpr (ACCUM) {
     __syncthreads();
-    round_flush<TURNED>(s, r.ranges, uj, p, sums, cnt, cent, part_sums, part_counts);
+    round_flush<TURNED>(s, r, uj, p, sums, cnt, cent, part_sums, part_counts);
   }
 }
 
@@ -488,13 +514,8 @@ __global__ __launch_bounds__(round_vector_threads<DM>()) void pq_round_vector_ke
   }
   if constexpr (ACCUM) {
     __syncthreads();
-    round_flush<false>(s, r.ranges, uj, p, sums, cnt, cent, part_sums, part_counts);
+    round_flush<false>(s, r, uj, p, sums, cnt, cent, part_sums, part_counts);
   }
-}
-
-__global__ void pq_zero_kernel(unsigned long long* p, size_t n) {
-  size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0ull;
 }
 
 // sums[u][j][c][e] += fix(keys[u][t][j*Dm+e]) for every token t with code c; counts[u][j][c] += 1.
@@ -610,32 +631,44 @@ __global__ __launch_bounds__(256) void pq_accum_kernel(BuildShape s, const T* __
   }
 }
 
-// cent = sums / counts where counts > 0, the sums and counts of a (unit, partition)'s token ranges added up
-__global__ __launch_bounds__(256) void pq_mean_kernel(BuildShape s, int ranges, const unsigned long long* __restrict__ sums,
-                                                      const unsigned* __restrict__ counts, float* __restrict__ cent) {
-  constexpr int U = 8;
-  const int n = s.C * s.Dm, i = blockIdx.x * 256 + threadIdx.x;
+// cent = sums / counts where counts > 0, the sets of a (unit, partition) added up; a set that is added to is cleared for the
+// next round.  A workgroup's 256 sums are those of whole centroids (sub-vectors have 16, 32, 64 or 128 dimensions), so that it
+// alone reads the counts that it clears.
+__global__ __launch_bounds__(256) void pq_mean_kernel(BuildShape s, int sets, unsigned long long* __restrict__ sums,
+                                                      unsigned* __restrict__ counts, float* __restrict__ cent) {
+  const int n = s.C * s.Dm, i = blockIdx.x * 256 + threadIdx.x, c = i / s.Dm;
   const size_t uj = blockIdx.y;
-  if (i >= n) return;
-  const int c = i / s.Dm;
+  const bool live = i < n;
   unsigned long long tot = 0ull;
   unsigned k = 0u;
-  for (int p0 = 0; p0 < ranges; p0 += U) {
-    unsigned long long v[U];
-    unsigned m[U];
+  if (sets == 1) {
+    if (live) {
+      tot = sums[uj * n + i];
+      k = counts[uj * s.C + c];
+    }
+    __syncthreads();
+    if (k) {
+      sums[uj * n + i] = 0ull;
+      if (i % s.Dm == 0) counts[uj * s.C + c] = 0u;
+    }
+  } else if (live) {
+    unsigned long long v[kSumSets];
+    unsigned m[kSumSets];
 #pragma unroll
-    for (int x = 0; x < U; ++x) {
-      const size_t slot = uj * ranges + min(p0 + x, ranges - 1);
-      v[x] = sums[slot * n + i];
-      m[x] = counts[slot * s.C + c];
+    for (int x = 0; x < kSumSets; ++x) {
+      v[x] = 0ull;
+      m[x] = 0u;
+      if (x < sets) {  // uniform
+        v[x] = sums[(uj * sets + x) * n + i];
+        m[x] = counts[(uj * sets + x) * s.C + c];
+      }
     }
     PQC_LOADS_ISSUED();
 #pragma unroll
-    for (int x = 0; x < U; ++x)
-      if (p0 + x < ranges) {
-        tot += v[x];
-        k += m[x];
-      }
+    for (int x = 0; x < kSumSets; ++x) {
+      tot += v[x];
+      k += m[x];
+    }
   }
   if (k) cent[uj * n + i] = fixed_mean(tot, k);
 }

@@ -194,3 +194,18 @@ def test_missing_library_is_an_error_not_a_fallback(monkeypatch):
     monkeypatch.setattr(binding, "LIB_PATH", os.path.join(ROOT, "paper_2407_12820_amd", "no_such_library.so"))
     with pytest.raises(RuntimeError, match="no CPU or PyTorch fallback"):
         binding.load()
+
+
+@pytest.mark.parametrize("name,units", [("tiny_f32", 1), ("llama8b_32k", 1), ("batch8_32k", 8), ("llama8b_128k", 17)])
+def test_build_workspace_serves_every_length(name, units):
+    # one workspace is kept for prompts of any length: neither what is asked for nor what is refused depends on n_tokens
+    lib = binding.load()
+    w = wl.get(name, batch=units, n_tokens=4000)
+    need = lib.pqc_pq_build_workspace_bytes(C.byref(binding.make_config(w)))
+    least = w.batch * w.n_kv_heads * w.pq_m * w.pq_centroids * (8 * w.sub_dim + 4)  # one sum per centroid value, one count per centroid
+    p = C.c_void_p(4096)
+    assert need >= least
+    for n in (1000, 2048, 20011, 131072):
+        cfg = binding.make_config(dataclasses.replace(w, n_tokens=n, topk=100))
+        assert lib.pqc_pq_build_workspace_bytes(C.byref(cfg)) == need, n
+        assert lib.pqc_pq_build(C.byref(cfg), p, p, 1, p, p, p, least - 1, None) == -3, n

@@ -270,6 +270,35 @@ def test_round_passes_over_what_is_not_a_number(pqc, dtype, m, c):
             assert np.all(np.abs(c1[0, 0, j, k] - want) <= 2.0 ** -20 + 2e-6 * (1.0 + np.abs(want))), (j, k)
 
 
+# A workspace taken once serves every length, also one that holds a single set of sums per (unit, partition): ranges of tokens
+# then add to it with atomics, which gives the sums of the sets bit for bit.
+@pytest.mark.parametrize("dtype,m,c,units", [("bf16", 2, 64, 8), ("bf16", 4, 48, 3), ("bf16", 2, 256, 2), ("f32", 2, 64, 9), ("f32", 8, 20, 1)])
+def test_build_in_the_smallest_workspace_at_several_lengths(pqc, dtype, m, c, units):
+    import ctypes
+    lib = pqc.load()
+    ws = None
+    for n in (20011, 700, 4096):
+        w = wl.Workload(name="round", batch=units, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=n, pq_m=m, pq_centroids=c,
+                        topk=n // 4, n_init=0, n_local=0, dtype=dtype, kmeans_iters=3, recipe="plain")
+        print(f"[case] smallest workspace {dtype} m={m} c={c} n={n} units={units}", flush=True)
+        gen = torch.Generator(device=DEV)
+        gen.manual_seed(n)
+        keys = torch.randn((units, 1, n, 128), generator=gen, device=DEV, dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+        init = torch.from_numpy(wl.kmeans_init_indices(w, seed=3)).to(DEV)
+        if ws is None:
+            up = lambda b: (b + 255) // 256 * 256
+            sets = units * m * c
+            ws = torch.full((up(8 * sets * w.sub_dim) + up(4 * sets),), 0xa5, dtype=torch.uint8, device=DEV)
+        cent = torch.empty((units, 1, m, c, w.sub_dim), dtype=torch.float32, device=DEV)
+        codes = torch.empty((units, 1, n, m), dtype=torch.uint8, device=DEV)
+        rc = lib.pqc_pq_build(ctypes.byref(pqc.make_config(w)), keys.data_ptr(), init.data_ptr(), 3, cent.data_ptr(), codes.data_ptr(),
+                              ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        want_cent, want_codes = pqc.pq_build(w, keys, init)
+        torch.cuda.synchronize()
+        assert torch.equal(cent, want_cent) and torch.equal(codes, want_codes), n
+
+
 def test_encode_token_writes_nearest_codes_in_place(pqc):
     w = wl.get("batch8_32k", batch=3, n_tokens=700)
     d = wl.generate(w, seed=13)
