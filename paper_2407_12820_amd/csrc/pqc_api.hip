@@ -708,10 +708,12 @@ constexpr size_t kRoundLds = 156 * 1024;  // of the compute unit's 160 KB
 RoundGrid round_grid(const BuildShape& s, int staged) {
   RoundGrid r{1, 1, (s.N + 15) / 16 * 16, staged};
   double best = 1e30;
-  for (int p = 1; p <= 128; ++p) {
+  const double least = (double)s.units * s.M * s.N / 256.0;  // all compute units busy
+  for (int p = 1; p <= 256; ++p) {
     const int tokens = ((s.N + p - 1) / p + 15) / 16 * 16;
     const int ranges = (s.N + tokens - 1) / tokens;
     const double rounds = std::ceil((double)s.units * s.M * ranges / 256.0);
+    if (least + rounds * 1024.0 >= best) break;  // (no cut that takes more rounds can cost less)
     const double cost = rounds * (tokens + 1024.0);
     if (cost < best * 0.999) {
       best = cost;
@@ -773,8 +775,34 @@ void launch_round_d(const BuildPlan& bp, const T* keys, float* cent, uint8_t* co
     else
       hipLaunchKernelGGL((pq_round_mfma_kernel<DM, 2, ACCUM>), grid, dim3(1024), lds, st, s, r, keys, cent, codes, sums, counts);
   } else {
-    hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, ACCUM>), grid, dim3(round_vector_threads<DM>()), vector_stage_bytes(r.staged, DM) + acc,
-                       st, s, r, keys, cent, codes, sums, counts);
+    static_assert(vector_stage_bytes(256, DM) <= kRoundLds, "all centroids are staged at once");
+    // one lane per token and two tokens per lane as soon as every wave has that many (8192 tokens x 8 heads, fp32, 4x256, which is
+    // 1024 tokens per workgroup: assignment 105 us with four lanes per token, 97 us with one)
+    constexpr int NT = DM >= 128 ? 512 : 1024, TT = DM <= 32 ? 2 : 1;
+    const size_t lds = vector_stage_bytes(s.C, DM) + acc;
+    if (r.tokens < NT) {
+      hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, NT, 4, 1, ACCUM>), grid, dim3(NT), lds, st, s, r, keys, cent, codes, sums, counts);
+    } else if constexpr (ACCUM || DM >= 128) {
+      if (r.tokens >= NT * TT)
+        hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, NT, 1, TT, ACCUM>), grid, dim3(NT), lds, st, s, r, keys, cent, codes, sums, counts);
+      else if constexpr (TT > 1)
+        hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, NT, 1, 1, ACCUM>), grid, dim3(NT), lds, st, s, r, keys, cent, codes, sums, counts);
+    } else {
+      // The assignment alone needs no room for sums, so that small workgroups share a compute unit, and they are many: a last
+      // one that is nearly empty holds nobody up (50001 tokens x 24 heads, fp32, 4x256: 1655 us with the ranges of a round,
+      // 1490 us so; with 128 dimensions a compute unit holds one workgroup either way).  Two batches per workgroup where
+      // there are enough of them; the number of workgroups has a limit.
+      constexpr int kSmall = DM >= 64 ? 512 : 256;
+      const bool wide = r.tokens >= NT * TT;
+      int tokens = kSmall * (wide ? TT : 1) * (DM <= 32 && r.tokens >= 2 * NT * TT ? 2 : 1);
+      while ((long long)s.units * s.M * ((s.N + tokens - 1) / tokens) > (1 << 20)) tokens *= 2;
+      const RoundGrid a{(s.N + tokens - 1) / tokens, 1, tokens, s.C};
+      const dim3 agrid((unsigned)(s.units * s.M * a.ranges));
+      if (wide)
+        hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, kSmall, 1, TT, false>), agrid, dim3(kSmall), lds, st, s, a, keys, cent, codes, sums, counts);
+      else if constexpr (TT > 1)
+        hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, kSmall, 1, 1, false>), agrid, dim3(kSmall), lds, st, s, a, keys, cent, codes, sums, counts);
+    }
   }
 }
 template <typename T, bool ACCUM>

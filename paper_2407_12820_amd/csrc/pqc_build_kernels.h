@@ -133,14 +133,15 @@ __device__ __forceinline__ float fixed_mean(unsigned long long sum, unsigned cou
   return (float)((double)(long long)sum * (1.0 / (double)(1 << kFixShift)) / (double)count);
 }
 
-template <bool TURNED>  // rows of Dm sums in the order of sum_place, or rows of Dm + 1 sums as they are
+enum class SumRow { kOdd, kPlain, kPlaced };  // rows of Dm + 1 sums; of Dm sums; of Dm sums in the order of sum_place
+template <SumRow ROW>
 __device__ __forceinline__ int sum_index(const BuildShape& s, int c, int e) {
-  return TURNED ? c * s.Dm + sum_place(e) : c * (s.Dm + 1) + e;
+  return ROW == SumRow::kOdd ? c * (s.Dm + 1) + e : c * s.Dm + (ROW == SumRow::kPlaced ? sum_place(e) : e);
 }
 
 // The accumulators to the workspace; a workgroup that owns all tokens of its (unit, partition) writes the new centroids
 // itself (nobody else reads them in this launch, and it has staged the old ones).
-template <bool TURNED>
+template <SumRow ROW>
 __device__ __forceinline__ void round_flush(const BuildShape& s, const RoundGrid& r, int uj, int p, const unsigned long long* sums,
                                             const unsigned* cnt, float* __restrict__ cent, unsigned long long* __restrict__ part_sums,
                                             unsigned* __restrict__ part_counts) {
@@ -152,7 +153,7 @@ __device__ __forceinline__ void round_flush(const BuildShape& s, const RoundGrid
   for (int i0 = threadIdx.x; i0 < n; i0 += blockDim.x) {
     const int i = i0 + first < n ? i0 + first : i0 + first - n;
     const int c = i / s.Dm, e = i - c * s.Dm;
-    const unsigned long long v = sums[sum_index<TURNED>(s, c, e)] - (unsigned long long)cnt[c] * (unsigned long long)kFixBiasBits;
+    const unsigned long long v = sums[sum_index<ROW>(s, c, e)] - (unsigned long long)cnt[c] * (unsigned long long)kFixBiasBits;
     if (r.ranges == 1) {
       if (cnt[c]) cent[(size_t)uj * n + i] = fixed_mean(v, cnt[c]);
     } else if (!shared) {
@@ -400,50 +401,70 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
   }
   if constexpr (ACCUM) {
     __syncthreads();
-    round_flush<TURNED>(s, r, uj, p, sums, cnt, cent, part_sums, part_counts);
+    round_flush<TURNED ? SumRow::kPlaced : SumRow::kOdd>(s, r, uj, p, sums, cnt, cent, part_sums, part_counts);
   }
 }
 
-// fp32 keys, and sub-vectors of 16 dimensions: on the vector ALU, distances as sum_e (x_e - c_e)^2, e ascending.  Four
-// lanes share a token (lane = 16*quad + token): quad q runs the chains of centroids q, q+4, ..., so that short caches
-// still occupy the chip (a single fp32 head of 10007 tokens is 157 waves at one token per lane), and adds the
-// dimensions q, q+4, ... of the key to the sums.
-template <int DM>
-constexpr int round_vector_threads() { return DM >= 128 ? 512 : 1024; }
-template <typename T, int DM, bool ACCUM>
-__global__ __launch_bounds__(round_vector_threads<DM>()) void pq_round_vector_kernel(BuildShape s, RoundGrid r, const T* __restrict__ keys,
-                                                                                     float* cent,
-                                                                                     uint8_t* __restrict__ codes,
-                                                                                     unsigned long long* __restrict__ part_sums,
-                                                                                     unsigned* __restrict__ part_counts) {
-  constexpr int NT = round_vector_threads<DM>(), NW = NT / 64, RS = DM + 4;
+// Values turned: value e becomes the one that was value (e + n) modulo N, n < 64.  (Bit masks instead of selections,
+// which the compiler turns into indexed registers.)
+template <int N>
+__device__ __forceinline__ void turn_values(float (&x)[N], int n) {
+#pragma unroll
+  for (int b = 1; b < N && b < 64; b <<= 1) {
+    unsigned y[N];
+    const unsigned mask = n & b ? ~0u : 0u;
+#pragma unroll
+    for (int e = 0; e < N; ++e) y[e] = (__float_as_uint(x[(e + b) % N]) & mask) | (__float_as_uint(x[e]) & ~mask);
+#pragma unroll
+    for (int e = 0; e < N; ++e) x[e] = __uint_as_float(y[e]);
+  }
+}
+
+// fp32 keys, and sub-vectors of 16 dimensions: on the vector ALU, distances as sum_e (x_e - c_e)^2, e ascending.  Bound by the
+// vector ALU: two instructions per dimension and centroid.
+// LANES = 1: a lane owns TT tokens and runs all their chains.  LANES = 4: four lanes share a token (lane = 16*quad + token):
+// quad q runs the chains of centroids q, q+4, ..., so that short caches still occupy the chip (a single fp32 head of 10007
+// tokens is 157 waves at one token per lane), and adds the dimensions q, q+4, ... of the key to the sums.
+template <typename T, int DM, int NT, int LANES, int TT, bool ACCUM>
+__global__ __launch_bounds__(NT) void pq_round_vector_kernel(BuildShape s, RoundGrid r, const T* __restrict__ keys, float* cent,
+                                                             uint8_t* __restrict__ codes, unsigned long long* __restrict__ part_sums,
+                                                             unsigned* __restrict__ part_counts) {
+  static_assert(DM % 8 == 0 && (LANES == 1 || (LANES == 4 && TT == 1)), "several tokens per lane, or several lanes per token");
+  constexpr int NW = NT / 64, RS = DM + 4;
+  constexpr int TS = 64 / LANES;  // tokens side by side in a wave
+  // Sixteen waves are all that fit a compute unit beside the sums, so that a wave needs several chains of its own: CC centroids of
+  // TT tokens, four differences of each ahead of the additions that wait for them, the next four values of the centroids read
+  // from LDS meanwhile.  (Assignment of 64 x 32768 tokens, one chain per wave and each difference right before its addition:
+  // 3670 us with 2x256 and 1290 with 1x64; so 2850 and 770.)
+  constexpr int CC = DM >= 128 ? 4 : 2;
+  // LANES = 1: a lane starts its additions at the dimension of its own number, and rows of DM sums make the bank of a sum depend
+  // on its dimension alone (DM a multiple of 32), so that lanes meet in few addresses whatever their centroids are (131072 equal
+  // tokens x 8 heads, bf16, 8x16, three rounds: 1900 us with the lanes of a wave in one address, 500 so).
+  constexpr bool TURNED = LANES == 1;
+  constexpr int SR = TURNED ? DM : DM + 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char round_lds[];
-  float* cs = reinterpret_cast<float*>(round_lds);  // [staged][RS]
-  unsigned long long* sums = reinterpret_cast<unsigned long long*>(round_lds + vector_stage_bytes(r.staged, DM));
-  unsigned* cnt = reinterpret_cast<unsigned*>(sums + s.C * (DM + 1));
+  float* cs = reinterpret_cast<float*>(round_lds);  // [C][RS]
+  unsigned long long* sums = reinterpret_cast<unsigned long long*>(round_lds + vector_stage_bytes(s.C, DM));
+  unsigned* cnt = reinterpret_cast<unsigned*>(sums + s.C * SR);
   int u, j, p;
   round_place(s, r.ranges, u, j, p);
   const int uj = u * s.M + j, tid = threadIdx.x;
-  const int lane = tid & 63, w = tid >> 6, col = lane & 15, quad = lane >> 4;
+  const int lane = tid & 63, w = tid >> 6, col = lane % TS, quad = lane / TS;
   const int t_begin = p * r.tokens, t_end = min(s.N, t_begin + r.tokens);
-  const bool one_group = s.C <= r.staged;
-  auto stage = [&](int c0) {
-    const int nc = min(r.staged, s.C - c0);
-    const f32x4_t* src = reinterpret_cast<const f32x4_t*>(cent + ((size_t)uj * s.C + c0) * DM);
-    for (int i = tid; i < nc * (DM / 4); i += NT) *reinterpret_cast<f32x4_t*>(&cs[(i / (DM / 4)) * RS + 4 * (i % (DM / 4))]) = src[i];
-  };
-  if (one_group) stage(0);
+  {
+    const f32x4_t* src = reinterpret_cast<const f32x4_t*>(cent + (size_t)uj * s.C * DM);
+    for (int i = tid; i < s.C * (DM / 4); i += NT) *reinterpret_cast<f32x4_t*>(&cs[(i / (DM / 4)) * RS + 4 * (i % (DM / 4))]) = src[i];
+  }
   if constexpr (ACCUM) {
-    for (int i = tid; i < s.C * (DM + 1); i += NT) sums[i] = 0ull;
+    for (int i = tid; i < s.C * SR; i += NT) sums[i] = 0ull;
     for (int i = tid; i < s.C; i += NT) cnt[i] = 0u;
   }
-  if (one_group) __syncthreads();
-  for (int b0 = t_begin; b0 < t_end; b0 += NW * 16) {  // workgroup-uniform
-    const int tok0 = b0 + w * 16;
-    const bool live = tok0 < t_end;  // wave-uniform
-    float x[DM];
-    if (live) {
-      const T* kp = keys + ((size_t)u * s.cap + min(tok0 + col, s.N - 1)) * kD + j * DM;
+  __syncthreads();
+  for (int tok0 = t_begin + w * TS * TT; tok0 < t_end; tok0 += NW * TS * TT) {  // wave-uniform
+    float x[TT][DM];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+      const T* kp = keys + ((size_t)u * s.cap + min(tok0 + tt * TS + col, s.N - 1)) * kD + j * DM;
       constexpr int EPV = 16 / (int)sizeof(T);
 #pragma unroll
       for (int v = 0; v < DM / EPV; ++v) {
@@ -452,69 +473,125 @@ __global__ __launch_bounds__(round_vector_threads<DM>()) void pq_round_vector_ke
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           if constexpr (sizeof(T) == 2) {
-            x[v * EPV + 2 * e] = __uint_as_float(rw[e] << 16);
-            x[v * EPV + 2 * e + 1] = __uint_as_float(rw[e] & 0xffff0000u);
+            x[tt][v * EPV + 2 * e] = __uint_as_float(rw[e] << 16);
+            x[tt][v * EPV + 2 * e + 1] = __uint_as_float(rw[e] & 0xffff0000u);
           } else {
-            x[v * EPV + e] = __uint_as_float(rw[e]);
+            x[tt][v * EPV + e] = __uint_as_float(rw[e]);
           }
         }
       }
     }
-    float best = INFINITY;
-    int arg = 0;
-    for (int c0 = 0; c0 < s.C; c0 += r.staged) {
-      if (!one_group) {
-        __syncthreads();
-        stage(c0);
-        __syncthreads();
+    float best[TT];
+    int arg[TT];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+      best[tt] = INFINITY;
+      arg[tt] = 0;
+    }
+    f32x4_t cv[2][CC];  // four values of each centroid, and the next four on their way
+    auto centroid = [&](int c0, int k) { return min(c0 + k * LANES, s.C - 1); };  // (the last one again: not nearer than itself)
+    auto read = [&](f32x4_t (&v)[CC], int c0, int e) {
+#pragma unroll
+      for (int k = 0; k < CC; ++k) v[k] = *reinterpret_cast<const f32x4_t*>(&cs[centroid(c0, k) * RS + 4 * e]);
+    };
+    const int c_first = LANES == 1 ? 0 : quad;
+    read(cv[0], c_first, 0);
+    for (int c0 = c_first; c0 < s.C; c0 += LANES * CC) {
+      float d2[CC][TT];
+#pragma unroll
+      for (int k = 0; k < CC; ++k)
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) d2[k][tt] = 0.0f;
+#pragma unroll
+      for (int e = 0; e < DM / 4; ++e) {
+        if (e + 1 < DM / 4)
+          read(cv[(e + 1) & 1], c0, e + 1);
+        else
+          read(cv[0], c0 + LANES * CC, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        float df[CC][TT][4];
+#pragma unroll
+        for (int k = 0; k < CC; ++k)
+#pragma unroll
+          for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+            for (int y = 0; y < 4; ++y) df[k][tt][y] = x[tt][4 * e + y] - cv[e & 1][k][y];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+#pragma unroll
+          for (int k = 0; k < CC; ++k)
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) d2[k][tt] = fmaf(df[k][tt][y], df[k][tt][y], d2[k][tt]);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      if (!live) continue;
-      const int nc = min(r.staged, s.C - c0);
-      for (int c = quad; c < nc; c += 4) {
-        const f32x4_t* cr = reinterpret_cast<const f32x4_t*>(&cs[c * RS]);
-        float d2 = 0.0f;
 #pragma unroll
-        for (int e = 0; e < DM / 4; ++e) {
-          const f32x4_t cv = cr[e];
+      for (int k = 0; k < CC; ++k)
 #pragma unroll
-          for (int y = 0; y < 4; ++y) {
-            const float df = x[4 * e + y] - cv[y];
-            d2 = fmaf(df, df, d2);
+        for (int tt = 0; tt < TT; ++tt) {
+          const bool lower = d2[k][tt] < best[tt];
+          best[tt] = lower ? d2[k][tt] : best[tt];
+          arg[tt] = lower ? centroid(c0, k) : arg[tt];
+        }
+    }
+    if constexpr (LANES == 4) {
+#pragma unroll
+      for (int o = 16; o <= 32; o <<= 1) {  // equal values: lower centroid index
+        const float ov = __shfl_xor(best[0], o);
+        const int oi = __shfl_xor(arg[0], o);
+        const bool take = ov < best[0] || (ov == best[0] && oi < arg[0]);
+        best[0] = take ? ov : best[0];
+        arg[0] = take ? oi : arg[0];
+      }
+    }
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+      const int t = tok0 + tt * TS + col;
+      if constexpr (!ACCUM) {
+        if (quad == 0 && t < t_end) codes[((size_t)u * s.cap + t) * s.M + j] = (uint8_t)arg[tt];
+      } else if constexpr (LANES == 4) {
+        if (t < t_end) {
+          unsigned long long* row = sums + arg[0] * SR + quad;
+          if (quad == 0) atomicAdd(&cnt[arg[0]], 1u);
+#pragma unroll
+          for (int e = 0; e < DM / 4; ++e) {
+            const float v = quad == 0 ? x[0][4 * e] : quad == 1 ? x[0][4 * e + 1] : quad == 2 ? x[0][4 * e + 2] : x[0][4 * e + 3];
+            atomicAdd(&row[4 * e], __builtin_expect(!(fabsf(v) < 1073741824.0f), 0) ? fix_biased_large(v) : fix_biased(v));
           }
         }
-        if (d2 < best) {
-          best = d2;
-          arg = c0 + c;
+      } else {
+        int turn = lane;
+        asm("" : "+v"(turn));  // (else the places of all additions are kept in registers across the loop)
+        turn_values(x[tt], turn);
+        if (t < t_end) {
+          // the members of the first lane's centroid are counted in one go: lanes that meet in one address add one by one
+          const int first = __builtin_amdgcn_readfirstlane(arg[tt]);
+          const unsigned long long same = __ballot(arg[tt] == first);
+          if (arg[tt] != first)
+            atomicAdd(&cnt[arg[tt]], 1u);
+          else if (lane == 0)
+            atomicAdd(&cnt[first], (unsigned)__popcll(same));
+          unsigned long long* row = sums + arg[tt] * SR;
+#pragma unroll
+          for (int e0 = 0; e0 < DM; e0 += 8) {
+            float top = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) top = __builtin_elementwise_maximum(fabsf(x[tt][e0 + e]), top);  // NaN stays
+            if (__builtin_expect(!(top < 1073741824.0f), 0)) {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) atomicAdd(&row[(turn + e0 + e) & (DM - 1)], fix_biased_large(x[tt][e0 + e]));
+            } else {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) atomicAdd(&row[(turn + e0 + e) & (DM - 1)], fix_biased(x[tt][e0 + e]));
+            }
+          }
         }
       }
-    }
-    if (!live) continue;
-#pragma unroll
-    for (int o = 16; o <= 32; o <<= 1) {  // equal values: lower centroid index
-      const float ov = __shfl_xor(best, o);
-      const int oi = __shfl_xor(arg, o);
-      const bool take = ov < best || (ov == best && oi < arg);
-      best = take ? ov : best;
-      arg = take ? oi : arg;
-    }
-    const int t = tok0 + col;
-    if constexpr (ACCUM) {
-      if (t < t_end) {
-        unsigned long long* row = sums + arg * (DM + 1) + quad;
-        if (quad == 0) atomicAdd(&cnt[arg], 1u);
-#pragma unroll
-        for (int e = 0; e < DM / 4; ++e) {
-          const float v = quad == 0 ? x[4 * e] : quad == 1 ? x[4 * e + 1] : quad == 2 ? x[4 * e + 2] : x[4 * e + 3];
-          atomicAdd(&row[4 * e], __builtin_expect(!(fabsf(v) < 1073741824.0f), 0) ? fix_biased_large(v) : fix_biased(v));
-        }
-      }
-    } else {
-      if (quad == 0 && t < t_end) codes[((size_t)u * s.cap + t) * s.M + j] = (uint8_t)arg;
     }
   }
   if constexpr (ACCUM) {
     __syncthreads();
-    round_flush<false>(s, r, uj, p, sums, cnt, cent, part_sums, part_counts);
+    round_flush<TURNED ? SumRow::kPlain : SumRow::kOdd>(s, r, uj, p, sums, cnt, cent, part_sums, part_counts);
   }
 }
 

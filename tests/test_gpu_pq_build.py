@@ -203,6 +203,10 @@ def test_build_at_full_length_matches_oracle(pqc, name, T):
     ("bf16", 8, 200, 500, 2, ""), ("f32", 8, 33, 257, 2, ""), ("f32", 4, 256, 1000, 1, ""), ("f32", 2, 64, 15, 2, ""),
     ("f32", 1, 256, 600, 1, ""), ("f32", 1, 9, 513, 2, ""), ("bf16", 2, 48, 1600, 2, "huge"), ("f32", 4, 16, 400, 2, "huge"),
     ("bf16", 4, 32, 900, 2, "twins"), ("bf16", 2, 32, 900, 2, "twins"), ("f32", 2, 32, 900, 2, "twins"),
+    # one range of tokens per (unit, partition), so that the vector kernel has whole tokens per lane: one and two at a time (two for
+    # 16 and 32 dimensions), a batch and a little of the next, fewer centroids than run side by side
+    ("f32", 2, 9, 2063, 128, ""), ("f32", 4, 17, 4111, 64, ""), ("f32", 4, 3, 1100, 64, "huge"), ("bf16", 8, 20, 4099, 32, ""),
+    ("bf16", 8, 2, 1031, 32, "twins"), ("f32", 1, 9, 519, 256, ""), ("f32", 1, 2, 1024, 256, "huge"), ("f32", 8, 18, 2048, 32, "twins"),
 ])
 def test_round_edges(pqc, dtype, m, c, n, units, kind):
     w = wl.Workload(name="round", batch=units, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=n, pq_m=m, pq_centroids=c,
@@ -297,6 +301,37 @@ def test_build_in_the_smallest_workspace_at_several_lengths(pqc, dtype, m, c, un
         want_cent, want_codes = pqc.pq_build(w, keys, init)
         torch.cuda.synchronize()
         assert torch.equal(cent, want_cent) and torch.equal(codes, want_codes), n
+
+
+def _shortest(fn):
+    """Milliseconds of one call: the shortest of eight runs of ten."""
+    best = float("inf")
+    for _ in range(9):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        for _ in range(10):
+            fn()
+        t1.record()
+        t1.synchronize()
+        best = min(best, t0.elapsed_time(t1) / 10)
+    return best
+
+
+# The vector kernel on long inputs, against a copy of the keys (read and written once) on the same card: with four lanes per token
+# whatever the length, and one range per unit on 128 compute units at most, these took 1.8 and 6.6 copies.
+@pytest.mark.parametrize("dtype,m,c,units,copies", [("bf16", 8, 16, 8, 1.3), ("f32", 1, 64, 1, 4.0)])
+def test_assignment_of_long_inputs_keeps_up(pqc, dtype, m, c, units, copies):
+    n = 131072
+    w = wl.Workload(name="round", batch=units, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=n, pq_m=m, pq_centroids=c,
+                    topk=n // 4, n_init=0, n_local=0, dtype=dtype, kmeans_iters=1, recipe="plain")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(1)
+    keys = torch.randn((units, 1, n, 128), generator=gen, device=DEV, dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    cent = torch.randn((units, 1, m, c, 128 // m), generator=gen, device=DEV)
+    copy = torch.empty_like(keys)
+    took, ref = _shortest(lambda: pqc.pq_assign(w, keys, cent)), _shortest(lambda: copy.copy_(keys))
+    print(f"[result] {dtype} m={m} c={c}: {took * 1e3:.1f} us, a copy {ref * 1e3:.1f} us", flush=True)
+    assert took <= copies * ref
 
 
 def test_encode_token_writes_nearest_codes_in_place(pqc):
