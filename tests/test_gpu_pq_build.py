@@ -334,6 +334,29 @@ def test_assignment_of_long_inputs_keeps_up(pqc, dtype, m, c, units, copies):
     assert took <= copies * ref
 
 
+# Keys of which all share a centroid (padding, a repeated token) against keys that spread: lanes that add to one address add one
+# after the other, which took up to 3.4 times as long before the additions of a wave were spread over the dimensions.
+@pytest.mark.parametrize("dtype,m,c", [("bf16", 4, 16), ("bf16", 4, 256), ("bf16", 2, 64), ("bf16", 8, 16), ("f32", 4, 64)])
+def test_equal_keys_build_as_fast_as_others(pqc, dtype, m, c):
+    n, units = 131072, 8
+    w = wl.Workload(name="round", batch=units, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=n, pq_m=m, pq_centroids=c,
+                    topk=n // 4, n_init=0, n_local=0, dtype=dtype, kmeans_iters=2, recipe="plain")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(2)
+    keys = torch.randn((units, 1, n, 128), generator=gen, device=DEV, dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    init = torch.from_numpy(wl.kmeans_init_indices(w, seed=3)).to(DEV)
+    spread = _shortest(lambda: pqc.pq_build(w, keys, init))
+    keys[:] = keys[:, :, :1].clone()
+    equal = _shortest(lambda: pqc.pq_build(w, keys, init))
+    print(f"[result] {dtype} m={m} c={c}: {spread * 1e3:.1f} us, equal keys {equal * 1e3:.1f} us", flush=True)
+    assert equal <= 1.5 * spread
+    # and the sums are right: after one round the lowest of the equal centroids is the mean of all tokens, and codes are all alike
+    cent, codes = pqc.pq_build(w, keys, init, iters=1)
+    want = keys[:, 0, 0].float().view(units, m, w.sub_dim)
+    assert (cent[:, 0, :, 0] - want).abs().max() <= 2.0 ** -20 + 2e-6 * want.abs().max()
+    assert torch.equal(codes, codes[:, :, :1].expand_as(codes))
+
+
 def test_encode_token_writes_nearest_codes_in_place(pqc):
     w = wl.get("batch8_32k", batch=3, n_tokens=700)
     d = wl.generate(w, seed=13)
