@@ -695,18 +695,18 @@ namespace {
 
 struct BuildPlan {
   BuildShape s;
-  RoundGrid round;    // a K-Means round: assignment and sums in one pass
-  RoundGrid assign;   // the assignment alone
-  bool fused;         // the accumulators of a round fit into LDS beside the centroids
-  bool mfma;
+  int staged;  // centroids staged at a time
+  bool fused;  // the accumulators of a round fit into LDS beside the centroids
 };
 
 constexpr size_t kRoundLds = 156 * 1024;  // of the compute unit's 160 KB
 
 // Token ranges per (unit, partition).  One workgroup fills a compute unit, so the time of a launch is that of its rounds of
 // 256 workgroups; each pays for staging the centroids and writing the sums what about 1024 tokens cost.
-RoundGrid round_grid(const BuildShape& s, int staged) {
-  RoundGrid r{1, 1, (s.N + 15) / 16 * 16, staged};
+// (A search of up to 256 steps: for calls that launch such a grid.)
+RoundGrid round_grid(const BuildPlan& bp) {
+  const BuildShape& s = bp.s;
+  RoundGrid r{1, 1, (s.N + 15) / 16 * 16, bp.staged};
   double best = 1e30;
   const double least = (double)s.units * s.M * s.N / 256.0;  // all compute units busy
   for (int p = 1; p <= 256; ++p) {
@@ -731,13 +731,11 @@ int make_build_plan(const pqc_config* cfg, BuildPlan* bp) {
   BuildShape& s = bp->s;
   s.units = p.s.B * p.s.Hkv;
   s.N = p.s.N; s.M = p.s.M; s.C = p.s.C; s.Dm = p.s.Dm; s.cap = p.s.cap;
-  bp->mfma = cfg->kv_dtype == PQC_BF16 && s.Dm >= 32;
-  auto stage_bytes = [&](int n) { return bp->mfma ? mfma_stage_bytes(n, s.Dm) : vector_stage_bytes(n, s.Dm); };
-  int staged = s.C;
-  while (stage_bytes(staged) > kRoundLds) staged = (staged / 2 + 15) / 16 * 16;
-  bp->assign = round_grid(s, staged);
+  const bool mfma = cfg->kv_dtype == PQC_BF16 && s.Dm >= 32;
+  auto stage_bytes = [&](int n) { return mfma ? mfma_stage_bytes(n, s.Dm) : vector_stage_bytes(n, s.Dm); };
+  bp->staged = s.C;
+  while (stage_bytes(bp->staged) > kRoundLds) bp->staged = (bp->staged / 2 + 15) / 16 * 16;
   bp->fused = stage_bytes(s.C) + round_sum_bytes(s.C, s.Dm) <= kRoundLds;
-  bp->round = bp->assign;
   return PQC_OK;
 }
 
@@ -758,10 +756,8 @@ int most_sum_sets(const BuildPlan& bp) {
 
 // One launch over all token ranges: with sums a K-Means round, without it the assignment (codes written).
 template <typename T, int DM, bool ACCUM>
-void launch_round_d(const BuildPlan& bp, const T* keys, float* cent, uint8_t* codes, unsigned long long* sums, unsigned* counts,
-                    hipStream_t st) {
-  const BuildShape& s = bp.s;
-  const RoundGrid& r = ACCUM ? bp.round : bp.assign;
+void launch_round_d(const BuildShape& s, const RoundGrid& r, const T* keys, float* cent, uint8_t* codes, unsigned long long* sums,
+                    unsigned* counts, hipStream_t st) {
   const dim3 grid((unsigned)(s.units * s.M * r.ranges));
   const size_t acc = ACCUM ? round_sum_bytes(s.C, s.Dm) : 0;
   if constexpr (sizeof(T) == 2 && DM >= 32) {
@@ -806,37 +802,37 @@ void launch_round_d(const BuildPlan& bp, const T* keys, float* cent, uint8_t* co
   }
 }
 template <typename T, bool ACCUM>
-void launch_round(const BuildPlan& bp, const T* keys, float* cent, uint8_t* codes, unsigned long long* sums, unsigned* counts,
-                  hipStream_t st) {
-  switch (bp.s.Dm) {
-    case 16: launch_round_d<T, 16, ACCUM>(bp, keys, cent, codes, sums, counts, st); break;
-    case 32: launch_round_d<T, 32, ACCUM>(bp, keys, cent, codes, sums, counts, st); break;
-    case 64: launch_round_d<T, 64, ACCUM>(bp, keys, cent, codes, sums, counts, st); break;
-    default: launch_round_d<T, 128, ACCUM>(bp, keys, cent, codes, sums, counts, st); break;
+void launch_round(const BuildShape& s, const RoundGrid& r, const T* keys, float* cent, uint8_t* codes, unsigned long long* sums,
+                  unsigned* counts, hipStream_t st) {
+  switch (s.Dm) {
+    case 16: launch_round_d<T, 16, ACCUM>(s, r, keys, cent, codes, sums, counts, st); break;
+    case 32: launch_round_d<T, 32, ACCUM>(s, r, keys, cent, codes, sums, counts, st); break;
+    case 64: launch_round_d<T, 64, ACCUM>(s, r, keys, cent, codes, sums, counts, st); break;
+    default: launch_round_d<T, 128, ACCUM>(s, r, keys, cent, codes, sums, counts, st); break;
   }
 }
 template <typename T>
-void launch_assign(const BuildPlan& bp, const T* keys, const float* cent, uint8_t* codes, hipStream_t st) {
-  launch_round<T, false>(bp, keys, const_cast<float*>(cent), codes, nullptr, nullptr, st);  // read only without sums
+void launch_assign(const BuildShape& s, const RoundGrid& r, const T* keys, const float* cent, uint8_t* codes, hipStream_t st) {
+  launch_round<T, false>(s, r, keys, const_cast<float*>(cent), codes, nullptr, nullptr, st);  // read only without sums
 }
 
 template <typename T>
-int pq_build_t(const BuildPlan& bp, const T* keys, const int32_t* init_idx, int iters, float* cent, uint8_t* codes,
+int pq_build_t(const BuildPlan& bp, const RoundGrid& r, const T* keys, const int32_t* init_idx, int iters, float* cent, uint8_t* codes,
                char* wsp, hipStream_t st) {
   const BuildShape& s = bp.s;
-  const int sets = bp.fused ? bp.round.sets : 1;
+  const int sets = bp.fused ? r.sets : 1;
   unsigned long long* sums = reinterpret_cast<unsigned long long*>(wsp);
   unsigned* counts = reinterpret_cast<unsigned*>(wsp + build_workspace(s, sets).off_counts);
   const unsigned uj = (unsigned)(s.units * s.M);
   const dim3 per_cent((unsigned)((s.C * s.Dm + 255) / 256), uj);
-  const bool means = !bp.fused || bp.round.ranges > 1;  // else a round writes them itself
+  const bool means = !bp.fused || r.ranges > 1;  // else a round writes them itself
   hipLaunchKernelGGL((pq_init_kernel<T>), per_cent, dim3(256), 0, st, s, keys, init_idx, cent,
                      means && sets == 1 ? sums : nullptr, counts);
   for (int it = 0; it < iters; ++it) {
     if (bp.fused) {
-      launch_round<T, true>(bp, keys, cent, codes, sums, counts, st);
+      launch_round<T, true>(s, r, keys, cent, codes, sums, counts, st);
     } else {  // the accumulators are too large for LDS: codes first, then the sums of the members of each code
-      launch_assign<T>(bp, keys, cent, codes, st);
+      launch_assign<T>(s, r, keys, cent, codes, st);
       const int tpw = accum_tokens_per_wg(s.C);
       const dim3 grid((s.N + tpw - 1) / tpw, uj);
       const size_t lds = (size_t)tpw * sizeof(unsigned short);
@@ -849,7 +845,7 @@ int pq_build_t(const BuildPlan& bp, const T* keys, const int32_t* init_idx, int 
     }
     if (means) hipLaunchKernelGGL(pq_mean_kernel, per_cent, dim3(256), 0, st, s, sets, sums, counts, cent);
   }
-  launch_assign<T>(bp, keys, cent, codes, st);
+  launch_assign<T>(s, r, keys, cent, codes, st);
   return hipGetLastError() == hipSuccess ? PQC_OK : PQC_EHIP;
 }
 
@@ -872,12 +868,12 @@ int pqc_pq_build(const pqc_config* cfg, const void* keys, const int32_t* init_id
   if (!aligned16(keys) || !aligned16(init_idx) || !aligned16(centroids) || !aligned16(codes)) return PQC_EINVAL;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kAlign) || workspace_bytes < build_workspace(bp.s, 1).total)
     return PQC_EWORKSPACE;
-  if (bp.round.ranges <= most_sum_sets(bp) && workspace_bytes >= build_workspace(bp.s, bp.round.ranges).total)
-    bp.round.sets = bp.round.ranges;
+  RoundGrid r = round_grid(bp);
+  if (r.ranges <= most_sum_sets(bp) && workspace_bytes >= build_workspace(bp.s, r.ranges).total) r.sets = r.ranges;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* wsp = static_cast<char*>(workspace);
-  if (cfg->kv_dtype == PQC_F32) return pq_build_t<float>(bp, static_cast<const float*>(keys), init_idx, iters, centroids, codes, wsp, st);
-  return pq_build_t<bf16_t>(bp, static_cast<const bf16_t*>(keys), init_idx, iters, centroids, codes, wsp, st);
+  if (cfg->kv_dtype == PQC_F32) return pq_build_t<float>(bp, r, static_cast<const float*>(keys), init_idx, iters, centroids, codes, wsp, st);
+  return pq_build_t<bf16_t>(bp, r, static_cast<const bf16_t*>(keys), init_idx, iters, centroids, codes, wsp, st);
 }
 
 int pqc_pq_assign(const pqc_config* cfg, const void* keys, const float* centroids, uint8_t* codes, void* stream) {
@@ -886,11 +882,12 @@ int pqc_pq_assign(const pqc_config* cfg, const void* keys, const float* centroid
   if (rc != PQC_OK) return rc;
   if (!keys || !centroids || !codes) return PQC_EINVAL;
   if (!aligned16(keys) || !aligned16(centroids) || !aligned16(codes)) return PQC_EINVAL;
+  const RoundGrid r = round_grid(bp);
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (cfg->kv_dtype == PQC_F32)
-    launch_assign<float>(bp, static_cast<const float*>(keys), centroids, codes, st);
+    launch_assign<float>(bp.s, r, static_cast<const float*>(keys), centroids, codes, st);
   else
-    launch_assign<bf16_t>(bp, static_cast<const bf16_t*>(keys), centroids, codes, st);
+    launch_assign<bf16_t>(bp.s, r, static_cast<const bf16_t*>(keys), centroids, codes, st);
   return hipGetLastError() == hipSuccess ? PQC_OK : PQC_EHIP;
 }
 

@@ -209,3 +209,23 @@ def test_build_workspace_serves_every_length(name, units):
         cfg = binding.make_config(dataclasses.replace(w, n_tokens=n, topk=100))
         assert lib.pqc_pq_build_workspace_bytes(C.byref(cfg)) == need, n
         assert lib.pqc_pq_build(C.byref(cfg), p, p, 1, p, p, p, least - 1, None) == -3, n
+
+
+@pytest.mark.parametrize("name", ["tiny_f32", "llama8b_128k"])
+def test_encoding_a_token_plans_no_build(name):
+    # a decode loop encodes a token per layer and step: the call checks its configuration and nothing more, like
+    # pqc_pair_counts_add (both refused here for want of buffers, after the configuration); a search for a build's token
+    # ranges took 2.7 times that call
+    import time
+    lib = binding.load()
+    cfg = C.byref(binding.make_config(wl.CONFIGS[name]))
+    best = {"encode": 1e9, "count": 1e9}
+    for _ in range(40):
+        for call, fn in (("encode", lambda: lib.pqc_pq_encode_token(cfg, None, None, None, 0, None)),
+                         ("count", lambda: lib.pqc_pair_counts_add(cfg, None, 0, None, None))):
+            assert fn() == -1
+            t = time.perf_counter()
+            for _ in range(500):
+                fn()
+            best[call] = min(best[call], time.perf_counter() - t)
+    assert best["encode"] <= 1.6 * best["count"], best
