@@ -832,13 +832,13 @@ int pq_build_t(const BuildPlan& bp, const RoundGrid& r, const T* keys, const int
     if (bp.fused) {
       launch_round<T, true>(s, r, keys, cent, codes, sums, counts, st);
     } else {  // the accumulators are too large for LDS: codes first, then the sums of the members of each code
+      static_assert(mfma_stage_bytes(256, 32) + round_sum_bytes(256, 32) <= kRoundLds, "and 16 and 32 dimensions always fit");
+      static_assert(vector_stage_bytes(256, 32) + round_sum_bytes(256, 32) <= kRoundLds, "and 16 and 32 dimensions always fit");
       launch_assign<T>(s, r, keys, cent, codes, st);
       const int tpw = accum_tokens_per_wg(s.C);
       const dim3 grid((s.N + tpw - 1) / tpw, uj);
       const size_t lds = (size_t)tpw * sizeof(unsigned short);
       switch (s.Dm) {
-        case 16: hipLaunchKernelGGL((pq_accum_kernel<T, 16>), grid, dim3(256), lds, st, s, keys, codes, sums, counts); break;
-        case 32: hipLaunchKernelGGL((pq_accum_kernel<T, 32>), grid, dim3(256), lds, st, s, keys, codes, sums, counts); break;
         case 64: hipLaunchKernelGGL((pq_accum_kernel<T, 64>), grid, dim3(256), lds, st, s, keys, codes, sums, counts); break;
         default: hipLaunchKernelGGL((pq_accum_kernel<T, 128>), grid, dim3(256), lds, st, s, keys, codes, sums, counts); break;
       }

@@ -616,12 +616,12 @@ __global__ __launch_bounds__(NT) void pq_round_vector_kernel(BuildShape s, Round
   }
 }
 
-// sums[u][j][c][e] += fix(keys[u][t][j*Dm+e]) for every token t with code c; counts[u][j][c] += 1.
+// sums[u][j][c][e] += fix(keys[u][t][j*Dm+e]) for every token t with code c; counts[u][j][c] += 1.  For sums that do not fit
+// into LDS (64 dimensions and more, many centroids).
 // A workgroup first sorts its tokens by code (a counting sort in LDS: one 32-bit atomic per token), then each wave
 // takes centroids in turn and sums the centroid's members in registers: a lane loads 16 bytes of a member's
 // sub-vector (8 bf16 or 4 fp32 values), a group of Dm*sizeof(T)/16 lanes covers one member and a wave several
-// members per load; the lane groups' partial sums meet in a wave-private LDS tile.  (Adding every value to an LDS
-// accumulator with an atomic, as a first version did, is bound by the LDS atomic rate of about one lane per clock.)
+// members per load; the lane groups' partial sums meet in a wave-private LDS tile.
 // Sums are 64-bit integers of the values in fixed point (2^-20), so the result does not depend on the order of
 // the members, of the waves or of the workgroups.
 __host__ __device__ constexpr int accum_tokens_per_wg(int C) { return 32 * C < 2048 ? 2048 : (32 * C > 8192 ? 8192 : 32 * C); }
