@@ -132,28 +132,41 @@ def test_kmeans_converges_like_the_oracle(pqc, name):
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("name,T", [("llama8b_128k", 2), ("batch8_32k", 1)])
 def test_build_at_full_length_matches_oracle(pqc, name, T):
-    # One unit at the benchmark's own length (131072 tokens with two partitions of 64 centroids; 32768 tokens
-    # with four partitions of 256): the launch shape per (unit, partition) is the one bench.py builds with.
+    # The benchmark's own builds (131072 tokens x 8 heads with two partitions of 64 centroids; 32768 tokens x 64 heads
+    # with four partitions of 256), so that token ranges and tiles are the ones bench.py builds with; the last head is
+    # compared with the oracle, the others hold other keys.
     # Round by round, so that a legitimate near-tie in one round cannot hide behind the next: the start,
     # every round's centroids given the previous GPU codes are the oracle's member means, the final codes are
     # the oracle's nearest centroids of the GPU's own centroids.
     w0 = wl.get(name)
     w = wl.get(name, batch=1, n_q_heads=w0.group, n_kv_heads=1)
-    print(f"[case] pq build at full length, T={T}: {w}", flush=True)
+    print(f"[case] pq build at full length, T={T}: {w0}", flush=True)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(15)
     d = wl.generate(w, seed=15)
     init = wl.kmeans_init_indices(w, seed=15)
     kf = wl.to_f32(d["k"], w.dtype)
-    keys, init_d = pqc.to_device(d["k"], w.dtype, DEV), torch.from_numpy(init).to(DEV)
+    keys = torch.randn((w0.batch, w0.n_kv_heads, w0.n_tokens, w0.head_dim), generator=gen, device=DEV, dtype=torch.bfloat16)
+    keys[-1:, -1:] = pqc.to_device(d["k"], w.dtype, DEV)
+    init_d = torch.from_numpy(wl.kmeans_init_indices(w0, seed=16)).to(DEV)
+    init_d[-1:, -1:] = torch.from_numpy(init).to(DEV)
+
+    def build(iters):
+        cent, codes = pqc.pq_build(w0, keys, init_d, iters=iters)
+        return cent[-1:, -1:].cpu().numpy(), codes[-1:, -1:].cpu().numpy()
+
+    def assign(cent):
+        full = torch.randn((w0.batch, w0.n_kv_heads, *cent.shape[2:]), generator=gen, device=DEV)
+        full[-1:, -1:] = torch.from_numpy(cent).to(DEV)
+        return pqc.pq_assign(w0, keys, full)[-1:, -1:].cpu().numpy()
+
     near = 0
     # whole run against the oracle's run from the same start
     c_ref, cd_ref, inertia_ref = oracle.pq_build(d["k"], w.dtype, w.pq_m, w.pq_centroids, T, init)
-    cent, codes = pqc.pq_build(w, keys, init_d, iters=T)
-    torch.cuda.synchronize()
-    cent, codes = cent.cpu().numpy(), codes.cpu().numpy()
+    cent, codes = build(T)
     # (1) the final assignment is the stand-alone assignment, and every returned code is a nearest centroid of
     # the returned centroids (double-precision distances, up to fp32 near-ties)
-    cd_self = pqc.pq_assign(w, keys, torch.from_numpy(cent).to(DEV)).cpu().numpy()
-    np.testing.assert_array_equal(cd_self, codes)
+    np.testing.assert_array_equal(assign(cent), codes)
     Dm = w.sub_dim
     for j in range(w.pq_m):
         cj = cent[0, 0, j].astype(np.float64)
@@ -163,21 +176,17 @@ def test_build_at_full_length_matches_oracle(pqc, name, T):
             chosen = d2[np.arange(len(x)), codes[0, 0, t0:t0 + 8192, j]]
             assert np.all(chosen <= d2.min(1) * (1 + 1e-5) + 1e-9)
     # (2) round 0 of both sides: same start, same codes up to near-ties
-    c0, cd0 = pqc.pq_build(w, keys, init_d, iters=0)
+    c0, cd0 = build(0)
     c0_ref, cd0_ref, _ = oracle.pq_build(d["k"], w.dtype, w.pq_m, w.pq_centroids, 0, init)
-    torch.cuda.synchronize()
-    np.testing.assert_array_equal(c0.cpu().numpy(), c0_ref)
-    near += _codes_agree(kf, c0_ref, cd0.cpu().numpy(), cd0_ref, w.pq_m)
+    np.testing.assert_array_equal(c0, c0_ref)
+    near += _codes_agree(kf, c0_ref, cd0, cd0_ref, w.pq_m)
     # (3) one update: member means of that assignment (exact agreement of the codes makes the means comparable)
-    c1, _ = pqc.pq_build(w, keys, init_d, iters=1)
+    c1, _ = build(1)
     c1_ref, cd1_ref, _ = oracle.pq_build(d["k"], w.dtype, w.pq_m, w.pq_centroids, 1, init)
-    torch.cuda.synchronize()
     if near == 0:
-        np.testing.assert_allclose(c1.cpu().numpy(), c1_ref, rtol=2e-6, atol=2e-6)
+        np.testing.assert_allclose(c1, c1_ref, rtol=2e-6, atol=2e-6)
     # (4) assignment against the oracle's final centroids
-    cd = pqc.pq_assign(w, keys, torch.from_numpy(c_ref).to(DEV))
-    torch.cuda.synchronize()
-    near += _codes_agree(kf, c_ref, cd.cpu().numpy(), cd_ref, w.pq_m)
+    near += _codes_agree(kf, c_ref, assign(c_ref), cd_ref, w.pq_m)
     assert near <= 1e-3 * cd_ref.size
     # (5) the GPU's own run ends with the oracle's clustering quality, and with its centroids and codes when no
     # near-tie moved a token on the way
@@ -194,9 +203,11 @@ def test_build_at_full_length_matches_oracle(pqc, name, T):
 
 
 # One round and the assignment at the edges of the kernels' tiles and ranges: fewer tokens than a 16-token tile, one more than a
-# tile, one more than a wave's and a workgroup's batch, one range and several per (unit, partition), accumulators that do not fit
-# LDS (two partitions of 256), centroids staged in groups (one partition of 256), 16-dimensional sub-vectors, centroid counts
-# that are not a multiple of 16, fp32 keys of every sub-vector length; "huge": keys beyond 2^30, which are converted another way.
+# tile, one range and several per (unit, partition), accumulators that do not fit LDS (two partitions of 256), centroids staged in
+# groups (one partition of 256), 16-dimensional sub-vectors, centroid counts that are not a multiple of 16, fp32 keys of every
+# sub-vector length; "huge": keys beyond 2^30, which are converted another way; "crowd": most tokens are one and the same.
+# Few (unit, partition) pairs are cut into ranges of a few tokens; 256 of them get one range each, which is what brings a range
+# past a batch of its workgroup's sixteen waves.
 @pytest.mark.parametrize("dtype,m,c,n,units,kind", [
     ("bf16", 2, 64, 1, 1, ""), ("bf16", 2, 64, 17, 3, ""), ("bf16", 4, 256, 2049, 2, ""), ("bf16", 4, 7, 129, 2, ""),
     ("bf16", 4, 256, 300, 96, ""), ("bf16", 2, 256, 1000, 2, ""), ("bf16", 1, 256, 700, 2, ""), ("bf16", 1, 20, 2100, 1, ""),
@@ -207,6 +218,15 @@ def test_build_at_full_length_matches_oracle(pqc, name, T):
     # 16 and 32 dimensions), a batch and a little of the next, fewer centroids than run side by side
     ("f32", 2, 9, 2063, 128, ""), ("f32", 4, 17, 4111, 64, ""), ("f32", 4, 3, 1100, 64, "huge"), ("bf16", 8, 20, 4099, 32, ""),
     ("bf16", 8, 2, 1031, 32, "twins"), ("f32", 1, 9, 519, 256, ""), ("f32", 1, 2, 1024, 256, "huge"), ("f32", 8, 18, 2048, 32, "twins"),
+    # four lanes per token, several batches of 256 (128 dimensions: 128) tokens
+    ("f32", 2, 9, 700, 128, ""), ("f32", 1, 5, 300, 256, ""), ("bf16", 8, 7, 530, 32, "crowd"),
+    # the matrix-core kernel with two tiles per wave, a batch of 512 tokens and some of the next
+    ("bf16", 4, 17, 700, 64, ""), ("bf16", 2, 9, 900, 128, ""), ("bf16", 1, 20, 700, 256, ""),
+    # with eight, five and three tiles per wave (32, 64 and 128 dimensions): batches of 2048, 1280 and 768 tokens and some of the next,
+    # several such ranges, large and equal keys
+    ("bf16", 4, 17, 2100, 64, ""), ("bf16", 2, 9, 1303, 128, ""), ("bf16", 1, 20, 900, 256, ""), ("bf16", 2, 20, 5200, 32, ""),
+    ("bf16", 4, 9, 2100, 64, "huge"), ("bf16", 2, 9, 1303, 128, "huge"), ("bf16", 1, 9, 900, 256, "huge"),
+    ("bf16", 4, 9, 2100, 64, "crowd"), ("bf16", 2, 9, 1303, 128, "crowd"), ("bf16", 4, 16, 1000, 3, "crowd"), ("f32", 4, 9, 2100, 64, "crowd"),
 ])
 def test_round_edges(pqc, dtype, m, c, n, units, kind):
     w = wl.Workload(name="round", batch=units, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=n, pq_m=m, pq_centroids=c,
@@ -217,6 +237,9 @@ def test_round_edges(pqc, dtype, m, c, n, units, kind):
     kf = wl.to_f32(d["k"], dtype).copy()
     if kind == "huge":
         kf[rng.random(kf.shape[:3]) < 0.05] *= 3.0e9
+    if kind == "crowd":
+        same = rng.random(kf.shape[:3]) < 0.7
+        kf = np.where(same[..., None], kf[:, :, :1], kf)
     keys_h = kf if dtype == "f32" else wl.f32_to_bf16_bits(kf)
     kf = wl.to_f32(keys_h, dtype)
     init = wl.kmeans_init_indices(w, seed=3)
@@ -239,39 +262,47 @@ def test_round_edges(pqc, dtype, m, c, n, units, kind):
     for u in range(units):
         for j in range(m):
             x = kf[u, 0, :, j * Dm:(j + 1) * Dm].astype(np.float64)
-            for k in range(c):
-                members = cd0[u, 0, :, j] == k
-                want = x[members].mean(0) if members.any() else c0[u, 0, j, k].astype(np.float64)
-                # 2^-20 per key and one fp32 rounding; the mean of keys of both signs may cancel
-                tol = 2e-6 * (1.0 + np.abs(want)) + (2.0 ** -20 if kind != "huge" else np.abs(x[members]).max(initial=1.0) * 2.0 ** -24)
-                assert np.all(np.abs(c1[u, 0, j, k] - want) <= tol), (u, j, k)
+            members = (cd0[u, 0, :, j][:, None] == np.arange(c)).astype(np.float64)  # [n][c]
+            count = members.sum(0)
+            want = np.where(count[:, None] > 0, members.T @ x / np.maximum(count, 1.0)[:, None], c0[u, 0, j].astype(np.float64))
+            # 2^-20 per key and one fp32 rounding; the mean of keys of both signs may cancel
+            tol = 2e-6 * (1.0 + np.abs(want)) + 2.0 ** -20
+            if kind == "huge":
+                largest = np.stack([np.abs(x[members[:, k] > 0]).max(initial=1.0) for k in range(c)])
+                tol = 2e-6 * (1.0 + np.abs(want)) + largest[:, None] * 2.0 ** -24
+            assert np.all(np.abs(c1[u, 0, j] - want) <= tol), (u, j)
 
 
 # A key value that is not a number adds nothing to the sum of its centroid (its token still counts as a member) and leaves
 # every other dimension alone, whichever conversion the kernel takes for the values around it.
-@pytest.mark.parametrize("dtype,m,c", [("bf16", 4, 16), ("bf16", 2, 64), ("bf16", 1, 32), ("bf16", 1, 256), ("f32", 2, 16)])
-def test_round_passes_over_what_is_not_a_number(pqc, dtype, m, c):
-    n, Dm = 700, 128 // m
-    w = wl.Workload(name="round", batch=1, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=n, pq_m=m, pq_centroids=c,
+@pytest.mark.parametrize("dtype,m,c,n,units", [
+    ("bf16", 4, 16, 700, 1), ("bf16", 2, 64, 700, 1), ("bf16", 1, 32, 700, 1), ("bf16", 1, 256, 700, 1), ("f32", 2, 16, 700, 1),
+    # one range per (unit, partition): eight, five and three tiles per wave, one and two tokens per lane
+    ("bf16", 4, 16, 2100, 64), ("bf16", 2, 16, 1303, 128), ("bf16", 1, 16, 900, 256), ("bf16", 8, 16, 2100, 32), ("f32", 2, 16, 1100, 128),
+])
+def test_round_passes_over_what_is_not_a_number(pqc, dtype, m, c, n, units):
+    Dm = 128 // m
+    w = wl.Workload(name="round", batch=units, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=n, pq_m=m, pq_centroids=c,
                     topk=n // 4, n_init=0, n_local=0, dtype=dtype, kmeans_iters=1, recipe="plain")
-    print(f"[case] not a number {dtype} m={m} c={c}", flush=True)
+    print(f"[case] not a number {dtype} m={m} c={c} n={n} units={units}", flush=True)
     d = wl.generate(w, seed=c)
     init = wl.kmeans_init_indices(w, seed=3)
     kf = wl.to_f32(d["k"], dtype).copy()
     bad = np.setdiff1d(np.arange(n), init.ravel())[::37]
-    kf[0, 0, bad, (5 * bad) % 128] = np.nan
+    kf[:, 0, bad, (5 * bad) % 128] = np.nan
     keys = pqc.to_device(kf if dtype == "f32" else wl.f32_to_bf16_bits(kf), dtype, DEV)
     init_d = torch.from_numpy(init).to(DEV)
     _, cd0 = pqc.pq_build(w, keys, init_d, iters=0)
     c1, _ = pqc.pq_build(w, keys, init_d, iters=1)
     torch.cuda.synchronize()
     cd0, c1 = cd0.cpu().numpy(), c1.cpu().numpy()
-    x = np.nan_to_num(keys.float().cpu().numpy()[0, 0].astype(np.float64), nan=0.0)
-    for j in range(m):
-        for k in np.unique(cd0[0, 0, :, j]):
-            want = x[cd0[0, 0, :, j] == k, j * Dm:(j + 1) * Dm].mean(0)
-            # 2^-20 per key and one fp32 rounding
-            assert np.all(np.abs(c1[0, 0, j, k] - want) <= 2.0 ** -20 + 2e-6 * (1.0 + np.abs(want))), (j, k)
+    for u in {0, units // 2, units - 1}:
+        x = np.nan_to_num(keys[u, 0].float().cpu().numpy().astype(np.float64), nan=0.0)
+        for j in range(m):
+            for k in np.unique(cd0[u, 0, :, j]):
+                want = x[cd0[u, 0, :, j] == k, j * Dm:(j + 1) * Dm].mean(0)
+                # 2^-20 per key and one fp32 rounding
+                assert np.all(np.abs(c1[u, 0, j, k] - want) <= 2.0 ** -20 + 2e-6 * (1.0 + np.abs(want))), (u, j, k)
 
 
 # A workspace taken once serves every length, also one that holds a single set of sums per (unit, partition): ranges of tokens
