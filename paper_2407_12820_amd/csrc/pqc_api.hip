@@ -701,8 +701,9 @@ struct BuildPlan {
 
 constexpr size_t kRoundLds = 156 * 1024;  // of the compute unit's 160 KB
 
-// Token ranges per (unit, partition).  One workgroup fills a compute unit, so the time of a launch is that of its rounds of
-// 256 workgroups; each pays for staging the centroids and writing the sums what about 1024 tokens cost.
+// Token ranges per (unit, partition), up to 256 of them (one unit with one partition then has a workgroup on every compute
+// unit).  One workgroup fills a compute unit, so the time of a launch is that of its rounds of 256 workgroups; each pays for
+// staging the centroids and writing the sums what about 1024 tokens cost.
 // (A search of up to 256 steps: for calls that launch such a grid.)
 RoundGrid round_grid(const BuildPlan& bp) {
   const BuildShape& s = bp.s;
