@@ -8,6 +8,8 @@
 // independent of summation order and therefore reproducible; an empty cluster keeps its
 // centroid.
 #pragma once
+#include <type_traits>
+
 #include "pqc_device.h"
 
 namespace pqc {
@@ -344,67 +346,72 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
       }
     }
     if constexpr (ACCUM) {
-      // Lanes that meet in one address add one after the other.  Where half of the wave's first tile shares a centroid, members
-      // are counted together and, with 32 dimensions, the additions turned too (131072 equal tokens x 8 heads, 4x16, three
-      // rounds: 1446 -> 294 us; 20000 of one head 67 -> 33 us; keys that spread take the plain additions).
-      const bool crowded = __popcll(__ballot(bidx[0] == __builtin_amdgcn_readfirstlane(bidx[0]))) >= 32;  // wave-uniform
+      auto add_tiles = [&](auto crowd) {
+        constexpr bool CROWDED = decltype(crowd)::value, TURN = TURNED || CROWDED;
 #pragma unroll
-      for (int tt = 0; tt < TT; ++tt) {
-        if (tok0 + tt * 16 + col < t_end) {
-          unsigned long long* row = sums + bidx[tt] * SR;
-          if (!crowded) {
-            if (quad == 0) atomicAdd(&cnt[bidx[tt]], 1u);
-          } else {  // the first token's centroid counts its members of the tile in one go
-            const int first = __builtin_amdgcn_readfirstlane(bidx[tt]);
-            const int same = __popcll(__ballot(bidx[tt] == first));  // four lanes per token
-            if (quad == 0) {
-              if (bidx[tt] != first)
-                atomicAdd(&cnt[bidx[tt]], 1u);
-              else if (col == 0)
-                atomicAdd(&cnt[first], (unsigned)same / 4);
-            }
-          }
-#pragma unroll
-          for (int k0 = 0; k0 < KK; k0 += 2) {
-            unsigned rw[2][4];
-            __builtin_memcpy(rw[0], &x[tt][k0], 16);
-            __builtin_memcpy(rw[1], &x[tt][k0 + 1 < KK ? k0 + 1 : k0], 16);
-            if constexpr (KK > 1) {  // the upper eight lanes of a quad take the other 32 dimensions first
-#pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const unsigned lo = rw[0][i];
-                rw[0][i] = upper ? rw[1][i] : lo;
-                rw[1][i] = upper ? lo : rw[1][i];
+        for (int tt = 0; tt < TT; ++tt) {
+          if (tok0 + tt * 16 + col < t_end) {
+            unsigned long long* row = sums + bidx[tt] * SR;
+            if constexpr (CROWDED) {  // the first token's centroid counts its members of the tile in one go
+              const int first = __builtin_amdgcn_readfirstlane(bidx[tt]);
+              const int same = __popcll(__ballot(bidx[tt] == first));  // four lanes per token
+              if (quad == 0) {
+                if (bidx[tt] != first)
+                  atomicAdd(&cnt[bidx[tt]], 1u);
+                else if (col == 0)
+                  atomicAdd(&cnt[first], (unsigned)same / 4);
               }
+            } else {
+              if (quad == 0) atomicAdd(&cnt[bidx[tt]], 1u);
             }
 #pragma unroll
-            for (int h = 0; h < (KK > 1 ? 2 : 1); ++h) {
-              // dimensions of 32 * kk + 8 * quad + {turn, turn + 1, ... modulo 8}
-              unsigned long long* part = row + 32 * k0 + (KK > 1 && (h == 1) != upper ? sum_place(32 + 8 * quad) : 8 * quad);
-              float f[8], top = 0.0f;
-              const bool turned = TURNED || crowded;
-              int by = turn;
-              if constexpr (!TURNED) asm("" : "+v"(by));  // (the places of eight additions are not worth eight registers)
-              if (turned) turn_left(rw[h], by);
+            for (int k0 = 0; k0 < KK; k0 += 2) {
+              unsigned rw[2][4];
+              __builtin_memcpy(rw[0], &x[tt][k0], 16);
+              __builtin_memcpy(rw[1], &x[tt][k0 + 1 < KK ? k0 + 1 : k0], 16);
+              if constexpr (KK > 1) {  // the upper eight lanes of a quad take the other 32 dimensions first
 #pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                f[2 * e] = __uint_as_float(rw[h][e] << 16);
-                f[2 * e + 1] = __uint_as_float(rw[h][e] & 0xffff0000u);
-                top = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(f[2 * e]), fabsf(f[2 * e + 1])), top);  // NaN stays
+                for (int i = 0; i < 4; ++i) {
+                  const unsigned lo = rw[0][i];
+                  rw[0][i] = upper ? rw[1][i] : lo;
+                  rw[1][i] = upper ? lo : rw[1][i];
+                }
               }
-              if (__builtin_expect(!(top < 1073741824.0f), 0)) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) atomicAdd(&part[turned ? (by + e) & 7 : e], fix_biased_large(f[e]));
-              } else if (turned) {
+              for (int h = 0; h < (KK > 1 ? 2 : 1); ++h) {
+                // dimensions of 32 * kk + 8 * quad + {turn, turn + 1, ... modulo 8}
+                unsigned long long* part = row + 32 * k0 + (KK > 1 && (h == 1) != upper ? sum_place(32 + 8 * quad) : 8 * quad);
+                float f[8], top = 0.0f;
+                int by = turn;
+                if constexpr (CROWDED) asm("" : "+v"(by));  // (the places of eight additions are not worth eight registers)
+                if constexpr (TURN) turn_left(rw[h], by);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) atomicAdd(&part[(by + e) & 7], fix_biased(f[e]));
-              } else {
+                for (int e = 0; e < 4; ++e) {
+                  f[2 * e] = __uint_as_float(rw[h][e] << 16);
+                  f[2 * e + 1] = __uint_as_float(rw[h][e] & 0xffff0000u);
+                  top = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(f[2 * e]), fabsf(f[2 * e + 1])), top);  // NaN stays
+                }
+                if (__builtin_expect(!(top < 1073741824.0f), 0)) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) atomicAdd(&part[e], fix_biased(f[e]));
+                  for (int e = 0; e < 8; ++e) atomicAdd(&part[TURN ? (by + e) & 7 : e], fix_biased_large(f[e]));
+                } else {
+#pragma unroll
+                  for (int e = 0; e < 8; ++e) atomicAdd(&part[TURN ? (by + e) & 7 : e], fix_biased(f[e]));
+                }
               }
             }
           }
         }
+      };
+      // Lanes that meet in one address add one after the other.  With 32 dimensions, where half of the wave's first tile shares a
+      // centroid, additions are turned too and members counted together (131072 equal tokens x 8 heads, 4x16, three rounds:
+      // 1446 -> 294 us; 20000 of one head 67 -> 33 us; keys that spread take the plain additions).
+      if constexpr (TURNED) {
+        add_tiles(std::false_type{});
+      } else if (__popcll(__ballot(bidx[0] == __builtin_amdgcn_readfirstlane(bidx[0]))) >= 32) {  // wave-uniform
+        add_tiles(std::true_type{});
+      } else {
+        add_tiles(std::false_type{});
       }
     } else {
       // lane (quad, col) writes the code of token col of tile 4*k + quad: one store for four tiles
