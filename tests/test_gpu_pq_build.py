@@ -334,6 +334,43 @@ def test_build_in_the_smallest_workspace_at_several_lengths(pqc, dtype, m, c, un
         assert torch.equal(cent, want_cent) and torch.equal(codes, want_codes), n
 
 
+# A build recorded into a HIP graph: every replay starts from its own cleared sums, whatever ran in the workspace in between.
+@pytest.mark.parametrize("dtype,m,c,units", [("bf16", 2, 64, 1), ("bf16", 2, 64, 8), ("bf16", 2, 256, 1), ("f32", 4, 20, 3)])
+def test_recorded_build_replays(pqc, dtype, m, c, units):
+    import ctypes
+    n = 5000
+    w = wl.Workload(name="round", batch=units, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=n, pq_m=m, pq_centroids=c,
+                    topk=n // 4, n_init=0, n_local=0, dtype=dtype, kmeans_iters=3, recipe="plain")
+    lib, cfg = pqc.load(), ctypes.byref(pqc.make_config(w))
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(n)
+    keys = torch.randn((units, 1, n, 128), generator=gen, device=DEV, dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    init = torch.from_numpy(wl.kmeans_init_indices(w, seed=3)).to(DEV)
+    ws = torch.full((lib.pqc_pq_build_workspace_bytes(cfg),), 0x5a, dtype=torch.uint8, device=DEV)
+    cent = torch.empty((units, 1, m, c, w.sub_dim), dtype=torch.float32, device=DEV)
+    codes = torch.empty((units, 1, n, m), dtype=torch.uint8, device=DEV)
+
+    def build():
+        assert lib.pqc_pq_build(cfg, keys.data_ptr(), init.data_ptr(), 3, cent.data_ptr(), codes.data_ptr(), ws.data_ptr(),
+                                ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
+
+    build()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        build()
+    for _ in range(4):
+        keys.copy_(torch.randn(keys.shape, generator=gen, device=DEV, dtype=keys.dtype))
+        want_cent, want_codes = pqc.pq_build(w, keys, init)
+        ws.fill_(0xa5)
+        cent.zero_()
+        codes.fill_(255)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(cent, want_cent) and torch.equal(codes, want_codes)
+
+
 def _shortest(fn):
     """Milliseconds of one call: the shortest of eight runs of ten."""
     best = float("inf")
