@@ -389,6 +389,8 @@ def pq_build(w: Workload, keys: torch.Tensor, init_idx: torch.Tensor, iters: Opt
     cent = torch.empty((w.batch, w.n_kv_heads, w.pq_m, w.pq_centroids, w.sub_dim), dtype=torch.float32, device=dev)
     codes = _new_codes(w, ntok, dev)
     st = _stream_of(stream, dev)
+    if isinstance(stream, torch.cuda.Stream):
+        ws.record_stream(stream)  # not given to another tensor before the build has run there
     rc = lib.pqc_pq_build(cfg, _need(keys, _kv_dtype(w), (w.batch, w.n_kv_heads, ntok, w.head_dim), "keys"),
                           _need(init_idx, torch.int32, (w.batch, w.n_kv_heads, w.pq_m, w.pq_centroids), "init_idx"),
                           iters, cent.data_ptr(), codes.data_ptr(), ws.data_ptr(), nbytes, st)

@@ -371,6 +371,31 @@ def test_recorded_build_replays(pqc, dtype, m, c, units):
         assert torch.equal(cent, want_cent) and torch.equal(codes, want_codes)
 
 
+def test_build_on_another_stream_keeps_its_workspace(pqc):
+    # the workspace belongs to the call: memory asked for on the current stream right after it must be other memory while the
+    # build waits on its own stream
+    w = wl.Workload(name="round", batch=1, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=20000, pq_m=2, pq_centroids=64,
+                    topk=100, n_init=0, n_local=0, dtype="bf16", kmeans_iters=3, recipe="plain")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(5)
+    keys = torch.randn((1, 1, w.n_tokens, 128), generator=gen, device=DEV, dtype=torch.bfloat16)
+    init = torch.from_numpy(wl.kmeans_init_indices(w, seed=3)).to(DEV)
+    want_cent, want_codes = pqc.pq_build(w, keys, init)
+    nbytes = pqc.load().pqc_pq_build_workspace_bytes(pqc._config(w))
+    side, busy = torch.cuda.Stream(), torch.randn((4096, 4096), device=DEV)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for _ in range(20):  # a few ms
+            busy = (busy @ busy).clamp_(-1.0, 1.0)
+    cent, codes = pqc.pq_build(w, keys, init, stream=side)
+    others = []
+    for _ in range(200):  # written over and over while the build runs
+        others = [torch.full((nbytes,), 0x7f, dtype=torch.uint8, device=DEV) for _ in range(4)]
+    torch.cuda.synchronize()
+    del others
+    assert torch.equal(cent, want_cent) and torch.equal(codes, want_codes)
+
+
 def _shortest(fn):
     """Milliseconds of one call: the shortest of eight runs of ten."""
     best = float("inf")
