@@ -181,10 +181,32 @@ __device__ __forceinline__ void turn_left(unsigned (&v)[4], int n) {
   for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_alignbit(b[(i + 1) & 3], b[i], (n & 1) * 16);
 }
 
+// if (low < best) { best = low; index = c; kept = v; }
+// Moves under a narrowed execution mask, about 2.5 cycles each.  (Selections by VCC stall when they follow one another, about 20
+// cycles each from the second on, whatever scalar instructions lie between them; with the mask in another register they take 4.4.)
+__device__ __forceinline__ void keep_lower(float& best, int& index, f32x4_t& kept, float low, int c, const f32x4_t& v) {
+  unsigned long long mask;
+  float k0 = kept[0], k1 = kept[1], k2 = kept[2], k3 = kept[3];
+  asm("v_cmp_lt_f32_e32 vcc, %[low], %[best]\n\t"
+      "s_and_saveexec_b64 %[mask], vcc\n\t"
+      "v_mov_b32_e32 %[best], %[low]\n\t"
+      "v_mov_b32_e32 %[index], %[c]\n\t"
+      "v_mov_b32_e32 %[k0], %[v0]\n\t"
+      "v_mov_b32_e32 %[k1], %[v1]\n\t"
+      "v_mov_b32_e32 %[k2], %[v2]\n\t"
+      "v_mov_b32_e32 %[k3], %[v3]\n\t"
+      "s_mov_b64 exec, %[mask]"
+      : [best] "+v"(best), [index] "+v"(index), [k0] "+v"(k0), [k1] "+v"(k1), [k2] "+v"(k2), [k3] "+v"(k3), [mask] "=&s"(mask)
+      : [low] "v"(low), [c] "v"(c), [v0] "v"(v[0]), [v1] "v"(v[1]), [v2] "v"(v[2]), [v3] "v"(v[3])
+      : "vcc", "scc");
+  kept = f32x4_t{k0, k1, k2, k3};
+}
+
 // bf16 keys and sub-vectors of 32, 64 or 128 dimensions: the assignment is a dense contraction (tokens x dimensions by
 // dimensions x centroids) and runs on the matrix cores.  The nearest centroid minimises |c|^2 - 2 x.c.  Keys are bf16
-// already; an fp32 centroid is split into three bf16 terms that add up to it exactly, so the products are exact and
-// only the fp32 accumulation rounds.  Per wave: TT tiles of 16 tokens as the B operand (kept in registers), 16-centroid
+// already; an fp32 centroid, times -2, is split into three bf16 terms that add up to it exactly, so the products are exact and
+// only the fp32 accumulation, which starts from |c|^2, rounds (assignments that differ from 64-bit arithmetic: 8 of 14.7 million
+// tokens and partitions, 9 with |c|^2 - 2 (x.c) computed from a finished product).  Per wave: TT tiles of 16 tokens as the B operand (kept in registers), 16-centroid
 // tiles as the A operand (from LDS), D[centroid 4*quad+i][token col]: a lane keeps the best of its four centroid rows
 // for one token per tile, so that the index costs one register per tile and only the four quads are merged at the end
 // (with the operands the other way round, sixteen columns of four tokens each had to be merged).
@@ -194,10 +216,15 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
                                                              unsigned long long* __restrict__ part_sums,
                                                              unsigned* __restrict__ part_counts) {
   constexpr int NT = 1024, NW = NT / 64, KK = DM / 32, RS = mfma_term_stride(DM);
-  // With short sub-vectors the comparisons, not the matrix products, bound the kernel: then the four scores of the best
-  // tile are kept (12 instructions for four scores instead of 16) and which of them it was is found at the end; with
-  // longer ones the products hide them and the registers hold keys.
+  // With short sub-vectors the comparisons take about as long as the matrix products and do not hide behind them: the four scores
+  // of the best tile are kept (9 instructions for four scores instead of 12) and which of them it was is found at the end.  64 heads
+  // x 32768 tokens, 4x256, assignment: 330 us, 440 with selections by VCC; the products alone take 230 us at the clock that the card
+  // holds under them (2.1 GHz).  With longer sub-vectors the registers hold keys.
   constexpr bool KEEP = DM == 32;
+  // The form for short ranges has few waves and is bound by latency: the products of its two tiles are under way together, and the
+  // compiler may place selections between them (4 heads x 8564 tokens, 4x64: 12.2 us a round, 12.6 with keep_lower).
+  constexpr bool SHORT = TT == 2;
+  constexpr int GANG = SHORT ? 2 : 1;
   // 64 and 128 dimensions: sums turned (see sum_place; 131072 tokens x 8 heads, 2x64, eight rounds 900 -> 770 us).  With 32 the
   // turning costs more than the banks give back, as the matrix products and comparisons take longer than the additions.
   constexpr bool TURNED = KK > 1;
@@ -216,8 +243,8 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
   const bool one_group = s.C <= r.staged;  // then the centroids are staged once
   auto stage = [&](int c0) {
     const int nc = min(r.staged, s.C - c0);
-    for (int i = tid; i < nc * DM; i += NT) {  // every value as three bf16 terms that add up to it exactly
-      const float v = cent[((size_t)uj * s.C + c0) * DM + i];
+    for (int i = tid; i < nc * DM; i += NT) {  // every value, times -2, as three bf16 terms that add up to it exactly
+      const float v = -2.0f * cent[((size_t)uj * s.C + c0) * DM + i];
       const unsigned h = bf16_round_bits(v);
       const float r1 = v - __uint_as_float(h << 16);
       const unsigned m = bf16_round_bits(r1);
@@ -302,30 +329,39 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
           }
         const f32x4_t cnv = *reinterpret_cast<const f32x4_t*>(&cn[nt * 16 + 4 * quad]);
         const int c = c0 + nt * 16 + 4 * quad;
+        if constexpr (SHORT) PQC_LOADS_ISSUED();
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt) {
-          f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int t0 = 0; t0 < TT; t0 += GANG) {
+          f32x4_t acc[GANG];
 #pragma unroll
           for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
             for (int term = 2; term >= 0; --term)  // small terms first
-              acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[term][kk], x[tt][kk], acc, 0, 0, 0);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) acc[i] = fmaf(-2.0f, acc[i], cnv[i]);
+              for (int g = 0; g < GANG; ++g)
+                acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[term][kk], x[t0 + g][kk], kk == 0 && term == 2 ? cnv : acc[g], 0, 0, 0);
           // strict comparisons: an earlier (lower) centroid of this lane keeps a tie
-          if constexpr (KEEP) {
-            const float low = fminf(fminf(fminf(fminf(best[tt], acc[0]), acc[1]), acc[2]), acc[3]);
-            const bool lower = low < best[tt];
-            best[tt] = low;
-            bidx[tt] = lower ? c : bidx[tt];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) kept[tt][i] = lower ? acc[i] : kept[tt][i];
-          } else {
+          for (int g = 0; g < GANG; ++g) {
+            const int tt = t0 + g;
+            if constexpr (KEEP) {
+              const float low = fminf(fminf(fminf(fminf(best[tt], acc[g][0]), acc[g][1]), acc[g][2]), acc[g][3]);
+              if constexpr (SHORT) {
+                const bool lower = low < best[tt];
+                best[tt] = low;
+                bidx[tt] = lower ? c : bidx[tt];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const bool lower = acc[i] < best[tt];
-              best[tt] = lower ? acc[i] : best[tt];
-              bidx[tt] = lower ? c + i : bidx[tt];
+                for (int i = 0; i < 4; ++i) kept[tt][i] = lower ? acc[g][i] : kept[tt][i];
+              } else {
+                keep_lower(best[tt], bidx[tt], kept[tt], low, c, acc[g]);
+              }
+            } else {
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const bool lower = acc[g][i] < best[tt];
+                best[tt] = lower ? acc[g][i] : best[tt];
+                bidx[tt] = lower ? c + i : bidx[tt];
+              }
             }
           }
         }
