@@ -21,7 +21,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Plan {
   Shape s;
-  size_t off_ctl, off_lut, off_range, off_hist, off_bins, off_crec, off_stage, off_cnt, off_part, off_trace, total;
+  size_t off_lut, off_range, off_hist, off_bins, off_crec, off_stage, off_cnt, off_part, off_trace, total;
   int rec_stride;
 };
 
@@ -44,7 +44,6 @@ void lay_out(Plan* p, size_t bins_per_unit, size_t stage_words_per_unit, size_t 
   const Shape& s = p->s;
   const size_t units = (size_t)s.B * s.Hkv;
   size_t off = 0;
-  p->off_ctl = off;   off = align_up(off + sizeof(BinParams) * units);
   p->off_lut = off;   off = align_up(off + sizeof(float) * units * s.M * s.C);
   p->off_range = off; off = align_up(off + sizeof(float2) * units);
   p->off_hist = off;  off = align_up(off + sizeof(unsigned) * units * (kHistCopies * kNB + 1));  // + record counters
@@ -382,7 +381,6 @@ namespace {
 void bind_workspace(pqc_ctx* ctx) {
   const Plan& p = ctx->plan;
   char* base = ctx->workspace;
-  ctx->ws.ctl = reinterpret_cast<BinParams*>(base + p.off_ctl);
   ctx->ws.lut = reinterpret_cast<float*>(base + p.off_lut);
   ctx->ws.hist = reinterpret_cast<unsigned*>(base + p.off_hist);
   ctx->ws.cand_count = ctx->ws.hist + (size_t)p.s.B * p.s.Hkv * kHistCopies * kNB;

@@ -66,15 +66,13 @@ __device__ __forceinline__ CandView cand_view(unsigned char* unit_base, int G) {
   return c;
 }
 
-struct BinParams;
 // Device pointers carved out of the caller's workspace.
 struct Workspace {
-  BinParams* ctl;              // [units]                       score -> bin map of the unit
   float* lut;                  // [units][M][C]
   float2* range;               // [units]                       (min, max) score, stand-alone top-k only
   unsigned* hist;              // [2][units][histCopies][kNB]   zero between uses (room for kHistCopies replicas)
   unsigned* cand_count;        // [2][units]   records handed out so far (directly behind hist, zeroed with it)
-  unsigned short* bins;        // [units][binStride]  per token: bin + 1, or kBinWindow inside the two windows
+  unsigned short* bins;        // [units][binStride]  per token: its bin, or kBinWindow inside the two windows
   unsigned char* cand_rec;     // [units] blocks of rec_stride bytes: the candidates' composites, logits and V rows (CandView)
   unsigned long long* stage;   // [units][nblkC][stageStride]: selected ids (front, int32) / candidate composites (ending at word tokC)
   int2* stage_cnt;             // [units][nblkC]     (selected, candidates)
@@ -138,47 +136,41 @@ __device__ __forceinline__ int composite_token(unsigned long long c) {
   return (int)(0xffffffffu - (unsigned)(c & 0xffffffffull));
 }
 
-// Monotone map score -> bin.  Bin 0 takes every score below c0, kFineBins fine bins
-// cover [c0, c1], kHighBins coarse bins lie above c1.  The piece is chosen by exact
-// comparisons and each piece is clamped to its own bin range, so the map is
-// non-decreasing in s whatever the parameters are (inside a piece: subtraction,
-// multiplication by a non-negative constant and truncation all preserve order).  Only
-// the number of boundary-bin candidates depends on how well [c0, c1] brackets the K-th
-// largest score; the selection itself never does.  (Should the K-th largest score lie
-// below c0, every token of bin 0 becomes a candidate: slow, still exact.)
+// Monotone map score -> bin.  Bin 0 takes every score below c0 and is not counted (it holds the middle tokens that no other
+// bin does), kFineBins fine bins cover [c0, c1], kHighBins coarse bins lie above c1: the lower of two lines, a steep one
+// through c0 and c1 and a flatter one from c1 on.  Each line is one fused multiply-add by a non-negative slope, which rounds
+// monotonically, and so do the minimum and the conversion: the map is non-decreasing in s whatever the parameters are.  Only
+// the number of boundary-bin candidates depends on how well [c0, c1] brackets the K-th largest score; the selection itself
+// never does.  (Should the K-th largest score lie below c0, every token of bin 0 becomes a candidate: slow, still exact.)
+// Four instructions a score; the piece chosen by comparison and selections took eleven, and the scan is bound by the
+// compute unit's instruction rate (128K tokens x 32 units, 4 partitions: 4.0 us of a histogram workgroup, now 2.6).
 constexpr int kHighBins = 256;
 constexpr unsigned kBinWindow = 0xffffu;  // stored bin of a window token: above every threshold
 constexpr int kFineBins = kNB - 1 - kHighBins;
-struct BinParams {
-  float lo, c0, c1, inv_c, inv_hi, hi, pad0, pad1;
+struct BinMap {
+  float ic, b0, ih, b1;  // slope and intercept of the fine and of the coarse line
 };
-// The layout travels as scalars held in registers (selecting among the fields of a struct
-// in memory makes the compiler index it like an array, which lands it in scratch or LDS).
-// (one subtraction, one multiplication and one conversion per score: the piece is selected first)
-__device__ __forceinline__ int score_bin(float s, float c0, float c1, float inv_c, float inv_hi) {
-  const bool up = s > c1;
-  const float x = (s - (up ? c1 : c0)) * (up ? inv_hi : inv_c);
-  const int b = min((int)x, up ? kHighBins - 1 : kFineBins - 1) + (up ? 1 + kFineBins : 1);  // the conversion truncates
-  return s < c0 ? 0 : b;
+__device__ __forceinline__ unsigned score_bin(float s, const BinMap& m) {
+  const float x = fminf(fminf(fmaf(s, m.ic, m.b0), fmaf(s, m.ih, m.b1)), (float)(kNB - 1));
+  unsigned b;
+  asm("v_cvt_u32_f32 %0, %1" : "=v"(b) : "v"(x));  // truncates; negative values and NaN give 0 (in C++ they would be undefined)
+  return b;
 }
 // Bin layout from bounds lo <= score <= hi and a window [q_lo, q_hi] expected to hold
 // the K-th largest score.
-__device__ __forceinline__ BinParams make_bins(float lo, float hi, float q_lo, float q_hi) {
-  BinParams bp;
-  bp.lo = lo;
-  bp.hi = hi;
-  bp.c0 = fmaxf(lo, q_lo);
-  bp.c1 = fminf(hi, q_hi);
-  if (!(bp.c1 > bp.c0)) {  // degenerate window: one fine piece over everything
-    bp.c0 = lo;
-    bp.c1 = hi;
+__device__ __forceinline__ BinMap make_bins(float lo, float hi, float q_lo, float q_hi) {
+  float c0 = fmaxf(lo, q_lo), c1 = fminf(hi, q_hi);
+  if (!(c1 > c0)) {  // degenerate window: the fine piece over everything
+    c0 = lo;
+    c1 = hi;
   }
-  const float wc = bp.c1 - bp.c0, wh = hi - bp.c1;
-  bp.inv_c = (wc > 1e-30f && wc < 3e38f) ? (float)kFineBins / wc : 0.0f;
-  bp.inv_hi = (wh > 1e-30f && wh < 3e38f) ? (float)kHighBins / wh : 0.0f;
-  bp.pad0 = 0.0f;
-  bp.pad1 = 0.0f;
-  return bp;
+  const float wc = c1 - c0, wh = hi - c1;
+  BinMap m;
+  m.ic = (wc > 1e-30f && wc < 3e38f) ? (float)kFineBins / wc : 0.0f;
+  m.ih = (wh > 1e-30f && wh < 3e38f) ? fminf((float)kHighBins / wh, m.ic) : 0.0f;  // flatter, so that the lines cross at c1
+  m.b0 = fmaf(-c0, m.ic, 1.0f);
+  m.b1 = fmaf(-c1, m.ih, (float)(1 + kFineBins));
+  return m;
 }
 
 // ------------------------------------------------------------ cross-lane helpers
@@ -229,6 +221,15 @@ __device__ __forceinline__ float group16_sum(float x) {
   x += dpp_f<0x141>(0.0f, x);  // row_half_mirror: other quad of the half row
   x += dpp_f<0x140>(0.0f, x);  // row_mirror: other half of the row
   return x;
+}
+
+// Two 16-bit values at a time: a - b (0 where b is larger), and the smaller of a and b.
+typedef __attribute__((ext_vector_type(2))) unsigned short u16x2_t;
+__device__ __forceinline__ unsigned pk_sub_sat_u16(unsigned a, unsigned b) {
+  return __builtin_bit_cast(unsigned, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
+}
+__device__ __forceinline__ unsigned pk_min_u16(unsigned a, unsigned b) {
+  return __builtin_bit_cast(unsigned, __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
 }
 
 // Exclusive prefix sum over the threads of a workgroup (NT threads, multiple of 64).
@@ -501,7 +502,7 @@ __device__ __forceinline__ float2 build_lut(const T* __restrict__ q /* [G][kD] o
 //   hist  LDS [>= kSampleBins], zero on entry, zero again on return      sm  LDS [2]
 constexpr int kSampleBins = 256;
 template <int NT>
-__device__ __forceinline__ BinParams sample_window(float lo, float hi, float my_score, bool have_sample, int rank_hi,
+__device__ __forceinline__ BinMap sample_window(float lo, float hi, float my_score, bool have_sample, int rank_hi,
                                                    int rank_lo, unsigned* hist, int* sm) {
   constexpr int NBS = kSampleBins, PER = NBS / 64;
   static_assert(PER == 4, "one 16-byte access per lane");
@@ -617,7 +618,7 @@ struct ThresholdSearch {
       for (int v = 0; v < PER / 4; ++v) x[c][v] = c < copies ? src[v] : make_uint4(0u, 0u, 0u, 0u);  // uniform
     }
   }
-  __device__ __forceinline__ Threshold resolve(int K, int* sm /* [2*(NT/64)+1+4] */) const {
+  __device__ __forceinline__ Threshold resolve(int K, int n_mid /* middle tokens of the unit */, int* sm /* [2*(NT/64)+1+4] */) const {
     constexpr int NW = NT / 64;
     const int tid = threadIdx.x;
     unsigned h[PER];  // descending bins: h[e] is bin kNB-1-(tid*PER+e)
@@ -637,6 +638,7 @@ struct ThresholdSearch {
     for (int e = 0; e < PER; ++e) sum += (int)h[e];
     int total;
     int cum = block_exclusive_scan<NT>(sum, &total, sm);
+    if (tid == NT - 1) h[PER - 1] = (unsigned)(n_mid - total);  // bin 0 is not counted: it holds the rest
     int* res = sm + 2 * NW + 1;
     if (tid == 0) {
       res[0] = kNB;

@@ -185,7 +185,7 @@ __global__ __launch_bounds__(1024) void score_range_kernel(Shape s, const float*
 // SRC = CodeChunks<M>: builds the unit's table first; score bounds come from the table.
 // SRC = ScoreChunks: bounds come from score_range_kernel.  Every workgroup of a unit
 // then derives the same bin layout from the same sampled tokens (workgroup 0 publishes
-// table and layout for the select kernel) and counts its own tokens.  Workgroups of a
+// the table for the select kernel) and counts its own tokens.  Workgroups of a
 // unit spread their counts over histCopies replicas.
 // VW: 16-byte pieces of the centroid tensor per thread (1024 * 4 * VW floats cover the unit's M*C*Dm);
 // VA: 16-byte chunks of codes (or scores) per thread (1024 * VA chunks cover the workgroup's tokA tokens).
@@ -255,39 +255,30 @@ __global__ __launch_bounds__(1024) void hist_kernel(Shape s, Workspace ws, const
   PQC_MARK(ws, 0, 1);
 #pragma unroll
   for (int v = 0; v < VA; ++v) src.fix_tail(raw[v], chunk0 + min(v * NT + tid, chunks - 1));
-  const BinParams bp =
-      sample_window<NT>(bounds.x, bounds.y, src.score_one(sample), have_sample, s.rankHi, s.rankLo, hist, scan_sm);
-  if (bx == 0 && tid == 0) ws.ctl[u] = bp;
-  const float b_c0 = bp.c0, b_c1 = bp.c1, b_ic = bp.inv_c, b_ihi = bp.inv_hi;
+  const BinMap map = sample_window<NT>(bounds.x, bounds.y, src.score_one(sample), have_sample, s.rankHi, s.rankLo, hist, scan_sm);
   PQC_MARK(ws, 0, 2);
-  // most tokens score below the window: they are counted in a register (bin 0), the rest
-  // go to their LDS bin (an LDS atomic costs in proportion to the lanes that take part)
-  int n_low = 0;
+  // most tokens score below the window and are not counted, the rest go to their LDS bin (an LDS atomic costs in proportion
+  // to the lanes that take part)
   unsigned short* bins_u = ws.bins + (size_t)u * s.binStride;
 #pragma unroll
   for (int v = 0; v < VA; ++v) {
     if (v * NT + tid < chunks) {
       const int t0 = (chunk0 + v * NT + tid) * P - src.lead;
-      unsigned st[P];  // what the select kernel will read back: bin + 1, or the window mark
+      unsigned st[P];  // what the select kernel will read back: bin, or the window mark
       if (t0 >= s.I && t0 + P <= s.N - s.L) {  // all P tokens are middle tokens (all but the chunks at the two ends)
 #pragma unroll
-        for (int i = 0; i < P; ++i) {
-          const float sc = src.score(raw[v], i);
-          const int bin = score_bin(sc, b_c0, b_c1, b_ic, b_ihi);
-          if (!(sc < b_c0)) atomicAdd(&hist[bin], 1u);
-          n_low += sc < b_c0 ? 1 : 0;
-          st[i] = (unsigned)bin + 1u;
-        }
+        for (int i = 0; i < P; ++i) st[i] = score_bin(src.score(raw[v], i), map);
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+          if (st[i]) atomicAdd(&hist[st[i]], 1u);
       } else {
 #pragma unroll
         for (int i = 0; i < P; ++i) {
           const int t = t0 + i;
-          const float sc = src.score(raw[v], i);
           const bool mid = t >= s.I && t < s.N - s.L;
-          const int bin = score_bin(sc, b_c0, b_c1, b_ic, b_ihi);
-          if (mid && !(sc < b_c0)) atomicAdd(&hist[bin], 1u);
-          n_low += (mid && sc < b_c0) ? 1 : 0;
-          st[i] = mid ? (unsigned)bin + 1u : kBinWindow;
+          const unsigned bin = score_bin(src.score(raw[v], i), map);
+          if (mid && bin) atomicAdd(&hist[bin], 1u);
+          st[i] = mid ? bin : kBinWindow;
         }
       }
       if (src.lead == 0 && t0 + P <= s.N) {  // the usual case: aligned, all P tokens exist
@@ -312,8 +303,6 @@ __global__ __launch_bounds__(1024) void hist_kernel(Shape s, Workspace ws, const
       }
     }
   }
-  n_low = wave_last(wave_inclusive_scan(n_low));
-  if ((tid & 63) == 0 && n_low) atomicAdd(&hist[0], (unsigned)n_low);
   __syncthreads();
   PQC_MARK(ws, 0, 3);
   unsigned* gh = ws.hist + ((size_t)u * s.histCopies + (bx % s.histCopies)) * kNB;
@@ -394,7 +383,7 @@ __global__ __launch_bounds__(256, 2) void select_kernel(Shape s, Workspace ws, c
       for (int x = 0; x < QV; ++x)
         if (x * NT + tid < G * kD) qlds[x * NT + tid] = qreg[x];
     }
-    th = ts.resolve(s.K, scan_sm);  // syncs: qlds ready
+    th = ts.resolve(s.K, s.N - s.I - s.L, scan_sm);  // syncs: qlds ready
   }
   PQC_MARK(ws, 1, 1);
 
@@ -402,39 +391,56 @@ __global__ __launch_bounds__(256, 2) void select_kernel(Shape s, Workspace ws, c
   unsigned short* seg = list + w * segN;
   const int wg_t0 = blockIdx.x * s.tokC;
   int nsel = 0, ncand = 0;
-  const unsigned thr = (unsigned)th.bstar + 1u;  // in stored form
+  const unsigned thr = PAIRS ? 1u : (unsigned)th.bstar;
 #pragma unroll
   for (int v = 0; v < kMaxVecC; ++v) {
     if (v < gpw) {  // uniform
       const int t0 = wave_t0 + (v * 64 + lane) * 8;
-      const unsigned wv[4] = {raw[v].x, raw[v].y, raw[v].z, raw[v].w};
-      unsigned selm = 0u, candm = 0u;
+      unsigned wv[4] = {raw[v].x, raw[v].y, raw[v].z, raw[v].w};  // two tokens each, in stored form: selected above thr, candidates at thr
+      if constexpr (PAIRS) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const unsigned st = (wv[i >> 1] >> (16 * (i & 1))) & 0xffffu;
-        if constexpr (PAIRS) {
-          const int t = t0 + i;
-          const bool window = t < s.I || t >= s.N - s.L;
-          const unsigned key =
-              score_key(__fadd_rn(pl.lut[min(st & 0xffu, (unsigned)kPairC - 1)], pl.lut[kPairC + min(st >> 8, (unsigned)kPairC - 1)]));
-          selm |= ((window || (!pth.none && key > pth.key)) ? 1u : 0u) << i;
-          candm |= ((!window && !pth.none && key == pth.key) ? 1u : 0u) << i;
-        } else {
-          selm |= (st > thr ? 1u : 0u) << i;
-          candm |= (st == thr ? 1u : 0u) << i;
+        for (int k = 0; k < 4; ++k) {
+          unsigned st[2];
+#pragma unroll
+          for (int y = 0; y < 2; ++y) {
+            const int t = t0 + 2 * k + y;
+            const unsigned cw = (wv[k] >> (16 * y)) & 0xffffu;
+            const unsigned key =
+                score_key(__fadd_rn(pl.lut[min(cw & 0xffu, (unsigned)kPairC - 1)], pl.lut[kPairC + min(cw >> 8, (unsigned)kPairC - 1)]));
+            const unsigned above = !pth.none && key > pth.key ? 2u : 0u, at = !pth.none && key == pth.key ? 1u : 0u;
+            st[y] = t < s.I || t >= s.N - s.L ? kBinWindow : above | at;
+          }
+          wv[k] = st[0] | (st[1] << 16);
         }
       }
       const int nreal = (v * 64 + lane) * 8 < tpw ? min(8, max(0, s.N - t0)) : 0;  // tokens of this group that exist
-      selm &= (1u << nreal) - 1u;
-      candm &= (1u << nreal) - 1u;
-      const int cnt = __popc(selm) | (__popc(candm) << 16);
+      if (__any(nreal < 8)) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) wv[k] = 2 * k + 1 < nreal ? wv[k] : 2 * k < nreal ? wv[k] & 0xffffu : 0u;
+      }
+      // counts of the group, two tokens at a time: (0 or 1) for each half of a word
+      unsigned above2 = 0u, other2 = 0u;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        above2 += pk_min_u16(pk_sub_sat_u16(wv[k], thr * 0x10001u), 0x10001u);
+        other2 += pk_min_u16(wv[k] ^ (thr * 0x10001u), 0x10001u);
+      }
+      const int n_abv = (int)((above2 & 0xffffu) + (above2 >> 16));
+      int n_cnd = 8 - (int)((other2 & 0xffffu) + (other2 >> 16));
+      if (thr == 0u) n_cnd = max(0, n_cnd - (8 - nreal));  // uniform, rare: tokens that do not exist look like candidates then
+      const int cnt = n_abv | (n_cnd << 16);
       const int inc = wave_inclusive_scan(cnt);
       const int tot = wave_last(inc);
-      int ps = nsel + ((inc - cnt) & 0xffff), pc = ncand + ((inc - cnt) >> 16);
+      int ps = nsel + ((inc - cnt) & 0xffff);
+      const int off0 = t0 - wg_t0;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        if (selm & (1u << i)) seg[ps++] = (unsigned short)(t0 + i - wg_t0);
-        if (candm & (1u << i)) seg[segN - 1 - (pc++)] = (unsigned short)(t0 + i - wg_t0);
+      for (int i = 0; i < 8; ++i)
+        if (((wv[i >> 1] >> (16 * (i & 1))) & 0xffffu) > thr) seg[ps++] = (unsigned short)(off0 + i);
+      if (tot >> 16) {  // uniform: the wave has candidates
+        int pc = ncand + ((inc - cnt) >> 16);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (i < nreal && ((wv[i >> 1] >> (16 * (i & 1))) & 0xffffu) == thr) seg[segN - 1 - (pc++)] = (unsigned short)(off0 + i);
       }
       nsel += tot & 0xffff;
       ncand += tot >> 16;
