@@ -146,8 +146,8 @@ int pqc_last_hip_error(const pqc_ctx* ctx);
  *
  * Codes of tokens inside the initial and local windows are ignored.
  *
- * The call enqueues kernel launches only (three; before a context's first call,
- * and after a call that failed, one more that clears the workspace) and a completed
+ * The call enqueues kernel launches only (three, two for short caches; before a context's first
+ * call, and after a call that failed, one more that clears the workspace) and a completed
  * call leaves the workspace as it found it.  It may therefore be recorded into a
  * HIP graph by stream capture and replayed, for instance one call per layer with
  * one context shared by all layers (Algorithm 2's loop over the layers); make one
@@ -159,7 +159,7 @@ int pqc_decode(pqc_ctx* ctx, const void* q, const float* centroids, const uint8_
 
 /* pqc_decode for a cache that has just received a token: besides the step, the code of that
  * token is written (Algorithm 2: the PQ search of a step and the code of the token that joins
- * the compressed part; Section 3.1: nearest centroid of each partition), inside the same three
+ * the compressed part; Section 3.1: nearest centroid of each partition), inside the same
  * launches -- nothing in the step reads it, so it costs no launch of its own.
  *   new_key   [B][Hkv][D]  kv_dtype   key of the token (e.g. its row of k_cache, copied)
  *   position  where its code goes: codes[b][h][position][0..M-1] (same result as
@@ -228,7 +228,8 @@ int pqc_pair_counts_add(const pqc_config* cfg, const uint8_t* codes, int32_t pos
 
 /* Profiling aid: the kernels of pqc_decode one at a time.  phase 0 = histogram, 1 =
  * select + attention, 2 = finalize; calling phases 0, 1, 2 in this order with the same
- * arguments is exactly one pqc_decode (same kernels, same results).  It lets a harness
+ * arguments is exactly one pqc_decode (same kernels, same results).  For short caches, whose select
+ * kernel finds the threshold by itself, phase 0 has nothing to launch.  It lets a harness
  * launch one phase for several contexts back to back between two events, which times
  * a kernel without an event in front of every launch.  A phase out of turn on a context
  * (not 0 after a complete step, not the successor of the phase before) is refused with

@@ -12,6 +12,42 @@
 #include "pqc_build_kernels.h"
 #include "pqc_kernels.h"
 
+namespace pqc {
+
+__global__ void reset_kernel(unsigned* a, size_t na) {
+  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+  if (i < na) a[i] = 0u;
+}
+
+// Score range of the middle tokens of a score array (stand-alone top-k only).
+__global__ __launch_bounds__(1024) void score_range_kernel(Shape s, const float* __restrict__ scores,
+                                                           float2* __restrict__ range) {
+  __shared__ float smn[16], smx[16];
+  const int u = blockIdx.y;
+  float mn = INFINITY, mx = -INFINITY;
+  for (int t = s.I + threadIdx.x; t < s.N - s.L; t += 1024) {
+    const float v = scores[(size_t)u * s.N + t];
+    mn = fminf(mn, v);
+    mx = fmaxf(mx, v);
+  }
+  mn = wave_min(mn);
+  mx = wave_max(mx);
+  if ((threadIdx.x & 63) == 0) {
+    smn[threadIdx.x >> 6] = mn;
+    smx[threadIdx.x >> 6] = mx;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 16; ++w) {
+      mn = fminf(mn, smn[w]);
+      mx = fmaxf(mx, smx[w]);
+    }
+    range[u] = make_float2(mn, mx);
+  }
+}
+
+}  // namespace pqc
+
 namespace {
 
 using namespace pqc;
@@ -21,6 +57,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Plan {
   Shape s;
+  bool short_form;  // the step's threshold is found by the select kernel itself (From::kShort), no histogram kernel
   size_t off_lut, off_range, off_hist, off_bins, off_crec, off_stage, off_cnt, off_part, off_trace, total;
   int rec_stride;
 };
@@ -58,7 +95,17 @@ void lay_out(Plan* p, size_t bins_per_unit, size_t stage_words_per_unit, size_t 
   p->total = off;
 }
 
-int make_plan(const pqc_config* c, Plan* p) {
+// Whether a step of this shape is quicker without the histogram kernel (From::kShort in pqc_kernels.h): a launch saved, about 4.5 us,
+// against scoring all N tokens in every workgroup, M look-ups a token.  Measured, us per layer without and with it (bf16, 4 query
+// heads per KV head unless said): 8 heads of 8192 tokens 2x64 19.4, 16.8; 16384 20.4, 18.5; 24576 22.0, 21.0; 32768 23.0, 23.1; 4x64 of
+// 12000 21.2, 19.8; three sequences of 20011 with 4 heads, fp32, 22.2, 22.9.  More than 64 centroids (half the threads build twice as
+// much of the table): 4x256 of 8192 20.9, 19.6; 16384 21.5, 22.1; 64 heads of 16384 32.6, 32.1.
+bool short_cache(const Shape& s) {
+  return (s.M == 2 || s.M == 4) && (long long)s.N * s.M <= (s.C <= 64 ? 49152 : 32768);
+}
+
+// The launch plan of a configuration; `general`: for calls other than the decode step, which have no short form.
+int make_plan(const pqc_config* c, Plan* p, bool general = true) {
   if (!c) return PQC_EINVAL;
   if (c->batch < 1 || c->n_q_heads < 1 || c->n_kv_heads < 1 || c->head_dim < 1 || c->n_tokens < 1 || c->pq_m < 1 ||
       c->pq_centroids < 1 || c->topk < 0 || c->n_init < 0 || c->n_local < 0)
@@ -102,9 +149,11 @@ int make_plan(const pqc_config* c, Plan* p) {
   s.histCopies = s.nblkA <= 32 ? 1 : s.nblkA <= 64 ? 2 : kHistCopies;
   // select kernel: 256-thread workgroups, two resident per compute unit
   int tokC = env_int("PQC_TOK_C", 0);
+  p->short_form = !general && short_cache(s);
   if (!tokC) {
     tokC = 512;
-    while (tokC < 8192 && units * ((s.N + tokC - 1) / tokC) > 512) tokC *= 2;
+    const int most = p->short_form ? 256 : 512;  // one workgroup per compute unit, of twice the size, in the short form
+    while (tokC < 8192 && units * ((s.N + tokC - 1) / tokC) > most) tokC *= 2;
   }
   if (tokC != 512 && tokC != 1024 && tokC != 2048 && tokC != 4096 && tokC != 8192) return PQC_EINVAL;
   s.tokC = tokC; s.nblkC = (s.N + tokC - 1) / tokC;
@@ -141,7 +190,11 @@ size_t workspace_bound(const pqc_config* c) {
   Plan p;
   if (make_plan(c, &p) != PQC_OK) return 0;
   const Shape& s = p.s;
-  if (s.cap == s.N) return p.total;
+  if (s.cap == s.N) {
+    Plan d;
+    make_plan(c, &d, false);
+    return p.total > d.total ? p.total : d.total;
+  }
   const size_t units = (size_t)s.B * s.Hkv, cap = (size_t)s.cap;
   // select kernel grid: tokens per workgroup double until the grid has at most 512 workgroups or
   // they reach 8192 (an override by environment may pin them as low as 512)
@@ -159,8 +212,10 @@ size_t workspace_bound(const pqc_config* c) {
 
 struct pqc_ctx {
   pqc_config cfg;
-  Plan plan;
-  Workspace ws;
+  Plan plan;           // of every call but the decode step
+  Plan decode_plan;    // of the decode step: `plan`, or its short form
+  Workspace ws;        // views of `plan`
+  Workspace decode_ws; // views of `decode_plan`; histograms and record counters lie in the same place
   AppendArgs append;       // set for the duration of a pqc_decode_append call
   char* workspace;         // the caller's device memory
   size_t workspace_bytes;
@@ -225,36 +280,41 @@ void launch_hist(const Shape& s, const Workspace& ws, const T* q, const float* c
 }
 
 template <typename T, int G>
-void launch_finalize(pqc_ctx* ctx, const T* qt, const T* kt, const T* vt, int32_t* out_idx, float* out_attn, hipStream_t st) {
-  const Shape& s = ctx->plan.s;
+void launch_finalize(pqc_ctx* ctx, const Shape& s, const Workspace& ws, const T* qt, const T* kt, const T* vt, int32_t* out_idx,
+                     float* out_attn, hipStream_t st) {
   const dim3 grid(G * s.slices + kCopyWgs + (ctx->append.key ? 1 : 0), (unsigned)(s.B * s.Hkv));
   // Tokens that share all their codes share a score: with few distinct code words the tie class at the threshold is
   // large (131072 tokens over 64 x 64 code pairs: up to 70 candidates), and the kernel requests more records up front.
   double words = 1.0;
   for (int j = 0; j < s.M; ++j) words *= s.C;
   if (s.slices == kMaxSlices && s.N >= 16.0 * words)
-    hipLaunchKernelGGL((finalize_kernel<T, G, true, true>), grid, dim3(256), finalize_lds_bytes(s, true), st, s, ctx->ws, qt, kt, vt,
+    hipLaunchKernelGGL((finalize_kernel<T, G, true, true>), grid, dim3(256), finalize_lds_bytes(s, true), st, s, ws, qt, kt, vt,
                        out_idx, out_attn, ctx->append);
   else
-    hipLaunchKernelGGL((finalize_kernel<T, G, true, false>), grid, dim3(256), finalize_lds_bytes(s, true), st, s, ctx->ws, qt, kt, vt,
+    hipLaunchKernelGGL((finalize_kernel<T, G, true, false>), grid, dim3(256), finalize_lds_bytes(s, true), st, s, ws, qt, kt, vt,
                        out_idx, out_attn, ctx->append);
 }
 
-// phases: bit k set = launch kernel k of the decode path (0 histogram, 1 select + attention, 2 finalize)
+// phases: bit k set = launch kernel k of the decode path (0 histogram, 1 select + attention, 2 finalize); the short form has no
+// kernel 0
 template <typename T, int G, int M>
 void launch_decode_tgm(pqc_ctx* ctx, const void* q, const float* cent, const uint8_t* codes, const void* k,
                        const void* v, int32_t* out_idx, float* out_attn, hipStream_t st, unsigned phases) {
-  const Shape& s = ctx->plan.s;
+  const Shape& s = ctx->decode_plan.s;
+  const Workspace& ws = ctx->decode_ws;
   const unsigned units = (unsigned)(s.B * s.Hkv);
   const T* qt = static_cast<const T*>(q);
   const T* kt = static_cast<const T*>(k);
   const T* vt = static_cast<const T*>(v);
-  if (phases & 1u) launch_hist<T, CodeChunks<M>>(s, ctx->ws, qt, cent, static_cast<const void*>(codes), sizeof(float) * lut_tile_floats(1024, M, s.C), st);
-  if (phases & 2u)
-    hipLaunchKernelGGL((select_kernel<T, G, CodeChunks<M>, true>), dim3(s.nblkC, units), dim3(256),
-                       s.tokC * sizeof(unsigned short), st, s, ctx->ws, qt, kt, vt, static_cast<const void*>(codes));
+  if (ctx->decode_plan.short_form) {
+    if (phases & 2u) launch_short_select(sizeof(T) == 2, s, ws, q, cent, codes, k, v, st);
+  } else {
+    if (phases & 1u) launch_hist<T, CodeChunks<M>>(s, ws, qt, cent, static_cast<const void*>(codes), sizeof(float) * lut_tile_floats(1024, M, s.C), st);
+    if (phases & 2u)
+      hipLaunchKernelGGL((select_kernel<T, G, CodeChunks<M>, true>), dim3(s.nblkC, units), dim3(256), list_bytes<From::kBins>(s.tokC), st, s, ws, qt, kt, vt, static_cast<const void*>(codes));
+  }
   if (phases & 4u)
-    launch_finalize<T, G>(ctx, qt, kt, vt, out_idx, out_attn, st);
+    launch_finalize<T, G>(ctx, s, ws, qt, kt, vt, out_idx, out_attn, st);
 }
 
 template <typename T, int G>
@@ -288,10 +348,10 @@ void launch_indexed_tg(pqc_ctx* ctx, const void* q, const float* cent, const uin
   const T* qt = static_cast<const T*>(q);
   const T* kt = static_cast<const T*>(k);
   const T* vt = static_cast<const T*>(v);
-  hipLaunchKernelGGL((select_kernel<T, G, CodeChunks<2>, true, true>), dim3(s.nblkC, units), dim3(256),
-                     s.tokC * sizeof(unsigned short), st, s, ctx->ws, qt, kt, vt, static_cast<const void*>(codes), cent,
+  hipLaunchKernelGGL((select_kernel<T, G, CodeChunks<2>, true, From::kPairs>), dim3(s.nblkC, units), dim3(256),
+                     list_bytes<From::kPairs>(s.tokC), st, s, ctx->ws, qt, kt, vt, static_cast<const void*>(codes), cent,
                      pair_counts, ctx->append.key ? ctx->append.position : -1);
-  launch_finalize<T, G>(ctx, qt, kt, vt, out_idx, out_attn, st);
+  launch_finalize<T, G>(ctx, s, ctx->ws, qt, kt, vt, out_idx, out_attn, st);
 }
 
 template <typename T>
@@ -377,23 +437,32 @@ size_t pqc_debug_trace_offset(const pqc_config* cfg) {
 size_t pqc_workspace_bytes(const pqc_config* cfg) { return workspace_bound(cfg); }
 
 namespace {
-// Point the context's views at the regions of its plan.
-void bind_workspace(pqc_ctx* ctx) {
-  const Plan& p = ctx->plan;
-  char* base = ctx->workspace;
-  ctx->ws.lut = reinterpret_cast<float*>(base + p.off_lut);
-  ctx->ws.hist = reinterpret_cast<unsigned*>(base + p.off_hist);
-  ctx->ws.cand_count = ctx->ws.hist + (size_t)p.s.B * p.s.Hkv * kHistCopies * kNB;
-  ctx->ws.range = reinterpret_cast<float2*>(base + p.off_range);
-  ctx->ws.bins = reinterpret_cast<unsigned short*>(base + p.off_bins);
-  ctx->ws.cand_rec = reinterpret_cast<unsigned char*>(base + p.off_crec);
-  ctx->ws.rec_stride = p.rec_stride;
-  ctx->ws.stage = reinterpret_cast<unsigned long long*>(base + p.off_stage);
-  ctx->ws.stage_cnt = reinterpret_cast<int2*>(base + p.off_cnt);
-  ctx->ws.partials = reinterpret_cast<float*>(base + p.off_part);
+// Views of the regions of a plan.
+Workspace views(char* base, const Plan& p) {
+  Workspace ws;
+  ws.lut = reinterpret_cast<float*>(base + p.off_lut);
+  ws.hist = reinterpret_cast<unsigned*>(base + p.off_hist);
+  ws.cand_count = ws.hist + (size_t)p.s.B * p.s.Hkv * kHistCopies * kNB;
+  ws.range = reinterpret_cast<float2*>(base + p.off_range);
+  ws.bins = reinterpret_cast<unsigned short*>(base + p.off_bins);
+  ws.cand_rec = reinterpret_cast<unsigned char*>(base + p.off_crec);
+  ws.rec_stride = p.rec_stride;
+  ws.stage = reinterpret_cast<unsigned long long*>(base + p.off_stage);
+  ws.stage_cnt = reinterpret_cast<int2*>(base + p.off_cnt);
+  ws.partials = reinterpret_cast<float*>(base + p.off_part);
 #ifdef PQC_TRACE
-  ctx->ws.trace = reinterpret_cast<unsigned long long*>(base + p.off_trace);
+  ws.trace = reinterpret_cast<unsigned long long*>(base + p.off_trace);
 #endif
+  return ws;
+}
+
+// The context's plans of its configuration (`p`: the general one), and their views.  A workspace that holds the general plan but
+// not the decode step's own takes the general one for it.
+void bind_plans(pqc_ctx* ctx, const Plan& p) {
+  ctx->plan = p;
+  if (make_plan(&ctx->cfg, &ctx->decode_plan, false) != PQC_OK || ctx->decode_plan.total > ctx->workspace_bytes) ctx->decode_plan = p;
+  ctx->ws = views(ctx->workspace, ctx->plan);
+  ctx->decode_ws = views(ctx->workspace, ctx->decode_plan);
 }
 }  // namespace
 
@@ -408,10 +477,9 @@ int pqc_create(pqc_ctx** out, const pqc_config* cfg, void* workspace, size_t wor
   if (!ctx) return PQC_EINVAL;
   ctx->cfg = *cfg;
   ctx->cfg.n_capacity = p.s.cap;
-  ctx->plan = p;
   ctx->workspace = static_cast<char*>(workspace);
   ctx->workspace_bytes = workspace_bytes;
-  bind_workspace(ctx);
+  bind_plans(ctx, p);
   ctx->hist_clean = false;
   ctx->next_phase = 0;
   ctx->last_hip = 0;
@@ -431,8 +499,7 @@ int pqc_set_length(pqc_ctx* ctx, int32_t n_tokens, int32_t topk) {
   if (p.total > ctx->workspace_bytes) return PQC_EWORKSPACE;
   // The histogram region does not move and a clean one is all zero, whatever the length: it stays clean.
   ctx->cfg = c;
-  ctx->plan = p;
-  bind_workspace(ctx);
+  bind_plans(ctx, p);
   return PQC_OK;
 }
 
@@ -596,7 +663,7 @@ int pqc_topk(pqc_ctx* ctx, const float* scores, int32_t* out_idx, void* stream) 
   const float* nof = nullptr;
   hipLaunchKernelGGL(score_range_kernel, dim3(1, units), dim3(1024), 0, st, s, scores, ctx->ws.range);
   launch_hist<float, ScoreChunks>(s, ctx->ws, nof, nof, static_cast<const void*>(scores), 0, st);
-  hipLaunchKernelGGL((select_kernel<float, 1, ScoreChunks, false>), dim3(s.nblkC, units), dim3(256), s.tokC * sizeof(unsigned short), st,
+  hipLaunchKernelGGL((select_kernel<float, 1, ScoreChunks, false>), dim3(s.nblkC, units), dim3(256), list_bytes<From::kBins>(s.tokC), st,
                      s, ctx->ws, nof, nof, nof, static_cast<const void*>(scores));
   hipLaunchKernelGGL((finalize_kernel<float, 1, false>), dim3(1 + kCopyWgs, units), dim3(256), finalize_lds_bytes(s, false), st, s,
                      ctx->ws, nof, nof, nof, out_idx, static_cast<float*>(nullptr), AppendArgs{nullptr, nullptr, nullptr, 0, nullptr});
@@ -666,18 +733,19 @@ size_t pqc_static_scratch_bytes(void) { return kStaticScratchBytes; }
 int pqc_decode_static(const pqc_config* cfg, const void* q, const float* centroids, const uint8_t* codes, const void* k_cache,
                       const void* v_cache, int32_t* out_idx, float* out_attn, void* stream) {
   pqc_ctx ctx;  // on the stack: nothing is allocated, on the host either
-  const int rc = make_plan(cfg, &ctx.plan);
+  Plan p;
+  const int rc = make_plan(cfg, &p);
   if (rc != PQC_OK) return rc;
-  if (ctx.plan.total > kStaticScratchBytes) return PQC_ESCRATCH;
+  if (p.total > kStaticScratchBytes) return PQC_ESCRATCH;
   unsigned char* base = nullptr;
   int hip_code = 0;
   const int rs = static_scratch(&base, &hip_code);
   if (rs != PQC_OK) return rs;
   ctx.cfg = *cfg;
-  ctx.cfg.n_capacity = ctx.plan.s.cap;
+  ctx.cfg.n_capacity = p.s.cap;
   ctx.workspace = reinterpret_cast<char*>(base);
   ctx.workspace_bytes = kStaticScratchBytes;
-  bind_workspace(&ctx);
+  bind_plans(&ctx, p);
   ctx.next_phase = 0;
   ctx.hist_clean = false;  // the array keeps what the last call (of any shape) left: the step's counters are cleared first,
                            // by a fill kernel, so that the call can be recorded into a graph

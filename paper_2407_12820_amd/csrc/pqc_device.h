@@ -272,9 +272,9 @@ __device__ __forceinline__ float load_as_float<bf16_t>(const bf16_t* p, int i) {
 }
 
 // Centroids travel global -> registers (coalesced, all loads in flight at once) -> a
-// padded LDS tile -> one thread per table entry runs the chain.  With 1024 threads the
+// padded LDS tile -> one thread per table entry runs the chain.  With 512 threads and more the
 // tile holds the whole table (C*(kD+M) floats, up to 136 KB of the CU's 160 KB) and there
-// is a single pass; with fewer threads the table goes through a tile of kLutTileFloats
+// is a single pass over the centroids; with fewer threads the table goes through a tile of kLutTileFloats
 // floats piece by piece.
 constexpr int kLutTileFloats = 8192;
 // Row stride of the whole-table tile.  Long rows (one or two partitions: few entries, few busy
@@ -282,7 +282,7 @@ constexpr int kLutTileFloats = 8192;
 // and measured faster with an odd stride and 32-bit accesses.
 __host__ __device__ constexpr int lut_row_stride(int M) { return M <= 2 ? kD / M + 4 : kD / M + 1; }
 __host__ __device__ constexpr int lut_tile_floats(int nt, int M, int C) {
-  return nt >= 1024 ? M * C * lut_row_stride(M) : kLutTileFloats + kLutTileFloats / (kD / M);
+  return nt >= 512 ? M * C * lut_row_stride(M) : kLutTileFloats + kLutTileFloats / (kD / M);
 }
 // VWP (whole-table mode): 16-byte pieces of the table per thread; VWP * NT * 4 floats must cover M*C*Dm.
 template <typename T, int NT, int M, class MarkFn, class IssueFn, int VWP = (256 * kD) / (4 * NT)>
@@ -292,7 +292,7 @@ __device__ __forceinline__ float2 build_lut(const T* __restrict__ q /* [G][kD] o
                                                float* tile /* [lut_tile_floats(NT, M, C)] */, MarkFn mark,
                                                IssueFn issue_more /* the caller's own loads, queued behind the table's */) {
   constexpr int Dm = kD / M, RS = lut_row_stride(M);
-  constexpr bool kWhole = NT >= 1024;
+  constexpr bool kWhole = NT >= 512;
   constexpr int VW = kWhole ? VWP : 1;                    // float4 per thread
   constexpr int VPG = kLutTileFloats / (4 * NT);      // float4 per thread per tile (piecewise mode)
   constexpr int NG = (256 * kD) / kLutTileFloats;      // tiles at the largest C (piecewise mode)
@@ -501,15 +501,18 @@ __device__ __forceinline__ float2 build_lut(const T* __restrict__ q /* [G][kD] o
 // (four bins per lane, a wave-wide prefix sum) and clears it again.
 //   hist  LDS [>= kSampleBins], zero on entry, zero again on return      sm  LDS [2]
 constexpr int kSampleBins = 256;
-template <int NT>
-__device__ __forceinline__ BinMap sample_window(float lo, float hi, float my_score, bool have_sample, int rank_hi,
-                                                   int rank_lo, unsigned* hist, int* sm) {
+// PS samples per thread: thread t holds the samples t, t + NT, ... below n.
+template <int NT, int PS>
+__device__ __forceinline__ BinMap sample_window(float lo, float hi, const float (&my_score)[PS], int n, int rank_hi, int rank_lo,
+                                                unsigned* hist, int* sm) {
   constexpr int NBS = kSampleBins, PER = NBS / 64;
   static_assert(PER == 4, "one 16-byte access per lane");
   const int tid = threadIdx.x;
   const float width = hi - lo;
   const float inv_u = (width > 1e-30f && width < 3e38f) ? (float)NBS / width : 0.0f;
-  if (have_sample) atomicAdd(&hist[max(0, min(NBS - 1, __float2int_rz((my_score - lo) * inv_u)))], 1u);
+#pragma unroll
+  for (int x = 0; x < PS; ++x)
+    if (x * NT + tid < n) atomicAdd(&hist[max(0, min(NBS - 1, __float2int_rz((my_score[x] - lo) * inv_u)))], 1u);
   __syncthreads();
   if (tid < 64) {  // lane l owns bins [NBS - (l+1)*PER, NBS - l*PER): the lanes run from the top bin down
     uint4* mine = reinterpret_cast<uint4*>(hist + NBS - (tid + 1) * PER);

@@ -1,7 +1,7 @@
 // Kernels of libpqcache (gfx950).  Grid layout: blockIdx.y = unit (sequence b, KV
 // head g); blockIdx.x = workgroup inside the unit (query head for finalize_kernel).
 //
-// Decode path (pqc_decode), three launches, every dependency at a kernel boundary:
+// Decode path (pqc_decode), three launches, two for short caches (From::kShort), every dependency at a kernel boundary:
 //   hist_kernel      table -> scan codes -> histogram of scores over kNB bins, and every
 //                    token's bin number left behind for the next kernel
 //   select_kernel    threshold bin from the histogram -> tokens whose stored bin lies
@@ -118,9 +118,15 @@ struct ScoreChunks {
 };
 
 // ------------------------------------------------------------------ utilities
-__global__ void reset_kernel(unsigned* a, size_t na) {
-  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  if (i < na) a[i] = 0u;
+// Workgroups are handed to the 8 XCDs round-robin in launch order (x fastest).  The workgroups of a unit that all read its centroids
+// (and codes) share an XCD and its L2: eight units at a time are interleaved.
+__device__ __forceinline__ void unit_of_workgroup(int units, int& u, int& bx) {
+  const int nx = gridDim.x, lin = blockIdx.y * nx + blockIdx.x;
+  if (lin < (units & ~7) * nx) {
+    const int i = lin % (8 * nx);
+    u = (lin / (8 * nx)) * 8 + (i & 7);
+    bx = i >> 3;
+  }
 }
 
 // Stand-alone table (pqc_lut).
@@ -154,33 +160,6 @@ __global__ __launch_bounds__(256) void scan_kernel(Shape s, const float* __restr
   }
 }
 
-// Score range of the middle tokens of a score array (stand-alone top-k only).
-__global__ __launch_bounds__(1024) void score_range_kernel(Shape s, const float* __restrict__ scores,
-                                                           float2* __restrict__ range) {
-  __shared__ float smn[16], smx[16];
-  const int u = blockIdx.y;
-  float mn = INFINITY, mx = -INFINITY;
-  for (int t = s.I + threadIdx.x; t < s.N - s.L; t += 1024) {
-    const float v = scores[(size_t)u * s.N + t];
-    mn = fminf(mn, v);
-    mx = fmaxf(mx, v);
-  }
-  mn = wave_min(mn);
-  mx = wave_max(mx);
-  if ((threadIdx.x & 63) == 0) {
-    smn[threadIdx.x >> 6] = mn;
-    smx[threadIdx.x >> 6] = mx;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < 16; ++w) {
-      mn = fminf(mn, smn[w]);
-      mx = fmaxf(mx, smx[w]);
-    }
-    range[u] = make_float2(mn, mx);
-  }
-}
-
 // ------------------------------------------------------------- 1. histogram
 // SRC = CodeChunks<M>: builds the unit's table first; score bounds come from the table.
 // SRC = ScoreChunks: bounds come from score_range_kernel.  Every workgroup of a unit
@@ -204,18 +183,8 @@ __global__ __launch_bounds__(1024) void hist_kernel(Shape s, Workspace ws, const
   __shared__ unsigned hist[kNB];
   __shared__ int scan_sm[2 * (NT / 64) + 1 + 2];
   const int tid = threadIdx.x, units = s.B * s.Hkv;
-  // Workgroups are handed to the 8 XCDs round-robin in launch order (x fastest).  The
-  // workgroups of a unit all read that unit's centroids, so eight units at a time are
-  // interleaved: the workgroups of one unit then share an XCD and its L2.
   int u = blockIdx.y, bx = blockIdx.x;
-  {
-    const int nx = gridDim.x, lin = blockIdx.y * nx + blockIdx.x;
-    if (lin < (units & ~7) * nx) {
-      const int i = lin % (8 * nx);
-      u = (lin / (8 * nx)) * 8 + (i & 7);
-      bx = i >> 3;
-    }
-  }
+  unit_of_workgroup(units, u, bx);
   PQC_MARK(ws, 0, 0);
 #ifdef PQC_TRACE
   PQC_NOTE(ws, 0, 15, (__builtin_amdgcn_s_getreg(20 | (3 << 11)) & 15) | (u << 8));  // XCC_ID[3:0], unit
@@ -228,7 +197,6 @@ __global__ __launch_bounds__(1024) void hist_kernel(Shape s, Workspace ws, const
   const int chunks = s.tokA / P, chunk0 = bx * chunks;
   typename SRC::Raw raw[VA];
   typename SRC::One sample;
-  const bool have_sample = tid < s.sampleN;
   auto issue_loads = [&]() {
 #pragma unroll
     for (int v = 0; v < VA; ++v) raw[v] = src.load(chunk0 + min(v * NT + tid, chunks - 1));
@@ -255,7 +223,8 @@ __global__ __launch_bounds__(1024) void hist_kernel(Shape s, Workspace ws, const
   PQC_MARK(ws, 0, 1);
 #pragma unroll
   for (int v = 0; v < VA; ++v) src.fix_tail(raw[v], chunk0 + min(v * NT + tid, chunks - 1));
-  const BinMap map = sample_window<NT>(bounds.x, bounds.y, src.score_one(sample), have_sample, s.rankHi, s.rankLo, hist, scan_sm);
+  const float sample_score[1] = {src.score_one(sample)};
+  const BinMap map = sample_window<NT, 1>(bounds.x, bounds.y, sample_score, s.sampleN, s.rankHi, s.rankLo, hist, scan_sm);
   PQC_MARK(ws, 0, 2);
   // most tokens score below the window and are not counted, the rest go to their LDS bin (an LDS atomic costs in proportion
   // to the lanes that take part)
@@ -312,89 +281,213 @@ __global__ __launch_bounds__(1024) void hist_kernel(Shape s, Workspace ws, const
 }
 
 // ---------------------------------------------------- 2. select (+ attention)
-// One workgroup owns tokens [blockIdx.x*tokC, +tokC) of its unit; its 4 waves each own
-// a contiguous quarter.  The histogram kernel left every token's bin behind, so a token
-// is classified by comparing that number with the threshold bin.  Per wave, lanes hold
-// 8 consecutive tokens, counts are prefix-summed across lanes, and the wave appends to
-// its own LDS segment: selected tokens (ascending) from the front, boundary-bin
-// candidates from the back.  SRC is only used to score the few candidates exactly.
+// One workgroup owns tokens [blockIdx.x*tokC, +tokC) of its unit, each of its waves a contiguous share.  The histogram kernel
+// left every token's bin behind, so a token is classified by comparing that number with the threshold bin.  Per wave, lanes hold
+// 8 consecutive tokens and counts are prefix-summed across lanes and waves; then the selected tokens (ascending) are written to the
+// front of one list in LDS and the boundary-bin candidates to its end.  SRC is only used to score the few candidates exactly.
+// (A list per wave took a search over the waves' counts at every look-up; 131072 tokens x 8 heads, a layer: 35.8 us, now 35.2.)
 constexpr int kMaxVecC = 4;  // 8-token groups per lane (tokC <= 8192)
 
-// PAIRS (M = 2 only): there is no histogram kernel in front; the threshold comes from the
-// code-pair counts (pair_threshold) and tokens are classified by their exact score keys.
-template <typename T, int G, class SRC, bool ATTN, bool PAIRS = false>
-__global__ __launch_bounds__(256, 2) void select_kernel(Shape s, Workspace ws, const T* __restrict__ q,
+// Where the threshold comes from.  kBins: from the histogram kernel in front.  kPairs (M = 2 only): from the code-pair counts
+// (pair_threshold), tokens are classified by their exact score keys; no histogram kernel.  kShort: every workgroup builds the table
+// and scores all tokens of its unit itself, so that it finds the threshold without the others; no histogram kernel either.
+//
+// kShort, why and how far: the histogram kernel of a short cache is launch, table and a scan of half a microsecond, and the select
+// kernel starts with reading back what it left.  One launch less, against a scan of the whole unit in each of its workgroups, which
+// is bound by LDS reads (M per token) and by latency: see short_cache().  A workgroup of 512 threads per compute unit (the table and
+// the waves' tiles share its LDS) keeps as many rows in flight as two of 256.  One fp32 head of 4096 tokens: 17.8 -> 14.3 us a step.
+enum class From { kBins, kPairs, kShort };
+template <From FROM>
+constexpr int select_threads() { return FROM == From::kShort ? 512 : 256; }
+constexpr int kShortChunks = 4;  // 16-byte code chunks per thread and step, the next step's in flight
+// dynamic LDS of the kShort form: the centroid tile, then (over it) V tiles, the waves' states, the list and the own tokens' bins
+template <From FROM>
+constexpr size_t list_bytes(int tokC) { return ((size_t)tokC + select_threads<FROM>()) * sizeof(unsigned short); }
+template <From FROM>
+constexpr int tiles_bytes(bool mfma) { return mfma ? select_threads<FROM>() / 64 * kVTileBytes : 16; }
+template <From FROM>
+constexpr int states_bytes(int G) { return select_threads<FROM>() / 64 * G * (kD + 2) * (int)sizeof(float); }
+constexpr size_t short_work_bytes(int tokC, int G, bool mfma) {
+  return tiles_bytes<From::kShort>(mfma) + states_bytes<From::kShort>(G) + list_bytes<From::kShort>(tokC) + (size_t)tokC * 2;
+}
+inline size_t short_lds_bytes(const Shape& s, bool mfma) {
+  const size_t tile = (size_t)lut_tile_floats(select_threads<From::kShort>(), s.M, s.C) * sizeof(float), work = short_work_bytes(s.tokC, s.G, mfma);
+  return tile > work ? tile : work;
+}
+
+template <typename T, int G, class SRC, bool ATTN, From FROM = From::kBins, int VW = 1 /* kShort: 16-byte pieces of the centroids per thread */>
+__global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape s, Workspace ws, const T* __restrict__ q,
                                                      const T* __restrict__ kc, const T* __restrict__ vc,
                                                      const void* __restrict__ src_ptr,
                                                      const float* __restrict__ cent = nullptr,
                                                      const unsigned* __restrict__ pair_counts = nullptr,
-                                                     int uncounted = -1 /* PAIRS: a window token not in the counts yet */) {
-  constexpr int NT = 256, NW = 4;
+                                                     int uncounted = -1 /* kPairs: a window token not in the counts yet */) {
+  constexpr bool PAIRS = FROM == From::kPairs, SHORT = FROM == From::kShort;
+  constexpr int NT = select_threads<FROM>(), NW = NT / 64;
   constexpr bool kMfma = ATTN && sizeof(T) == 2 && kMatrixCoreAttention;
   static_assert(!PAIRS || (SRC::kFromCodes && SRC::M == 2), "pair counts exist for two partitions only");
-  extern __shared__ unsigned short list[];  // [tokC] token offsets from the workgroup's first token
+  static_assert(!SHORT || (SRC::kFromCodes && ATTN && (SRC::P == 4 || SRC::P == 8)), "the short form is that of the decode step with two or four partitions");
+  constexpr int LM = SRC::kFromCodes ? SRC::M : 1;
+  extern __shared__ __attribute__((aligned(16))) unsigned char select_lds[];
+  constexpr int kList = SHORT ? tiles_bytes<FROM>(kMfma) + states_bytes<FROM>(G) : 0;
+  unsigned short* list = reinterpret_cast<unsigned short*>(select_lds + kList);  // [tokC] token offsets from the workgroup's first token, [NT] see below
   __shared__ std::conditional_t<PAIRS, PairLds, int> pl;
   __shared__ int scan_sm[2 * NW + 1 + 4];
-  __shared__ int wcnt[2 * NW];
-  __shared__ float red[ATTN ? NW * G * (kD + 2) : 1];
+  __shared__ int wcnt[NW];
+  __shared__ float red_own[ATTN && !SHORT ? states_bytes<FROM>(G) / 4 : 1];
   __shared__ float qlds[ATTN ? G * kD : 1];
-  __shared__ __attribute__((aligned(16))) unsigned char vtile[kMfma ? NW * kVTileBytes : 16];
-  const int u = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  __shared__ __attribute__((aligned(16))) unsigned char vtile_own[SHORT ? 16 : tiles_bytes<FROM>(kMfma)];
+  __shared__ float lut[SHORT ? LM * kLutRow : 1];
+  __shared__ __attribute__((aligned(16))) unsigned hist[SHORT ? kNB + 64 : 4];  // behind the bins: a place per lane for what is not counted
+  unsigned short* own_bins = list + s.tokC + NT;  // kShort: [tokC], stored form
+  unsigned char* vtile = SHORT ? select_lds : vtile_own;
+  float* red = SHORT ? reinterpret_cast<float*>(select_lds + tiles_bytes<FROM>(kMfma)) : red_own;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  int u = blockIdx.y, bx = blockIdx.x;
+  if constexpr (SHORT) unit_of_workgroup(s.B * s.Hkv, u, bx);
   const int b = u / s.Hkv, g = u % s.Hkv;
   PQC_MARK(ws, 1, 0);
-  // this wave's stored bins, the query and the histogram: all requested up front
   const int tpw = s.tokC / NW;           // tokens per wave, in groups of 8 per lane
   const int gpw = (tpw + 511) / 512;     // groups per lane: 1, 2 or 4 (the last lanes idle when tpw < 512)
-  const int wave_t0 = blockIdx.x * s.tokC + w * tpw;
-  // 16 bytes per group of 8 tokens: their stored bins, or (PAIRS) their codes
-  const unsigned short* bins_u =
-      PAIRS ? reinterpret_cast<const unsigned short*>(static_cast<const uint8_t*>(src_ptr) + (size_t)u * s.cap * 2)
-            : ws.bins + (size_t)u * s.binStride;
-  const int last_group = PAIRS ? s.cap - 8 : s.binStride - 8;  // PAIRS: the capacity is a multiple of 8
+  const int wave_t0 = bx * s.tokC + w * tpw;
   uint4 raw[kMaxVecC];
-#pragma unroll
-  for (int v = 0; v < kMaxVecC; ++v)
-    raw[v] = *reinterpret_cast<const uint4*>(bins_u + min(wave_t0 + min((v * 64 + lane) * 8, tpw - 8), last_group));
-  constexpr int QV = ATTN ? (G * kD + NT - 1) / NT : 1;  // query elements per thread
-  float qreg[QV];
-  if constexpr (ATTN) {
-#pragma unroll
-    for (int x = 0; x < QV; ++x)
-      qreg[x] = load_as_float<T>(q + ((size_t)b * s.Hq + (size_t)g * G) * kD, min(x * NT + tid, G * kD - 1));
-  }
   Threshold th{0, 0, 0, 0};
   PairThreshold pth{0u, true};
-  if constexpr (PAIRS) {
-    PQC_LOADS_ISSUED();
-    if constexpr (ATTN) {
+  if constexpr (SHORT) {
+    __shared__ __attribute__((aligned(16))) float qs[kD];
+    __shared__ float lut_red[32];
+    SRC src;
+    src.init(src_ptr, u, s.cap, s.B * s.Hkv, lut, ws.hist);
+    const int chunks = (s.N + src.lead + SRC::P - 1) / SRC::P;  // of the unit
+    typename SRC::Raw code[kShortChunks];
+    constexpr int PS = 1024 / NT, QN = (G * kD + NT - 1) / NT;
+    typename SRC::One sample[PS];
+    auto issue_loads = [&]() {
 #pragma unroll
-      for (int x = 0; x < QV; ++x)
-        if (x * NT + tid < G * kD) qlds[x * NT + tid] = qreg[x];
+      for (int x = 0; x < PS; ++x) {
+        const int i = min(x * NT + tid, s.sampleN - 1);
+        sample[x] = src.load_one(min(s.N - 1, s.I + (int)(((long long)i * max(0, s.N - s.I - s.L)) / s.sampleN)), u, s.cap);
+      }
+#pragma unroll
+      for (int v = 0; v < kShortChunks; ++v) code[v] = src.load(min(v * NT + tid, chunks - 1));
+    };
+    float qv[QN];
+#pragma unroll
+    for (int x = 0; x < QN; ++x) qv[x] = load_as_float<T>(q + ((size_t)b * s.Hq + (size_t)g * G) * kD, min(x * NT + tid, G * kD - 1));
+    for (int i = tid; i < kNB; i += NT) hist[i] = 0u;
+    auto mark = [&](int) {};
+    const float2 bounds = build_lut<T, NT, LM, decltype(mark), decltype(issue_loads), VW>(
+        q + ((size_t)b * s.Hq + (size_t)g * G) * kD, cent + (size_t)u * LM * s.C * (kD / LM), G, s.C, lut, qs, lut_red,
+        reinterpret_cast<float*>(select_lds), mark, issue_loads);
+#pragma unroll
+    for (int x = 0; x < QN; ++x)
+      if (x * NT + tid < G * kD) qlds[x * NT + tid] = qv[x];
+    float sample_score[PS];
+#pragma unroll
+    for (int x = 0; x < PS; ++x) sample_score[x] = src.score_one(sample[x]);
+    const BinMap map = sample_window<NT, PS>(bounds.x, bounds.y, sample_score, s.sampleN, s.rankHi, s.rankLo, hist, scan_sm);
+    PQC_MARK(ws, 1, 9);
+    const int own_lo = bx * s.tokC, own_hi = own_lo + s.tokC;
+    for (int c0 = 0; c0 < chunks; c0 += kShortChunks * NT) {
+      typename SRC::Raw next[kShortChunks];
+      if (c0 + kShortChunks * NT < chunks) {
+#pragma unroll
+        for (int v = 0; v < kShortChunks; ++v) next[v] = src.load(min(c0 + (kShortChunks + v) * NT + tid, chunks - 1));
+      }
+      PQC_LOADS_ISSUED();
+#pragma unroll
+      for (int v = 0; v < kShortChunks; ++v) {
+        const int c = c0 + v * NT + tid;
+        if (c < chunks) {
+          src.fix_tail(code[v], c);
+          const int t0 = c * SRC::P - src.lead;
+          unsigned st[SRC::P], hb[SRC::P];
+#pragma unroll
+          for (int i = 0; i < SRC::P; ++i) hb[i] = st[i] = score_bin(src.score(code[v], i), map);
+          if (t0 < s.I || t0 + SRC::P > s.N - s.L) {
+#pragma unroll
+            for (int i = 0; i < SRC::P; ++i) {
+              const bool mid = t0 + i >= s.I && t0 + i < s.N - s.L;
+              st[i] = mid ? st[i] : kBinWindow;
+              hb[i] = mid ? hb[i] : 0u;
+            }
+          }
+#pragma unroll
+          for (int i = 0; i < SRC::P; ++i) atomicAdd(&hist[hb[i] ? hb[i] : kNB + lane], 1u);
+          if (t0 + SRC::P > own_lo && t0 < own_hi) {
+            if (src.lead == 0) {  // uniform; then a chunk is the workgroup's as a whole (tokC is a multiple of P)
+              unsigned short* dst = own_bins + (t0 - own_lo);
+              unsigned pw[SRC::P / 2];
+#pragma unroll
+              for (int i = 0; i < SRC::P / 2; ++i) pw[i] = st[2 * i] | (st[2 * i + 1] << 16);
+              if constexpr (SRC::P == 4) *reinterpret_cast<uint2*>(dst) = make_uint2(pw[0], pw[1]);
+              if constexpr (SRC::P == 8) *reinterpret_cast<uint4*>(dst) = make_uint4(pw[0], pw[1], pw[2], pw[3]);
+            } else {
+#pragma unroll
+              for (int i = 0; i < SRC::P; ++i)
+                if (t0 + i >= own_lo && t0 + i < own_hi) own_bins[t0 + i - own_lo] = (unsigned short)st[i];
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < kShortChunks; ++v) code[v] = next[v];
     }
-    pth = pair_threshold<T, NT>(s, q + ((size_t)b * s.Hq + (size_t)g * G) * kD, cent + (size_t)u * 2 * s.C * (kD / 2),
-                                pair_counts + (size_t)u * s.C * s.C, static_cast<const uint8_t*>(src_ptr) + (size_t)u * s.cap * 2,
-                                pl, scan_sm, [&](int slot) { PQC_MARK(ws, 1, slot); }, uncounted);  // syncs: qlds ready
-  } else {
+    __syncthreads();
+    PQC_MARK(ws, 1, 10);
     ThresholdSearch<NT> ts;
-    ts.load(ws.hist + (size_t)u * s.histCopies * kNB, s.histCopies);
-    PQC_LOADS_ISSUED();
+    ts.load(hist, 1);
+    th = ts.resolve(s.K, s.N - s.I - s.L, scan_sm);
+  } else {
+    // this wave's stored bins, the query and the histogram: all requested up front
+    // 16 bytes per group of 8 tokens: their stored bins, or (kPairs) their codes
+    const unsigned short* bins_u =
+        PAIRS ? reinterpret_cast<const unsigned short*>(static_cast<const uint8_t*>(src_ptr) + (size_t)u * s.cap * 2)
+              : ws.bins + (size_t)u * s.binStride;
+    const int last_group = PAIRS ? s.cap - 8 : s.binStride - 8;  // kPairs: the capacity is a multiple of 8
+#pragma unroll
+    for (int v = 0; v < kMaxVecC; ++v)
+      raw[v] = *reinterpret_cast<const uint4*>(bins_u + min(wave_t0 + min((v * 64 + lane) * 8, tpw - 8), last_group));
+    constexpr int QV = ATTN ? (G * kD + NT - 1) / NT : 1;  // query elements per thread
+    float qreg[QV];
     if constexpr (ATTN) {
 #pragma unroll
       for (int x = 0; x < QV; ++x)
-        if (x * NT + tid < G * kD) qlds[x * NT + tid] = qreg[x];
+        qreg[x] = load_as_float<T>(q + ((size_t)b * s.Hq + (size_t)g * G) * kD, min(x * NT + tid, G * kD - 1));
     }
-    th = ts.resolve(s.K, s.N - s.I - s.L, scan_sm);  // syncs: qlds ready
+    if constexpr (PAIRS) {
+      PQC_LOADS_ISSUED();
+      if constexpr (ATTN) {
+#pragma unroll
+        for (int x = 0; x < QV; ++x)
+          if (x * NT + tid < G * kD) qlds[x * NT + tid] = qreg[x];
+      }
+      pth = pair_threshold<T, NT>(s, q + ((size_t)b * s.Hq + (size_t)g * G) * kD, cent + (size_t)u * 2 * s.C * (kD / 2),
+                                  pair_counts + (size_t)u * s.C * s.C, static_cast<const uint8_t*>(src_ptr) + (size_t)u * s.cap * 2,
+                                  pl, scan_sm, [&](int slot) { PQC_MARK(ws, 1, slot); }, uncounted);  // syncs: qlds ready
+    } else {
+      ThresholdSearch<NT> ts;
+      ts.load(ws.hist + (size_t)u * s.histCopies * kNB, s.histCopies);
+      PQC_LOADS_ISSUED();
+      if constexpr (ATTN) {
+#pragma unroll
+        for (int x = 0; x < QV; ++x)
+          if (x * NT + tid < G * kD) qlds[x * NT + tid] = qreg[x];
+      }
+      th = ts.resolve(s.K, s.N - s.I - s.L, scan_sm);  // syncs: qlds ready
+    }
   }
   PQC_MARK(ws, 1, 1);
 
-  const int segN = s.tokC / NW;
-  unsigned short* seg = list + w * segN;
-  const int wg_t0 = blockIdx.x * s.tokC;
-  int nsel = 0, ncand = 0;
+  const int wg_t0 = bx * s.tokC;
+  constexpr int GV = SHORT ? kMaxVecC / 2 : kMaxVecC;  // groups per lane, at most
+  int place[GV];   // (selected, candidates << 16) of the wave in front of the group
+  int count = 0;   // the same, of the wave
   const unsigned thr = PAIRS ? 1u : (unsigned)th.bstar;
 #pragma unroll
-  for (int v = 0; v < kMaxVecC; ++v) {
+  for (int v = 0; v < GV; ++v) {
     if (v < gpw) {  // uniform
+      if constexpr (SHORT) raw[v] = *reinterpret_cast<const uint4*>(own_bins + w * tpw + min((v * 64 + lane) * 8, tpw - 8));
       const int t0 = wave_t0 + (v * 64 + lane) * 8;
       unsigned wv[4] = {raw[v].x, raw[v].y, raw[v].z, raw[v].w};  // two tokens each, in stored form: selected above thr, candidates at thr
       if constexpr (PAIRS) {
@@ -430,38 +523,47 @@ __global__ __launch_bounds__(256, 2) void select_kernel(Shape s, Workspace ws, c
       if (thr == 0u) n_cnd = max(0, n_cnd - (8 - nreal));  // uniform, rare: tokens that do not exist look like candidates then
       const int cnt = n_abv | (n_cnd << 16);
       const int inc = wave_inclusive_scan(cnt);
-      const int tot = wave_last(inc);
-      int ps = nsel + ((inc - cnt) & 0xffff);
-      const int off0 = t0 - wg_t0;
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (((wv[i >> 1] >> (16 * (i & 1))) & 0xffffu) > thr) seg[ps++] = (unsigned short)(off0 + i);
-      if (tot >> 16) {  // uniform: the wave has candidates
-        int pc = ncand + ((inc - cnt) >> 16);
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-          if (i < nreal && ((wv[i >> 1] >> (16 * (i & 1))) & 0xffffu) == thr) seg[segN - 1 - (pc++)] = (unsigned short)(off0 + i);
-      }
-      nsel += tot & 0xffff;
-      ncand += tot >> 16;
+      place[v] = count + inc - cnt;
+      count += wave_last(inc);
+      raw[v] = make_uint4(wv[0], wv[1], wv[2], wv[3]);
     }
   }
   PQC_MARK(ws, 1, 8);
-  if (lane == 0) {
-    wcnt[w] = nsel;
-    wcnt[NW + w] = ncand;
+  if (lane == 0) wcnt[w] = count;
+  __syncthreads();
+  int before = 0, total = 0;  // of the waves in front of this one, and of all
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    const int c = wcnt[i];
+    before += i < w ? c : 0;
+    total += c;
+  }
+  const int tot_sel = total & 0xffff, tot_cand = total >> 16;
+#pragma unroll
+  for (int v = 0; v < GV; ++v) {
+    if (v < gpw) {  // uniform
+      const unsigned wv[4] = {raw[v].x, raw[v].y, raw[v].z, raw[v].w};
+      const int off0 = (wave_t0 - wg_t0) + (v * 64 + lane) * 8;
+      int ps = (before + place[v]) & 0xffff;
+      // every token is stored, those not selected in a place of the thread's own behind the list: a store under a condition of its
+      // own costs a wave about fifty cycles, and few waves are there to hide them
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const bool sel = ((wv[i >> 1] >> (16 * (i & 1))) & 0xffffu) > thr;
+        list[sel ? ps : s.tokC + tid] = (unsigned short)(off0 + i);
+        ps += sel ? 1 : 0;
+      }
+      if (count >> 16) {  // uniform: the wave has candidates; they go to the list's end, backwards
+        int pc = (before + place[v]) >> 16;
+        const int nreal = off0 < (w + 1) * tpw ? min(8, max(0, s.N - wg_t0 - off0)) : 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (i < nreal && ((wv[i >> 1] >> (16 * (i & 1))) & 0xffffu) == thr) list[s.tokC - 1 - (pc++)] = (unsigned short)(off0 + i);
+      }
+    }
   }
   __syncthreads();
   PQC_MARK(ws, 1, 2);
-  int csel[NW + 1], ccand[NW + 1];
-  csel[0] = 0;
-  ccand[0] = 0;
-#pragma unroll
-  for (int i = 0; i < NW; ++i) {
-    csel[i + 1] = csel[i] + wcnt[i];
-    ccand[i + 1] = ccand[i] + wcnt[NW + i];
-  }
-  const int tot_sel = csel[NW], tot_cand = ccand[NW];
   // record slots for this workgroup's candidates: requested now, needed only after the
   // attention below, which hides the round trip of the returning atomic
   int rec_base;  // set and read by thread 0 only; no initialiser, or the merge with it would wait for the atomic here
@@ -472,12 +574,7 @@ __global__ __launch_bounds__(256, 2) void select_kernel(Shape s, Workspace ws, c
     unsigned cb[SRC::kFromCodes ? SRC::M : 1];
     float sc;
   };
-  auto cand_token = [&](int c) -> int {
-    int i = 0;
-#pragma unroll
-    for (int x = 1; x < NW; ++x) i += (c >= ccand[x]) ? 1 : 0;
-    return wg_t0 + list[i * segN + segN - 1 - (c - ccand[i])];
-  };
+  auto cand_token = [&](int c) -> int { return wg_t0 + list[s.tokC - 1 - c]; };
   auto cand_key_load = [&](int t) -> CandKey {
     CandKey k;
     k.sc = 0.0f;
@@ -492,7 +589,12 @@ __global__ __launch_bounds__(256, 2) void select_kernel(Shape s, Workspace ws, c
     return k;
   };
   auto cand_score = [&](const CandKey& k) -> float {
-    if constexpr (PAIRS) {
+    if constexpr (SHORT) {
+      float sc = lut[k.cb[0]];
+#pragma unroll
+      for (int j = 1; j < SRC::M; ++j) sc = __fadd_rn(sc, lut[j * kLutRow + k.cb[j]]);
+      return sc;
+    } else if constexpr (PAIRS) {
       return __fadd_rn(pl.lut[min(k.cb[0], (unsigned)kPairC - 1)], pl.lut[kPairC + min(k.cb[1], (unsigned)kPairC - 1)]);
     } else if constexpr (SRC::kFromCodes) {
       const float* tb = ws.lut + (size_t)u * SRC::M * s.C;
@@ -504,15 +606,10 @@ __global__ __launch_bounds__(256, 2) void select_kernel(Shape s, Workspace ws, c
       return k.sc;
     }
   };
-  auto sel_at = [&](int p) -> int {
-    int i = 0;
-#pragma unroll
-    for (int x = 1; x < NW; ++x) i += (p >= csel[x]) ? 1 : 0;
-    return wg_t0 + list[i * segN + (p - csel[i])];
-  };
+  auto sel_at = [&](int p) -> int { return wg_t0 + list[p]; };
 
   // selected list for the finalize kernel's index output
-  unsigned long long* stage = ws.stage + ((size_t)u * s.nblkC + blockIdx.x) * s.stageStride;
+  unsigned long long* stage = ws.stage + ((size_t)u * s.nblkC + bx) * s.stageStride;
   int* stage32 = reinterpret_cast<int*>(stage);
   PQC_MARK(ws, 1, 3);
 
@@ -541,14 +638,14 @@ __global__ __launch_bounds__(256, 2) void select_kernel(Shape s, Workspace ws, c
   // window tokens it happens to hold (the list's first nI and last nL entries), every
   // nblkC-th token of the two windows, so that the window rows are spread over the unit's
   // workgroups.
-  const int tok_lo = (int)blockIdx.x * s.tokC, tok_hi = min(s.N, ((int)blockIdx.x + 1) * s.tokC);
+  const int tok_lo = bx * s.tokC, tok_hi = min(s.N, (bx + 1) * s.tokC);
   const int nI = max(0, min(s.I, tok_hi) - tok_lo), nL = max(0, tok_hi - max(s.N - s.L, tok_lo));
   const int n_own = tot_sel - nI - nL;
-  const int n_win = (int)blockIdx.x < s.I + s.L ? (s.I + s.L - (int)blockIdx.x + s.nblkC - 1) / s.nblkC : 0;
+  const int n_win = bx < s.I + s.L ? (s.I + s.L - bx + s.nblkC - 1) / s.nblkC : 0;
   const int n_att = n_own + n_win;
   auto att_at = [&](int p) -> int {
     if (p < n_own) return sel_at(p + nI);
-    const int wt = (int)blockIdx.x + (p - n_own) * s.nblkC;
+    const int wt = bx + (p - n_own) * s.nblkC;
     return wt < s.I ? wt : s.N - s.L + (wt - s.I);
   };
   if constexpr (ATTN) {
@@ -574,8 +671,8 @@ __global__ __launch_bounds__(256, 2) void select_kernel(Shape s, Workspace ws, c
     __syncthreads();
     // this workgroup's partial state: the accumulators as 128 floats per head ([j][h][kD] over the unit's workgroups j),
     // the (m, l) pairs in a dense array per head behind all accumulators ([units][h][j]); see finalize_kernel
-    float* pacc = ws.partials + (((size_t)u * s.npart + blockIdx.x) * G) * kD;
-    float2* pml = reinterpret_cast<float2*>(ws.partials + (size_t)s.B * s.Hkv * s.npart * G * kD) + (size_t)u * G * s.npart + blockIdx.x;
+    float* pacc = ws.partials + (((size_t)u * s.npart + bx) * G) * kD;
+    float2* pml = reinterpret_cast<float2*>(ws.partials + (size_t)s.B * s.Hkv * s.npart * G * kD) + (size_t)u * G * s.npart + bx;
     for (int o = tid; o < G * kD; o += NT) {
       const int h = o / kD, d = o % kD;
       float m, l, acc;
@@ -587,7 +684,7 @@ __global__ __launch_bounds__(256, 2) void select_kernel(Shape s, Workspace ws, c
   // (written after the attention: stores issued while the K/V loads of the co-resident workgroup
   // fill the memory pipeline would only delay this workgroup's own first loads)
   for (int p = tid; p < tot_sel; p += NT) stage32[p] = sel_at(p);
-  if (tid == 0) ws.stage_cnt[(size_t)u * s.nblkC + blockIdx.x] = make_int2(tot_sel, tot_cand);
+  if (tid == 0) ws.stage_cnt[(size_t)u * s.nblkC + bx] = make_int2(tot_sel, tot_cand);
   PQC_MARK(ws, 1, 5);
   PQC_NOTE(ws, 1, 14, tot_sel);
   PQC_NOTE(ws, 1, 15, tot_cand);
@@ -1321,5 +1418,9 @@ __global__ __launch_bounds__(256) void merge_kernel(Shape s, Workspace ws, int n
   __syncthreads();
   if (half == 0) out_attn[((size_t)b * s.Hq + (size_t)g * G + hq) * kD + d] = (acc + half_acc[d]) / lstar;
 }
+
+// The kShort form for a step of this shape (pqc_short.hip).
+void launch_short_select(bool bf16, const Shape& s, const Workspace& ws, const void* q, const float* cent, const uint8_t* codes, const void* k,
+                         const void* v, hipStream_t st);
 
 }  // namespace pqc

@@ -1,0 +1,92 @@
+"""GPU parity of decode steps without a histogram kernel (short caches) at the edges of its tiles and of the rule that chooses
+it, and of thresholds outside the sampled window on both forms, against the CPU oracle: index sets equal, attention within the
+tolerance of tests/parity_utils.py."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2407_12820_amd import workloads as wl
+
+from parity_utils import ATTN_TOL, attn_error, build_problem, check_indices, check_structure
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def pqc():
+    from paper_2407_12820_amd import binding
+    binding.load()
+    return binding
+
+
+def _w(**kw):
+    base = dict(name="short", batch=1, n_q_heads=4, n_kv_heads=2, head_dim=128, n_tokens=3000, pq_m=2, pq_centroids=64,
+                topk=300, n_init=4, n_local=64, dtype="bf16", kmeans_iters=1, recipe="plain")
+    base.update(kw)
+    return wl.Workload(**base)
+
+
+def _decode_and_check(pqc, p):
+    w = p.w
+    every = list(range(w.batch * w.n_kv_heads))
+    dev = [pqc.to_device(p.q, w.dtype, DEV), torch.from_numpy(p.centroids).to(DEV), torch.from_numpy(p.codes).to(DEV),
+           pqc.to_device(p.k, w.dtype, DEV), pqc.to_device(p.v, w.dtype, DEV)]
+    ctx = pqc.PQCache(w, DEV)
+    for _ in range(2):  # the second step finds the workspace as the first left it
+        idx, out = ctx.decode(*dev)
+    torch.cuda.synchronize()
+    idx, out = idx.cpu().numpy(), out.cpu().numpy()
+    assert check_indices(p, idx, units=every) == 0
+    err = attn_error(p, idx, out, units=every)
+    assert err <= ATTN_TOL[w.dtype], f"attention error {err:.3e}"
+    check_structure(p, idx, out)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(n_tokens=513, topk=60),                                                    # a workgroup with one token
+    dict(n_tokens=16385, topk=1600, n_q_heads=2, n_kv_heads=1),                     # one chunk beyond a step of the scan
+    dict(n_tokens=24576, topk=2400),                                                # the last short length, 2 x 64
+    dict(n_tokens=24577, topk=2400),                                                # and the first with a histogram kernel
+    dict(n_tokens=12288, topk=1200, pq_m=4, n_q_heads=16),                          # the same, 4 x 64; G = 8
+    dict(n_tokens=12289, topk=1200, pq_m=4, n_q_heads=2, dtype="f32"),
+    dict(n_tokens=8192, topk=800, pq_m=4, pq_centroids=256),                        # 4 x 256
+    dict(n_tokens=8191, topk=800, pq_m=4, pq_centroids=129, n_q_heads=2, dtype="f32"),
+    dict(n_tokens=16384, topk=3200, pq_centroids=256, n_q_heads=8),                 # 2 x 256
+    dict(n_tokens=3001, batch=3, n_q_heads=5, n_kv_heads=5, topk=700, pq_centroids=48),  # units at every alignment of the codes
+    dict(n_tokens=2999, batch=5, n_q_heads=5, n_kv_heads=5, topk=150, pq_m=4, n_init=0, n_local=1),
+    dict(n_tokens=300, batch=75, n_q_heads=4, n_kv_heads=4, topk=30),               # more units than workgroups fit at once
+    dict(n_tokens=2048, batch=66, n_q_heads=8, n_kv_heads=4, topk=1980),            # every token; 264 units of 512 tokens a workgroup
+], ids=lambda kw: ",".join(f"{k}={v}" for k, v in kw.items()))
+def test_short_caches(pqc, kw):
+    w = _w(**kw)
+    print(f"[case] short cache {w}", flush=True)
+    _decode_and_check(pqc, build_problem(w, seed=3, checked_units=[]))
+
+
+@pytest.mark.parametrize("n_tokens", [6007, 30001])  # without and with a histogram kernel
+@pytest.mark.parametrize("where", ["below", "above"])
+def test_threshold_outside_the_window(pqc, n_tokens, where):
+    # The sampled tokens (every nmid / 1024-th) all score best or all score worst, so that the K-th largest score lies below or
+    # above the window that the sample puts around it: slower, but the same selection.
+    w = _w(n_tokens=n_tokens, topk=2000, n_init=5, n_local=33)
+    p0 = build_problem(w, seed=4, checked_units=[])
+    codes = p0.codes.copy()
+    s32, _ = oracle.scores(p0.q, w.dtype, p0.centroids, p0.codes)
+    nmid = n_tokens - w.n_init - w.n_local
+    sampled = w.n_init + (np.arange(1024) * nmid) // 1024
+    for g in range(w.n_kv_heads):
+        mid = np.arange(w.n_init, n_tokens - w.n_local)
+        order = mid[np.argsort(s32[0, g, mid], kind="stable")]
+        codes[0, g, sampled] = p0.codes[0, g, order[-1] if where == "below" else order[0]]
+    p = dataclasses.replace(p0, codes=codes)
+    print(f"[case] threshold {where} the window {w}", flush=True)
+    _decode_and_check(pqc, p)
+    # and the stand-alone top-k on the same scores
+    s32, _ = oracle.scores(p.q, w.dtype, p.centroids, p.codes)
+    idx = pqc.PQCache(w, DEV).topk(torch.from_numpy(s32).to(DEV)).cpu().numpy()
+    np.testing.assert_array_equal(np.sort(idx, -1), np.sort(oracle.select(s32, w.topk, w.n_init, w.n_local), -1))
