@@ -263,8 +263,8 @@ int pqc_gather_attn(pqc_ctx* ctx, const void* q, const void* k_cache, const void
 /* ---- PQ construction and maintenance (context-free; shapes come from cfg) ---- */
 
 /* Bytes of device workspace pqc_pq_build makes use of (0 for an invalid configuration): the same for every n_tokens,
- * so that one workspace serves a cache at all its lengths.  At most 16 sets of sums per (sequence, KV head, partition),
- * at most 256 in all unless there are more of those; a set is 8 bytes per centroid value and 4 per centroid. */
+ * so that one workspace serves a cache at all its lengths.  At most three sets of sums per (sequence, KV head, partition),
+ * a set being 8 bytes per centroid value and 4 per centroid, and a second copy of the centroids. */
 size_t pqc_pq_build_workspace_bytes(const pqc_config* cfg);
 
 /*
@@ -286,7 +286,7 @@ size_t pqc_pq_build_workspace_bytes(const pqc_config* cfg);
  *   centroids  [B][Hkv][M][C][Dm]    f32        (out)
  *   codes      [B][Hkv][N][M]        uint8      (out)
  *   workspace  device memory, 256-byte aligned, of pqc_pq_build_workspace_bytes(cfg); one set (sums rounded up to
- *              256 bytes, then counts) is enough for the same result, up to a tenth slower on middle lengths
+ *              256 bytes, then counts) is enough for the same result, with one more launch per round
  * The fields topk, n_init, n_local and softmax_scale of cfg are validated but unused.
  */
 int pqc_pq_build(const pqc_config* cfg, const void* keys, const int32_t* init_idx, int32_t iters,

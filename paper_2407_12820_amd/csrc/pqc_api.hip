@@ -773,7 +773,7 @@ constexpr size_t kRoundLds = 156 * 1024;  // of the compute unit's 160 KB
 // (A search of up to 256 steps: for calls that launch such a grid.)
 RoundGrid round_grid(const BuildPlan& bp) {
   const BuildShape& s = bp.s;
-  RoundGrid r{1, 1, (s.N + 15) / 16 * 16, bp.staged};
+  RoundGrid r{1, (s.N + 15) / 16 * 16, bp.staged};
   double best = 1e30;
   const double least = (double)s.units * s.M * s.N / 256.0;  // all compute units busy
   for (int p = 1; p <= 256; ++p) {
@@ -806,37 +806,38 @@ int make_build_plan(const pqc_config* cfg, BuildPlan* bp) {
   return PQC_OK;
 }
 
-// The workspace holds sets of sums and counts.  Neither the least a build runs in nor the most it makes use of depends on
-// n_tokens, so that one workspace serves every length of a cache: one set per (unit, partition), and as many as short of
-// one workgroup per compute unit can fill.
+// The workspace holds sets of sums and counts, one sum per centroid value.  Neither the least a build runs in (one set) nor what it
+// makes use of depends on n_tokens, so that one workspace serves every length of a cache.
 struct BuildWorkspace {
-  size_t off_counts, total;
+  size_t off_counts, off_cent, total;
 };
-BuildWorkspace build_workspace(const BuildShape& s, int sets) {
-  const size_t n = (size_t)s.units * s.M * s.C * sets;
-  const size_t off = align_up(sizeof(unsigned long long) * n * s.Dm);
-  return {off, align_up(off + sizeof(unsigned) * n)};
-}
-int most_sum_sets(const BuildPlan& bp) {
-  return bp.fused ? std::max(1, std::min(kSumSets, 256 / (bp.s.units * bp.s.M))) : 1;
+constexpr int kLinkedSets = 3;  // of the round in front, of the round itself, and cleared meanwhile for the round behind
+BuildWorkspace build_workspace(const BuildShape& s, bool linked) {
+  const size_t n = (size_t)s.units * s.M * s.C, sets = linked ? kLinkedSets : 1;
+  BuildWorkspace b;
+  b.off_counts = align_up(sizeof(unsigned long long) * n * s.Dm * sets);
+  b.off_cent = align_up(b.off_counts + sizeof(unsigned) * n * sets);
+  b.total = linked ? align_up(b.off_cent + sizeof(float) * n * s.Dm) : b.off_cent;
+  return b;
 }
 
 // One launch over all token ranges: with sums a K-Means round, without it the assignment (codes written).
 template <typename T, int DM, bool ACCUM>
-void launch_round_d(const BuildShape& s, const RoundGrid& r, const T* keys, float* cent, uint8_t* codes, unsigned long long* sums,
+void launch_round_d(const BuildShape& s, const RoundGrid& r, const RoundLink& link, const T* keys, float* cent, uint8_t* codes, unsigned long long* sums,
                     unsigned* counts, hipStream_t st) {
   const dim3 grid((unsigned)(s.units * s.M * r.ranges));
   const size_t acc = ACCUM ? round_sum_bytes(s.C, s.Dm) : 0;
   if constexpr (sizeof(T) == 2 && DM >= 32) {
+    static_assert(DM > 64 || mfma_stage_bytes(256, DM) <= kRoundLds, "all centroids are staged at once, which the kernel knows");
     const size_t lds = mfma_stage_bytes(r.staged, DM) + acc;
     // eight tiles per wave read each staged centroid once for 128 tokens (as many as the registers of four waves per SIMD hold
     // with longer sub-vectors: six of 64 dimensions spill and take 1197 us for the eight rounds that five do in 770 us, four in
     // 777 us); short ranges take two, so that more than a few of the sixteen waves have tokens
     constexpr int kTiles = DM >= 128 ? 3 : DM == 64 ? 5 : 8;
     if (r.tokens >= 16 * 16 * kTiles)
-      hipLaunchKernelGGL((pq_round_mfma_kernel<DM, kTiles, ACCUM>), grid, dim3(1024), lds, st, s, r, keys, cent, codes, sums, counts);
+      hipLaunchKernelGGL((pq_round_mfma_kernel<DM, kTiles, ACCUM>), grid, dim3(1024), lds, st, s, r, link, keys, cent, codes, sums, counts);
     else
-      hipLaunchKernelGGL((pq_round_mfma_kernel<DM, 2, ACCUM>), grid, dim3(1024), lds, st, s, r, keys, cent, codes, sums, counts);
+      hipLaunchKernelGGL((pq_round_mfma_kernel<DM, 2, ACCUM>), grid, dim3(1024), lds, st, s, r, link, keys, cent, codes, sums, counts);
   } else {
     static_assert(vector_stage_bytes(256, DM) <= kRoundLds, "all centroids are staged at once");
     // one lane per token and two tokens per lane as soon as every wave has that many (8192 tokens x 8 heads, fp32, 4x256, which is
@@ -844,12 +845,12 @@ void launch_round_d(const BuildShape& s, const RoundGrid& r, const T* keys, floa
     constexpr int NT = DM >= 128 ? 512 : 1024, TT = DM <= 32 ? 2 : 1;
     const size_t lds = vector_stage_bytes(s.C, DM) + acc;
     if (r.tokens < NT) {
-      hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, NT, 4, 1, ACCUM>), grid, dim3(NT), lds, st, s, r, keys, cent, codes, sums, counts);
+      hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, NT, 4, 1, ACCUM>), grid, dim3(NT), lds, st, s, r, link, keys, cent, codes, sums, counts);
     } else if constexpr (ACCUM || DM >= 128) {
       if (r.tokens >= NT * TT)
-        hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, NT, 1, TT, ACCUM>), grid, dim3(NT), lds, st, s, r, keys, cent, codes, sums, counts);
+        hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, NT, 1, TT, ACCUM>), grid, dim3(NT), lds, st, s, r, link, keys, cent, codes, sums, counts);
       else if constexpr (TT > 1)
-        hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, NT, 1, 1, ACCUM>), grid, dim3(NT), lds, st, s, r, keys, cent, codes, sums, counts);
+        hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, NT, 1, 1, ACCUM>), grid, dim3(NT), lds, st, s, r, link, keys, cent, codes, sums, counts);
     } else {
       // The assignment alone needs no room for sums, so that small workgroups share a compute unit, and they are many: a last
       // one that is nearly empty holds nobody up (50001 tokens x 24 heads, fp32, 4x256: 1655 us with the ranges of a round,
@@ -859,49 +860,71 @@ void launch_round_d(const BuildShape& s, const RoundGrid& r, const T* keys, floa
       const bool wide = r.tokens >= NT * TT;
       int tokens = kSmall * (wide ? TT : 1) * (DM <= 32 && r.tokens >= 2 * NT * TT ? 2 : 1);
       while ((long long)s.units * s.M * ((s.N + tokens - 1) / tokens) > (1 << 20)) tokens *= 2;
-      const RoundGrid a{(s.N + tokens - 1) / tokens, 1, tokens, s.C};
+      const RoundGrid a{(s.N + tokens - 1) / tokens, tokens, s.C};
       const dim3 agrid((unsigned)(s.units * s.M * a.ranges));
       if (wide)
-        hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, kSmall, 1, TT, false>), agrid, dim3(kSmall), lds, st, s, a, keys, cent, codes, sums, counts);
+        hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, kSmall, 1, TT, false>), agrid, dim3(kSmall), lds, st, s, a, link, keys, cent, codes, sums, counts);
       else if constexpr (TT > 1)
-        hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, kSmall, 1, 1, false>), agrid, dim3(kSmall), lds, st, s, a, keys, cent, codes, sums, counts);
+        hipLaunchKernelGGL((pq_round_vector_kernel<T, DM, kSmall, 1, 1, false>), agrid, dim3(kSmall), lds, st, s, a, link, keys, cent, codes, sums, counts);
     }
   }
 }
 template <typename T, bool ACCUM>
-void launch_round(const BuildShape& s, const RoundGrid& r, const T* keys, float* cent, uint8_t* codes, unsigned long long* sums,
+void launch_round(const BuildShape& s, const RoundGrid& r, const RoundLink& link, const T* keys, float* cent, uint8_t* codes, unsigned long long* sums,
                   unsigned* counts, hipStream_t st) {
   switch (s.Dm) {
-    case 16: launch_round_d<T, 16, ACCUM>(s, r, keys, cent, codes, sums, counts, st); break;
-    case 32: launch_round_d<T, 32, ACCUM>(s, r, keys, cent, codes, sums, counts, st); break;
-    case 64: launch_round_d<T, 64, ACCUM>(s, r, keys, cent, codes, sums, counts, st); break;
-    default: launch_round_d<T, 128, ACCUM>(s, r, keys, cent, codes, sums, counts, st); break;
+    case 16: launch_round_d<T, 16, ACCUM>(s, r, link, keys, cent, codes, sums, counts, st); break;
+    case 32: launch_round_d<T, 32, ACCUM>(s, r, link, keys, cent, codes, sums, counts, st); break;
+    case 64: launch_round_d<T, 64, ACCUM>(s, r, link, keys, cent, codes, sums, counts, st); break;
+    default: launch_round_d<T, 128, ACCUM>(s, r, link, keys, cent, codes, sums, counts, st); break;
   }
 }
+constexpr RoundLink kNoLink{nullptr, nullptr, nullptr, nullptr, nullptr};
 template <typename T>
-void launch_assign(const BuildShape& s, const RoundGrid& r, const T* keys, const float* cent, uint8_t* codes, hipStream_t st) {
-  launch_round<T, false>(s, r, keys, const_cast<float*>(cent), codes, nullptr, nullptr, st);  // read only without sums
+void launch_assign(const BuildShape& s, const RoundGrid& r, const RoundLink& link, const T* keys, const float* cent, uint8_t* codes, hipStream_t st) {
+  launch_round<T, false>(s, r, link, keys, const_cast<float*>(cent), codes, nullptr, nullptr, st);  // read only without sums
+}
+
+// Whether a build's rounds are linked: a round takes the means of the round in front when it stages its centroids, instead of a
+// launch of their own in between.  Where one workgroup owns all tokens it writes the means itself, and where a round is two
+// launches (sums that do not fit LDS) there is one that takes them anyway.
+bool linked_rounds(const BuildPlan& bp, const RoundGrid& r) { return bp.fused && r.ranges > 1; }
+// The assignment on the vector ALU runs in small workgroups when ranges are long, too many for each to read the sums.
+template <typename T>
+bool linked_assignment(const BuildShape& s, const RoundGrid& r) {
+  return (sizeof(T) == 2 && s.Dm >= 32) || r.tokens < (s.Dm >= 128 ? 512 : 1024);
 }
 
 template <typename T>
-int pq_build_t(const BuildPlan& bp, const RoundGrid& r, const T* keys, const int32_t* init_idx, int iters, float* cent, uint8_t* codes,
+int pq_build_t(const BuildPlan& bp, const RoundGrid& r, bool linked, const T* keys, const int32_t* init_idx, int iters, float* cent, uint8_t* codes,
                char* wsp, hipStream_t st) {
   const BuildShape& s = bp.s;
-  const int sets = bp.fused ? r.sets : 1;
-  unsigned long long* sums = reinterpret_cast<unsigned long long*>(wsp);
-  unsigned* counts = reinterpret_cast<unsigned*>(wsp + build_workspace(s, sets).off_counts);
+  const BuildWorkspace b = build_workspace(s, linked);
   const unsigned uj = (unsigned)(s.units * s.M);
+  const size_t n_cent = (size_t)uj * s.C, n_val = n_cent * s.Dm;
+  unsigned long long* const sums = reinterpret_cast<unsigned long long*>(wsp);
+  unsigned* const counts = reinterpret_cast<unsigned*>(wsp + b.off_counts);
   const dim3 per_cent((unsigned)((s.C * s.Dm + 255) / 256), uj);
   const bool means = !bp.fused || r.ranges > 1;  // else a round writes them itself
-  hipLaunchKernelGGL((pq_init_kernel<T>), per_cent, dim3(256), 0, st, s, keys, init_idx, cent,
-                     means && sets == 1 ? sums : nullptr, counts);
+  // linked: two places for the centroids in turn, the last ones to the caller's
+  auto place = [&](int it) { return linked && ((iters - it) & 1) ? reinterpret_cast<float*>(wsp + b.off_cent) : cent; };
+  auto link_of = [&](int it) {  // what launch `it` takes over from round it - 1; the last launch is the assignment
+    if (!linked || it == 0) return kNoLink;
+    const int prev = (it - 1) % kLinkedSets, next = (it + 1) % kLinkedSets;
+    const bool more = it + 1 < iters;
+    return RoundLink{sums + prev * n_val, counts + prev * n_cent, place(it), more ? sums + next * n_val : nullptr,
+                     more ? counts + next * n_cent : nullptr};
+  };
+  hipLaunchKernelGGL((pq_init_kernel<T>), per_cent, dim3(256), 0, st, s, keys, init_idx, place(0), means ? sums : nullptr, counts,
+                     linked ? 2 : 1);
   for (int it = 0; it < iters; ++it) {
     if (bp.fused) {
-      launch_round<T, true>(s, r, keys, cent, codes, sums, counts, st);
+      const int set = linked ? it % kLinkedSets : 0;
+      launch_round<T, true>(s, r, link_of(it), keys, place(std::max(it - 1, 0)), codes, sums + set * n_val, counts + set * n_cent, st);
     } else {  // the accumulators are too large for LDS: codes first, then the sums of the members of each code
       static_assert(mfma_stage_bytes(256, 32) + round_sum_bytes(256, 32) <= kRoundLds, "and 16 and 32 dimensions always fit");
       static_assert(vector_stage_bytes(256, 32) + round_sum_bytes(256, 32) <= kRoundLds, "and 16 and 32 dimensions always fit");
-      launch_assign<T>(s, r, keys, cent, codes, st);
+      launch_assign<T>(s, r, kNoLink, keys, cent, codes, st);
       const int tpw = accum_tokens_per_wg(s.C);
       const dim3 grid((s.N + tpw - 1) / tpw, uj);
       const size_t lds = (size_t)tpw * sizeof(unsigned short);
@@ -910,9 +933,17 @@ int pq_build_t(const BuildPlan& bp, const RoundGrid& r, const T* keys, const int
         default: hipLaunchKernelGGL((pq_accum_kernel<T, 128>), grid, dim3(256), lds, st, s, keys, codes, sums, counts); break;
       }
     }
-    if (means) hipLaunchKernelGGL(pq_mean_kernel, per_cent, dim3(256), 0, st, s, sets, sums, counts, cent);
+    if (means && !linked) hipLaunchKernelGGL(pq_mean_kernel, per_cent, dim3(256), 0, st, s, sums, counts, cent, cent);
   }
-  launch_assign<T>(s, r, keys, cent, codes, st);
+  if (linked && iters > 0 && linked_assignment<T>(s, r)) {
+    launch_assign<T>(s, r, link_of(iters), keys, place(iters - 1), codes, st);
+  } else {
+    if (linked && iters > 0) {
+      const int last = (iters - 1) % kLinkedSets;
+      hipLaunchKernelGGL(pq_mean_kernel, per_cent, dim3(256), 0, st, s, sums + last * n_val, counts + last * n_cent, place(iters - 1), cent);
+    }
+    launch_assign<T>(s, r, kNoLink, keys, cent, codes, st);
+  }
   return hipGetLastError() == hipSuccess ? PQC_OK : PQC_EHIP;
 }
 
@@ -923,7 +954,7 @@ extern "C" {
 size_t pqc_pq_build_workspace_bytes(const pqc_config* cfg) {
   BuildPlan bp;
   if (make_build_plan(cfg, &bp) != PQC_OK) return 0;
-  return build_workspace(bp.s, most_sum_sets(bp)).total;
+  return build_workspace(bp.s, bp.fused).total;
 }
 
 int pqc_pq_build(const pqc_config* cfg, const void* keys, const int32_t* init_idx, int32_t iters, float* centroids,
@@ -933,14 +964,14 @@ int pqc_pq_build(const pqc_config* cfg, const void* keys, const int32_t* init_id
   if (rc != PQC_OK) return rc;
   if (!keys || !init_idx || !centroids || !codes || iters < 0) return PQC_EINVAL;
   if (!aligned16(keys) || !aligned16(init_idx) || !aligned16(centroids) || !aligned16(codes)) return PQC_EINVAL;
-  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kAlign) || workspace_bytes < build_workspace(bp.s, 1).total)
+  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kAlign) || workspace_bytes < build_workspace(bp.s, false).total)
     return PQC_EWORKSPACE;
-  RoundGrid r = round_grid(bp);
-  if (r.ranges <= most_sum_sets(bp) && workspace_bytes >= build_workspace(bp.s, r.ranges).total) r.sets = r.ranges;
+  const RoundGrid r = round_grid(bp);
+  const bool linked = linked_rounds(bp, r) && workspace_bytes >= build_workspace(bp.s, true).total;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* wsp = static_cast<char*>(workspace);
-  if (cfg->kv_dtype == PQC_F32) return pq_build_t<float>(bp, r, static_cast<const float*>(keys), init_idx, iters, centroids, codes, wsp, st);
-  return pq_build_t<bf16_t>(bp, r, static_cast<const bf16_t*>(keys), init_idx, iters, centroids, codes, wsp, st);
+  if (cfg->kv_dtype == PQC_F32) return pq_build_t<float>(bp, r, linked, static_cast<const float*>(keys), init_idx, iters, centroids, codes, wsp, st);
+  return pq_build_t<bf16_t>(bp, r, linked, static_cast<const bf16_t*>(keys), init_idx, iters, centroids, codes, wsp, st);
 }
 
 int pqc_pq_assign(const pqc_config* cfg, const void* keys, const float* centroids, uint8_t* codes, void* stream) {
@@ -952,9 +983,9 @@ int pqc_pq_assign(const pqc_config* cfg, const void* keys, const float* centroid
   const RoundGrid r = round_grid(bp);
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (cfg->kv_dtype == PQC_F32)
-    launch_assign<float>(bp.s, r, static_cast<const float*>(keys), centroids, codes, st);
+    launch_assign<float>(bp.s, r, kNoLink, static_cast<const float*>(keys), centroids, codes, st);
   else
-    launch_assign<bf16_t>(bp.s, r, static_cast<const bf16_t*>(keys), centroids, codes, st);
+    launch_assign<bf16_t>(bp.s, r, kNoLink, static_cast<const bf16_t*>(keys), centroids, codes, st);
   return hipGetLastError() == hipSuccess ? PQC_OK : PQC_EHIP;
 }
 

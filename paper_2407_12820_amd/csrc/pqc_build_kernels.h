@@ -21,11 +21,11 @@ struct BuildShape {
   int cap;  // tokens the key and code tensors hold per unit (>= N): their stride between units
 };
 
-// centroids[u][j][c][:] = keys[u][init_idx[u][j][c]][j*Dm : (j+1)*Dm]; member sums and counts of the first round cleared
+// centroids[u][j][c][:] = keys[u][init_idx[u][j][c]][j*Dm : (j+1)*Dm]; member sums and counts cleared, so many sets of them
 template <typename T>
 __global__ __launch_bounds__(256) void pq_init_kernel(BuildShape s, const T* __restrict__ keys,
                                                       const int* __restrict__ init_idx, float* __restrict__ cent,
-                                                      unsigned long long* __restrict__ sums, unsigned* __restrict__ counts) {
+                                                      unsigned long long* __restrict__ sums, unsigned* __restrict__ counts, int sets) {
   const int uj = blockIdx.y, u = uj / s.M, j = uj % s.M;
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= s.C * s.Dm) return;
@@ -34,8 +34,11 @@ __global__ __launch_bounds__(256) void pq_init_kernel(BuildShape s, const T* __r
   t = max(0, min(s.N - 1, t));
   cent[(size_t)uj * s.C * s.Dm + i] = load_as_float<T>(keys, ((size_t)u * s.cap + t) * kD + j * s.Dm + e);
   if (!sums) return;  // no round adds to them
-  sums[(size_t)uj * s.C * s.Dm + i] = 0ull;
-  if (e == 0) counts[(size_t)uj * s.C + c] = 0u;
+  for (int x = 0; x < sets; ++x) {
+    const size_t set = (size_t)x * s.units * s.M + uj;
+    sums[set * s.C * s.Dm + i] = 0ull;
+    if (e == 0) counts[set * s.C + c] = 0u;
+  }
 }
 
 // One token per unit (the code of an appended token): one thread per centroid, the same distance chain
@@ -73,26 +76,33 @@ __global__ __launch_bounds__(256) void pq_encode_kernel(BuildShape s, const T* _
 // Assignment of every token to its nearest centroid and, in the same pass over the keys, the sums of the new
 // centroids' members.  A workgroup owns one range of tokens of one (unit, partition): it stages the centroids in LDS
 // once, streams its keys through registers, and adds each key to an LDS accumulator of its centroid; at the end the
-// accumulators go to the workspace and pq_mean_kernel takes the means.  Up to kSumSets ranges of a (unit, partition) write
-// a set of sums each, as they are; more of them, or where the workspace holds one set only, add to one set with atomics
-// (integers: the same sums), which the start and every mean clear.  With ACCUM = false the kernel is the assignment alone
-// and writes codes.
+// accumulators are added to the sums of the (unit, partition) in the workspace with atomics (integers: whatever the order).
+// The means are taken by the launch behind, by each of its workgroups when it stages the centroids (RoundLink), so that a
+// round is one launch; the sums take turns in three places, as one is read, one added to and one cleared at a time.
+// With ACCUM = false the kernel is the assignment alone and writes codes.
 //
-// Why the line lies there (four rounds, sets against atomics): 8192 tokens x 8 heads, 4x256, 8 ranges 141 against 156 us;
-// 16384 tokens x 8 heads, 2x64, 16 ranges 102 against 107 us; 8192 tokens x 2 heads, 4x256, 32 ranges 106 against 92 us;
-// 2048 tokens of one head, 2x64, 128 ranges 102 against 57 us.  Atomics cost about 0.3 ns each, however many ranges there are; the
-// mean's walk over the sets grows with their number.
+// Why so for every number of ranges: a launch of the means costs about 6 us a round with its gap, taking them here about 1.5 and
+// the additions of all workgroups at about the same time up to 4.  Against a launch that adds up a set of sums per range (up to 16
+// ranges) or takes the means of a shared one, four rounds: 2048 tokens of one head, 2x64, 59 -> 45 us; 8 heads 69 -> 55; 131072
+// tokens x 8 heads 400 -> 377; 2048 tokens x 4 heads, 4x256, 98 -> 71; 8192 x 8 heads, 4x256, 145 -> 141.  The other way round only
+// where 8 to 16 ranges of one batch each end together with 256 centroids: 32768 tokens x 4 heads, 189 -> 191 us.
 //
 // Sums are 64-bit integers of the values in fixed point (2^-20, round to nearest even), so the result does not depend
 // on the order of tokens, waves or workgroups.  The conversion is one addition in double precision: x + 1.5 * 2^32 has
 // its last bit at 2^-20, so its bit pattern is the pattern of 1.5 * 2^32 plus the fixed-point integer; the constant is
 // taken out again count times when the accumulators are written.  (|x| >= 2^30 takes a conversion of its own.)
-constexpr int kSumSets = 16;  // most sets of sums per (unit, partition)
 struct RoundGrid {
   int ranges;   // token ranges per (unit, partition)
-  int sets;     // sets of sums per (unit, partition) in the workspace: ranges (a set each) or 1
   int tokens;   // tokens per range, a multiple of 16
   int staged;   // centroids staged at a time (all of them when they fit; always all with ACCUM)
+};
+// What a launch takes over from the round in front of it.  sums null: nothing, the centroids it is given are the ones to use.
+struct RoundLink {
+  const unsigned long long* sums;  // of that round's members, complete
+  const unsigned* counts;
+  float* cent;                     // where the means go; not where this launch reads the centroids of the round in front
+  unsigned long long* next_sums;   // cleared for the round behind this one, or null
+  unsigned* next_counts;
 };
 constexpr double kFixBias = 6442450944.0;  // 1.5 * 2^32
 constexpr long long kFixBiasBits = 0x41f8000000000000ll;
@@ -131,46 +141,85 @@ __device__ __forceinline__ void round_place(const BuildShape& s, int ranges, int
   p = item % ranges;
 }
 
+// One division serves the values of a centroid; the quotient is corrected by its remainder.
 __device__ __forceinline__ float fixed_mean(unsigned long long sum, unsigned count) {
-  return (float)((double)(long long)sum * (1.0 / (double)(1 << kFixShift)) / (double)count);
+  const double n = (double)count, inv = 1.0 / n, v = (double)(long long)sum * (1.0 / (double)(1 << kFixShift)), q = v * inv;
+  return (float)fma(fma(-q, n, v), inv, q);
 }
 
 enum class SumRow { kOdd, kPlain, kPlaced };  // rows of Dm + 1 sums; of Dm sums; of Dm sums in the order of sum_place
-template <SumRow ROW>
-__device__ __forceinline__ int sum_index(const BuildShape& s, int c, int e) {
-  return ROW == SumRow::kOdd ? c * (s.Dm + 1) + e : c * s.Dm + (ROW == SumRow::kPlaced ? sum_place(e) : e);
+template <SumRow ROW, int DM>
+__device__ __forceinline__ int sum_index(int c, int e) {
+  return ROW == SumRow::kOdd ? c * (DM + 1) + e : c * DM + (ROW == SumRow::kPlaced ? sum_place(e) : e);
+}
+
+// The means of the round in front, handed to put(first of four values, the values) one by one over the workgroup; an empty
+// cluster keeps its centroid.  The first range of a (unit, partition) writes them out for the launch behind, and every range
+// clears its share of the sums that launch adds to.
+template <int DM, int NT, class Put>
+__device__ __forceinline__ void linked_means(const BuildShape& s, const RoundGrid& r, const RoundLink& k, int uj, int p,
+                                             const float* cent, Put put) {
+  constexpr int B = 2;  // groups of four values in flight per thread
+  const int n = s.C * DM, n4 = n / 4;
+  const ulonglong2* sp = reinterpret_cast<const ulonglong2*>(k.sums + (size_t)uj * n);
+  const f32x4_t* op = reinterpret_cast<const f32x4_t*>(cent + (size_t)uj * n);
+  f32x4_t* out = reinterpret_cast<f32x4_t*>(k.cent + (size_t)uj * n);
+  for (int i0 = threadIdx.x; i0 < n4; i0 += B * NT) {
+    ulonglong2 a[B], b[B];
+    unsigned m[B];
+#pragma unroll
+    for (int x = 0; x < B; ++x) {
+      const int i = min(i0 + x * NT, n4 - 1);
+      a[x] = sp[2 * i];
+      b[x] = sp[2 * i + 1];
+      m[x] = k.counts[(size_t)uj * s.C + i / (DM / 4)];
+    }
+    PQC_LOADS_ISSUED();
+#pragma unroll
+    for (int x = 0; x < B; ++x) {
+      const int i = i0 + x * NT;
+      if (i < n4) {
+        f32x4_t v;
+        if (m[x])
+          v = f32x4_t{fixed_mean(a[x].x, m[x]), fixed_mean(a[x].y, m[x]), fixed_mean(b[x].x, m[x]), fixed_mean(b[x].y, m[x])};
+        else
+          v = op[i];
+        put(4 * i, v);
+        if (p == 0) out[i] = v;
+      }
+    }
+  }
+  if (k.next_sums) {
+    const int end = (int)((long long)n * (p + 1) / r.ranges), cend = (int)((long long)s.C * (p + 1) / r.ranges);
+    for (int i = (int)((long long)n * p / r.ranges) + threadIdx.x; i < end; i += NT) k.next_sums[(size_t)uj * n + i] = 0ull;
+    for (int i = (int)((long long)s.C * p / r.ranges) + threadIdx.x; i < cend; i += NT) k.next_counts[(size_t)uj * s.C + i] = 0u;
+  }
 }
 
 // The accumulators to the workspace; a workgroup that owns all tokens of its (unit, partition) writes the new centroids
 // itself (nobody else reads them in this launch, and it has staged the old ones).
-template <SumRow ROW>
+template <SumRow ROW, int DM>
 __device__ __forceinline__ void round_flush(const BuildShape& s, const RoundGrid& r, int uj, int p, const unsigned long long* sums,
                                             const unsigned* cnt, float* __restrict__ cent, unsigned long long* __restrict__ part_sums,
                                             unsigned* __restrict__ part_counts) {
-  const int n = s.C * s.Dm;
-  const bool shared = r.sets < r.ranges;
-  const size_t set = (size_t)uj * r.sets + (shared ? 0 : p);
-  // ranges that add to one set start at different places of it: they finish at about the same time
-  const int first = shared ? (int)((long long)n * p / r.ranges) & ~63 : 0;
-  for (int i0 = threadIdx.x; i0 < n; i0 += blockDim.x) {
+  const int n = s.C * DM;
+  // ranges start at different places of the sums they share: they finish at about the same time
+  const int first = (int)((long long)n * p / r.ranges) & ~63;
+  int tid = threadIdx.x;
+  asm("" : "+v"(tid));  // (else places of the flush are kept in registers across the whole round)
+  for (int i0 = tid; i0 < n; i0 += blockDim.x) {
     const int i = i0 + first < n ? i0 + first : i0 + first - n;
-    const int c = i / s.Dm, e = i - c * s.Dm;
-    const unsigned long long v = sums[sum_index<ROW>(s, c, e)] - (unsigned long long)cnt[c] * (unsigned long long)kFixBiasBits;
-    if (r.ranges == 1) {
-      if (cnt[c]) cent[(size_t)uj * n + i] = fixed_mean(v, cnt[c]);
-    } else if (!shared) {
-      part_sums[set * n + i] = v;
-    } else if (cnt[c]) {
-      atomicAdd(&part_sums[set * n + i], v);
-    }
+    const int c = i / DM, e = i % DM;
+    const unsigned long long v = sums[sum_index<ROW, DM>(c, e)] - (unsigned long long)cnt[c] * (unsigned long long)kFixBiasBits;
+    if (!cnt[c]) continue;
+    if (r.ranges == 1)
+      cent[(size_t)uj * n + i] = fixed_mean(v, cnt[c]);
+    else
+      atomicAdd(&part_sums[(size_t)uj * n + i], v);
   }
   if (r.ranges > 1)
-    for (int i = threadIdx.x; i < s.C; i += blockDim.x) {
-      if (!shared)
-        part_counts[set * s.C + i] = cnt[i];
-      else if (cnt[i])
-        atomicAdd(&part_counts[set * s.C + i], cnt[i]);
-    }
+    for (int i = tid; i < s.C; i += blockDim.x)
+      if (cnt[i]) atomicAdd(&part_counts[(size_t)uj * s.C + i], cnt[i]);
 }
 
 // Eight bf16 values turned: value e becomes the one that was value (e + n) modulo 8, n < 8.
@@ -211,7 +260,7 @@ __device__ __forceinline__ void keep_lower(float& best, int& index, f32x4_t& kep
 // for one token per tile, so that the index costs one register per tile and only the four quads are merged at the end
 // (with the operands the other way round, sixteen columns of four tokens each had to be merged).
 template <int DM, int TT, bool ACCUM>
-__global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, RoundGrid r, const bf16_t* __restrict__ keys,
+__global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, RoundGrid r, RoundLink link, const bf16_t* __restrict__ keys,
                                                              float* cent, uint8_t* __restrict__ codes,
                                                              unsigned long long* __restrict__ part_sums,
                                                              unsigned* __restrict__ part_counts) {
@@ -240,46 +289,52 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
   const int uj = u * s.M + j, tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6, col = lane & 15, quad = lane >> 4;
   const int t_begin = p * r.tokens, t_end = min(s.N, t_begin + r.tokens);
-  const bool one_group = s.C <= r.staged;  // then the centroids are staged once
-  auto stage = [&](int c0) {
-    const int nc = min(r.staged, s.C - c0);
-    for (int i = tid; i < nc * DM; i += NT) {  // every value, times -2, as three bf16 terms that add up to it exactly
-      const float v = -2.0f * cent[((size_t)uj * s.C + c0) * DM + i];
-      const unsigned h = bf16_round_bits(v);
-      const float r1 = v - __uint_as_float(h << 16);
-      const unsigned m = bf16_round_bits(r1);
-      const float r2 = r1 - __uint_as_float(m << 16);
-      const unsigned l = bf16_round_bits(r2);
-      const int o = (i / DM) * RS + (i % DM);
-      ct[o] = (unsigned short)h;
-      ct[rows * RS + o] = (unsigned short)m;
-      ct[2 * rows * RS + o] = (unsigned short)l;
-    }
-    // squared norms: four threads per centroid, a quarter of the dimensions each; rows that hold no centroid lose always
-    for (int cb = 0; cb < rows; cb += NT / 4) {
-      const int c = cb + (tid >> 2), seg = tid & 3;
-      const float4* cr = reinterpret_cast<const float4*>(cent + ((size_t)uj * s.C + c0 + min(c, nc - 1)) * DM + seg * (DM / 4));
-      float n2 = 0.0f;
+  const bool one_group = DM <= 64 || s.C <= r.staged;  // then the centroids are staged once (256 of 64 dimensions fit)
+  // four values of a staged centroid, times -2, as three bf16 terms that add up to each exactly, and its squared norm from the DM / 4
+  // lanes that hold its values
+  auto put = [&](int i, const f32x4_t& v) {
+    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
+    const int row = i / DM, e = i % DM;
+    f32x4_t left = -2.0f * v;
 #pragma unroll
-      for (int e = 0; e < DM / 16; ++e) {
-        const float4 v = cr[e];
-        n2 = fmaf(v.x, v.x, n2);
-        n2 = fmaf(v.y, v.y, n2);
-        n2 = fmaf(v.z, v.z, n2);
-        n2 = fmaf(v.w, v.w, n2);
-      }
-      n2 += dpp_f<0xB1>(0.0f, n2);
-      n2 += dpp_f<0x4E>(0.0f, n2);
-      if (seg == 0 && c < rows) cn[c] = c < nc ? n2 : INFINITY;
+    for (int term = 0; term < 3; ++term) {
+      const bf16x4_t b = __builtin_convertvector(left, bf16x4_t);
+      left -= __builtin_convertvector(b, f32x4_t);
+      __builtin_memcpy(&ct[(term * rows + row) * RS + e], &b, 8);
     }
-    for (int i = tid; i < (rows - nc) * DM; i += NT) {  // (zero, so that no stale bits of LDS reach the products)
+    float n2 = fmaf(v[3], v[3], fmaf(v[2], v[2], fmaf(v[1], v[1], v[0] * v[0])));
+    n2 += dpp_f<0xB1>(0.0f, n2);
+    n2 += dpp_f<0x4E>(0.0f, n2);
+    n2 += dpp_f<0x141>(0.0f, n2);
+    if constexpr (DM >= 64) n2 += dpp_f<0x140>(0.0f, n2);
+    if constexpr (DM >= 128) n2 += __shfl_xor(n2, 16);
+    if (e == 0) cn[row] = n2;
+  };
+  auto pad = [&](int nc) {  // rows that hold no centroid lose always (and zero, so that no stale bits of LDS reach the products)
+    for (int i = tid; i < (rows - nc) * DM; i += NT) {
       const int o = (nc + i / DM) * RS + (i % DM);
       ct[o] = ct[rows * RS + o] = ct[2 * rows * RS + o] = 0;
     }
+    for (int i = nc + tid; i < rows; i += NT) cn[i] = INFINITY;
+  };
+  auto stage = [&](int c0) {
+    const int nc = min(r.staged, s.C - c0), n4 = nc * (DM / 4);
+    const f32x4_t* src = reinterpret_cast<const f32x4_t*>(cent + ((size_t)uj * s.C + c0) * DM);
+    for (int i0 = tid; i0 < n4; i0 += 2 * NT) {
+      const f32x4_t v0 = src[i0], v1 = src[min(i0 + NT, n4 - 1)];
+      put(4 * i0, v0);
+      if (i0 + NT < n4) put(4 * (i0 + NT), v1);
+    }
+    pad(nc);
   };
   const int turn = col & 7;      // where a lane starts in the eight dimensions it holds, so that the lanes of a quad spread
   const bool upper = col >= 8;
-  if (one_group) stage(0);
+  if (link.sums) {  // (all centroids are staged at once)
+    linked_means<DM, NT>(s, r, link, uj, p, cent, put);
+    pad(s.C);
+  } else if (one_group) {
+    stage(0);
+  }
   if constexpr (ACCUM) {
     for (int i = tid; i < s.C * SR; i += NT) sums[i] = 0ull;
     for (int i = tid; i < s.C; i += NT) cnt[i] = 0u;
@@ -465,7 +520,7 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
   }
   if constexpr (ACCUM) {
     __syncthreads();
-    round_flush<TURNED ? SumRow::kPlaced : SumRow::kOdd>(s, r, uj, p, sums, cnt, cent, part_sums, part_counts);
+    round_flush<TURNED ? SumRow::kPlaced : SumRow::kOdd, DM>(s, r, uj, p, sums, cnt, cent, part_sums, part_counts);
   }
 }
 
@@ -490,7 +545,7 @@ __device__ __forceinline__ void turn_values(float (&x)[N], int n) {
 // quad q runs the chains of centroids q, q+4, ..., so that short caches still occupy the chip (a single fp32 head of 10007
 // tokens is 157 waves at one token per lane), and adds the dimensions q, q+4, ... of the key to the sums.
 template <typename T, int DM, int NT, int LANES, int TT, bool ACCUM>
-__global__ __launch_bounds__(NT) void pq_round_vector_kernel(BuildShape s, RoundGrid r, const T* __restrict__ keys, float* cent,
+__global__ __launch_bounds__(NT) void pq_round_vector_kernel(BuildShape s, RoundGrid r, RoundLink link, const T* __restrict__ keys, float* cent,
                                                              uint8_t* __restrict__ codes, unsigned long long* __restrict__ part_sums,
                                                              unsigned* __restrict__ part_counts) {
   static_assert(DM % 8 == 0 && (LANES == 1 || (LANES == 4 && TT == 1)), "several tokens per lane, or several lanes per token");
@@ -515,7 +570,10 @@ __global__ __launch_bounds__(NT) void pq_round_vector_kernel(BuildShape s, Round
   const int uj = u * s.M + j, tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6, col = lane % TS, quad = lane / TS;
   const int t_begin = p * r.tokens, t_end = min(s.N, t_begin + r.tokens);
-  {
+  if (link.sums) {
+    linked_means<DM, NT>(s, r, link, uj, p, cent,
+                         [&](int i, const f32x4_t& v) { *reinterpret_cast<f32x4_t*>(&cs[(i / DM) * RS + (i % DM)]) = v; });
+  } else {
     const f32x4_t* src = reinterpret_cast<const f32x4_t*>(cent + (size_t)uj * s.C * DM);
     for (int i = tid; i < s.C * (DM / 4); i += NT) *reinterpret_cast<f32x4_t*>(&cs[(i / (DM / 4)) * RS + 4 * (i % (DM / 4))]) = src[i];
   }
@@ -655,7 +713,7 @@ __global__ __launch_bounds__(NT) void pq_round_vector_kernel(BuildShape s, Round
   }
   if constexpr (ACCUM) {
     __syncthreads();
-    round_flush<TURNED ? SumRow::kPlain : SumRow::kOdd>(s, r, uj, p, sums, cnt, cent, part_sums, part_counts);
+    round_flush<TURNED ? SumRow::kPlain : SumRow::kOdd, DM>(s, r, uj, p, sums, cnt, cent, part_sums, part_counts);
   }
 }
 
@@ -772,46 +830,23 @@ __global__ __launch_bounds__(256) void pq_accum_kernel(BuildShape s, const T* __
   }
 }
 
-// cent = sums / counts where counts > 0, the sets of a (unit, partition) added up; a set that is added to is cleared for the
-// next round.  A workgroup's 256 sums are those of whole centroids (sub-vectors have 16, 32, 64 or 128 dimensions), so that it
-// alone reads the counts that it clears.
-__global__ __launch_bounds__(256) void pq_mean_kernel(BuildShape s, int sets, unsigned long long* __restrict__ sums,
-                                                      unsigned* __restrict__ counts, float* __restrict__ cent) {
+// cent = sums / counts where counts > 0, else the centroid as it was; the sums are cleared for the next round.  A workgroup's 256
+// sums are those of whole centroids (sub-vectors have 16, 32, 64 or 128 dimensions), so that it alone reads the counts that it clears.
+__global__ __launch_bounds__(256) void pq_mean_kernel(BuildShape s, unsigned long long* __restrict__ sums, unsigned* __restrict__ counts,
+                                                      const float* old /* may be cent */, float* cent) {
   const int n = s.C * s.Dm, i = blockIdx.x * 256 + threadIdx.x, c = i / s.Dm;
   const size_t uj = blockIdx.y;
   const bool live = i < n;
-  unsigned long long tot = 0ull;
-  unsigned k = 0u;
-  if (sets == 1) {
-    if (live) {
-      tot = sums[uj * n + i];
-      k = counts[uj * s.C + c];
-    }
-    __syncthreads();
-    if (k) {
-      sums[uj * n + i] = 0ull;
-      if (i % s.Dm == 0) counts[uj * s.C + c] = 0u;
-    }
-  } else if (live) {
-    unsigned long long v[kSumSets];
-    unsigned m[kSumSets];
-#pragma unroll
-    for (int x = 0; x < kSumSets; ++x) {
-      v[x] = 0ull;
-      m[x] = 0u;
-      if (x < sets) {  // uniform
-        v[x] = sums[(uj * sets + x) * n + i];
-        m[x] = counts[(uj * sets + x) * s.C + c];
-      }
-    }
-    PQC_LOADS_ISSUED();
-#pragma unroll
-    for (int x = 0; x < kSumSets; ++x) {
-      tot += v[x];
-      k += m[x];
-    }
+  const unsigned k = live ? counts[uj * s.C + c] : 0u;
+  const unsigned long long v = live ? sums[uj * n + i] : 0ull;
+  const float o = live ? old[uj * n + i] : 0.0f;
+  __syncthreads();
+  if (!live) return;
+  cent[uj * n + i] = k ? fixed_mean(v, k) : o;
+  if (k) {
+    sums[uj * n + i] = 0ull;
+    if (i % s.Dm == 0) counts[uj * s.C + c] = 0u;
   }
-  if (k) cent[uj * n + i] = fixed_mean(tot, k);
 }
 
 // ------------------------------------------------------------ block statistics

@@ -334,6 +334,36 @@ def test_build_in_the_smallest_workspace_at_several_lengths(pqc, dtype, m, c, un
         assert torch.equal(cent, want_cent) and torch.equal(codes, want_codes), n
 
 
+# Rounds that take the means of the round in front themselves (sums in three places in turn, centroids in two) against a launch for
+# the means after each round, which the smallest workspace asks for: the same bits after any number of rounds.
+@pytest.mark.parametrize("dtype,m,c,n,units", [("bf16", 2, 64, 1031, 1), ("bf16", 4, 256, 5003, 1), ("bf16", 2, 50, 40009, 2), ("bf16", 1, 64, 9001, 3),
+                                               ("bf16", 8, 20, 3001, 2), ("f32", 2, 64, 2048, 1), ("f32", 4, 33, 70001, 2)])
+def test_linked_rounds(pqc, dtype, m, c, n, units):
+    import ctypes
+    lib = pqc.load()
+    w = wl.Workload(name="round", batch=units, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=n, pq_m=m, pq_centroids=c,
+                    topk=n // 4, n_init=0, n_local=0, dtype=dtype, kmeans_iters=3, recipe="plain")
+    cfg = ctypes.byref(pqc.make_config(w))
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(n)
+    keys = torch.randn((units, 1, n, 128), generator=gen, device=DEV, dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    init = torch.from_numpy(wl.kmeans_init_indices(w, seed=3)).to(DEV)
+    init[:, :, :, 1] = init[:, :, :, 0]  # the second of two equal centroids has no members and stays as it is
+    up = lambda b: (b + 255) // 256 * 256
+    least = up(8 * units * m * c * w.sub_dim) + up(4 * units * m * c)
+    for iters in (0, 1, 2, 3, 4, 7):
+        got = []
+        for nbytes in (lib.pqc_pq_build_workspace_bytes(cfg), least):
+            ws = torch.full((nbytes,), 0xa5, dtype=torch.uint8, device=DEV)
+            cent = torch.empty((units, 1, m, c, w.sub_dim), dtype=torch.float32, device=DEV)
+            codes = torch.empty((units, 1, n, m), dtype=torch.uint8, device=DEV)
+            assert lib.pqc_pq_build(cfg, keys.data_ptr(), init.data_ptr(), iters, cent.data_ptr(), codes.data_ptr(), ws.data_ptr(), nbytes,
+                                    torch.cuda.current_stream().cuda_stream) == 0
+            torch.cuda.synchronize()
+            got.append((cent, codes))
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), iters
+
+
 # A build recorded into a HIP graph: every replay starts from its own cleared sums, whatever ran in the workspace in between.
 @pytest.mark.parametrize("dtype,m,c,units", [("bf16", 2, 64, 1), ("bf16", 2, 64, 8), ("bf16", 2, 256, 1), ("f32", 4, 20, 3)])
 def test_recorded_build_replays(pqc, dtype, m, c, units):
