@@ -138,8 +138,8 @@ __device__ __forceinline__ int composite_token(unsigned long long c) {
 
 // Monotone map score -> bin.  Bin 0 takes every score below c0 and is not counted (it holds the middle tokens that no other
 // bin does), kFineBins fine bins cover [c0, c1], kHighBins coarse bins lie above c1: the lower of two lines, a steep one
-// through c0 and c1 and a flatter one from c1 on.  Each line is one fused multiply-add by a non-negative slope, which rounds
-// monotonically, and so do the minimum and the conversion: the map is non-decreasing in s whatever the parameters are.  Only
+// through c0 and c1 and a flatter one from c1 on.  Each line is one fused multiply-add by a positive slope, which rounds
+// monotonically, and so do minimum and conversion: the map is non-decreasing in s, infinities among them.  Only
 // the number of boundary-bin candidates depends on how well [c0, c1] brackets the K-th largest score; the selection itself
 // never does.  (Should the K-th largest score lie below c0, every token of bin 0 becomes a candidate: slow, still exact.)
 // Four instructions a score; the piece chosen by comparison and selections took eleven, and the scan is bound by the
@@ -151,7 +151,8 @@ struct BinMap {
   float ic, b0, ih, b1;  // slope and intercept of the fine and of the coarse line
 };
 __device__ __forceinline__ unsigned score_bin(float s, const BinMap& m) {
-  const float x = fminf(fminf(fmaf(s, m.ic, m.b0), fmaf(s, m.ih, m.b1)), (float)(kNB - 1));
+  // (these minima keep a NaN, which only a score that is one gives)
+  const float x = __builtin_elementwise_minimum(__builtin_elementwise_minimum(fmaf(s, m.ic, m.b0), fmaf(s, m.ih, m.b1)), (float)(kNB - 1));
   unsigned b;
   asm("v_cvt_u32_f32 %0, %1" : "=v"(b) : "v"(x));  // truncates; negative values and NaN give 0 (in C++ they would be undefined)
   return b;
@@ -164,10 +165,14 @@ __device__ __forceinline__ BinMap make_bins(float lo, float hi, float q_lo, floa
     c0 = lo;
     c1 = hi;
   }
+  // An infinite score must not meet a slope of zero or an infinite intercept: the NaN would leave its place to the other line.
+  constexpr float kMost = 3.402823466e38f, kFlat = 1.17549435e-38f;  // largest finite value, smallest normal slope
+  c0 = fmaxf(fminf(c0, kMost), -kMost);
+  c1 = fmaxf(fminf(c1, kMost), -kMost);
   const float wc = c1 - c0, wh = hi - c1;
   BinMap m;
-  m.ic = (wc > 1e-30f && wc < 3e38f) ? (float)kFineBins / wc : 0.0f;
-  m.ih = (wh > 1e-30f && wh < 3e38f) ? fminf((float)kHighBins / wh, m.ic) : 0.0f;  // flatter, so that the lines cross at c1
+  m.ic = (wc > 1e-30f && wc < 3e38f) ? (float)kFineBins / wc : kFlat;
+  m.ih = (wh > 1e-30f && wh < 3e38f) ? fminf((float)kHighBins / wh, m.ic) : kFlat;  // flatter, so that the lines cross at c1
   m.b0 = fmaf(-c0, m.ic, 1.0f);
   m.b1 = fmaf(-c1, m.ih, (float)(1 + kFineBins));
   return m;

@@ -90,3 +90,18 @@ def test_threshold_outside_the_window(pqc, n_tokens, where):
     s32, _ = oracle.scores(p.q, w.dtype, p.centroids, p.codes)
     idx = pqc.PQCache(w, DEV).topk(torch.from_numpy(s32).to(DEV)).cpu().numpy()
     np.testing.assert_array_equal(np.sort(idx, -1), np.sort(oracle.select(s32, w.topk, w.n_init, w.n_local), -1))
+
+
+@pytest.mark.parametrize("low, high", [(0.9, 0.0), (0.3, 0.0), (0.0, 0.02), (0.4, 0.4), (0.5, 0.5), (1.0, 0.0)])
+def test_topk_of_infinite_scores(pqc, low, high):
+    # Masked tokens (-inf) and overflowed ones (+inf), few and many of them: the map from scores to bins keeps their order, also
+    # where the window that the sample puts around the K-th largest score has infinite ends.
+    w = _w(n_tokens=20068, topk=5000)
+    rng = np.random.default_rng(12)
+    s32 = rng.standard_normal((1, 2, w.n_tokens)).astype(np.float32)
+    x = rng.random(s32.shape)
+    s32[x < low] = -np.inf
+    s32[x >= 1.0 - high] = np.inf
+    print(f"[case] infinite scores low={low} high={high}", flush=True)
+    idx = pqc.PQCache(w, DEV).topk(torch.from_numpy(s32).to(DEV)).cpu().numpy()
+    np.testing.assert_array_equal(np.sort(idx, -1), np.sort(oracle.select(s32, w.topk, w.n_init, w.n_local), -1))
