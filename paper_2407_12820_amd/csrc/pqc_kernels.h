@@ -484,6 +484,9 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
   int place[GV];   // (selected, candidates << 16) of the wave in front of the group
   int count = 0;   // the same, of the wave
   const unsigned thr = PAIRS ? 1u : (unsigned)th.bstar;
+  // kPairs: keys below the threshold's become 0, the threshold's 1, higher ones 2 or more, without a selection by comparison (no
+  // score has the lowest key, so that the threshold's is at least 1; nothing lies above the highest)
+  const unsigned pair_base = pth.none ? 0xffffffffu : max(pth.key, 1u) - 1u;
 #pragma unroll
   for (int v = 0; v < GV; ++v) {
     if (v < gpw) {  // uniform
@@ -496,14 +499,21 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
           unsigned st[2];
 #pragma unroll
           for (int y = 0; y < 2; ++y) {
-            const int t = t0 + 2 * k + y;
             const unsigned cw = (wv[k] >> (16 * y)) & 0xffffu;
             const unsigned key =
                 score_key(__fadd_rn(pl.lut[min(cw & 0xffu, (unsigned)kPairC - 1)], pl.lut[kPairC + min(cw >> 8, (unsigned)kPairC - 1)]));
-            const unsigned above = !pth.none && key > pth.key ? 2u : 0u, at = !pth.none && key == pth.key ? 1u : 0u;
-            st[y] = t < s.I || t >= s.N - s.L ? kBinWindow : above | at;
+            st[y] = min(__builtin_elementwise_sub_sat(key, pair_base), 2u);
           }
           wv[k] = st[0] | (st[1] << 16);
+        }
+        if (__any(t0 < s.I || t0 + 8 > s.N - s.L)) {  // uniform, rare
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+              const int t = t0 + 2 * k + y;
+              if (t < s.I || t >= s.N - s.L) wv[k] |= kBinWindow << (16 * y);
+            }
         }
       }
       const int nreal = (v * 64 + lane) * 8 < tpw ? min(8, max(0, s.N - t0)) : 0;  // tokens of this group that exist
