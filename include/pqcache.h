@@ -138,13 +138,15 @@ int pqc_last_hip_error(const pqc_ctx* ctx);
  *   k_cache    [B][Hkv][N][D]        kv_dtype
  *   v_cache    [B][Hkv][N][D]        kv_dtype
  *   out_idx    [B][Hkv][I+K+L]       int32      attended tokens: 0..I-1, then the K
- *                                               retrieved tokens (those above the
- *                                               threshold ascending, then the ones
- *                                               admitted at the threshold best first:
- *                                               compare as a set), then N-L..N-1
+ *                                               retrieved tokens, then N-L..N-1
  *   out_attn   [B][Hq][D]            f32        attention output
  *
  * Codes of tokens inside the initial and local windows are ignored.
+ *
+ * Order of the retrieved tokens: those whose score lies in a bin above that of the K-th largest score, by index, then
+ * the ones of that bin, best first (equal scores: by index).  The bins are 2048 intervals of scores, whose edges follow
+ * in single precision from the score bounds and the scores of 1024 tokens spread evenly over the middle; the order is
+ * the same for equal inputs whichever kernels a length takes, but carries no meaning: compare as a set.
  *
  * The call enqueues kernel launches only (three, two for short caches; before a context's first
  * call, and after a call that failed, one more that clears the workspace) and a completed

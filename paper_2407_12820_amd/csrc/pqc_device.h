@@ -137,44 +137,47 @@ __device__ __forceinline__ int composite_token(unsigned long long c) {
 }
 
 // Monotone map score -> bin.  Bin 0 takes every score below c0 and is not counted (it holds the middle tokens that no other
-// bin does), kFineBins fine bins cover [c0, c1], kHighBins coarse bins lie above c1: the lower of two lines, a steep one
-// through c0 and c1 and a flatter one from c1 on.  Each line is one fused multiply-add by a positive slope, which rounds
-// monotonically, and so do minimum and conversion: the map is non-decreasing in s, infinities among them.  Only
-// the number of boundary-bin candidates depends on how well [c0, c1] brackets the K-th largest score; the selection itself
-// never does.  (Should the K-th largest score lie below c0, every token of bin 0 becomes a candidate: slow, still exact.)
-// Four instructions a score; the piece chosen by comparison and selections took eleven, and the scan is bound by the
-// compute unit's instruction rate (128K tokens x 32 units, 4 partitions: 4.0 us of a histogram workgroup, now 2.6).
+// bin does), kFineBins fine bins cover [c0, c1], kHighBins coarse bins lie above c1.  Inside a piece, subtraction, multiplication
+// by a non-negative constant and rounding down preserve order.  Only the number of boundary-bin candidates depends on how well
+// [c0, c1] brackets the K-th largest score; which tokens are selected never does.  (Should the K-th largest score lie below c0,
+// every token of bin 0 becomes a candidate: slow, still exact.)  The order of the retrieved tokens does depend on the edges of the
+// threshold bin (its members come last, best first), and so on how (s - c0) * ic rounds: another form of the map (a fused
+// multiply-add s * ic + b, for one, which is four instructions instead of eleven) selects the same tokens and puts some in another
+// place.  A layer of 8 heads x 32768 tokens, 2x64: 26.7 us, 26.4 with the fused form; 8 x 131072 35.8 and 35.6; 32 x 131072, 4x256, 76.6
+// both.
 constexpr int kHighBins = 256;
 constexpr unsigned kBinWindow = 0xffffu;  // stored bin of a window token: above every threshold
 constexpr int kFineBins = kNB - 1 - kHighBins;
 struct BinMap {
-  float ic, b0, ih, b1;  // slope and intercept of the fine and of the coarse line
+  float c0, ic, c1, nih;  // start and slope of the fine piece, start and slope (negated) of the coarse piece
 };
+// Both pieces are computed and added, each clamped to its own bins, without comparisons and selections: a score above c1 fills the
+// fine piece, one up to c1 adds nothing of the coarse one.
 __device__ __forceinline__ unsigned score_bin(float s, const BinMap& m) {
-  // (these minima keep a NaN, which only a score that is one gives)
-  const float x = __builtin_elementwise_minimum(__builtin_elementwise_minimum(fmaf(s, m.ic, m.b0), fmaf(s, m.ih, m.b1)), (float)(kNB - 1));
-  unsigned b;
-  asm("v_cvt_u32_f32 %0, %1" : "=v"(b) : "v"(x));  // truncates; negative values and NaN give 0 (in C++ they would be undefined)
-  return b;
+  const float y = (s - m.c0) * m.ic, down = m.c1 - s, z = down * m.nih;
+  int fine;
+  unsigned high;  // (these conversions saturate; in C++ they would be undefined for values out of range and NaN)
+  asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(fine) : "v"(y));  // rounds down: negative below c0
+  asm("v_cvt_u32_f32 %0, %1" : "=v"(high) : "v"(z));      // truncates; negative values and NaN give 0
+  fine = max(-1, min(fine, kFineBins - 1));
+  high = min(high, (unsigned)(kHighBins - 1));
+  return (unsigned)fine + high + 1u + (__float_as_uint(down) >> 31);  // the last: 1 above c1
 }
 // Bin layout from bounds lo <= score <= hi and a window [q_lo, q_hi] expected to hold
 // the K-th largest score.
 __device__ __forceinline__ BinMap make_bins(float lo, float hi, float q_lo, float q_hi) {
-  float c0 = fmaxf(lo, q_lo), c1 = fminf(hi, q_hi);
-  if (!(c1 > c0)) {  // degenerate window: the fine piece over everything
-    c0 = lo;
-    c1 = hi;
-  }
-  // An infinite score must not meet a slope of zero or an infinite intercept: the NaN would leave its place to the other line.
-  constexpr float kMost = 3.402823466e38f, kFlat = 1.17549435e-38f;  // largest finite value, smallest normal slope
-  c0 = fmaxf(fminf(c0, kMost), -kMost);
-  c1 = fmaxf(fminf(c1, kMost), -kMost);
-  const float wc = c1 - c0, wh = hi - c1;
   BinMap m;
-  m.ic = (wc > 1e-30f && wc < 3e38f) ? (float)kFineBins / wc : kFlat;
-  m.ih = (wh > 1e-30f && wh < 3e38f) ? fminf((float)kHighBins / wh, m.ic) : kFlat;  // flatter, so that the lines cross at c1
-  m.b0 = fmaf(-c0, m.ic, 1.0f);
-  m.b1 = fmaf(-c1, m.ih, (float)(1 + kFineBins));
+  m.c0 = fmaxf(lo, q_lo);
+  m.c1 = fminf(hi, q_hi);
+  if (!(m.c1 > m.c0)) {  // degenerate window: the fine piece over everything
+    m.c0 = lo;
+    m.c1 = hi;
+  }
+  // Where a bound is infinite (or the spread is below 1e-28) one of the pieces is a single bin.  For the fine one the slope is not a
+  // number: then all products are none, infinite scores' among them, and whatever the conversion makes of that is the same for all.
+  const float wc = m.c1 - m.c0, wh = hi - m.c1;
+  m.ic = (wc > 1e-30f && wc < 3e38f) ? (float)kFineBins / wc : __builtin_nanf("");
+  m.nih = (wh > 1e-30f && wh < 3e38f) ? -((float)kHighBins / wh) : 0.0f;
   return m;
 }
 
@@ -549,8 +552,8 @@ __device__ __forceinline__ BinMap sample_window(float lo, float hi, const float 
   __syncthreads();
   const int b_hi = sm[0], b_lo = sm[1];
   const float wu = width * (1.0f / (float)NBS);
-  const float q_hi = b_hi >= 0 ? lo + (float)(b_hi + 1) * wu : hi;
-  const float q_lo = b_lo >= 0 ? lo + (float)b_lo * wu : lo;
+  const float q_hi = b_hi >= 0 ? fmaf((float)(b_hi + 1), wu, lo) : hi;
+  const float q_lo = b_lo >= 0 ? fmaf((float)b_lo, wu, lo) : lo;
   return make_bins(lo, hi, q_lo, q_hi);
 }
 
