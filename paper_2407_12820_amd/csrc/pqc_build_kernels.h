@@ -231,8 +231,7 @@ __device__ __forceinline__ void turn_left(unsigned (&v)[4], int n) {
 }
 
 // if (low < best) { best = low; index = c; kept = v; }
-// Moves under a narrowed execution mask, about 2.5 cycles each.  (Selections by VCC stall when they follow one another, about 20
-// cycles each from the second on, whatever scalar instructions lie between them; with the mask in another register they take 4.4.)
+// Moves under a narrowed execution mask; selections by VCC that follow one another take longer (pq_round_mfma_kernel: KEEP).
 __device__ __forceinline__ void keep_lower(float& best, int& index, f32x4_t& kept, float low, int c, const f32x4_t& v) {
   unsigned long long mask;
   float k0 = kept[0], k1 = kept[1], k2 = kept[2], k3 = kept[3];
@@ -253,9 +252,14 @@ __device__ __forceinline__ void keep_lower(float& best, int& index, f32x4_t& kep
 
 // bf16 keys and sub-vectors of 32, 64 or 128 dimensions: the assignment is a dense contraction (tokens x dimensions by
 // dimensions x centroids) and runs on the matrix cores.  The nearest centroid minimises |c|^2 - 2 x.c.  Keys are bf16
-// already; an fp32 centroid, times -2, is split into three bf16 terms that add up to it exactly, so the products are exact and
-// only the fp32 accumulation, which starts from |c|^2, rounds (assignments that differ from 64-bit arithmetic: 8 of 14.7 million
-// tokens and partitions, 9 with |c|^2 - 2 (x.c) computed from a finished product).  Per wave: TT tiles of 16 tokens as the B operand (kept in registers), 16-centroid
+// already; an fp32 centroid is split into three bf16 terms that add up to it exactly, so the products are exact and
+// only the fp32 accumulation rounds.  With 64 and 128 dimensions the terms are those of -2c and the accumulation starts from |c|^2;
+// with 32 the finished product is taken from |c|^2 / 2.  Why the line lies there: with one product per term, starting from |c|^2
+// rounds three times at that size instead of twice, with more it takes the partial sums down instead of up.  Sum over all
+// tokens and partitions of (squared distance of the assigned centroid - that of the nearest), 64-bit, 8 heads x 131072 tokens
+// ~N(0,1) + N(0,4) per channel, ten draws, 256 centroids, taken from the finished product against started from |c|^2: 32
+// dimensions 2.60e-2 and 2.77e-2; 64 dimensions 7.6e-2 and 4.7e-2; 128 dimensions 2.1e-1 and 9.7e-2.
+// Per wave: TT tiles of 16 tokens as the B operand (kept in registers), 16-centroid
 // tiles as the A operand (from LDS), D[centroid 4*quad+i][token col]: a lane keeps the best of its four centroid rows
 // for one token per tile, so that the index costs one register per tile and only the four quads are merged at the end
 // (with the operands the other way round, sixteen columns of four tokens each had to be merged).
@@ -267,9 +271,10 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
   constexpr int NT = 1024, NW = NT / 64, KK = DM / 32, RS = mfma_term_stride(DM);
   // With short sub-vectors the comparisons take about as long as the matrix products and do not hide behind them: the four scores
   // of the best tile are kept (9 instructions for four scores instead of 12) and which of them it was is found at the end.  64 heads
-  // x 32768 tokens, 4x256, assignment: 330 us, 440 with selections by VCC; the products alone take 230 us at the clock that the card
-  // holds under them (2.1 GHz).  With longer sub-vectors the registers hold keys.
+  // x 32768 tokens, 4x256, assignment: 364 us, 387 with selections by VCC (327 started from |c|^2, see above).  With longer
+  // sub-vectors the registers hold keys.
   constexpr bool KEEP = DM == 32;
+  constexpr bool FROM_NORM = DM > 32;
   // The form for short ranges has few waves and is bound by latency: the products of its two tiles are under way together, and the
   // compiler may place selections between them (4 heads x 8564 tokens, 4x64: 12.2 us a round, 12.6 with keep_lower).
   constexpr bool SHORT = TT == 2;
@@ -290,12 +295,12 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
   const int lane = tid & 63, w = tid >> 6, col = lane & 15, quad = lane >> 4;
   const int t_begin = p * r.tokens, t_end = min(s.N, t_begin + r.tokens);
   const bool one_group = DM <= 64 || s.C <= r.staged;  // then the centroids are staged once (256 of 64 dimensions fit)
-  // four values of a staged centroid, times -2, as three bf16 terms that add up to each exactly, and its squared norm from the DM / 4
-  // lanes that hold its values
+  // four values of a staged centroid (FROM_NORM: times -2) as three bf16 terms that add up to each exactly, and its squared norm (or
+  // half of it) from the DM / 4 lanes that hold its values
   auto put = [&](int i, const f32x4_t& v) {
     typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
     const int row = i / DM, e = i % DM;
-    f32x4_t left = -2.0f * v;
+    f32x4_t left = FROM_NORM ? -2.0f * v : v;
 #pragma unroll
     for (int term = 0; term < 3; ++term) {
       const bf16x4_t b = __builtin_convertvector(left, bf16x4_t);
@@ -303,12 +308,20 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
       __builtin_memcpy(&ct[(term * rows + row) * RS + e], &b, 8);
     }
     float n2 = fmaf(v[3], v[3], fmaf(v[2], v[2], fmaf(v[1], v[1], v[0] * v[0])));
-    n2 += dpp_f<0xB1>(0.0f, n2);
-    n2 += dpp_f<0x4E>(0.0f, n2);
-    n2 += dpp_f<0x141>(0.0f, n2);
-    if constexpr (DM >= 64) n2 += dpp_f<0x140>(0.0f, n2);
-    if constexpr (DM >= 128) n2 += __shfl_xor(n2, 16);
-    if (e == 0) cn[row] = n2;
+    if constexpr (DM == 32) {  // eight values in one chain, the sums of the chains in pairs
+      const float before = dpp_f<0x111>(0.0f, n2);
+      n2 = fmaf(v[3], v[3], fmaf(v[2], v[2], fmaf(v[1], v[1], fmaf(v[0], v[0], before))));  // (in every second lane)
+      n2 += dpp_f<0x112>(0.0f, n2);
+      n2 += dpp_f<0x114>(0.0f, n2);
+      if (e == DM - 4) cn[row] = 0.5f * n2;
+    } else {
+      n2 += dpp_f<0xB1>(0.0f, n2);
+      n2 += dpp_f<0x4E>(0.0f, n2);
+      n2 += dpp_f<0x141>(0.0f, n2);
+      n2 += dpp_f<0x140>(0.0f, n2);
+      if constexpr (DM >= 128) n2 += __shfl_xor(n2, 16);
+      if (e == 0) cn[row] = n2;
+    }
   };
   auto pad = [&](int nc) {  // rows that hold no centroid lose always (and zero, so that no stale bits of LDS reach the products)
     for (int i = tid; i < (rows - nc) * DM; i += NT) {
@@ -391,10 +404,16 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
 #pragma unroll
           for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
-            for (int term = 2; term >= 0; --term)  // small terms first
+            for (int term = 2; term >= 0; --term)  // small terms first: from zero they are added up among themselves
 #pragma unroll
               for (int g = 0; g < GANG; ++g)
-                acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[term][kk], x[t0 + g][kk], kk == 0 && term == 2 ? cnv : acc[g], 0, 0, 0);
+                acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[term][kk], x[t0 + g][kk],
+                                                                  kk || term < 2 ? acc[g] : FROM_NORM ? cnv : f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+          if constexpr (!FROM_NORM)
+#pragma unroll
+            for (int g = 0; g < GANG; ++g)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) acc[g][i] = cnv[i] - acc[g][i];
           // strict comparisons: an earlier (lower) centroid of this lane keeps a tie
 #pragma unroll
           for (int g = 0; g < GANG; ++g) {

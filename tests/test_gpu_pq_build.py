@@ -608,3 +608,60 @@ def test_block_cache_refresh_matches_oracle(pqc, policy, n_slots, k_cache, block
         np.testing.assert_array_equal(stats.cpu().numpy(), want_stats, err_msg=f"step {step}: stats")
     if k_cache and n_slots >= 4:
         assert want_stats[..., 0].min() > 0  # the hot tokens do get hits
+
+
+# The nearest centroid by |c|^2 - 2 x.c with sub-vectors of 32 dimensions: x.c is a finished sum before |c|^2 = 1.5 * 2^24 (of which
+# the last bit is 2) comes in.  Three bf16 terms of a centroid contribute -0.9 each, which added one by one to |c|^2 are lost, or
+# taken for -2 each, whichever way the sum is rounded; together they are -2.7.  Against them a centroid at |c|^2 and one at |c|^2 - 4.
+@pytest.mark.parametrize("n", [40, 9001, 70000])  # ranges of a few tokens, of two tiles per wave, of eight
+@pytest.mark.parametrize("rival", [0.0, 4.0])
+def test_products_are_summed_before_the_norm(pqc, n, rival):
+    C, M = 20, 4
+    w = wl.Workload(name="sum", batch=1, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=n, pq_m=M, pq_centroids=C, topk=0, n_init=1,
+                    n_local=0, dtype="bf16", kmeans_iters=1, recipe="plain")
+    x = np.zeros(32, np.float32)
+    x[1], x[2], x[3] = 28.75, 14720.0, 14720.0
+    x[4], x[5], x[8] = 7536640.0, 7536640.0, 128.0
+    near, other = np.zeros(32, np.float32), np.zeros(32, np.float32)
+    near[[0, 6, 7]] = other[[0, 6, 7]] = 4096.0, 2048.0, 2048.0  # |c|^2 = 1.5 * 2^24
+    near[1] = 2.0 ** -6
+    near[2], near[3] = 2.0 ** -6 + 2.0 ** -15, -(2.0 ** -6)                              # differ in the second term
+    near[4], near[5] = 2.0 ** -6 + 2.0 ** -15 + 2.0 ** -24, -(2.0 ** -6 + 2.0 ** -15)    # differ in the third term
+    other[8] = rival / 256.0
+    assert np.array_equal(wl.to_f32(wl.f32_to_bf16_bits(x), "bf16"), x)
+    d = [(c.astype(np.float64) ** 2).sum() - 2.0 * (x.astype(np.float64) * c).sum() for c in (other, near)]
+    assert abs(d[0] - 1.5 * 2 ** 24 + rival) < 0.1 and abs(d[1] - 1.5 * 2 ** 24 + 2.7) < 0.1
+    cent = np.zeros((1, 1, M, C, 32), np.float32)
+    cent[..., 0] = 8192.0  # far
+    cent[..., 3, :], cent[..., 11, :] = other, near
+    keys = torch.from_numpy(np.tile(x, M)).to(DEV).to(torch.bfloat16).repeat(1, 1, n, 1).contiguous()
+    codes = pqc.pq_assign(w, keys, torch.from_numpy(cent).to(DEV))
+    assert torch.equal(codes, torch.full_like(codes, 11 if rival == 0.0 else 3))
+
+
+# Assignments against 64-bit arithmetic, keys with the channel means that real caches have: the squared distances of the assigned and
+# of the nearest centroid differ by no more than the errors of their two scores, each (3 products per 32 dimensions + 1) roundings
+# of at most 2^-23 of the numbers that are added, |c|^2 + 2 |x|.|c|.
+@pytest.mark.parametrize("m,c,n", [(4, 256, 30000), (4, 64, 2000), (2, 64, 30000), (2, 256, 1000), (1, 64, 30000), (1, 256, 3000)])
+def test_assignments_are_nearest_to_rounding(pqc, m, c, n):
+    H, dm = 8, 128 // m
+    w = wl.Workload(name="near", batch=1, n_q_heads=H, n_kv_heads=H, head_dim=128, n_tokens=n, pq_m=m, pq_centroids=c, topk=0, n_init=1,
+                    n_local=0, dtype="bf16", kmeans_iters=2, recipe="plain")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(n + c)
+    randn = lambda *s: torch.randn(s, generator=gen, device=DEV)
+    keys = (randn(1, H, n, 128) + 4.0 * randn(1, H, 1, 128)).to(torch.bfloat16)
+    cent, codes = pqc.pq_build(w, keys, torch.from_numpy(wl.kmeans_init_indices(w, seed=1)).to(DEV))
+    off = 0
+    for h in range(H):
+        for j in range(m):
+            x, ce = keys[0, h, :, j * dm:(j + 1) * dm].double().contiguous(), cent[0, h, j].double()
+            score = ce.square().sum(-1) - 2.0 * torch.mm(x, ce.t().contiguous())
+            size = ce.square().sum(-1) + 2.0 * torch.mm(x.abs(), ce.abs().t().contiguous())
+            best, at = score.min(-1)
+            got = codes[0, h, :, j].long().unsqueeze(1)
+            bound = (3 * dm // 32 + 1) * 2.0 ** -23 * (size.gather(1, got) + size.gather(1, at.unsqueeze(1))).squeeze(1)
+            excess = score.gather(1, got).squeeze(1) - best
+            off += int((excess > 0).sum())
+            assert bool((excess <= bound).all())
+    print(f"[case] {m}x{c} n={n}: {off} of {H * m * n} not the nearest", flush=True)
