@@ -95,13 +95,29 @@ void lay_out(Plan* p, size_t bins_per_unit, size_t stage_words_per_unit, size_t 
   p->total = off;
 }
 
-// Whether a step of this shape is quicker without the histogram kernel (From::kShort in pqc_kernels.h): a launch saved, about 4.5 us,
-// against scoring all N tokens in every workgroup, M look-ups a token.  Measured, us per layer without and with it (bf16, 4 query
-// heads per KV head unless said): 8 heads of 8192 tokens 2x64 19.4, 16.8; 16384 20.4, 18.5; 24576 22.0, 21.0; 32768 23.0, 23.1; 4x64 of
-// 12000 21.2, 19.8; three sequences of 20011 with 4 heads, fp32, 22.2, 22.9.  More than 64 centroids (half the threads build twice as
-// much of the table): 4x256 of 8192 20.9, 19.6; 16384 21.5, 22.1; 64 heads of 16384 32.6, 32.1.
+// Whether a step of this shape is quicker without the histogram kernel (From::kShort in pqc_kernels.h): a launch saved against
+// scoring all N tokens in every workgroup, M look-ups a token.  Measured on layers of their own K/V, centroids and codes in turn (4 to
+// 32 of them, over 1.5 GB), us per layer with and without the histogram kernel, bf16, 4 query heads per unit, a tenth retrieved:
+//   tokens        2048         8192         12288        16384        24576      (2x64)
+//   1 unit        18.3, 15.8   19.1, 16.9   19.2, 17.6   19.3, 18.3   19.6, 20.2
+//   8 units       20.0, 16.6   20.3, 17.5   20.6, 18.6   21.0, 19.9   22.6, 22.0
+//   64 units      22.0, 18.4   26.2, 22.4   29.6, 25.9   30.6, 28.9   39.9, 38.9
+//   1 unit        18.4, 15.9   19.1, 17.3   19.2, 18.7   19.3, 19.7   19.5, 22.1  (4x64)
+//   8 units       19.9, 16.5   20.3, 18.0   20.5, 19.7   20.9, 20.9   22.7, 23.8
+//   1 unit        20.7, 18.3   20.7, 19.7   20.8, 21.0   21.1, 22.0   21.2, 24.3  (4x256)
+//   8 units       21.5, 18.7   22.1, 20.5   22.8, 22.5   23.0, 23.6   24.5, 26.4
+// One query head per unit and a twentieth retrieved leave the least to hide behind: 1 unit of 18432 (2x64) 18.2, 18.2; 8 units of 22528
+// 19.6, 19.7, of 24576 19.9, 20.2; 7 units of 12288 (4x64) 18.3, 18.5.  Beyond one workgroup per compute unit those of a unit scan it
+// one after the other: 96 units of 20000 47.2, 57.4; with as many workgroups as compute units and much to attend, two smaller
+// ones per unit hide each other's latency: a fifth retrieved, 240 units of 8192 76.8, 78.6, 120 of 12288 61.4, 62.4, 80 of 22528 64.2,
+// 65.7, but a tenth retrieved 61.2, 58.2, 46.9, 44.1 and 47.0, 44.6.
 bool short_cache(const Shape& s) {
-  return (s.M == 2 || s.M == 4) && (long long)s.N * s.M <= (s.C <= 64 ? 49152 : 32768);
+  if (s.M != 2 && s.M != 4) return false;
+  const long long units = (long long)s.B * s.Hkv, blocks = units * ((s.N + 8191) / 8192);
+  const long long few = s.M == 2 ? 32768 : 45056, many = s.M == 2 ? 45056 : 49152;
+  if ((long long)s.N * s.M > (s.C > 64 ? 32768 : units < 8 ? few : many)) return false;
+  if (s.N > 8192 && blocks > 256) return false;
+  return s.N < 8192 || blocks < 208 || 6ll * s.K < s.N;
 }
 
 // The launch plan of a configuration; `general`: for calls other than the decode step, which have no short form.

@@ -1,6 +1,7 @@
 """GPU parity of decode steps without a histogram kernel (short caches) at the edges of its tiles and of the rule that chooses
 it, and of thresholds outside the sampled window on both forms, against the CPU oracle: index sets equal, attention within the
-tolerance of tests/parity_utils.py."""
+tolerance of tests/parity_utils.py.  Which lengths take it is counted in the launches of a recorded step."""
+import ctypes
 import dataclasses
 
 import numpy as np
@@ -50,9 +51,13 @@ def _decode_and_check(pqc, p):
 @pytest.mark.parametrize("kw", [
     dict(n_tokens=513, topk=60),                                                    # a workgroup with one token
     dict(n_tokens=16385, topk=1600, n_q_heads=2, n_kv_heads=1),                     # one chunk beyond a step of the scan
-    dict(n_tokens=24576, topk=2400),                                                # the last short length, 2 x 64
-    dict(n_tokens=24577, topk=2400),                                                # and the first with a histogram kernel
-    dict(n_tokens=12288, topk=1200, pq_m=4, n_q_heads=16),                          # the same, 4 x 64; G = 8
+    dict(n_tokens=16384, topk=1600),                                                # the last short length of a few units, 2 x 64
+    dict(n_tokens=22528, topk=2250, batch=4),                                       # of more units
+    dict(n_tokens=24576, topk=2400),
+    dict(n_tokens=24577, topk=2400),
+    dict(n_tokens=11264, topk=1100, pq_m=4, n_q_heads=4),                           # the last short length of a few units, 4 x 64
+    dict(n_tokens=12288, topk=1200, pq_m=4, n_q_heads=8, n_kv_heads=8),             # of more units
+    dict(n_tokens=12288, topk=1200, pq_m=4, n_q_heads=16),                          # G = 8
     dict(n_tokens=12289, topk=1200, pq_m=4, n_q_heads=2, dtype="f32"),
     dict(n_tokens=8192, topk=800, pq_m=4, pq_centroids=256),                        # 4 x 256
     dict(n_tokens=8191, topk=800, pq_m=4, pq_centroids=129, n_q_heads=2, dtype="f32"),
@@ -105,3 +110,80 @@ def test_topk_of_infinite_scores(pqc, low, high):
     print(f"[case] infinite scores low={low} high={high}", flush=True)
     idx = pqc.PQCache(w, DEV).topk(torch.from_numpy(s32).to(DEV)).cpu().numpy()
     np.testing.assert_array_equal(np.sort(idx, -1), np.sort(oracle.select(s32, w.topk, w.n_init, w.n_local), -1))
+
+
+def _launches(call):
+    """Kernel launches that `call` makes, counted in a recorded graph (which is not run)."""
+    from paper_2407_12820_amd import binding
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream(device=DEV)):
+        call()
+    n = ctypes.c_size_t(0)
+    get = binding.load().hipGraphGetNodes  # of the HIP runtime that the library is linked to
+    get.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
+    assert get(graph.raw_cuda_graph(), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("units, n_tokens, m, c, den, launches", [
+    (1, 16384, 2, 64, 10, 2), (1, 16385, 2, 64, 10, 3), (7, 16385, 2, 48, 10, 3), (8, 16385, 2, 64, 10, 2), (1, 24576, 2, 64, 10, 3),
+    (8, 22528, 2, 64, 10, 2), (8, 22529, 2, 64, 10, 3), (1, 11264, 4, 64, 10, 2), (1, 11265, 4, 64, 10, 3), (8, 12288, 4, 64, 10, 2),
+    (8, 12289, 4, 64, 10, 3), (1, 8192, 4, 256, 10, 2), (1, 8193, 4, 256, 10, 3), (1, 16384, 2, 65, 10, 2), (1, 16385, 2, 256, 10, 3),
+    (8, 2048, 8, 64, 10, 3), (8, 2048, 1, 64, 10, 3), (96, 20000, 2, 64, 20, 3), (80, 20000, 2, 64, 10, 2), (80, 20000, 2, 64, 5, 3),
+    (207, 8192, 2, 64, 5, 2), (208, 8192, 2, 64, 5, 3), (208, 8192, 2, 64, 7, 2), (256, 8191, 2, 64, 5, 2)])
+def test_launches_of_a_step(pqc, units, n_tokens, m, c, den, launches):
+    w = _w(batch=units, n_q_heads=1, n_kv_heads=1, n_tokens=n_tokens, pq_m=m, pq_centroids=c, topk=n_tokens // den)
+    print(f"[case] launches {w}", flush=True)
+    new = lambda shape, dtype: torch.zeros(shape, dtype=dtype, device=DEV)
+    kv = torch.bfloat16
+    k = new((units, 1, n_tokens, 128), kv)
+    args = [new((units, 1, 128), kv), new((units, 1, m, c, 128 // m), torch.float32), new((units, 1, n_tokens, m), torch.uint8), k, k]
+    ctx = pqc.PQCache(w, DEV)
+    outs = ctx.empty_outputs()
+    assert _launches(lambda: ctx.decode(*args, *outs)) == launches
+
+
+# A workspace that holds the plan of every other call but not that of the step without a histogram kernel: the step takes the
+# general form, with the same result.
+@pytest.mark.parametrize("kw", [dict(n_tokens=10755, topk=1000, pq_m=4, batch=16), dict(n_tokens=2147, topk=200, batch=50)])
+def test_smallest_workspace(pqc, kw):
+    lib = pqc.load()
+    w = _w(**kw)
+    p = build_problem(w, seed=6, checked_units=[])
+    cfg = pqc.make_config(w)
+    dev = [pqc.to_device(p.q, w.dtype, DEV), torch.from_numpy(p.centroids).to(DEV), torch.from_numpy(p.codes).to(DEV),
+           pqc.to_device(p.k, w.dtype, DEV), pqc.to_device(p.v, w.dtype, DEV)]
+    got, launches = [], []
+    full = lib.pqc_workspace_bytes(ctypes.byref(cfg))
+    room = torch.full((full,), 0xa5, dtype=torch.uint8, device=DEV)
+
+    def create(nbytes):
+        h = ctypes.c_void_p()
+        return h if lib.pqc_create(ctypes.byref(h), ctypes.byref(cfg), room.data_ptr(), nbytes) == 0 else None
+
+    least = full
+    while (h := create(least - 256)) is not None:
+        lib.pqc_destroy(h)
+        least -= 256
+    assert least < full
+    for nbytes in (full, least):
+        room.fill_(0xa5)
+        h = create(nbytes)
+        idx = torch.empty((w.batch, w.n_kv_heads, w.n_selected), dtype=torch.int32, device=DEV)
+        out = torch.empty((w.batch, w.n_q_heads, 128), dtype=torch.float32, device=DEV)
+
+        def call():
+            assert lib.pqc_decode(h, *[t.data_ptr() for t in dev], idx.data_ptr(), out.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+
+        launches.append(_launches(call))
+        call()
+        torch.cuda.synchronize()
+        lib.pqc_destroy(h)
+        got.append((idx.cpu().numpy(), out.cpu().numpy()))
+    assert launches == [2, 3]
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    assert check_indices(p, got[1][0], units=list(range(0, w.batch * w.n_kv_heads, 7))) == 0
+    for idx, out in got:
+        assert attn_error(p, idx, out, units=list(range(0, w.batch * w.n_kv_heads, 7))) <= ATTN_TOL[w.dtype]
