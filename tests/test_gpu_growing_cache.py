@@ -63,6 +63,9 @@ def _full_check(p, idx, out):
     (dict(n_tokens=5000, topk=700, pq_m=4, batch=2, pq_centroids=64), 5003),
     (dict(n_tokens=1500, topk=100, pq_m=8, dtype="f32", n_q_heads=2, n_kv_heads=2), 1600),
     (dict(n_tokens=9000, topk=1000, pq_m=1, pq_centroids=256, n_q_heads=8, n_kv_heads=1), 20000),
+    (dict(n_tokens=16999), 17003),                                # with a histogram kernel
+    (dict(n_tokens=17001), 17008),
+    (dict(n_tokens=12001, topk=700, pq_m=4, pq_centroids=64), 12003),
 ])
 def test_decode_inside_larger_buffers(pqc, kw, cap):
     w = _workload(**kw)
@@ -118,12 +121,16 @@ def test_pq_build_inside_larger_buffers(pqc):
 
 
 @pytest.mark.parametrize("fused", [False, True], ids=["separate", "fused"])
-@pytest.mark.parametrize("kw", [dict(), dict(pq_m=4, pq_centroids=64, batch=2, n_q_heads=8, n_kv_heads=1),
-                                dict(pq_m=8, pq_centroids=200, dtype="f32", n_q_heads=2, n_kv_heads=2)])
-def test_decode_loop_with_a_growing_cache(pqc, kw, fused):
+@pytest.mark.parametrize("kw,n0", [(dict(), 1990), (dict(pq_m=4, pq_centroids=64, batch=2, n_q_heads=8, n_kv_heads=1), 1990),
+                                   (dict(pq_m=8, pq_centroids=200, dtype="f32", n_q_heads=2, n_kv_heads=2), 1990),
+                                   # with a histogram kernel, and into the lengths that have one (16385 and 11265 tokens on)
+                                   (dict(), 17006), (dict(pq_m=4, pq_centroids=64), 12006), (dict(), 16374),
+                                   (dict(pq_m=4, pq_centroids=64, n_kv_heads=1), 11254)])
+def test_decode_loop_with_a_growing_cache(pqc, kw, n0, fused):
     # 20 decode steps: append the token's K/V, give it its code, count its code pair, lengthen the context,
-    # decode (both entry points where the second applies), each step against the oracle on the dense prefix
-    steps, n0, cap = 20, 1990, 2016
+    # decode (both entry points where the second applies), each step against the oracle on the dense prefix;
+    # then back to the length of the first step
+    steps, cap = 20, n0 + 26
     w_cap = _workload(n_tokens=cap, n_local=16, kmeans_iters=3, **kw)
     print(f"[case] growing cache {w_cap}", flush=True)
     d = wl.generate(w_cap, seed=23)
@@ -188,27 +195,33 @@ def test_decode_loop_with_a_growing_cache(pqc, kw, fused):
             np.testing.assert_array_equal(np.sort(idx2.cpu().numpy(), -1), np.sort(idx.cpu().numpy(), -1), err_msg=f"step {step}")
             _full_check(p, idx2.cpu().numpy(), out2.cpu().numpy())
     assert n == n0 + steps
+    ctx.set_length(n0 + 1, (n0 + 1) // 10)
+    idx, out = ctx.decode(q_dev, cent_dev, codes_dev, k_dev, v_dev)
+    torch.cuda.synchronize()
+    p = Problem(ctx.w, q, d["k"][:, :, :n0 + 1], d["v"][:, :, :n0 + 1], cent, codes_h[:, :, :n0 + 1], units)
+    _full_check(p, idx.cpu().numpy(), out.cpu().numpy())
     with pytest.raises(pqc.PQCacheError, match="PQC_EINVAL"):
         ctx.set_length(cap + 1, 10)
 
 
-def test_decode_append_rejects_a_position_the_step_reads(pqc):
-    w = _workload()
+@pytest.mark.parametrize("n_tokens,cap", [(3000, 3008), (17000, 17008)])  # without and with a histogram kernel
+def test_decode_append_rejects_a_position_the_step_reads(pqc, n_tokens, cap):
+    w = _workload(n_tokens=n_tokens)
     p = build_problem(w, seed=21)
-    dev = _upload_padded(pqc, p, 3008)
-    ctx = pqc.PQCache(w, DEV, capacity=3008)
+    dev = _upload_padded(pqc, p, cap)
+    ctx = pqc.PQCache(w, DEV, capacity=cap)
     key = dev["k"][:, :, 0].contiguous()
-    for bad in (-1, w.n_init, 1500, w.n_tokens - w.n_local - 1, 3008):
+    for bad in (-1, w.n_init, 1500, w.n_tokens - w.n_local - 1, cap):
         with pytest.raises(pqc.PQCacheError, match="PQC_EINVAL"):
             ctx.decode_append(dev["q"], dev["centroids"], dev["codes"], dev["k"], dev["v"], key, bad)
-    for ok in (0, w.n_init - 1, w.n_tokens - w.n_local, w.n_tokens - 1, w.n_tokens, 3007):
+    for ok in (0, w.n_init - 1, w.n_tokens - w.n_local, w.n_tokens - 1, w.n_tokens, cap - 1):
         before = dev["codes"].clone()
         idx, out = ctx.decode_append(dev["q"], dev["centroids"], dev["codes"], dev["k"], dev["v"], key, ok)
         torch.cuda.synchronize()
         _full_check(p, idx.cpu().numpy(), out.cpu().numpy())
         want = oracle.nearest_codes(np.ascontiguousarray(p.k[:, :, 0]), w.dtype, p.centroids)
         np.testing.assert_array_equal(dev["codes"][:, :, ok].cpu().numpy(), want)
-        mask = torch.ones(3008, dtype=torch.bool, device=DEV)
+        mask = torch.ones(cap, dtype=torch.bool, device=DEV)
         mask[ok] = False
         assert torch.equal(dev["codes"][:, :, mask], before[:, :, mask])
         dev["codes"].copy_(before)

@@ -174,6 +174,14 @@ def _small(**kw):
     # many units: more than the 256 compute units, a multiple of 8 and not (the last ones are not interleaved over the XCDs)
     dict(batch=40, n_q_heads=16, n_kv_heads=8, n_tokens=600, topk=60),
     dict(batch=37, n_q_heads=6, n_kv_heads=3, n_tokens=777, topk=99, pq_m=4),
+    # with a histogram kernel whatever the number of partitions: windows only, every token, no windows, big tie classes
+    dict(n_tokens=16401, topk=0),
+    dict(n_tokens=16402, topk=16402 - 68, pq_centroids=64),
+    dict(n_tokens=16403, n_init=0, n_local=0, topk=17),
+    dict(n_tokens=11301, topk=0, pq_m=4),
+    dict(n_tokens=11302, topk=11302 - 68, pq_m=4, dtype="f32"),
+    dict(n_tokens=11303, n_init=0, n_local=0, topk=1130, pq_m=4, pq_centroids=2, n_q_heads=16),
+    dict(n_tokens=16500, n_init=500, n_local=9000, topk=100, pq_centroids=3),
     # more select workgroups per unit than the finalize kernel has threads
     dict(n_tokens=140001, topk=9000, n_q_heads=2, n_kv_heads=1, pq_centroids=64),
     dict(n_tokens=200003, topk=30000, n_q_heads=8, n_kv_heads=1, pq_centroids=64),
@@ -196,7 +204,7 @@ def test_maximum_context_length(pqc):
     full_check(p, idx, out)
 
 
-def _random_shapes(n, seed):
+def _random_shapes(n, seed, tokens=(1, 7000)):
     rng = np.random.default_rng(seed)
     out = []
     for _ in range(n):
@@ -204,7 +212,7 @@ def _random_shapes(n, seed):
         hkv = int(rng.choice([1, 2, 3]))
         m = int(rng.choice([1, 2, 4, 8]))
         c = int(rng.choice([2, 5, 16, 64, 200, 256]))
-        n_tok = int(rng.integers(1, 7000))
+        n_tok = int(rng.integers(*tokens))
         n_init = int(rng.integers(0, min(n_tok, 9) + 1))
         n_local = int(rng.integers(0, min(n_tok - n_init, 100) + 1))
         mid = n_tok - n_init - n_local
@@ -226,6 +234,20 @@ def test_random_shapes(pqc, kw):
     p = build_problem(w, seed=21)
     idx, out = run_decode(pqc, p)
     full_check(p, idx, out)
+
+
+@pytest.mark.parametrize("kw", _random_shapes(16, seed=2025, tokens=(16385, 26000)), ids=lambda kw: "-".join(str(v) for v in kw.values()))
+def test_random_shapes_with_a_histogram_kernel(pqc, kw):
+    # the same where two and four partitions have a histogram kernel too; codes need no clustering here
+    w = _small(**kw)
+    print(f"[case] random shape {kw}", flush=True)
+    p = build_problem(w, seed=22, checked_units=[])
+    idx, out = run_decode(pqc, p)
+    every = range(w.batch * w.n_kv_heads)
+    assert check_indices(p, idx, units=every) == 0
+    err = attn_error(p, idx, out, units=every)
+    assert err <= ATTN_TOL[w.dtype], f"attention error {err:.3e}"
+    check_structure(p, idx, out)
 
 
 def test_all_scores_equal_takes_lowest_indices(pqc):
@@ -288,9 +310,10 @@ def test_topk_when_the_sample_misleads(pqc, sample_value):
     np.testing.assert_array_equal(np.sort(got.cpu().numpy(), -1), np.sort(want, -1))
 
 
-def test_context_reuse_and_two_contexts(pqc):
+@pytest.mark.parametrize("na,nb", [(3000, 5000), (17001, 12001), (17001, 5000)])  # without, with, and one each with a histogram kernel
+def test_context_reuse_and_two_contexts(pqc, na, nb):
     # Calls on one context leave the workspace ready for the next call; contexts do not interfere.
-    wa, wb = _small(topk=123), _small(n_tokens=5000, topk=900, pq_m=4)
+    wa, wb = _small(n_tokens=na, topk=123), _small(n_tokens=nb, topk=900, pq_m=4)
     pa1, pa2, pb = build_problem(wa, 5), build_problem(wa, 6), build_problem(wb, 7)
     ca, cb = pqc.PQCache(wa, DEV), pqc.PQCache(wb, DEV)
     for _ in range(2):
@@ -305,9 +328,10 @@ def test_context_reuse_and_two_contexts(pqc):
     full_check(pa2, idx, out)
 
 
-def test_decode_phase_by_phase_equals_decode(pqc):
-    # the profiling entry point launches the same three kernels one at a time
-    w = _small(n_tokens=9000, topk=1200, pq_m=4)
+@pytest.mark.parametrize("n_tokens", [9000, 13001])  # phase 0 has nothing to launch, and leaves a histogram behind
+def test_decode_phase_by_phase_equals_decode(pqc, n_tokens):
+    # the profiling entry point launches the same kernels one at a time
+    w = _small(n_tokens=n_tokens, topk=1200, pq_m=4)
     p = build_problem(w, seed=9)
     dev, ctx = upload(pqc, p), pqc.PQCache(w, DEV)
     a = run_decode(pqc, p, ctx, dev)
@@ -398,8 +422,9 @@ def test_pair_counts_follow_an_appended_code(pqc):
     np.testing.assert_array_equal(full.cpu().numpy(), part.cpu().numpy())
 
 
-def test_decode_is_deterministic(pqc):
-    w = wl.get("llama8b_128k", n_tokens=20011)
+@pytest.mark.parametrize("n_tokens", [20011, 24011])  # without and with a histogram kernel
+def test_decode_is_deterministic(pqc, n_tokens):
+    w = wl.get("llama8b_128k", n_tokens=n_tokens)
     p = build_problem(w, seed=1)
     dev, ctx = upload(pqc, p), pqc.PQCache(w, DEV)
     a = run_decode(pqc, p, ctx, dev)
@@ -408,8 +433,9 @@ def test_decode_is_deterministic(pqc):
     np.testing.assert_array_equal(a[1].view(np.uint32), b[1].view(np.uint32))
 
 
-def test_runs_on_a_side_stream(pqc):
-    w = _small(topk=200)
+@pytest.mark.parametrize("n_tokens", [3000, 17001])  # without and with a histogram kernel
+def test_runs_on_a_side_stream(pqc, n_tokens):
+    w = _small(n_tokens=n_tokens, topk=200)
     p = build_problem(w, seed=8)
     dev, ctx = upload(pqc, p), pqc.PQCache(w, DEV)
     torch.cuda.synchronize()
@@ -419,12 +445,13 @@ def test_runs_on_a_side_stream(pqc):
     full_check(p, idx.cpu().numpy(), out.cpu().numpy())
 
 
+@pytest.mark.parametrize("n_tokens", [9000, 17000])  # without and with a histogram kernel in the general step
 @pytest.mark.parametrize("indexed", [False, True])
-def test_layers_recorded_into_a_hip_graph_replay_correctly(pqc, indexed):
+def test_layers_recorded_into_a_hip_graph_replay_correctly(pqc, indexed, n_tokens):
     # Algorithm 2 loops over the layers: one call per layer on a shared context, recorded once by stream
     # capture, replayed with eager calls on the same context in between.  Every replay must reproduce the
     # eager results bit for bit (a call leaves the workspace as it found it).
-    w = _small(n_tokens=9000, topk=1100)
+    w = _small(n_tokens=n_tokens, topk=1100)
     layers = [build_problem(w, seed=40 + i) for i in range(3)]
     other = build_problem(w, seed=50)
     devs, dev_other, ctx = [upload(pqc, p) for p in layers], upload(pqc, other), pqc.PQCache(w, DEV)
