@@ -84,14 +84,14 @@ void lay_out(Plan* p, size_t bins_per_unit, size_t stage_words_per_unit, size_t 
   p->off_lut = off;   off = align_up(off + sizeof(float) * units * s.M * s.C);
   p->off_range = off; off = align_up(off + sizeof(float2) * units);
   p->off_hist = off;  off = align_up(off + sizeof(unsigned) * units * (kHistCopies * kNB + 1));  // + record counters
+#ifdef PQC_TRACE  // in front of what depends on the length, so that it lies in one place for every plan of a context
+  p->off_trace = off; off = align_up(off + sizeof(unsigned long long) * 3 * kTraceWgs * kTraceSlots);
+#endif
   p->off_bins = off;  off = align_up(off + sizeof(unsigned short) * units * bins_per_unit);
   p->off_crec = off;  off = align_up(off + (size_t)p->rec_stride * units);
   p->off_stage = off; off = align_up(off + sizeof(unsigned long long) * units * stage_words_per_unit);
   p->off_cnt = off;   off = align_up(off + sizeof(int2) * units * counts_per_unit);
   p->off_part = off;  off = align_up(off + sizeof(float) * units * partials_per_unit * s.G * (kD + 2));
-#ifdef PQC_TRACE
-  p->off_trace = off; off = align_up(off + sizeof(unsigned long long) * 3 * kTraceWgs * kTraceSlots);
-#endif
   p->total = off;
 }
 
