@@ -16,6 +16,7 @@ four benchmark shapes (`also`), and the CPU oracle's time for the same step as a
 baseline, with a comparison of the GPU's results against the oracle's for every shape.
 """
 import argparse
+import ctypes
 import hashlib
 import json
 import os
@@ -118,10 +119,25 @@ def main() -> int:
             out.append(ev0.elapsed_time(ev1) / steps * 1e3)
         return np.array(out), issue_ms / (reps * steps), wall_ms / (reps * steps)
 
+    def launches(call):
+        """Kernel launches of one call, counted in a recorded graph."""
+        n = ctypes.c_size_t(0)
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph, stream=torch.cuda.Stream(device=dev)):
+            call(torch.cuda.current_stream(dev).cuda_stream)
+        get_nodes = binding.load().hipGraphGetNodes  # of the HIP runtime that the library is linked to
+        get_nodes.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
+        assert get_nodes(graph.raw_cuda_graph(), None, ctypes.byref(n)) == 0
+        return n.value
+
+    def by_kernel(kern_us):
+        return {n: None if np.isnan(x) else round(float(x), 3) for n, x in zip(KERNELS, kern_us)}
+
     def kernel_times(w, ctx, sets, margs, rounds):
         """Per-kernel durations: each kernel of the path is launched for every input set back to back (one
         context per set) between two HIP events on the launch stream, so that no event sits in front of a
-        timed launch; duration = span / number of launches."""
+        timed launch; duration = span / number of launches.  Not a number for the histogram kernel of a
+        step that has none (short caches)."""
         nk = len(KERNELS)
         kern_us = np.zeros(nk)
         if rounds <= 0:
@@ -137,6 +153,8 @@ def main() -> int:
             torch.cuda.synchronize()
             if rnd >= 2:
                 kern_us += np.array([evs[i].elapsed_time(evs[i + 1]) for i in range(nk)]) * 1e3 / len(sets)
+        if launches(lambda s: ctx.decode_marshalled(margs[0], s)) < nk:
+            kern_us[0] = np.nan
         return kern_us / rounds
 
     def against_oracle(w, ctx, st, host, out_idx, out_attn):
@@ -212,7 +230,7 @@ def main() -> int:
         "achieved_hbm_gbps": round(path_gbps, 1), "hbm_frac": round(path_gbps / HBM_PEAK_GBPS, 4),
         "algorithmic_bytes_per_step": path_bytes, "host_wall_ms_per_step": round(wall_ms, 6),
         "host_issue_ms_per_step": round(issue_ms, 6),
-        "kernel_us": {n: round(float(x), 3) for n, x in zip(KERNELS, kern_us)},
+        "kernel_us": by_kernel(kern_us),
         "roofline": {"kernel": "select_kernel", "bound": "hbm", "achieved": round(sel_gbps, 1), "peak": HBM_PEAK_GBPS,
                      "unit": "GB/s", "frac": round(sel_gbps / HBM_PEAK_GBPS, 4), "traffic": traffic,
                      "traffic_stale": traffic_stale, "bytes_per_launch": sel_bytes, "avg_us": round(float(kern_us[1]), 3)},
@@ -261,8 +279,6 @@ def main() -> int:
     # the step as it runs inside a decode loop (Algorithm 2): the code of one more token per head is written
     # (pqc_pq_encode_token; here a token that already has that code, so the inputs stay as they are), then the step
     if not args.no_append:
-        import ctypes as C
-
         pos = w.n_tokens - w.n_local - 1
         cfg = binding.make_config(w)
         lib = binding.load()
@@ -270,7 +286,7 @@ def main() -> int:
 
         def sep(i):
             a = margs[i]
-            rc = lib.pqc_pq_encode_token(C.byref(cfg), keys1[i].data_ptr(), a[1], a[2], pos, stream_handle)
+            rc = lib.pqc_pq_encode_token(ctypes.byref(cfg), keys1[i].data_ptr(), a[1], a[2], pos, stream_handle)
             assert rc == 0
             step(i)
 
@@ -353,7 +369,7 @@ def main() -> int:
                  "us_max": round(float(r2.max()), 3), "steps": args.also_steps, "repetitions": args.reps, "input_sets": n_sets,
                  "dtype": w2.dtype, "algorithmic_bytes_per_step": b2,
                  "hbm_frac": round(b2 / (us2 * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4),
-                 "kernel_us": {n: round(float(x), 3) for n, x in zip(KERNELS, k2)},
+                 "kernel_us": by_kernel(k2),
                  "select_kernel_hbm_frac": round(sb2 / (k2[1] * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4) if k2[1] > 0 else None}
         if with_cpu:
             entry["gpu_matches_oracle"], t_o, _ = against_oracle(w2, ctx2, sets2[0], host2, idx2, attn2)
