@@ -83,9 +83,10 @@ __global__ __launch_bounds__(256) void pq_encode_kernel(BuildShape s, const T* _
 //
 // Why so for every number of ranges: a launch of the means costs about 6 us a round with its gap, taking them here about 1.5 and
 // the additions of all workgroups at about the same time up to 4.  Against a launch that adds up a set of sums per range (up to 16
-// ranges) or takes the means of a shared one, four rounds: 2048 tokens of one head, 2x64, 59 -> 45 us; 8 heads 69 -> 55; 131072
-// tokens x 8 heads 400 -> 377; 2048 tokens x 4 heads, 4x256, 98 -> 71; 8192 x 8 heads, 4x256, 145 -> 141.  The other way round only
-// where 8 to 16 ranges of one batch each end together with 256 centroids: 32768 tokens x 4 heads, 189 -> 191 us.
+// ranges) or takes the means of a shared one, eight rounds: 2048 tokens of one head, 2x64, 108 -> 86 us; 8 heads 129 -> 105; 131072
+// tokens x 8 heads 717 -> 665; 2048 tokens x 4 heads, 4x256, 185 -> 132.  About even where 4 to 16 ranges of one batch each end together
+// with 256 centroids: 8192 tokens x 8 heads 259 -> 258, 32768 x 4 347 -> 353; one shared set with a launch for the means is slower there
+// too, 277 and 365 us.
 //
 // Sums are 64-bit integers of the values in fixed point (2^-20, round to nearest even), so the result does not depend
 // on the order of tokens, waves or workgroups.  The conversion is one addition in double precision: x + 1.5 * 2^32 has
@@ -271,12 +272,11 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
   constexpr int NT = 1024, NW = NT / 64, KK = DM / 32, RS = mfma_term_stride(DM);
   // With short sub-vectors the comparisons take about as long as the matrix products and do not hide behind them: the four scores
   // of the best tile are kept (9 instructions for four scores instead of 12) and which of them it was is found at the end.  64 heads
-  // x 32768 tokens, 4x256, assignment: 364 us, 387 with selections by VCC (327 started from |c|^2, see above).  With longer
-  // sub-vectors the registers hold keys.
+  // x 32768 tokens, 4x256, assignment: 395 us, 419 with selections by VCC.  With longer sub-vectors the registers hold keys.
   constexpr bool KEEP = DM == 32;
   constexpr bool FROM_NORM = DM > 32;
-  // The form for short ranges has few waves and is bound by latency: the products of its two tiles are under way together, and the
-  // compiler may place selections between them (4 heads x 8564 tokens, 4x64: 12.2 us a round, 12.6 with keep_lower).
+  // The form for short ranges has few waves and is bound by latency: the products of its two tiles are under way together (4 heads x
+  // 8564 tokens, 4x64, twenty rounds: 229 us, 233 with one tile after the other; 5000 tokens, 4x256, eight: 170 and 172).
   constexpr bool SHORT = TT == 2;
   constexpr int GANG = SHORT ? 2 : 1;
   // 64 and 128 dimensions: sums turned (see sum_place; 131072 tokens x 8 heads, 2x64, eight rounds 900 -> 770 us).  With 32 the
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
 #pragma unroll
           for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
-            for (int term = 2; term >= 0; --term)  // small terms first: from zero they are added up among themselves
+            for (int term = 2; term >= 0; --term)  // small terms first: from zero they add up among themselves
 #pragma unroll
               for (int g = 0; g < GANG; ++g)
                 acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[term][kk], x[t0 + g][kk],
@@ -420,15 +420,7 @@ __global__ __launch_bounds__(1024) void pq_round_mfma_kernel(BuildShape s, Round
             const int tt = t0 + g;
             if constexpr (KEEP) {
               const float low = fminf(fminf(fminf(fminf(best[tt], acc[g][0]), acc[g][1]), acc[g][2]), acc[g][3]);
-              if constexpr (SHORT) {
-                const bool lower = low < best[tt];
-                best[tt] = low;
-                bidx[tt] = lower ? c : bidx[tt];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) kept[tt][i] = lower ? acc[g][i] : kept[tt][i];
-              } else {
-                keep_lower(best[tt], bidx[tt], kept[tt], low, c, acc[g]);
-              }
+              keep_lower(best[tt], bidx[tt], kept[tt], low, c, acc[g]);
             } else {
 #pragma unroll
               for (int i = 0; i < 4; ++i) {

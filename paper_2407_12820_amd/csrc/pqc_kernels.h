@@ -556,8 +556,8 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
       const unsigned wv[4] = {raw[v].x, raw[v].y, raw[v].z, raw[v].w};
       const int off0 = (wave_t0 - wg_t0) + (v * 64 + lane) * 8;
       int ps = (before + place[v]) & 0xffff;
-      // every token is stored, those not selected in a place of the thread's own behind the list: a store under a condition of its
-      // own costs a wave about fifty cycles, and few waves are there to hide them
+      // every token is stored, those not selected in a place of the thread's own behind the list: eight stores under conditions of
+      // their own are eight branches, and few waves are there to hide them
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const bool sel = ((wv[i >> 1] >> (16 * (i & 1))) & 0xffffu) > thr;
