@@ -931,8 +931,8 @@ int pq_build_t(const BuildPlan& bp, const RoundGrid& r, bool linked, const T* ke
     return RoundLink{sums + prev * n_val, counts + prev * n_cent, place(it), more ? sums + next * n_val : nullptr,
                      more ? counts + next * n_cent : nullptr};
   };
-  hipLaunchKernelGGL((pq_init_kernel<T>), per_cent, dim3(256), 0, st, s, keys, init_idx, place(0), means ? sums : nullptr, counts,
-                     linked ? 2 : 1);
+  hipLaunchKernelGGL((pq_init_kernel<T>), per_cent, dim3(256), 0, st, s, keys, init_idx, place(0), means && iters > 0 ? sums : nullptr,
+                     counts, linked ? std::min(iters, 2) : 1);
   for (int it = 0; it < iters; ++it) {
     if (bp.fused) {
       const int set = linked ? it % kLinkedSets : 0;

@@ -364,6 +364,28 @@ def test_linked_rounds(pqc, dtype, m, c, n, units):
         assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), iters
 
 
+# As many sets of sums are cleared as rounds add to them: none without rounds, the first two (or the one there is) at most.
+@pytest.mark.parametrize("dtype,m,c,n,units", [("bf16", 2, 64, 20000, 2), ("f32", 4, 64, 3001, 1)])
+def test_sums_nobody_reads_are_left_alone(pqc, dtype, m, c, n, units):
+    import ctypes
+    lib = pqc.load()
+    w = wl.Workload(name="sums", batch=units, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=n, pq_m=m, pq_centroids=c,
+                    topk=0, n_init=1, n_local=0, dtype=dtype, kmeans_iters=1, recipe="plain")
+    cfg = ctypes.byref(pqc.make_config(w))
+    keys = torch.randn((units, 1, n, 128), device=DEV, dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    init = torch.from_numpy(wl.kmeans_init_indices(w, seed=3)).to(DEV)
+    nbytes, a_set = lib.pqc_pq_build_workspace_bytes(cfg), 8 * units * 128 * c
+    for iters, sets in ((0, 0), (1, 1), (2, 2)):
+        ws = torch.full((nbytes,), 0xa5, dtype=torch.uint8, device=DEV)
+        cent = torch.empty((units, 1, m, c, w.sub_dim), dtype=torch.float32, device=DEV)
+        codes = torch.empty((units, 1, n, m), dtype=torch.uint8, device=DEV)
+        assert lib.pqc_pq_build(cfg, keys.data_ptr(), init.data_ptr(), iters, cent.data_ptr(), codes.data_ptr(), ws.data_ptr(), nbytes,
+                                torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        untouched = [bool((ws[x * a_set:(x + 1) * a_set] == 0xa5).all()) for x in range(3)]
+        assert untouched == [x >= sets for x in range(3)], iters
+
+
 # A build recorded into a HIP graph: every replay starts from its own cleared sums, whatever ran in the workspace in between.
 @pytest.mark.parametrize("dtype,m,c,units", [("bf16", 2, 64, 1), ("bf16", 2, 64, 8), ("bf16", 2, 256, 1), ("f32", 4, 20, 3)])
 def test_recorded_build_replays(pqc, dtype, m, c, units):
