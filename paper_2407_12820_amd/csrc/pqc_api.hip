@@ -3,6 +3,7 @@
 // nothing synchronises the host: every entry point only enqueues kernels.
 #include "../../include/pqcache.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -57,7 +58,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Plan {
   Shape s;
-  bool short_form;  // the step's threshold is found by the select kernel itself (From::kShort), no histogram kernel
+  bool short_form;  // the decode step's threshold is found by the select kernel itself (From::kCount, kShort), no histogram kernel
   size_t off_lut, off_range, off_hist, off_bins, off_crec, off_stage, off_cnt, off_part, off_trace, total;
   int rec_stride;
 };
@@ -95,33 +96,38 @@ void lay_out(Plan* p, size_t bins_per_unit, size_t stage_words_per_unit, size_t 
   p->total = off;
 }
 
-// Whether a step of this shape is quicker without the histogram kernel (From::kShort in pqc_kernels.h): a launch saved against
-// scoring all N tokens in every workgroup, M look-ups a token.  Measured on layers of their own K/V, centroids and codes in turn (4 to
-// 32 of them, over 1.5 GB), us per layer with and without the histogram kernel, bf16, 4 query heads per unit, a tenth retrieved:
-//   tokens        2048         8192         12288        16384        24576      (2x64)
-//   1 unit        18.3, 15.8   19.1, 16.9   19.2, 17.6   19.3, 18.3   19.6, 20.2
-//   8 units       20.0, 16.6   20.3, 17.5   20.6, 18.6   21.0, 19.9   22.6, 22.0
-//   64 units      22.0, 18.4   26.2, 22.4   29.6, 25.9   30.6, 28.9   39.9, 38.9
-//   1 unit        18.4, 15.9   19.1, 17.3   19.2, 18.7   19.3, 19.7   19.5, 22.1  (4x64)
-//   8 units       19.9, 16.5   20.3, 18.0   20.5, 19.7   20.9, 20.9   22.7, 23.8
-//   1 unit        20.7, 18.3   20.7, 19.7   20.8, 21.0   21.1, 22.0   21.2, 24.3  (4x256)
-//   8 units       21.5, 18.7   22.1, 20.5   22.8, 22.5   23.0, 23.6   24.5, 26.4
-// One query head per unit and a twentieth retrieved leave the least to hide behind: 1 unit of 18432 (2x64) 18.2, 18.2; 8 units of 22528
-// 19.6, 19.7, of 24576 19.9, 20.2; 7 units of 12288 (4x64) 18.3, 18.5.  Beyond one workgroup per compute unit those of a unit scan it
-// one after the other: 96 units of 20000 47.2, 57.4; with as many workgroups as compute units and much to attend, two smaller
-// ones per unit hide each other's latency: a fifth retrieved, 240 units of 8192 76.8, 78.6, 120 of 12288 61.4, 62.4, 80 of 22528 64.2,
-// 65.7, but a tenth retrieved 61.2, 58.2, 46.9, 44.1 and 47.0, 44.6.
+// Whether a step of this shape is quicker without the histogram kernel (From::kCount, kShort in pqc_kernels.h): a launch, the table's
+// second build and the stored bins saved, against work over all N tokens in every workgroup.  Measured on layers of their own K/V,
+// centroids and codes in turn (4 to 32 of them, over 1.5 GB), us per layer with and without the histogram kernel, bf16, 4 query heads
+// per unit, a tenth retrieved:
+//   kCount tokens 2048         8192         16384        24576        32768        49152        57344        65536      (2x64)
+//   1 unit        18.3, 15.4   18.5, 15.5   18.9, 16.3   19.1, 17.0   19.5, 17.9   21.0, 20.8   21.2, 21.4   21.8, 22.5
+//   8 units       19.5, 15.7   20.1, 16.4   20.7, 17.7   22.0, 19.3   22.9, 21.0   25.4, 24.2   26.4, 25.9   27.0, 27.1
+//   32 units                   22.8, 18.7   25.8, 22.4   29.7, 25.9   30.2, 28.2   40.8, 37.7                46.3, 43.8
+//   64 units                   25.8, 21.3   30.7, 27.6   40.3, 35.8   45.2, 41.3
+// A fifth retrieved, 1 unit of 49152 21.7, 21.6, 8 units of 53248 31.7, 31.4, of 57344 31.7, 31.9; one query head and a twentieth, 1 unit
+// of 49152 19.4, 19.3; 16 units of 57344 31.3, 30.2, of 65536 32.1, 32.2.
+//   kShort tokens 8192         12288        16384
+//   1 unit        19.1, 17.3   19.2, 18.7   19.3, 19.7   (4x64)
+//   8 units       20.3, 18.0   20.5, 19.7   20.9, 20.9
+//   1 unit        20.7, 19.7   20.8, 21.0   21.1, 22.0   (4x256)
+//   8 units       22.1, 20.5   22.8, 22.5   23.0, 23.6
+// 7 units of 12288 (4x64), one query head, a twentieth 18.3, 18.5.  Beyond one workgroup per compute unit those of a unit go over it one
+// after the other: 128 units of 24000 (2x64) 66.9, 71.5.  With as many workgroups as compute units and much to attend, two smaller ones
+// per unit hide each other's latency: a fifth retrieved, 240 units of 8192 77.1, 79.9, 128 of 12288 64.3, 65.0, but of 16384 71.2, 69.9,
+// 64 of 32768 66.3, 63.9; a tenth retrieved, 240 of 8192 53.7, 51.0, 128 of 12288 43.9, 40.3.
 bool short_cache(const Shape& s) {
   if (s.M != 2 && s.M != 4) return false;
   const long long units = (long long)s.B * s.Hkv, blocks = units * ((s.N + 8191) / 8192);
-  const long long few = s.M == 2 ? 32768 : 45056, many = s.M == 2 ? 45056 : 49152;
-  if ((long long)s.N * s.M > (s.C > 64 ? 32768 : units < 8 ? few : many)) return false;
   if (s.N > 8192 && blocks > 256) return false;
-  return s.N < 8192 || blocks < 208 || 6ll * s.K < s.N;
+  const bool roomy = s.N < 8192 || blocks < 208 || 6ll * s.K < s.N;
+  if (counts_pairs(s)) return s.N <= (units < 8 ? 49152 : units < 16 ? 53248 : units < 32 ? 57344 : 65536) && (roomy || s.N >= 16384);
+  return (long long)s.N * s.M <= (s.C > 64 ? 32768 : units < 8 ? 45056 : 49152) && roomy;
 }
 
-// The launch plan of a configuration; `general`: for calls other than the decode step, which have no short form.
-int make_plan(const pqc_config* c, Plan* p, bool general = true) {
+// What a launch plan is for: the decode step, the step with given pair counts, or any other call.
+enum class For { kOther, kDecode, kPairs };
+int make_plan(const pqc_config* c, Plan* p, For call = For::kOther) {
   if (!c) return PQC_EINVAL;
   if (c->batch < 1 || c->n_q_heads < 1 || c->n_kv_heads < 1 || c->head_dim < 1 || c->n_tokens < 1 || c->pq_m < 1 ||
       c->pq_centroids < 1 || c->topk < 0 || c->n_init < 0 || c->n_local < 0)
@@ -165,13 +171,14 @@ int make_plan(const pqc_config* c, Plan* p, bool general = true) {
   s.histCopies = s.nblkA <= 32 ? 1 : s.nblkA <= 64 ? 2 : kHistCopies;
   // select kernel: 256-thread workgroups, two resident per compute unit
   int tokC = env_int("PQC_TOK_C", 0);
-  p->short_form = !general && short_cache(s);
+  p->short_form = call == For::kDecode && short_cache(s);
+  const From form = call == For::kPairs ? From::kPairs : p->short_form ? From::kShort : From::kBins;
   if (!tokC) {
     tokC = 512;
-    const int most = p->short_form ? 256 : 512;  // one workgroup per compute unit, of twice the size, in the short form
-    while (tokC < 8192 && units * ((s.N + tokC - 1) / tokC) > most) tokC *= 2;
+    const int most = form == From::kBins ? 512 : 256;  // one workgroup per compute unit, of twice the size, where there is no histogram kernel
+    while (tokC < max_tokens_per_select(form) && units * ((s.N + tokC - 1) / tokC) > most) tokC *= 2;
   }
-  if (tokC != 512 && tokC != 1024 && tokC != 2048 && tokC != 4096 && tokC != 8192) return PQC_EINVAL;
+  if (tokC < 512 || tokC > max_tokens_per_select(form) || (tokC & (tokC - 1))) return PQC_EINVAL;
   s.tokC = tokC; s.nblkC = (s.N + tokC - 1) / tokC;
   s.binStride = s.nblkC * s.tokC;
   s.stageStride = s.tokC + 40;
@@ -199,6 +206,11 @@ int make_plan(const pqc_config* c, Plan* p, bool general = true) {
   return PQC_OK;
 }
 
+// Whether the step with given pair counts takes this configuration.
+bool pairs_supported(const pqc_config* c) {
+  return c->pq_m == 2 && c->pq_centroids <= kPairC && (c->n_capacity ? c->n_capacity : c->n_tokens) % 8 == 0;
+}
+
 // Workspace needed by any context of this configuration whose length is changed later
 // (pqc_set_length) to anything up to the capacity: every size that depends on the length,
 // replaced by a bound over all lengths.
@@ -207,20 +219,26 @@ size_t workspace_bound(const pqc_config* c) {
   if (make_plan(c, &p) != PQC_OK) return 0;
   const Shape& s = p.s;
   if (s.cap == s.N) {
-    Plan d;
-    make_plan(c, &d, false);
-    return p.total > d.total ? p.total : d.total;
+    size_t most = p.total;
+    for (For call : {For::kDecode, For::kPairs}) {
+      Plan d;
+      if (call == For::kPairs && !pairs_supported(c)) continue;
+      make_plan(c, &d, call);
+      most = std::max(most, d.total);
+    }
+    return most;
   }
   const size_t units = (size_t)s.B * s.Hkv, cap = (size_t)s.cap;
   // select kernel grid: tokens per workgroup double until the grid has at most 512 workgroups or
-  // they reach 8192 (an override by environment may pin them as low as 512)
+  // they reach 8192, or 16384 with given pair counts (an override by environment may pin them as low as 512)
   const size_t tok_min = env_int("PQC_TOK_C", 0) ? (size_t)env_int("PQC_TOK_C", 0) : 8192;
   size_t nb = 512 / units;
   if (nb < (cap + tok_min - 1) / tok_min) nb = (cap + tok_min - 1) / tok_min;
   if (nb < 1) nb = 1;
   size_t npart = (cap + s.rowsP - 1) / s.rowsP;
   if (npart < nb) npart = nb;
-  lay_out(&p, cap + 8192, cap + 8192 + 40 * nb, nb, npart);
+  const size_t last = max_tokens_per_select(pairs_supported(c) ? From::kPairs : From::kBins);  // what the last workgroup may hold beyond the length
+  lay_out(&p, cap + last, cap + last + 40 * nb, nb, npart);
   return p.total;
 }
 
@@ -230,8 +248,10 @@ struct pqc_ctx {
   pqc_config cfg;
   Plan plan;           // of every call but the decode step
   Plan decode_plan;    // of the decode step: `plan`, or its short form
+  Plan pairs_plan;     // of the step with given pair counts
   Workspace ws;        // views of `plan`
-  Workspace decode_ws; // views of `decode_plan`; histograms and record counters lie in the same place
+  Workspace decode_ws; // views of `decode_plan` and of `pairs_plan`; histograms and record counters lie in the same place
+  Workspace pairs_ws;
   AppendArgs append;       // set for the duration of a pqc_decode_append call
   char* workspace;         // the caller's device memory
   size_t workspace_bytes;
@@ -356,33 +376,21 @@ void launch_decode_t(pqc_ctx* ctx, const void* q, const float* cent, const uint8
 }
 
 // decode with the threshold taken from code-pair counts (M = 2): select + finalize, no histogram kernel
-template <typename T, int G>
-void launch_indexed_tg(pqc_ctx* ctx, const void* q, const float* cent, const uint8_t* codes, const unsigned* pair_counts,
-                       const void* k, const void* v, int32_t* out_idx, float* out_attn, hipStream_t st) {
-  const Shape& s = ctx->plan.s;
-  const unsigned units = (unsigned)(s.B * s.Hkv);
-  const T* qt = static_cast<const T*>(q);
-  const T* kt = static_cast<const T*>(k);
-  const T* vt = static_cast<const T*>(v);
-  hipLaunchKernelGGL((select_kernel<T, G, CodeChunks<2>, true, From::kPairs>), dim3(s.nblkC, units), dim3(256),
-                     list_bytes<From::kPairs>(s.tokC), st, s, ctx->ws, qt, kt, vt, static_cast<const void*>(codes), cent,
-                     pair_counts, ctx->append.key ? ctx->append.position : -1);
-  launch_finalize<T, G>(ctx, s, ctx->ws, qt, kt, vt, out_idx, out_attn, st);
-}
-
 template <typename T>
 void launch_indexed_t(pqc_ctx* ctx, const void* q, const float* cent, const uint8_t* codes, const unsigned* pair_counts,
                       const void* k, const void* v, int32_t* out_idx, float* out_attn, hipStream_t st) {
-  switch (ctx->plan.s.G) {
-    case 1: launch_indexed_tg<T, 1>(ctx, q, cent, codes, pair_counts, k, v, out_idx, out_attn, st); break;
-    case 2: launch_indexed_tg<T, 2>(ctx, q, cent, codes, pair_counts, k, v, out_idx, out_attn, st); break;
-    case 4: launch_indexed_tg<T, 4>(ctx, q, cent, codes, pair_counts, k, v, out_idx, out_attn, st); break;
-    default: launch_indexed_tg<T, 8>(ctx, q, cent, codes, pair_counts, k, v, out_idx, out_attn, st); break;
+  const Shape& s = ctx->pairs_plan.s;
+  const Workspace& ws = ctx->pairs_ws;
+  const T* qt = static_cast<const T*>(q);
+  const T* kt = static_cast<const T*>(k);
+  const T* vt = static_cast<const T*>(v);
+  launch_pairs_select(sizeof(T) == 2, s, ws, q, cent, codes, pair_counts, ctx->append.key ? ctx->append.position : -1, k, v, st);
+  switch (s.G) {
+    case 1: launch_finalize<T, 1>(ctx, s, ws, qt, kt, vt, out_idx, out_attn, st); break;
+    case 2: launch_finalize<T, 2>(ctx, s, ws, qt, kt, vt, out_idx, out_attn, st); break;
+    case 4: launch_finalize<T, 4>(ctx, s, ws, qt, kt, vt, out_idx, out_attn, st); break;
+    default: launch_finalize<T, 8>(ctx, s, ws, qt, kt, vt, out_idx, out_attn, st); break;
   }
-}
-
-bool pairs_supported(const pqc_config* c) {
-  return c->pq_m == 2 && c->pq_centroids <= kPairC && (c->n_capacity ? c->n_capacity : c->n_tokens) % 8 == 0;
 }
 
 template <typename T, int G>
@@ -473,12 +481,14 @@ Workspace views(char* base, const Plan& p) {
 }
 
 // The context's plans of its configuration (`p`: the general one), and their views.  A workspace that holds the general plan but
-// not the decode step's own takes the general one for it.
+// not a step's own takes the general one for it.
 void bind_plans(pqc_ctx* ctx, const Plan& p) {
   ctx->plan = p;
-  if (make_plan(&ctx->cfg, &ctx->decode_plan, false) != PQC_OK || ctx->decode_plan.total > ctx->workspace_bytes) ctx->decode_plan = p;
+  if (make_plan(&ctx->cfg, &ctx->decode_plan, For::kDecode) != PQC_OK || ctx->decode_plan.total > ctx->workspace_bytes) ctx->decode_plan = p;
+  if (make_plan(&ctx->cfg, &ctx->pairs_plan, For::kPairs) != PQC_OK || ctx->pairs_plan.total > ctx->workspace_bytes) ctx->pairs_plan = p;
   ctx->ws = views(ctx->workspace, ctx->plan);
   ctx->decode_ws = views(ctx->workspace, ctx->decode_plan);
+  ctx->pairs_ws = views(ctx->workspace, ctx->pairs_plan);
 }
 }  // namespace
 

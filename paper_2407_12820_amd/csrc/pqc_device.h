@@ -25,6 +25,7 @@ struct bf16_t {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4_t;
 
 // Geometry of one decode step, passed by value to every kernel.
 struct Shape {
@@ -221,6 +222,15 @@ __device__ __forceinline__ float wave_max(float v) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 __device__ __forceinline__ float wave_min(float v) { return -wave_max(-v); }
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
+  v = max(v, (unsigned)dpp_i<0x111>(0, (int)v));
+  v = max(v, (unsigned)dpp_i<0x112>(0, (int)v));
+  v = max(v, (unsigned)dpp_i<0x114>(0, (int)v));
+  v = max(v, (unsigned)dpp_i<0x118>(0, (int)v));
+  v = max(v, (unsigned)dpp_i<0x142, 0xa>(0, (int)v));
+  v = max(v, (unsigned)dpp_i<0x143, 0xc>(0, (int)v));
+  return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
 
 // Sum over the 16 lanes of a DPP row; every lane of the row receives the total.
 __device__ __forceinline__ float group16_sum(float x) {
@@ -292,72 +302,81 @@ __host__ __device__ constexpr int lut_row_stride(int M) { return M <= 2 ? kD / M
 __host__ __device__ constexpr int lut_tile_floats(int nt, int M, int C) {
   return nt >= 512 ? M * C * lut_row_stride(M) : kLutTileFloats + kLutTileFloats / (kD / M);
 }
-// VWP (whole-table mode): 16-byte pieces of the table per thread; VWP * NT * 4 floats must cover M*C*Dm.
+// The group's query heads: all loads first (clamped, straight-line), then the sum in head order.
+template <typename T, class IssueFn>
+__device__ __forceinline__ void sum_query(const T* __restrict__ q, int G, float* qs, IssueFn issue_more) {
+  const int dq = threadIdx.x & (kD - 1);
+  float qv[8];
+#pragma unroll
+  for (int h = 0; h < 8; ++h) qv[h] = load_as_float<T>(q, min(h, G - 1) * kD + dq);
+  // Loads return in issue order: whatever the caller streams from HBM goes behind the table's
+  // (mostly L2-resident) centroids, so that the table is built while that stream arrives.
+  PQC_LOADS_ISSUED();
+  issue_more();
+  PQC_LOADS_ISSUED();
+  float a = qv[0];
+#pragma unroll
+  for (int h = 1; h < 8; ++h) {
+    const float t = __fadd_rn(a, qv[h]);
+    a = h < G ? t : a;  // select, not branch: keeps the eight loads above in flight together
+  }
+  qs[dq] = a;  // every thread (tid and tid + kD hold the same sum): a branch here would split the block, and the
+               // compiler would then move the centroid loads above down to their use, behind this wait
+}
+
+// The first half of it in whole-table mode: the group's query heads summed into qs and the centroids in the tile, visible behind a
+// barrier of the caller's.  VWP: 16-byte pieces of the table per thread; VWP * NT * 4 floats must cover M*C*Dm.
+template <typename T, int NT, int M, int VWP, class MarkFn, class EarlyFn, class IssueFn>
+__device__ __forceinline__ void lut_stage(const T* __restrict__ q /* [G][kD] of this unit */, const float* __restrict__ cent /* [M][C][Dm] */,
+                                          int G, int C, float* qs, float* tile /* [lut_tile_floats(NT, M, C)] */, MarkFn mark,
+                                          EarlyFn issue_early /* the caller's loads that go right behind the thread's centroid loads, always as
+                                                                 many: the wait for the centroids counts them */,
+                                          IssueFn issue_more /* and those behind its tile stores */) {
+  constexpr int Dm = kD / M, RS = lut_row_stride(M);
+  const int tid = threadIdx.x, total = M * C * Dm;  // floats, a multiple of 4
+  // (a native vector type: a float4 struct copied from global memory to LDS is turned into one 16-byte copy at
+  // the place of the store, which puts every load behind the waits in front of it, one round trip after the other)
+  const f32x4_t* centv = reinterpret_cast<const f32x4_t*>(cent);
+  f32x4_t vw[VWP];
+#pragma unroll
+  for (int x = 0; x < VWP; ++x) vw[x] = centv[min(x * NT + tid, total / 4 - 1)];
+  sum_query<T>(q, G, qs, issue_early);
+  mark(8);
+#pragma unroll
+  for (int x = 0; x < VWP; ++x) {
+    // No branch around the store: a thread beyond the table holds the table's last float4 (its load was clamped)
+    // and writes it to that float4's place once more.  With a branch here the compiler moves each load down into
+    // its branch and waits for it there, one memory round trip after the other.
+    const int fl = min((x * NT + tid) * 4, total - 4);  // float index inside the table
+    const int row = fl / Dm, col = fl % Dm;             // Dm is a multiple of 4: one row per float4
+    float* dst = tile + row * RS + col;
+    if constexpr (RS % 4 == 0) {
+      *reinterpret_cast<f32x4_t*>(dst) = vw[x];
+    } else {
+      dst[0] = vw[x][0]; dst[1] = vw[x][1]; dst[2] = vw[x][2]; dst[3] = vw[x][3];
+    }
+  }
+  // the caller's stream from HBM is requested now, behind every wave's centroid loads (a compute unit's loads
+  // pass through one address unit): the table is built while that stream arrives
+  issue_more();
+  PQC_LOADS_ISSUED();
+  mark(10);
+}
+
 template <typename T, int NT, int M, class MarkFn, class IssueFn, int VWP = (256 * kD) / (4 * NT)>
-__device__ __forceinline__ float2 build_lut(const T* __restrict__ q /* [G][kD] of this unit */,
-                                               const float* __restrict__ cent /* [M][C][Dm] */, int G, int C,
-                                               float* lut, float* qs, float* red /* [4*8] */,
-                                               float* tile /* [lut_tile_floats(NT, M, C)] */, MarkFn mark,
-                                               IssueFn issue_more /* the caller's own loads, queued behind the table's */) {
+__device__ __forceinline__ float2 build_lut(const T* __restrict__ q, const float* __restrict__ cent, int G, int C, float* lut, float* qs,
+                                            float* red /* [4*8] */, float* tile, MarkFn mark, IssueFn issue_more) {
   constexpr int Dm = kD / M, RS = lut_row_stride(M);
   constexpr bool kWhole = NT >= 512;
-  constexpr int VW = kWhole ? VWP : 1;                    // float4 per thread
   constexpr int VPG = kLutTileFloats / (4 * NT);      // float4 per thread per tile (piecewise mode)
   constexpr int NG = (256 * kD) / kLutTileFloats;      // tiles at the largest C (piecewise mode)
   const int tid = threadIdx.x;
   const int total = M * C * Dm;                        // floats, a multiple of 4
   const float4* cent4 = reinterpret_cast<const float4*>(cent);
-  // (a native vector type: a float4 struct copied from global memory to LDS is turned into one 16-byte copy at
-  // the place of the store, which puts every load behind the waits in front of it, one round trip after the other)
-  const f32x4_t* centv = reinterpret_cast<const f32x4_t*>(cent);
-  f32x4_t vw[VW];
   if constexpr (kWhole) {
-#pragma unroll
-    for (int x = 0; x < VW; ++x) vw[x] = centv[min(x * NT + tid, total / 4 - 1)];
-  }
-  {
-    // the group's query heads: all loads first (clamped, straight-line), then the sum in head order
-    const int dq = tid & (kD - 1);
-    float qv[8];
-#pragma unroll
-    for (int h = 0; h < 8; ++h) qv[h] = load_as_float<T>(q, min(h, G - 1) * kD + dq);
-    // Loads return in issue order: whatever the caller streams from HBM goes behind the table's
-    // (mostly L2-resident) centroids, so that the table is built while that stream arrives.
-    PQC_LOADS_ISSUED();
-    if constexpr (!kWhole) issue_more();
-    PQC_LOADS_ISSUED();
-    float a = qv[0];
-#pragma unroll
-    for (int h = 1; h < 8; ++h) {
-      const float t = __fadd_rn(a, qv[h]);
-      a = h < G ? t : a;  // select, not branch: keeps the eight loads above in flight together
-    }
-    qs[dq] = a;  // every thread (tid and tid + kD hold the same sum): a branch here would split the block, and the
-                 // compiler would then move the centroid loads above down to their use, behind this wait
-  }
-  mark(8);
-  if constexpr (kWhole) {
-#pragma unroll
-    for (int x = 0; x < VW; ++x) {
-      // No branch around the store: a thread beyond the table holds the table's last float4 (its load was clamped)
-      // and writes it to that float4's place once more.  With a branch here the compiler moves each load down into
-      // its branch and waits for it there, one memory round trip after the other.
-      const int fl = min((x * NT + tid) * 4, total - 4);  // float index inside the table
-      const int row = fl / Dm, col = fl % Dm;             // Dm is a multiple of 4: one row per float4
-      float* dst = tile + row * RS + col;
-      if constexpr (RS % 4 == 0) {
-        *reinterpret_cast<f32x4_t*>(dst) = vw[x];
-      } else {
-        dst[0] = vw[x][0]; dst[1] = vw[x][1]; dst[2] = vw[x][2]; dst[3] = vw[x][3];
-      }
-    }
-    // the caller's stream from HBM is requested now, behind every wave's centroid loads (a compute unit's loads
-    // pass through one address unit): the table is built while that stream arrives
-    issue_more();
-    PQC_LOADS_ISSUED();
+    lut_stage<T, NT, M, VWP>(q, cent, G, C, qs, tile, mark, []() {}, issue_more);
     unsigned* mm = reinterpret_cast<unsigned*>(red);  // [0..8): smallest entry of a partition, [8..16): largest, as score keys
     if (tid < 16) mm[tid] = tid < 8 ? 0xffffffffu : 0u;
-    mark(10);
     __syncthreads();  // tile, qs and mm visible
     mark(11);
     for (int e0 = 0; e0 + (tid & ~63) < M * C; e0 += NT) {  // per wave: the wave-wide reductions below need every lane
@@ -428,6 +447,8 @@ __device__ __forceinline__ float2 build_lut(const T* __restrict__ q /* [G][kD] o
     }
     mark(9);
   } else {
+    sum_query<T>(q, G, qs, issue_more);
+    mark(8);
     float4 v[VPG];
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
@@ -500,61 +521,81 @@ __device__ __forceinline__ float2 build_lut(const T* __restrict__ q /* [G][kD] o
   return make_float2(lo, hi);
 }
 
+// The token of sample i of n, spread evenly over the nmid middle tokens: i * nmid / n with n = 1024 or, with fewer tokens, n = nmid
+// (there are at most 2^22 tokens).
+__device__ __forceinline__ int sample_token(const Shape& s, int i) {
+  const unsigned step = s.sampleN == 1024 ? (unsigned)max(0, s.N - s.I - s.L) : 1024u;
+  return min(s.N - 1, s.I + (int)(((unsigned)i * step) >> 10));
+}
+
 // Where the fine bins go: every workgroup of a unit scores the same `n` sampled tokens,
 // histograms them over kSampleBins uniform bins of [lo, hi] and takes the bins that hold the
 // sample's rank_hi-th and rank_lo-th largest scores as the window.  The ranks bracket
 // the K-th largest of all tokens by several standard errors of the sample quantile, so
 // the window almost always holds it (and when it does not, only speed is lost).
-// Two barriers: the samples are counted, then the first wave alone walks the histogram
-// (four bins per lane, a wave-wide prefix sum) and clears it again.
-//   hist  LDS [>= kSampleBins], zero on entry, zero again on return      sm  LDS [2]
 constexpr int kSampleBins = 256;
+__device__ __forceinline__ float sample_scale(float lo, float hi) {
+  const float width = hi - lo;
+  return (width > 1e-30f && width < 3e38f) ? (float)kSampleBins / width : 0.0f;
+}
+__device__ __forceinline__ int sample_bin(float score, float lo, float inv_u) {
+  return max(0, min(kSampleBins - 1, __float2int_rz((score - lo) * inv_u)));
+}
+// One wave walks the histogram (four bins per lane, a wave-wide prefix sum) and, on demand, clears it again; b_hi and b_lo: the bins
+// of the two ranks, or -1.
+template <bool CLEAR>
+__device__ __forceinline__ void walk_samples(unsigned* hist, int rank_hi, int rank_lo, int& b_hi, int& b_lo) {
+  constexpr int NBS = kSampleBins, PER = NBS / 64;
+  static_assert(PER == 4, "one 16-byte access per lane");
+  const int lane = threadIdx.x & 63;
+  // lane l owns bins [NBS - (l+1)*PER, NBS - l*PER): the lanes run from the top bin down
+  uint4* mine = reinterpret_cast<uint4*>(hist + NBS - (lane + 1) * PER);
+  const uint4 x = *mine;
+  if constexpr (CLEAR) *mine = make_uint4(0u, 0u, 0u, 0u);
+  const int h[PER] = {(int)x.x, (int)x.y, (int)x.z, (int)x.w};
+  const int sum = h[0] + h[1] + h[2] + h[3];
+  int cum = wave_inclusive_scan(sum) - sum;  // samples in the bins above this lane's
+  int r0 = -1, r1 = -1;
+#pragma unroll
+  for (int e = PER - 1; e >= 0; --e) {  // this lane's bins, from its top one down
+    const int b = NBS - (lane + 1) * PER + e;
+    if (rank_hi >= 1 && cum < rank_hi && cum + h[e] >= rank_hi) r0 = b;
+    if (rank_lo >= 1 && cum < rank_lo && cum + h[e] >= rank_lo) r1 = b;
+    cum += h[e];
+  }
+  // at most one lane finds each of the two bins: its number from that lane
+  const unsigned long long m0 = __ballot(r0 >= 0), m1 = __ballot(r1 >= 0);
+  b_hi = m0 ? __builtin_amdgcn_readlane(r0, __ffsll((long long)m0) - 1) : -1;
+  b_lo = m1 ? __builtin_amdgcn_readlane(r1, __ffsll((long long)m1) - 1) : -1;
+}
+__device__ __forceinline__ BinMap window_bins(float lo, float hi, int b_hi, int b_lo) {
+  const float wu = (hi - lo) * (1.0f / (float)kSampleBins);
+  const float q_hi = b_hi >= 0 ? fmaf((float)(b_hi + 1), wu, lo) : hi;
+  const float q_lo = b_lo >= 0 ? fmaf((float)b_lo, wu, lo) : lo;
+  return make_bins(lo, hi, q_lo, q_hi);
+}
+// Two barriers: the samples are counted, then the first wave alone walks the histogram.
+//   hist  LDS [>= kSampleBins], zero on entry, zero again on return      sm  LDS [2]
 // PS samples per thread: thread t holds the samples t, t + NT, ... below n.
 template <int NT, int PS>
 __device__ __forceinline__ BinMap sample_window(float lo, float hi, const float (&my_score)[PS], int n, int rank_hi, int rank_lo,
                                                 unsigned* hist, int* sm) {
-  constexpr int NBS = kSampleBins, PER = NBS / 64;
-  static_assert(PER == 4, "one 16-byte access per lane");
   const int tid = threadIdx.x;
-  const float width = hi - lo;
-  const float inv_u = (width > 1e-30f && width < 3e38f) ? (float)NBS / width : 0.0f;
+  const float inv_u = sample_scale(lo, hi);
 #pragma unroll
   for (int x = 0; x < PS; ++x)
-    if (x * NT + tid < n) atomicAdd(&hist[max(0, min(NBS - 1, __float2int_rz((my_score[x] - lo) * inv_u)))], 1u);
+    if (x * NT + tid < n) atomicAdd(&hist[sample_bin(my_score[x], lo, inv_u)], 1u);
   __syncthreads();
-  if (tid < 64) {  // lane l owns bins [NBS - (l+1)*PER, NBS - l*PER): the lanes run from the top bin down
-    uint4* mine = reinterpret_cast<uint4*>(hist + NBS - (tid + 1) * PER);
-    const uint4 x = *mine;
-    *mine = make_uint4(0u, 0u, 0u, 0u);
-    const int h[PER] = {(int)x.x, (int)x.y, (int)x.z, (int)x.w};
-    const int sum = h[0] + h[1] + h[2] + h[3];
-    int cum = wave_inclusive_scan(sum) - sum;  // samples in the bins above this lane's
-    int r0 = -1, r1 = -1;
-#pragma unroll
-    for (int e = PER - 1; e >= 0; --e) {  // this lane's bins, from its top one down
-      const int b = NBS - (tid + 1) * PER + e;
-      if (rank_hi >= 1 && cum < rank_hi && cum + h[e] >= rank_hi) r0 = b;
-      if (rank_lo >= 1 && cum < rank_lo && cum + h[e] >= rank_lo) r1 = b;
-      cum += h[e];
-    }
-    // at most one lane finds each of the two bins: a wave-wide maximum, read from the last lane
-    r0 = max(r0, dpp_i<0x111>(-1, r0)); r1 = max(r1, dpp_i<0x111>(-1, r1));
-    r0 = max(r0, dpp_i<0x112>(-1, r0)); r1 = max(r1, dpp_i<0x112>(-1, r1));
-    r0 = max(r0, dpp_i<0x114>(-1, r0)); r1 = max(r1, dpp_i<0x114>(-1, r1));
-    r0 = max(r0, dpp_i<0x118>(-1, r0)); r1 = max(r1, dpp_i<0x118>(-1, r1));
-    r0 = max(r0, dpp_i<0x142, 0xa>(-1, r0)); r1 = max(r1, dpp_i<0x142, 0xa>(-1, r1));
-    r0 = max(r0, dpp_i<0x143, 0xc>(-1, r0)); r1 = max(r1, dpp_i<0x143, 0xc>(-1, r1));
-    if (tid == 63) {
-      sm[0] = r0;
-      sm[1] = r1;
+  if (tid < 64) {
+    int b_hi, b_lo;
+    walk_samples<true>(hist, rank_hi, rank_lo, b_hi, b_lo);
+    if (tid == 0) {
+      sm[0] = b_hi;
+      sm[1] = b_lo;
     }
   }
   __syncthreads();
-  const int b_hi = sm[0], b_lo = sm[1];
-  const float wu = width * (1.0f / (float)NBS);
-  const float q_hi = b_hi >= 0 ? fmaf((float)(b_hi + 1), wu, lo) : hi;
-  const float q_lo = b_lo >= 0 ? fmaf((float)b_lo, wu, lo) : lo;
-  return make_bins(lo, hi, q_lo, q_hi);
+  return window_bins(lo, hi, sm[0], sm[1]);
 }
 
 // ------------------------------------------------------------------- code scan
@@ -589,7 +630,7 @@ __device__ __forceinline__ float score_from_word(typename CodeWord<M>::type w, c
 
 // 16 bytes of codes = P = 16/M consecutive tokens; word i of the chunk.
 template <int M>
-__device__ __forceinline__ typename CodeWord<M>::type chunk_word(const uint4& raw, int i) {
+__device__ __forceinline__ typename CodeWord<M>::type chunk_word(const u32x4_t& raw, int i) {
   const unsigned w[4] = {raw.x, raw.y, raw.z, raw.w};
   if constexpr (M == 8) {
     return ((unsigned long long)w[2 * i + 1] << 32) | w[2 * i];
@@ -629,9 +670,10 @@ struct ThresholdSearch {
       for (int v = 0; v < PER / 4; ++v) x[c][v] = c < copies ? src[v] : make_uint4(0u, 0u, 0u, 0u);  // uniform
     }
   }
-  __device__ __forceinline__ Threshold resolve(int K, int n_mid /* middle tokens of the unit */, int* sm /* [2*(NT/64)+1+4] */) const {
+  // Two barriers; a barrier of the caller's lies between the last use of sm in front of the call and the first one behind it.
+  __device__ __forceinline__ Threshold resolve(int K, int n_mid /* middle tokens of the unit; negative: bin 0 is counted like the others */, int* sm /* [2*(NT/64)+1+4] */) const {
     constexpr int NW = NT / 64;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     unsigned h[PER];  // descending bins: h[e] is bin kNB-1-(tid*PER+e)
 #pragma unroll
     for (int e = 0; e < PER; ++e) h[e] = 0u;
@@ -647,10 +689,9 @@ struct ThresholdSearch {
     int sum = 0;
 #pragma unroll
     for (int e = 0; e < PER; ++e) sum += (int)h[e];
-    int total;
-    int cum = block_exclusive_scan<NT>(sum, &total, sm);
-    if (tid == NT - 1) h[PER - 1] = (unsigned)(n_mid - total);  // bin 0 is not counted: it holds the rest
+    const int inc = wave_inclusive_scan(sum);
     int* res = sm + 2 * NW + 1;
+    if (lane == 63) sm[w] = inc;
     if (tid == 0) {
       res[0] = kNB;
       res[1] = 0;
@@ -658,6 +699,14 @@ struct ThresholdSearch {
       res[3] = 0;
     }
     __syncthreads();
+    int cum = inc - sum, total = 0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      const int v = sm[i];
+      cum += i < w ? v : 0;
+      total += v;
+    }
+    if (n_mid >= 0 && tid == NT - 1) h[PER - 1] = (unsigned)(n_mid - total);  // bin 0 is not counted: it holds the rest
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
       if (K > 0 && cum < K && cum + (int)h[e] >= K) {
@@ -669,225 +718,184 @@ struct ThresholdSearch {
       cum += (int)h[e];
     }
     __syncthreads();
-    Threshold t{res[0], res[1], res[2], res[3]};
-    __syncthreads();
-    return t;
+    return Threshold{res[0], res[1], res[2], res[3]};
   }
 };
 
 // ------------------------------------------------- threshold from code-pair counts
-// With M = 2 and C <= 64 a token's score takes one of C*C values, one per pair of codes.
-// Given how many tokens carry each pair (a statistic of the codes alone, kept with them),
-// the K-th largest score follows from the table without a pass over the tokens: weight
-// the C*C pair scores by their counts, find the uniform score bin that holds the K-th
-// largest, then resolve the few pairs inside that bin exactly.  The result is the score
-// key of the K-th largest middle token: larger keys are selected, equal keys are
-// candidates (ranked by token index later).  Scores use the same fp32 order as everywhere.
-constexpr int kPairSlots = 4096;  // C*C <= kPairSlots
+// With M = 2 and C <= 64 a token's score takes one of C*C values, one per pair of codes: given how many middle tokens carry each
+// pair, the threshold follows from the table without a pass over the tokens, and a token is classified by one look-up.  A pair has
+// the slot c0 + 64 * c1 whatever C is, and a thread of 512 the eight slots 8 * thread + i: they share c1, and have one 16-byte
+// piece of every array of 16-bit entries to themselves.
+constexpr int kPairSlots = 4096;
 constexpr int kPairC = 64;        // largest C
+constexpr int kPairPer = 8;       // slots per thread
 constexpr int kPairList = 256;    // pairs resolved by direct ranking; more fall back to a radix search
 struct PairLds {
-  unsigned cnt[kPairSlots];       // tokens per pair (c0 + C*c1), window tokens taken out
-  float lut[2 * kPairC];          // table[j][c] at j*kPairC + c
-  float qs[kD];
-  unsigned hist[kNB];
-  unsigned long long lst[kPairList];  // (key << 32) | count of the pairs in the threshold bin
-  int res[8];
+  unsigned cnt[kPairSlots];                  // tokens per pair: the middle tokens, or the window tokens that the given counts hold besides
+  unsigned short cls[kPairSlots];            // what a token of the pair is, in stored form
+  unsigned long long lst[kPairList];         // (key << 32) | count of the pairs in the threshold bin
+  int res[4];
+  unsigned samples[kSampleBins];             // sampled tokens per coarse bin
+  float bounds[4];                           // smallest and largest table entry of either partition
 };
-struct PairThreshold {
-  unsigned key;  // score key of the K-th largest middle token
-  bool none;     // K == 0: nothing is retrieved
-};
+// Slots of two tokens whose codes lie in one word (codes beyond 63, which name no centroid, are taken modulo 64).
+__device__ __forceinline__ void pair_slots(unsigned word, unsigned& s0, unsigned& s1) {
+  const unsigned w = word & 0x3f3f3f3fu;
+  s0 = __builtin_amdgcn_udot4(w, 0x00004001u, 0u, false);
+  s1 = __builtin_amdgcn_udot4(w, 0x40010000u, 0u, false);
+}
+// One partition's table of two, up to 64 centroids, by one wave: a lane has one entry.  lo, hi: the smallest and the largest one.
+__device__ __forceinline__ void pair_table(const float* tile, const float* qs, int C, int j, float* lut, float& lo, float& hi) {
+  constexpr int Dm = kD / 2, RS = lut_row_stride(2), kStages = Dm / 16;
+  const int lane = threadIdx.x & 63;
+  const f32x4_t* cv = reinterpret_cast<const f32x4_t*>(tile + (j * C + min(lane, C - 1)) * RS);
+  const f32x4_t* qv = reinterpret_cast<const f32x4_t*>(qs + j * Dm);
+  float p = 0.0f;
+  f32x4_t qa[2][4], ca[2][4];  // two stages of four 16-byte pieces: read ahead of the chain
+  auto read = [&](int st) {
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      qa[st & 1][y] = qv[st * 4 + y];
+      ca[st & 1][y] = cv[st * 4 + y];
+    }
+  };
+  read(0);
+  read(1);
+#pragma unroll
+  for (int st = 0; st < kStages; ++st) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int y = 0; y < 4; ++y)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) p = __fmaf_rn(qa[st & 1][y][e], ca[st & 1][y][e], p);
+    __builtin_amdgcn_sched_barrier(0);
+    if (st + 2 < kStages) read(st + 2);
+  }
+  if (lane < C) lut[j * kLutRow + lane] = p;
+  if (C == 64) {  // uniform
+    lo = key_score(score_key(wave_min(p)));
+    hi = key_score(score_key(wave_max(p)));
+  } else {
+    const unsigned key = score_key(p);
+    lo = key_score(~wave_max_u32(lane < C ? ~key : 0u));
+    hi = key_score(wave_max_u32(lane < C ? key : 0u));
+  }
+}
+// The scores of this thread's slots (entries of centroids that do not exist hold anything).
+__device__ __forceinline__ void pair_scores(const float* lut, float (&sc)[kPairPer]) {
+  const int c0 = (threadIdx.x & 7) * 8, c1 = threadIdx.x >> 3;
+  const f32x4_t a = *reinterpret_cast<const f32x4_t*>(&lut[c0]), b = *reinterpret_cast<const f32x4_t*>(&lut[c0 + 4]);
+  const float y = lut[kLutRow + c1];
+#pragma unroll
+  for (int i = 0; i < kPairPer; ++i) sc[i] = __fadd_rn(i < 4 ? a[i & 3] : b[i & 3], y);
+}
+__device__ __forceinline__ void store_classes(unsigned short* cls, const unsigned (&v)[kPairPer]) {
+  *reinterpret_cast<uint4*>(&cls[threadIdx.x * kPairPer]) = make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
+}
 
-template <typename T, int NT, class MarkFn>
-__device__ __forceinline__ PairThreshold pair_threshold(const Shape& s, const T* __restrict__ q /* [G][kD] of the unit */,
-                                                        const float* __restrict__ cent /* [2][C][64] of the unit */,
-                                                        const unsigned* __restrict__ pair_counts /* [C*C] of the unit */,
-                                                        const uint8_t* __restrict__ codes_u /* [N][2] of the unit */,
-                                                        PairLds& L, int* scan_sm /* [2*(NT/64)+1] */, MarkFn mark,
-                                                        int uncounted /* a window token the counts do not hold yet, or -1 */) {
-  static_assert(NT == 256, "written for 256 threads");
-  constexpr int Dm = kD / 2, PPT = kPairSlots / NT, BPT = kNB / NT;
-  const int tid = threadIdx.x, C = s.C, np = C * C;
-  // ---- loads: one table entry's centroid per thread (2C threads), query, counts, window codes
-  const int e = min(tid, 2 * C - 1);
-  const float4* crow = reinterpret_cast<const float4*>(cent + (size_t)e * Dm);
-  float4 cr[Dm / 4];
-#pragma unroll
-  for (int x = 0; x < Dm / 4; ++x) cr[x] = crow[x];
-  float qv[8];
-#pragma unroll
-  for (int h = 0; h < 8; ++h) qv[h] = load_as_float<T>(q, min(h, s.G - 1) * kD + (tid & (kD - 1)));
-  unsigned pc[PPT];  // pair x*NT + tid
-#pragma unroll
-  for (int x = 0; x < PPT; ++x) pc[x] = pair_counts[min(x * NT + tid, np - 1)];
-  const int nwin = s.I + s.L;
-  unsigned short wcode = 0;  // first window token of this thread (the usual case: I + L <= NT)
-  {
-    const int wt = min(tid, max(nwin - 1, 0));
-    const int t = wt < s.I ? wt : s.N - s.L + (wt - s.I);
-    wcode = *reinterpret_cast<const unsigned short*>(codes_u + (size_t)min(max(t, 0), s.N - 1) * 2);
-  }
-  PQC_LOADS_ISSUED();
-  {
-    float a = qv[0];
-#pragma unroll
-    for (int h = 1; h < 8; ++h) {
-      const float t = __fadd_rn(a, qv[h]);
-      a = h < s.G ? t : a;
-    }
-    if (tid < kD) L.qs[tid] = a;
-  }
-#pragma unroll
-  for (int x = 0; x < PPT; ++x)
-    if (x * NT + tid < np) L.cnt[x * NT + tid] = pc[x];
-#pragma unroll
-  for (int x = 0; x < BPT; ++x) L.hist[x * NT + tid] = 0u;
-  if (tid < 8) L.res[tid] = (tid == 4 || tid == 6) ? -1 : 0;  // slots 4..7: (min, max) keys of the two partitions
-  __syncthreads();
-  mark(9);
-  // ---- table entries (fixed-order chain) and the window tokens taken out of the counts
-  if (tid < 2 * C) {
-    const int j = tid / C, c = tid - j * C;
-    const float* qj = L.qs + j * Dm;
-    float p = 0.0f;
-#pragma unroll
-    for (int x = 0; x < Dm / 4; ++x) {
-      p = __fmaf_rn(qj[4 * x + 0], cr[x].x, p);
-      p = __fmaf_rn(qj[4 * x + 1], cr[x].y, p);
-      p = __fmaf_rn(qj[4 * x + 2], cr[x].z, p);
-      p = __fmaf_rn(qj[4 * x + 3], cr[x].w, p);
-    }
-    L.lut[j * kPairC + c] = p;
-    const unsigned pk = score_key(p);  // per-partition minimum and maximum, through order-preserving keys
-    atomicMin(reinterpret_cast<unsigned*>(&L.res[4 + 2 * j]), pk);
-    atomicMax(reinterpret_cast<unsigned*>(&L.res[5 + 2 * j]), pk);
-  }
-  for (int wt = tid; wt < nwin; wt += NT) {
-    unsigned short cw = wcode;
-    const int t = wt < s.I ? wt : s.N - s.L + (wt - s.I);
-    if (wt >= NT) cw = *reinterpret_cast<const unsigned short*>(codes_u + (size_t)t * 2);
-    const int w0 = cw & 0xff, w1 = cw >> 8;  // a code outside [0, C) was never counted
-    if (w0 < C && w1 < C && t != uncounted) atomicSub(&L.cnt[w0 + C * w1], 1u);
-  }
-  __syncthreads();
-  mark(10);
-  // ---- bounds (added in the same order as a score), weighted histogram over uniform bins
-  const float mn0 = key_score((unsigned)L.res[4]), mx0 = key_score((unsigned)L.res[5]);
-  const float mn1 = key_score((unsigned)L.res[6]), mx1 = key_score((unsigned)L.res[7]);
-  const float lo = __fadd_rn(mn0, mn1), hi = __fadd_rn(mx0, mx1), width = hi - lo;
+// The classes of all pairs by exact score keys: 0 below the K-th largest score, 1 at it, 2 above; visible behind a barrier of the
+// caller's.  `count`: middle tokens of this thread's slots; `hist` is zero on entry.
+// The pair scores, weighted by their counts, are counted into uniform bins; the few pairs of the bin that holds the K-th largest
+// are then ranked.  Scores use the same fp32 order as everywhere.
+template <int NT>
+__device__ __forceinline__ void pair_classes(const Shape& s, const float* lut, float lo, float hi, const unsigned (&count)[kPairPer], PairLds& L,
+                                             unsigned* hist, int* scan_sm) {
+  static_assert(NT * kPairPer == kPairSlots, "one thread per eight slots");
+  const int tid = threadIdx.x;
+  const float width = hi - lo;
   const float inv = (width > 1e-30f && width < 3e38f) ? (float)kNB / width : 0.0f;
-  unsigned pkey[PPT];
-  int pbin[PPT];
+  float sc[kPairPer];
+  unsigned key[kPairPer];
+  int bin[kPairPer];
+  pair_scores(lut, sc);
+  if (tid == 0) L.res[0] = L.res[1] = 0;
 #pragma unroll
-  for (int x = 0; x < PPT; ++x) {
-    const int pr = x * NT + tid;
-    int c1, c0;
-    if (C == kPairC) {  // uniform; spares an integer division per pair
-      c1 = pr >> 6;
-      c0 = pr & (kPairC - 1);
-    } else {
-      c1 = min(pr, np - 1) / C;
-      c0 = min(pr, np - 1) - c1 * C;
-    }
-    const float sc = __fadd_rn(L.lut[c0], L.lut[kPairC + c1]);
-    pkey[x] = score_key(sc);
-    pbin[x] = max(0, min(kNB - 1, __float2int_rz((sc - lo) * inv)));
-    pc[x] = pr < np ? L.cnt[pr] : 0u;
-    if (pc[x]) atomicAdd(&L.hist[pbin[x]], pc[x]);
+  for (int i = 0; i < kPairPer; ++i) {
+    key[i] = score_key(sc[i]);
+    bin[i] = max(0, min(kNB - 1, __float2int_rz((sc[i] - lo) * inv)));
+    if (count[i]) atomicAdd(&hist[bin[i]], count[i]);
   }
   __syncthreads();
-  mark(11);
-  // ---- the bin that holds the K-th largest: thread tid owns bins kNB-1-(tid*BPT+e), descending
-  unsigned h[BPT];
-  int sum = 0;
+  ThresholdSearch<NT> ts;
+  ts.load(hist, 1);
+  const Threshold th = ts.resolve(s.K, -1, scan_sm);
+  unsigned kth = 0u;
+  if (th.bstar < kNB) {  // uniform
 #pragma unroll
-  for (int x = 0; x < BPT; ++x) {
-    h[x] = L.hist[kNB - 1 - (tid * BPT + x)];
-    sum += (int)h[x];
-  }
-  int total;
-  int cum = block_exclusive_scan<NT>(sum, &total, scan_sm);
-  if (tid == 0) {
-    L.res[0] = -1;  // threshold bin
-    L.res[1] = 0;   // tokens in bins above it
-  }
-  __syncthreads();
-#pragma unroll
-  for (int x = 0; x < BPT; ++x) {
-    if (s.K > 0 && cum < s.K && cum + (int)h[x] >= s.K) {
-      L.res[0] = kNB - 1 - (tid * BPT + x);
-      L.res[1] = cum;
-    }
-    cum += (int)h[x];
-  }
-  __syncthreads();
-  const int bstar = L.res[0];
-  const int want = s.K - L.res[1];  // rank of the K-th largest among the tokens of bin bstar (1-based)
-  PairThreshold out;
-  out.none = bstar < 0;
-  out.key = 0xffffffffu;
-  if (bstar < 0) return out;  // uniform
-  mark(12);
-  // ---- the pairs of that bin
-#pragma unroll
-  for (int x = 0; x < PPT; ++x)
-    if (pc[x] && pbin[x] == bstar) {
-      const int slot = atomicAdd(&L.res[2], 1);
-      if (slot < kPairList) L.lst[slot] = ((unsigned long long)pkey[x] << 32) | pc[x];
-    }
-  __syncthreads();
-  const int n_in = L.res[2];
-  if (n_in <= kPairList) {
-    if (tid < n_in) {
-      const unsigned long long mine = L.lst[tid];
+    for (int i = 0; i < kPairPer; ++i)
+      if (count[i] && bin[i] == th.bstar) {
+        const int slot = atomicAdd(&L.res[0], 1);
+        if (slot < kPairList) L.lst[slot] = ((unsigned long long)key[i] << 32) | count[i];
+      }
+    __syncthreads();
+    const int n_in = L.res[0];
+    if (n_in <= 64) {  // uniform; the usual case: every wave ranks them by itself, a pair per lane
+      const int lane = tid & 63;
+      const unsigned long long mine = L.lst[min(lane, n_in - 1)];
       const unsigned mk = (unsigned)(mine >> 32);
-      long long above = 0, same = 0;
-      for (int j0 = 0; j0 < n_in; j0 += 8) {  // eight independent LDS reads per round
-        unsigned long long o[8];
+      unsigned above = 0u, same = 0u;
+      for (int j0 = 0; j0 < n_in; j0 += 4) {  // four independent LDS reads per round
+        unsigned long long o[4];
 #pragma unroll
-        for (int x = 0; x < 8; ++x) o[x] = L.lst[min(j0 + x, n_in - 1)];
+        for (int x = 0; x < 4; ++x) o[x] = L.lst[min(j0 + x, n_in - 1)];
 #pragma unroll
-        for (int x = 0; x < 8; ++x) {
+        for (int x = 0; x < 4; ++x) {
           const unsigned ok = (unsigned)(o[x] >> 32), oc = j0 + x < n_in ? (unsigned)o[x] : 0u;
           above += ok > mk ? oc : 0u;
           same += ok == mk ? oc : 0u;
         }
       }
-      if (above < want && want <= above + same) L.res[3] = (int)mk;
-    }
-    __syncthreads();
-    out.key = (unsigned)L.res[3];
-  } else {
-    // many pairs share the bin (nearly equal scores): 8-bit radix search over their keys
-    unsigned prefix = 0u;
-    long long w = want;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-      L.hist[tid] = 0u;  // 256 digits
-      __syncthreads();
-#pragma unroll
-      for (int x = 0; x < PPT; ++x)
-        if (pc[x] && pbin[x] == bstar && (shift == 24 || (pkey[x] >> (shift + 8)) == (prefix >> (shift + 8))))
-          atomicAdd(&L.hist[(pkey[x] >> shift) & 255u], pc[x]);
-      __syncthreads();
-      if (tid == 0) {
-        long long c2 = 0;
-        int dg = 255;
-        for (; dg > 0; --dg) {
-          if (c2 + (long long)L.hist[dg] >= w) break;
-          c2 += L.hist[dg];
+      const unsigned long long hit = __ballot((int)above < th.need && th.need <= (int)(above + same));
+      kth = hit ? (unsigned)__builtin_amdgcn_readlane((int)mk, __ffsll((long long)hit) - 1) : 0u;
+    } else if (n_in <= kPairList) {
+      if (tid < n_in) {
+        const unsigned long long mine = L.lst[tid];
+        const unsigned mk = (unsigned)(mine >> 32);
+        long long above = 0, same = 0;
+        for (int j = 0; j < n_in; ++j) {
+          const unsigned long long o = L.lst[j];
+          above += (unsigned)(o >> 32) > mk ? (unsigned)o : 0u;
+          same += (unsigned)(o >> 32) == mk ? (unsigned)o : 0u;
         }
-        L.res[4] = dg;
-        L.res[5] = (int)(w - c2);
+        if (above < th.need && th.need <= above + same) L.res[1] = (int)mk;
       }
       __syncthreads();
-      prefix |= (unsigned)L.res[4] << shift;
-      w = L.res[5];
-      __syncthreads();
+      kth = (unsigned)L.res[1];
+    } else {
+      // many pairs share the bin (nearly equal scores): 8-bit radix search over their keys
+      long long want = th.need;
+      for (int shift = 24; shift >= 0; shift -= 8) {
+        if (tid < 256) hist[tid] = 0u;  // digits
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kPairPer; ++i)
+          if (count[i] && bin[i] == th.bstar && (shift == 24 || (key[i] >> (shift + 8)) == (kth >> (shift + 8))))
+            atomicAdd(&hist[(key[i] >> shift) & 255u], count[i]);
+        __syncthreads();
+        if (tid == 0) {
+          long long c2 = 0;
+          int dg = 255;
+          for (; dg > 0; --dg) {
+            if (c2 + (long long)hist[dg] >= want) break;
+            c2 += hist[dg];
+          }
+          L.res[2] = dg;
+          L.res[3] = (int)(want - c2);
+        }
+        __syncthreads();
+        kth |= (unsigned)L.res[2] << shift;
+        want = L.res[3];
+        __syncthreads();
+      }
     }
-    out.key = prefix;
   }
-  return out;
+  // No score has the lowest key, so that the K-th largest's is at least 1; nothing lies above the highest.
+  const unsigned base = th.bstar < kNB ? max(kth, 1u) - 1u : 0xffffffffu;
+  unsigned c[kPairPer];
+#pragma unroll
+  for (int i = 0; i < kPairPer; ++i) c[i] = min(__builtin_elementwise_sub_sat(key[i], base), 2u);
+  store_classes(L.cls, c);
 }
 
 // ------------------------------------------------------- attention, vector ALU

@@ -33,7 +33,7 @@ struct CodeChunks {
   static constexpr int M = M_;
   static constexpr int P = 16 / M_;  // tokens per chunk
   static constexpr bool kFromCodes = true;
-  using Raw = uint4;
+  using Raw = u32x4_t;
   const uint8_t* all;       // whole code tensor
   long long total_bytes;    // its size
   long long unit_byte0;     // aligned-down byte offset of this unit's codes
@@ -59,26 +59,25 @@ struct CodeChunks {
     off = off < last_full ? off : last_full;
     off = off > 0 ? off : 0;
     const uint8_t* p = total_bytes < 16 ? spare : all + off;
-    return *reinterpret_cast<const uint4*>(p);
+    return *reinterpret_cast<const u32x4_t*>(p);
   }
   __device__ __forceinline__ void fix_tail(Raw& r, int chunk) const {
     const long long off = unit_byte0 + 16ll * chunk;
     if (off + 16 > total_bytes && off < total_bytes) {  // at most one chunk in the whole tensor
-      unsigned w[4] = {0u, 0u, 0u, 0u};
-      for (int b = 0; b < 16; ++b)
-        if (off + b < total_bytes) w[b >> 2] |= (unsigned)all[off + b] << (8 * (b & 3));
-      r = make_uint4(w[0], w[1], w[2], w[3]);
+      u32x4_t t = {0u, 0u, 0u, 0u};
+#pragma unroll 1
+      for (int b = 15; b >= 0; --b) {  // the bytes enter at the bottom and move up
+        t = u32x4_t{t[0] << 8, __builtin_amdgcn_alignbit(t[1], t[0], 24), __builtin_amdgcn_alignbit(t[2], t[1], 24), __builtin_amdgcn_alignbit(t[3], t[2], 24)};
+        if (off + b < total_bytes) t[0] |= (unsigned)all[off + b];
+      }
+      r = t;
     }
   }
   __device__ __forceinline__ float score(const Raw& r, int i) const { return score_from_word<M>(chunk_word<M>(r, i), lut); }
   // one token: the load (issue early) and the table look-up (after the table is ready)
   using One = typename CodeWord<M>::type;
   __device__ __forceinline__ One load_one(int t, int u, int N) const {
-    const uint8_t* p = all + ((long long)u * N + t) * M;
-    One w = 0;
-#pragma unroll
-    for (int j = 0; j < M; ++j) w |= (One)p[j] << (8 * j);
-    return w;
+    return (reinterpret_cast<const One*>(all) + (size_t)u * N)[(unsigned)t];  // (the tensor is 16-byte aligned)
   }
   __device__ __forceinline__ float score_one(One w) const { return score_from_word<M>(w, lut); }
   __device__ __forceinline__ float score_of_token(int t, int u, int N) const { return score_one(load_one(t, u, N)); }
@@ -120,8 +119,8 @@ struct ScoreChunks {
 // ------------------------------------------------------------------ utilities
 // Workgroups are handed to the 8 XCDs round-robin in launch order (x fastest).  The workgroups of a unit that all read its centroids
 // (and codes) share an XCD and its L2: eight units at a time are interleaved.
-__device__ __forceinline__ void unit_of_workgroup(int units, int& u, int& bx) {
-  const int nx = gridDim.x, lin = blockIdx.y * nx + blockIdx.x;
+__device__ __forceinline__ void unit_of_workgroup(int units, int nx /* workgroups per unit */, int& u, int& bx) {
+  const int lin = blockIdx.y * nx + blockIdx.x;
   if (lin < (units & ~7) * nx) {
     const int i = lin % (8 * nx);
     u = (lin / (8 * nx)) * 8 + (i & 7);
@@ -184,7 +183,7 @@ __global__ __launch_bounds__(1024) void hist_kernel(Shape s, Workspace ws, const
   __shared__ int scan_sm[2 * (NT / 64) + 1 + 2];
   const int tid = threadIdx.x, units = s.B * s.Hkv;
   int u = blockIdx.y, bx = blockIdx.x;
-  unit_of_workgroup(units, u, bx);
+  unit_of_workgroup(units, s.nblkA, u, bx);
   PQC_MARK(ws, 0, 0);
 #ifdef PQC_TRACE
   PQC_NOTE(ws, 0, 15, (__builtin_amdgcn_s_getreg(20 | (3 << 11)) & 15) | (u << 8));  // XCC_ID[3:0], unit
@@ -200,8 +199,7 @@ __global__ __launch_bounds__(1024) void hist_kernel(Shape s, Workspace ws, const
   auto issue_loads = [&]() {
 #pragma unroll
     for (int v = 0; v < VA; ++v) raw[v] = src.load(chunk0 + min(v * NT + tid, chunks - 1));
-    const int sample_i = min(tid, s.sampleN - 1);
-    sample = src.load_one(min(s.N - 1, s.I + (int)(((long long)sample_i * max(0, s.N - s.I - s.L)) / s.sampleN)), u, src_stride);
+    sample = src.load_one(sample_token(s, min(tid, s.sampleN - 1)), u, src_stride);
   };
   float2 bounds;
   if constexpr (SRC::kFromCodes) {
@@ -286,168 +284,405 @@ __global__ __launch_bounds__(1024) void hist_kernel(Shape s, Workspace ws, const
 // 8 consecutive tokens and counts are prefix-summed across lanes and waves; then the selected tokens (ascending) are written to the
 // front of one list in LDS and the boundary-bin candidates to its end.  SRC is only used to score the few candidates exactly.
 // (A list per wave took a search over the waves' counts at every look-up; 131072 tokens x 8 heads, a layer: 35.8 us, now 35.2.)
-constexpr int kMaxVecC = 4;  // 8-token groups per lane (tokC <= 8192)
 
-// Where the threshold comes from.  kBins: from the histogram kernel in front.  kPairs (M = 2 only): from the code-pair counts
-// (pair_threshold), tokens are classified by their exact score keys; no histogram kernel.  kShort: every workgroup builds the table
-// and scores all tokens of its unit itself, so that it finds the threshold without the others; no histogram kernel either.
-//
-// kShort, why and how far: the histogram kernel of a short cache is launch, table and a scan of half a microsecond, and the select
-// kernel starts with reading back what it left.  One launch less, against a scan of the whole unit in each of its workgroups, which
-// is bound by LDS reads (M per token) and by latency: see short_cache().  A workgroup of 512 threads per compute unit (the table and
-// the waves' tiles share its LDS) keeps as many rows in flight as two of 256.
-enum class From { kBins, kPairs, kShort };
+// Where the threshold comes from.  kBins: from the histogram kernel in front.  The other forms have no histogram kernel: every workgroup
+// builds the table itself and finds the threshold without the others.
+//   kPairs  (M = 2, up to 64 centroids) from code-pair counts of the caller's (pair_classes); tokens above it are those with a higher
+//           exact score, its own are the candidates.
+//   kCount  (M = 2, up to 64 centroids) from code-pair counts that the workgroup takes of all tokens of its unit while the table is built:
+//           the pairs' scores go to the bins that the histogram kernel would have put the tokens into.
+//   kShort  (M = 2 or 4) scores all tokens of its unit.
+// In the last two the launch of the histogram kernel, its table and what it leaves in memory are saved, against work in each workgroup that
+// grows with the unit: one LDS addition per token (kCount), or M look-ups and a bin (kShort); see short_cache().  A workgroup of 512
+// threads per compute unit (the table and the waves' tiles share its LDS) keeps as many rows in flight as two of 256, and does
+// what does not depend on its own tokens once instead of twice.
+enum class From { kBins, kPairs, kCount, kShort };
 template <From FROM>
-constexpr int select_threads() { return FROM == From::kShort ? 512 : 256; }
+constexpr int select_threads() { return FROM == From::kBins ? 256 : 512; }
 constexpr int kShortChunks = 4;  // 16-byte code chunks per thread and step, the next step's in flight
-// dynamic LDS of the kShort form: the centroid tile, then (over it) V tiles, the waves' states, the list and the own tokens' bins
+// kCount: while two waves build the table the other six count, kCountEarly chunks per thread (about as long as the table takes), requested
+// in front of the wait for the centroids; then all count the rest, kCountChunks per thread under way (together 33792 tokens).
+constexpr int kCountEarly = 3;
+constexpr int kCountChunks = 6;
+constexpr int max_tokens_per_select(From f) { return f == From::kPairs ? 16384 : 8192; }
+// Of the two the one with counted pairs wherever there are few enough pairs, kShort and kCount, 2x64, us per layer, bf16, 4 query heads per
+// unit, a tenth retrieved: 8 units of 2048 tokens 15.6, 15.7, of 8192 16.9, 16.4, of 16384 19.1, 17.7, of 24576 21.7, 19.3; 1 unit of 4096 15.3, 15.3.
+inline bool counts_pairs(const Shape& s) { return s.M == 2 && s.C <= kPairC; }
 template <From FROM>
 constexpr size_t list_bytes(int tokC) { return ((size_t)tokC + select_threads<FROM>()) * sizeof(unsigned short); }
 template <From FROM>
 constexpr int tiles_bytes(bool mfma) { return mfma ? select_threads<FROM>() / 64 * kVTileBytes : 16; }
 template <From FROM>
 constexpr int states_bytes(int G) { return select_threads<FROM>() / 64 * G * (kD + 2) * (int)sizeof(float); }
-constexpr size_t short_work_bytes(int tokC, int G, bool mfma) {
-  return tiles_bytes<From::kShort>(mfma) + states_bytes<From::kShort>(G) + list_bytes<From::kShort>(tokC) + (size_t)tokC * 2;
-}
-inline size_t short_lds_bytes(const Shape& s, bool mfma) {
-  const size_t tile = (size_t)lut_tile_floats(select_threads<From::kShort>(), s.M, s.C) * sizeof(float), work = short_work_bytes(s.tokC, s.G, mfma);
+// Dynamic LDS of the forms with a table of their own: the centroid tile, then (over it) V tiles, the waves' states, the list and the
+// own tokens' bins (kShort).
+template <From FROM>
+constexpr size_t table_form_lds_bytes(const Shape& s, bool mfma) {
+  const size_t tile = (size_t)lut_tile_floats(select_threads<FROM>(), s.M, s.C) * sizeof(float);
+  const size_t work = tiles_bytes<FROM>(mfma) + states_bytes<FROM>(s.G) + list_bytes<FROM>(s.tokC) + (FROM == From::kShort ? (size_t)s.tokC * 2 : 0);
   return tile > work ? tile : work;
 }
 
-template <typename T, int G, class SRC, bool ATTN, From FROM = From::kBins, int VW = 1 /* kShort: 16-byte pieces of the centroids per thread */>
+// The workgroup's own tokens [lo, hi): what is known of each is kept in LDS, two bytes a token.
+struct OwnTokens {
+  unsigned short* at;
+  int lo, hi;
+};
+template <int P>
+__device__ __forceinline__ void keep_own(const OwnTokens& own, int lead, int t0, const unsigned (&v)[P]) {
+  if (t0 + P > own.lo && t0 < own.hi) {
+    if (lead == 0) {  // uniform; then a chunk is the workgroup's as a whole (tokC is a multiple of P)
+      unsigned short* dst = own.at + (t0 - own.lo);
+      unsigned pw[P / 2];
+#pragma unroll
+      for (int i = 0; i < P / 2; ++i) pw[i] = v[2 * i] | (v[2 * i + 1] << 16);
+      if constexpr (P == 4) *reinterpret_cast<uint2*>(dst) = make_uint2(pw[0], pw[1]);
+      if constexpr (P == 8) *reinterpret_cast<uint4*>(dst) = make_uint4(pw[0], pw[1], pw[2], pw[3]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < P; ++i)
+        if (t0 + i >= own.lo && t0 + i < own.hi) own.at[t0 + i - own.lo] = (unsigned short)v[i];
+    }
+  }
+}
+// kCount: the chunks that hold middle tokens only, and the middle tokens beside them (fewer than eight at each end).
+struct MiddleChunks {
+  int n;               // chunks
+  int head, head_end;  // tokens in front
+  int tail, tail_end;  // tokens behind
+  const uint8_t* base;
+  __device__ __forceinline__ MiddleChunks(const CodeChunks<2>& src, int mid_lo, int mid_hi) {
+    const int first = (mid_lo + src.lead + 7) / 8;
+    n = max(0, (mid_hi + src.lead) / 8 - first);
+    head = mid_lo;
+    head_end = min(first * 8 - src.lead, mid_hi);
+    tail = max((first + n) * 8 - src.lead, head_end);
+    tail_end = mid_hi;
+    base = n > 0 ? src.all + src.unit_byte0 + 16ll * first : src.spare;
+  }
+  // (the chunk nearest to c; all of them lie inside the tensor)
+  __device__ __forceinline__ u32x4_t load(int c) const {
+    return *reinterpret_cast<const u32x4_t*>(base + 16u * (unsigned)max(min(c, n - 1), 0));
+  }
+};
+struct Absent {
+  template <class... A>
+  __device__ __forceinline__ Absent(const A&...) {}
+};
+// Counts the pairs of the chunks from `begin` on below `end`, NT threads (`t`: this one) in turns of one chunk each, U of a thread under
+// way: its first U have been requested, and a chunk's registers take the next one as soon as it has been read.  One addition per token,
+// bound by LDS: 64 lanes in 64 random places of 4096 take 9 clocks (32768 tokens 2.0 us).  The code is kept small: that of a step's
+// kernels lives in 64 KB of instruction cache.  Chunks whose lanes meet in one address (padding, a repeated token: they add one after the
+// other, two clocks each) are read again in a part of its own.
+template <int NT, int U>
+__device__ __forceinline__ void count_pairs(u32x4_t (&code)[U], const MiddleChunks& m, int begin, int end, int t, unsigned* cnt) {
+  const int lane = threadIdx.x & 63;
+  for (int c0 = begin; c0 < end; c0 += U * NT) {
+    unsigned crowded = 0u;  // wave-uniform: turns with such chunks
+#pragma unroll
+    for (int v = 0; v < U; ++v) {
+      if (c0 + v * NT < end) {  // uniform
+        const int c = c0 + v * NT + t;
+        unsigned slot[8];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pair_slots(code[v][k], slot[2 * k], slot[2 * k + 1]);
+        if (c0 + (U + v) * NT < end) code[v] = m.load(c + U * NT);  // uniform
+        if (__popcll(__ballot(c < end && slot[0] == (unsigned)__builtin_amdgcn_readfirstlane((int)slot[0]))) >= 32) {
+          crowded |= 1u << v;
+        } else if (c < end) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) atomicAdd(&cnt[slot[i]], 1u);
+        }
+      }
+    }
+    while (crowded) {  // wave-uniform
+      const int c = c0 + (__ffs((int)crowded) - 1) * NT + t;
+      crowded &= crowded - 1u;
+      if (c < end) {
+        const u32x4_t r = m.load(c);
+#pragma unroll 1
+        for (int i = 0; i < 8; ++i) {
+          unsigned s0, s1;
+          pair_slots(i < 2 ? r[0] : i < 4 ? r[1] : i < 6 ? r[2] : r[3], s0, s1);
+          const unsigned slot = i & 1 ? s1 : s0, first = (unsigned)__builtin_amdgcn_readfirstlane((int)slot);
+          const unsigned long long same = __ballot(slot == first);  // counted in one go
+          if (slot != first) atomicAdd(&cnt[slot], 1u);
+          else if (lane == __ffsll((long long)same) - 1) atomicAdd(&cnt[first], (unsigned)__popcll(same));
+        }
+      }
+    }
+  }
+}
+// Codes of the eight tokens from t on, two partitions.  (A unit's tokens need not begin at a multiple of 16 bytes; global loads take
+// any address.)  A load that would reach beyond the tensor is moved back, and mended by fix.
+struct OwnCodes {
+  const uint8_t* base;  // of the unit
+  int room;             // bytes from there to the tensor's end, or more than any token's place
+  __device__ __forceinline__ OwnCodes(const CodeChunks<2>& src, int u, int cap) {
+    const long long at = (long long)u * cap * 2, left = src.total_bytes - at;
+    room = (int)min(left, 1ll << 24);
+    base = left < 16 ? src.spare : src.all + at;
+  }
+  __device__ __forceinline__ u32x4_t load(int t) const {
+    u32x4_t r;
+    __builtin_memcpy(&r, base + (unsigned)max(min(2 * t, room - 16), 0), 16);
+    return r;
+  }
+  __device__ __forceinline__ void fix(const CodeChunks<2>& src, int u, int cap, int t, u32x4_t& r) const {
+    if (__any(2 * t + 16 > room)) {  // wave-uniform, the last tokens of the tensor
+      r = u32x4_t{0u, 0u, 0u, 0u};
+#pragma unroll 1
+      for (int i = 7; i >= 0; --i) {  // tokens enter at the bottom and move up
+        r = u32x4_t{r[0] << 16, __builtin_amdgcn_alignbit(r[1], r[0], 16), __builtin_amdgcn_alignbit(r[2], r[1], 16), __builtin_amdgcn_alignbit(r[3], r[2], 16)};
+        if (2 * (t + i) + 2 <= room) r[0] |= src.load_one(t + i, u, cap);
+      }
+    }
+  }
+};
+// kShort: middle tokens per score bin, and the stored bins of the workgroup's own tokens.
+template <int NT, int U, class SRC>
+__device__ __forceinline__ void bin_scores(const SRC& src, typename SRC::Raw (&code)[U], int chunks, int mid_lo, int mid_hi, const OwnTokens& own,
+                                           const BinMap& map, unsigned* hist /* [kNB + 64] */) {
+  constexpr int P = SRC::P;
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int c0 = 0; c0 < chunks; c0 += U * NT) {
+#pragma unroll
+    for (int v = 0; v < U; ++v) {
+      const int c = c0 + v * NT + tid;
+      if (c < chunks) {
+        src.fix_tail(code[v], c);
+        const int t0 = c * P - src.lead;
+        unsigned st[P], hb[P];
+#pragma unroll
+        for (int i = 0; i < P; ++i) hb[i] = st[i] = score_bin(src.score(code[v], i), map);
+        if (t0 < mid_lo || t0 + P > mid_hi) {
+#pragma unroll
+          for (int i = 0; i < P; ++i) {
+            const bool mid = t0 + i >= mid_lo && t0 + i < mid_hi;
+            st[i] = mid ? st[i] : kBinWindow;
+            hb[i] = mid ? hb[i] : 0u;
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < P; ++i) atomicAdd(&hist[hb[i] ? hb[i] : kNB + lane], 1u);
+        keep_own<P>(own, src.lead, t0, st);
+      }
+      if (c0 + (U + v) * NT < chunks) code[v] = src.load(min(c + U * NT, chunks - 1));  // uniform
+    }
+  }
+}
+
+template <typename T, int G, class SRC, bool ATTN, From FROM = From::kBins, int VW = 1 /* 16-byte pieces of the centroids per thread, for the table */>
 __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape s, Workspace ws, const T* __restrict__ q,
                                                      const T* __restrict__ kc, const T* __restrict__ vc,
                                                      const void* __restrict__ src_ptr,
                                                      const float* __restrict__ cent = nullptr,
                                                      const unsigned* __restrict__ pair_counts = nullptr,
                                                      int uncounted = -1 /* kPairs: a window token not in the counts yet */) {
-  constexpr bool PAIRS = FROM == From::kPairs, SHORT = FROM == From::kShort;
+  constexpr bool PAIRS = FROM == From::kPairs, COUNT = FROM == From::kCount, SHORT = FROM == From::kShort;
+  constexpr bool TABLE = FROM != From::kBins;
   constexpr int NT = select_threads<FROM>(), NW = NT / 64;
   constexpr bool kMfma = ATTN && sizeof(T) == 2 && kMatrixCoreAttention;
-  static_assert(!PAIRS || (SRC::kFromCodes && SRC::M == 2), "pair counts exist for two partitions only");
-  static_assert(!SHORT || (SRC::kFromCodes && ATTN && (SRC::P == 4 || SRC::P == 8)), "the short form is that of the decode step with two or four partitions");
+  static_assert(!(PAIRS || COUNT) || (SRC::kFromCodes && SRC::M == 2), "pair counts exist for two partitions only");
+  static_assert(!TABLE || (SRC::kFromCodes && ATTN && (SRC::P == 4 || SRC::P == 8)), "the forms with a table are those of the decode step with two or four partitions");
   constexpr int LM = SRC::kFromCodes ? SRC::M : 1;
+  constexpr int GV = max_tokens_per_select(FROM) / (8 * NT);  // 8-token groups per lane, at most
   extern __shared__ __attribute__((aligned(16))) unsigned char select_lds[];
-  constexpr int kList = SHORT ? tiles_bytes<FROM>(kMfma) + states_bytes<FROM>(G) : 0;
+  constexpr int kList = TABLE ? tiles_bytes<FROM>(kMfma) + states_bytes<FROM>(G) : 0;
   unsigned short* list = reinterpret_cast<unsigned short*>(select_lds + kList);  // [tokC] token offsets from the workgroup's first token, [NT] see below
-  __shared__ std::conditional_t<PAIRS, PairLds, int> pl;
+  __shared__ std::conditional_t<PAIRS || COUNT, PairLds, int> pl;
   __shared__ int scan_sm[2 * NW + 1 + 4];
   __shared__ int wcnt[NW];
-  __shared__ float red_own[ATTN && !SHORT ? states_bytes<FROM>(G) / 4 : 1];
+  __shared__ float red_own[ATTN && !TABLE ? states_bytes<FROM>(G) / 4 : 1];
   __shared__ float qlds[ATTN ? G * kD : 1];
-  __shared__ __attribute__((aligned(16))) unsigned char vtile_own[SHORT ? 16 : tiles_bytes<FROM>(kMfma)];
-  __shared__ float lut[SHORT ? LM * kLutRow : 1];
-  __shared__ __attribute__((aligned(16))) unsigned hist[SHORT ? kNB + 64 : 4];  // behind the bins: a place per lane for what is not counted
-  unsigned short* own_bins = list + s.tokC + NT;  // kShort: [tokC], stored form
-  unsigned char* vtile = SHORT ? select_lds : vtile_own;
-  float* red = SHORT ? reinterpret_cast<float*>(select_lds + tiles_bytes<FROM>(kMfma)) : red_own;
+  __shared__ __attribute__((aligned(16))) unsigned char vtile_own[TABLE ? 16 : tiles_bytes<FROM>(kMfma)];
+  __shared__ __attribute__((aligned(16))) float lut[TABLE ? LM * kLutRow : 1];
+  __shared__ __attribute__((aligned(16))) unsigned hist[TABLE ? kNB + 64 : 4];  // behind the bins: a place per lane for what is not counted
+  unsigned char* vtile = TABLE ? select_lds : vtile_own;
+  float* red = TABLE ? reinterpret_cast<float*>(select_lds + tiles_bytes<FROM>(kMfma)) : red_own;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if constexpr (TABLE)  // the arguments that the first loads wait for, in one go
+    asm volatile("" ::"s"(s.Hkv), "s"(s.B), "s"(s.N), "s"(s.C), "s"(s.I), "s"(s.L), "s"(s.cap), "s"(s.tokC), "s"(s.nblkC), "s"(q), "s"(src_ptr), "s"(cent));
   int u = blockIdx.y, bx = blockIdx.x;
-  if constexpr (SHORT) unit_of_workgroup(s.B * s.Hkv, u, bx);
+  if constexpr (TABLE) unit_of_workgroup(s.B * s.Hkv, s.nblkC, u, bx);
   const int b = u / s.Hkv, g = u % s.Hkv;
   PQC_MARK(ws, 1, 0);
   const int tpw = s.tokC / NW;           // tokens per wave, in groups of 8 per lane
   const int gpw = (tpw + 511) / 512;     // groups per lane: 1, 2 or 4 (the last lanes idle when tpw < 512)
   const int wave_t0 = bx * s.tokC + w * tpw;
-  uint4 raw[kMaxVecC];
+  u32x4_t raw[GV];
   Threshold th{0, 0, 0, 0};
-  PairThreshold pth{0u, true};
-  if constexpr (SHORT) {
+  unsigned short* own = nullptr;  // kShort: [tokC] stored bins
+  if constexpr (TABLE) {
+    own = reinterpret_cast<unsigned short*>(select_lds + kList + list_bytes<FROM>(s.tokC));
     __shared__ __attribute__((aligned(16))) float qs[kD];
-    __shared__ float lut_red[32];
+    [[maybe_unused]] __shared__ float lut_red[32];
     SRC src;
     src.init(src_ptr, u, s.cap, s.B * s.Hkv, lut, ws.hist);
     const int chunks = (s.N + src.lead + SRC::P - 1) / SRC::P;  // of the unit
-    typename SRC::Raw code[kShortChunks];
+    [[maybe_unused]] const std::conditional_t<COUNT, MiddleChunks, Absent> mids(src, s.I, s.N - s.L);
+    [[maybe_unused]] int n_early = 0;  // kCount: chunks counted while the table is built
+    if constexpr (COUNT) n_early = min(mids.n, kCountEarly * (NT - 128));
+    [[maybe_unused]] unsigned short edge = 0;  // kCount: the code word of a token beside those chunks
+    constexpr int U = PAIRS ? 1 : COUNT ? kCountChunks : kShortChunks;
+    typename SRC::Raw code[U];
+    [[maybe_unused]] u32x4_t early[kCountEarly];
     constexpr int PS = 1024 / NT, QN = (G * kD + NT - 1) / NT;
     typename SRC::One sample[PS];
-    auto issue_loads = [&]() {
+    u32x4_t given[kPairPer / 4];  // kPairs: the counts of this thread's slots
+    unsigned short wcode = 0;  // kPairs: this thread's first window token (the usual case: I + L <= NT)
+    [[maybe_unused]] const std::conditional_t<PAIRS || COUNT, OwnCodes, Absent> own_codes(src, u, s.cap);
+    auto own_token = [&](int v) -> int { return min(wave_t0 + min((v * 64 + lane) * 8, tpw - 8), s.N - 1); };
+    auto issue_early = [&]() {
+      if constexpr (COUNT) {
 #pragma unroll
-      for (int x = 0; x < PS; ++x) {
-        const int i = min(x * NT + tid, s.sampleN - 1);
-        sample[x] = src.load_one(min(s.N - 1, s.I + (int)(((long long)i * max(0, s.N - s.I - s.L)) / s.sampleN)), u, s.cap);
-      }
-#pragma unroll
-      for (int v = 0; v < kShortChunks; ++v) code[v] = src.load(min(v * NT + tid, chunks - 1));
-    };
-    float qv[QN];
-#pragma unroll
-    for (int x = 0; x < QN; ++x) qv[x] = load_as_float<T>(q + ((size_t)b * s.Hq + (size_t)g * G) * kD, min(x * NT + tid, G * kD - 1));
-    for (int i = tid; i < kNB; i += NT) hist[i] = 0u;
-    auto mark = [&](int) {};
-    const float2 bounds = build_lut<T, NT, LM, decltype(mark), decltype(issue_loads), VW>(
-        q + ((size_t)b * s.Hq + (size_t)g * G) * kD, cent + (size_t)u * LM * s.C * (kD / LM), G, s.C, lut, qs, lut_red,
-        reinterpret_cast<float*>(select_lds), mark, issue_loads);
-#pragma unroll
-    for (int x = 0; x < QN; ++x)
-      if (x * NT + tid < G * kD) qlds[x * NT + tid] = qv[x];
-    float sample_score[PS];
-#pragma unroll
-    for (int x = 0; x < PS; ++x) sample_score[x] = src.score_one(sample[x]);
-    const BinMap map = sample_window<NT, PS>(bounds.x, bounds.y, sample_score, s.sampleN, s.rankHi, s.rankLo, hist, scan_sm);
-    PQC_MARK(ws, 1, 9);
-    const int own_lo = bx * s.tokC, own_hi = own_lo + s.tokC;
-    for (int c0 = 0; c0 < chunks; c0 += kShortChunks * NT) {
-      typename SRC::Raw next[kShortChunks];
-      if (c0 + kShortChunks * NT < chunks) {
-#pragma unroll
-        for (int v = 0; v < kShortChunks; ++v) next[v] = src.load(min(c0 + (kShortChunks + v) * NT + tid, chunks - 1));
+        for (int v = 0; v < kCountEarly; ++v) early[v] = mids.load(v * (NT - 128) + tid - 128);
       }
       PQC_LOADS_ISSUED();
+      if constexpr (PAIRS || COUNT) {
 #pragma unroll
-      for (int v = 0; v < kShortChunks; ++v) {
-        const int c = c0 + v * NT + tid;
-        if (c < chunks) {
-          src.fix_tail(code[v], c);
-          const int t0 = c * SRC::P - src.lead;
-          unsigned st[SRC::P], hb[SRC::P];
-#pragma unroll
-          for (int i = 0; i < SRC::P; ++i) hb[i] = st[i] = score_bin(src.score(code[v], i), map);
-          if (t0 < s.I || t0 + SRC::P > s.N - s.L) {
-#pragma unroll
-            for (int i = 0; i < SRC::P; ++i) {
-              const bool mid = t0 + i >= s.I && t0 + i < s.N - s.L;
-              st[i] = mid ? st[i] : kBinWindow;
-              hb[i] = mid ? hb[i] : 0u;
-            }
-          }
-#pragma unroll
-          for (int i = 0; i < SRC::P; ++i) atomicAdd(&hist[hb[i] ? hb[i] : kNB + lane], 1u);
-          if (t0 + SRC::P > own_lo && t0 < own_hi) {
-            if (src.lead == 0) {  // uniform; then a chunk is the workgroup's as a whole (tokC is a multiple of P)
-              unsigned short* dst = own_bins + (t0 - own_lo);
-              unsigned pw[SRC::P / 2];
-#pragma unroll
-              for (int i = 0; i < SRC::P / 2; ++i) pw[i] = st[2 * i] | (st[2 * i + 1] << 16);
-              if constexpr (SRC::P == 4) *reinterpret_cast<uint2*>(dst) = make_uint2(pw[0], pw[1]);
-              if constexpr (SRC::P == 8) *reinterpret_cast<uint4*>(dst) = make_uint4(pw[0], pw[1], pw[2], pw[3]);
-            } else {
-#pragma unroll
-              for (int i = 0; i < SRC::P; ++i)
-                if (t0 + i >= own_lo && t0 + i < own_hi) own_bins[t0 + i - own_lo] = (unsigned short)st[i];
-            }
-          }
-        }
+        for (int i = 0; i < kPairPer / 4; ++i) reinterpret_cast<uint4*>(pl.cnt)[i * NT + tid] = make_uint4(0u, 0u, 0u, 0u);
+        if (tid < kSampleBins / 4) reinterpret_cast<uint4*>(pl.samples)[tid] = make_uint4(0u, 0u, 0u, 0u);
       }
+      reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
+    };
+    auto issue_loads = [&]() {
+      if constexpr (PAIRS) {
+        const unsigned* pc = pair_counts + (size_t)u * s.C * s.C;
+        const int c0 = (tid & 7) * 8, c1 = tid >> 3;
+        if (s.C == kPairC) {  // uniform
+          given[0] = reinterpret_cast<const u32x4_t*>(pc)[2 * tid];
+          given[1] = reinterpret_cast<const u32x4_t*>(pc)[2 * tid + 1];
+        } else {
 #pragma unroll
-      for (int v = 0; v < kShortChunks; ++v) code[v] = next[v];
+          for (int i = 0; i < kPairPer; ++i) given[i / 4][i % 4] = pc[min(c1, s.C - 1) * s.C + min(c0 + i, s.C - 1)];
+        }
+        const int wt = min(max(tid - 128, 0), max(s.I + s.L - 1, 0)), t = wt < s.I ? wt : s.N - s.L + (wt - s.I);
+        wcode = src.load_one(min(max(t, 0), s.N - 1), u, s.cap);
+      } else if constexpr (COUNT) {
+#pragma unroll
+        for (int x = 0; x < PS; ++x) sample[x] = src.load_one(sample_token(s, min(x * NT + tid, s.sampleN - 1)), u, s.cap);
+        edge = src.load_one(min(max((tid & 8 ? mids.tail : mids.head) + (tid & 7), 0), s.N - 1), u, s.cap);
+#pragma unroll
+        for (int v = 0; v < U; ++v)
+          if (n_early + v * NT < mids.n) code[v] = mids.load(n_early + v * NT + tid);  // uniform
+      } else {
+#pragma unroll
+        for (int x = 0; x < PS; ++x) sample[x] = src.load_one(sample_token(s, min(x * NT + tid, s.sampleN - 1)), u, s.cap);
+#pragma unroll
+        for (int v = 0; v < U; ++v)
+          if (v * NT < chunks) code[v] = src.load(min(v * NT + tid, chunks - 1));  // uniform
+      }
+      if constexpr (PAIRS || COUNT) {
+#pragma unroll
+        for (int v = 0; v < GV; ++v)
+          if (v < gpw) raw[v] = own_codes.load(own_token(v));  // uniform
+      }
+    };
+    static_assert(kNB == 4 * NT, "one 16-byte piece per thread");
+    const T* qu = q + ((size_t)b * s.Hq + (size_t)g * G) * kD;
+    const float* cu = cent + (size_t)u * LM * s.C * (kD / LM);
+    float* tile = reinterpret_cast<float*>(select_lds);
+    float qv[QN];
+#pragma unroll
+    for (int x = 0; x < QN; ++x) qv[x] = load_as_float<T>(qu, min(x * NT + tid, G * kD - 1));
+    auto mark = [&](int slot) {};
+    auto store_query = [&]() {
+#pragma unroll
+      for (int x = 0; x < QN; ++x)
+        if (x * NT + tid < G * kD) qlds[x * NT + tid] = qv[x];
+    };
+    if constexpr (PAIRS || COUNT) {
+      lut_stage<T, NT, LM, VW>(qu, cu, G, s.C, qs, tile, mark, issue_early, issue_loads);
+      store_query();
+      __syncthreads();
+      PQC_MARK(ws, 1, 11);
+#pragma unroll
+      for (int v = 0; v < GV; ++v)
+        if (v < gpw) own_codes.fix(src, u, s.cap, own_token(v), raw[v]);
+      if (w < 2) {
+        float lo, hi;
+        pair_table(tile, qs, s.C, w, lut, lo, hi);
+        if (lane == 0) {
+          pl.bounds[2 * w] = lo;
+          pl.bounds[2 * w + 1] = hi;
+        }
+      } else if constexpr (PAIRS) {  // the window tokens among the counted ones
+        for (int wt = tid - 128; wt < s.I + s.L; wt += NT - 128) {
+          const int t = wt < s.I ? wt : s.N - s.L + (wt - s.I);
+          unsigned cw = wcode;
+          if (wt >= NT - 128) cw = src.load_one(t, u, s.cap);
+          // (a code outside [0, C) was never counted)
+          if ((cw & 0xffu) < (unsigned)s.C && (cw >> 8) < (unsigned)s.C && t != uncounted) atomicAdd(&pl.cnt[(cw & 0xffu) + kPairC * (cw >> 8)], 1u);
+        }
+      } else {
+        count_pairs<NT - 128, kCountEarly>(early, mids, 0, n_early, tid - 128, pl.cnt);
+      }
+      __syncthreads();
+      PQC_MARK(ws, 1, 12);
+      const float lo = __fadd_rn(pl.bounds[0], pl.bounds[2]), hi = __fadd_rn(pl.bounds[1], pl.bounds[3]);  // added like a score, so that lo <= score <= hi in fp32
+      if constexpr (COUNT) {
+        const float inv_u = sample_scale(lo, hi);
+#pragma unroll
+        for (int x = 0; x < PS; ++x)
+          if (x * NT + tid < s.sampleN) atomicAdd(&pl.samples[sample_bin(src.score_one(sample[x]), lo, inv_u)], 1u);
+        if (tid < 16 && (tid & 8 ? mids.tail + (tid & 7) < mids.tail_end : mids.head + (tid & 7) < mids.head_end)) {
+          unsigned s0, s1;
+          pair_slots(edge, s0, s1);
+          atomicAdd(&pl.cnt[s0], 1u);
+        }
+        count_pairs<NT, U>(code, mids, n_early, mids.n, tid, pl.cnt);
+        __syncthreads();
+      }
+      PQC_MARK(ws, 1, 9);
+      const uint4 x = reinterpret_cast<const uint4*>(pl.cnt)[2 * tid], y = reinterpret_cast<const uint4*>(pl.cnt)[2 * tid + 1];
+      unsigned count[kPairPer] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+      if constexpr (PAIRS) {
+        const int c0 = (tid & 7) * 8, c1 = tid >> 3;
+#pragma unroll
+        for (int i = 0; i < kPairPer; ++i) count[i] = c1 < s.C && c0 + i < s.C ? given[i / 4][i % 4] - count[i] : 0u;
+        pair_classes<NT>(s, lut, lo, hi, count, pl, hist, scan_sm);
+        th.bstar = 1;
+        __syncthreads();
+      } else {
+        int b_hi, b_lo;  // (every wave walks the samples by itself)
+        walk_samples<false>(pl.samples, s.rankHi, s.rankLo, b_hi, b_lo);
+        const BinMap map = window_bins(lo, hi, b_hi, b_lo);
+        float sc[kPairPer];
+        unsigned bin[kPairPer];
+        pair_scores(lut, sc);
+#pragma unroll
+        for (int i = 0; i < kPairPer; ++i) bin[i] = score_bin(sc[i], map);
+        store_classes(pl.cls, bin);
+#pragma unroll
+        for (int i = 0; i < kPairPer; ++i)
+          if (bin[i] && count[i]) atomicAdd(&hist[bin[i]], count[i]);
+      }
+    } else {
+      reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
+      const float2 bounds = build_lut<T, NT, LM, decltype(mark), decltype(issue_loads), VW>(qu, cu, G, s.C, lut, qs, lut_red, tile, mark, issue_loads);
+      store_query();
+      float sample_score[PS];
+#pragma unroll
+      for (int x = 0; x < PS; ++x) sample_score[x] = src.score_one(sample[x]);
+      const BinMap map = sample_window<NT, PS>(bounds.x, bounds.y, sample_score, s.sampleN, s.rankHi, s.rankLo, hist, scan_sm);
+      PQC_MARK(ws, 1, 9);
+      const OwnTokens mine{own, bx * s.tokC, bx * s.tokC + s.tokC};
+      bin_scores<NT, U>(src, code, chunks, s.I, s.N - s.L, mine, map, hist);
     }
-    __syncthreads();
-    PQC_MARK(ws, 1, 10);
-    ThresholdSearch<NT> ts;
-    ts.load(hist, 1);
-    th = ts.resolve(s.K, s.N - s.I - s.L, scan_sm);
+    if constexpr (!PAIRS) {
+      __syncthreads();
+      PQC_MARK(ws, 1, 10);
+      ThresholdSearch<NT> ts;
+      ts.load(hist, 1);
+      th = ts.resolve(s.K, s.N - s.I - s.L, scan_sm);
+    }
   } else {
     // this wave's stored bins, the query and the histogram: all requested up front
-    // 16 bytes per group of 8 tokens: their stored bins, or (kPairs) their codes
-    const unsigned short* bins_u =
-        PAIRS ? reinterpret_cast<const unsigned short*>(static_cast<const uint8_t*>(src_ptr) + (size_t)u * s.cap * 2)
-              : ws.bins + (size_t)u * s.binStride;
-    const int last_group = PAIRS ? s.cap - 8 : s.binStride - 8;  // kPairs: the capacity is a multiple of 8
+    const unsigned short* bins_u = ws.bins + (size_t)u * s.binStride;
 #pragma unroll
-    for (int v = 0; v < kMaxVecC; ++v)
-      raw[v] = *reinterpret_cast<const uint4*>(bins_u + min(wave_t0 + min((v * 64 + lane) * 8, tpw - 8), last_group));
+    for (int v = 0; v < GV; ++v)
+      raw[v] = *reinterpret_cast<const u32x4_t*>(bins_u + min(wave_t0 + min((v * 64 + lane) * 8, tpw - 8), s.binStride - 8));
     constexpr int QV = ATTN ? (G * kD + NT - 1) / NT : 1;  // query elements per thread
     float qreg[QV];
     if constexpr (ATTN) {
@@ -455,57 +690,34 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
       for (int x = 0; x < QV; ++x)
         qreg[x] = load_as_float<T>(q + ((size_t)b * s.Hq + (size_t)g * G) * kD, min(x * NT + tid, G * kD - 1));
     }
-    if constexpr (PAIRS) {
-      PQC_LOADS_ISSUED();
-      if constexpr (ATTN) {
+    ThresholdSearch<NT> ts;
+    ts.load(ws.hist + (size_t)u * s.histCopies * kNB, s.histCopies);
+    PQC_LOADS_ISSUED();
+    if constexpr (ATTN) {
 #pragma unroll
-        for (int x = 0; x < QV; ++x)
-          if (x * NT + tid < G * kD) qlds[x * NT + tid] = qreg[x];
-      }
-      pth = pair_threshold<T, NT>(s, q + ((size_t)b * s.Hq + (size_t)g * G) * kD, cent + (size_t)u * 2 * s.C * (kD / 2),
-                                  pair_counts + (size_t)u * s.C * s.C, static_cast<const uint8_t*>(src_ptr) + (size_t)u * s.cap * 2,
-                                  pl, scan_sm, [&](int slot) { PQC_MARK(ws, 1, slot); }, uncounted);  // syncs: qlds ready
-    } else {
-      ThresholdSearch<NT> ts;
-      ts.load(ws.hist + (size_t)u * s.histCopies * kNB, s.histCopies);
-      PQC_LOADS_ISSUED();
-      if constexpr (ATTN) {
-#pragma unroll
-        for (int x = 0; x < QV; ++x)
-          if (x * NT + tid < G * kD) qlds[x * NT + tid] = qreg[x];
-      }
-      th = ts.resolve(s.K, s.N - s.I - s.L, scan_sm);  // syncs: qlds ready
+      for (int x = 0; x < QV; ++x)
+        if (x * NT + tid < G * kD) qlds[x * NT + tid] = qreg[x];
     }
+    th = ts.resolve(s.K, s.N - s.I - s.L, scan_sm);  // syncs: qlds ready
   }
   PQC_MARK(ws, 1, 1);
 
   const int wg_t0 = bx * s.tokC;
-  constexpr int GV = SHORT ? kMaxVecC / 2 : kMaxVecC;  // groups per lane, at most
   int place[GV];   // (selected, candidates << 16) of the wave in front of the group
   int count = 0;   // the same, of the wave
-  const unsigned thr = PAIRS ? 1u : (unsigned)th.bstar;
-  // kPairs: keys below the threshold's become 0, the threshold's 1, higher ones 2 or more, without a selection by comparison (no
-  // score has the lowest key, so that the threshold's is at least 1; nothing lies above the highest).  131072 tokens x 8 heads, a
-  // layer: 35.2 us with two comparisons, three selections and a window test per token, now 34.5.
-  const unsigned pair_base = pth.none ? 0xffffffffu : max(pth.key, 1u) - 1u;
+  const unsigned thr = (unsigned)th.bstar;
 #pragma unroll
   for (int v = 0; v < GV; ++v) {
     if (v < gpw) {  // uniform
-      if constexpr (SHORT) raw[v] = *reinterpret_cast<const uint4*>(own_bins + w * tpw + min((v * 64 + lane) * 8, tpw - 8));
+      if constexpr (SHORT) raw[v] = *reinterpret_cast<const u32x4_t*>(own + w * tpw + min((v * 64 + lane) * 8, tpw - 8));
       const int t0 = wave_t0 + (v * 64 + lane) * 8;
       unsigned wv[4] = {raw[v].x, raw[v].y, raw[v].z, raw[v].w};  // two tokens each, in stored form: selected above thr, candidates at thr
-      if constexpr (PAIRS) {
+      if constexpr (PAIRS || COUNT) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          unsigned st[2];
-#pragma unroll
-          for (int y = 0; y < 2; ++y) {
-            const unsigned cw = (wv[k] >> (16 * y)) & 0xffffu;
-            const unsigned key =
-                score_key(__fadd_rn(pl.lut[min(cw & 0xffu, (unsigned)kPairC - 1)], pl.lut[kPairC + min(cw >> 8, (unsigned)kPairC - 1)]));
-            st[y] = min(__builtin_elementwise_sub_sat(key, pair_base), 2u);
-          }
-          wv[k] = st[0] | (st[1] << 16);
+          unsigned s0, s1;
+          pair_slots(wv[k], s0, s1);
+          wv[k] = pl.cls[s0] | ((unsigned)pl.cls[s1] << 16);
         }
         if (__any(t0 < s.I || t0 + 8 > s.N - s.L)) {  // uniform, rare
 #pragma unroll
@@ -536,7 +748,7 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
       const int inc = wave_inclusive_scan(cnt);
       place[v] = count + inc - cnt;
       count += wave_last(inc);
-      raw[v] = make_uint4(wv[0], wv[1], wv[2], wv[3]);
+      raw[v] = u32x4_t{wv[0], wv[1], wv[2], wv[3]};
     }
   }
   PQC_MARK(ws, 1, 8);
@@ -600,13 +812,11 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
     return k;
   };
   auto cand_score = [&](const CandKey& k) -> float {
-    if constexpr (SHORT) {
+    if constexpr (TABLE) {
       float sc = lut[k.cb[0]];
 #pragma unroll
       for (int j = 1; j < SRC::M; ++j) sc = __fadd_rn(sc, lut[j * kLutRow + k.cb[j]]);
       return sc;
-    } else if constexpr (PAIRS) {
-      return __fadd_rn(pl.lut[min(k.cb[0], (unsigned)kPairC - 1)], pl.lut[kPairC + min(k.cb[1], (unsigned)kPairC - 1)]);
     } else if constexpr (SRC::kFromCodes) {
       const float* tb = ws.lut + (size_t)u * SRC::M * s.C;
       float sc = tb[k.cb[0]];
@@ -1430,7 +1640,9 @@ __global__ __launch_bounds__(256) void merge_kernel(Shape s, Workspace ws, int n
   if (half == 0) out_attn[((size_t)b * s.Hq + (size_t)g * G + hq) * kD + d] = (acc + half_acc[d]) / lstar;
 }
 
-// The kShort form for a step of this shape (pqc_short.hip).
+// Select kernels without a histogram kernel in front (pqc_short.hip): of a decode step (kCount or kShort), and with given pair counts.
+void launch_pairs_select(bool bf16, const Shape& s, const Workspace& ws, const void* q, const float* cent, const uint8_t* codes,
+                         const unsigned* pair_counts, int uncounted, const void* k, const void* v, hipStream_t st);
 void launch_short_select(bool bf16, const Shape& s, const Workspace& ws, const void* q, const float* cent, const uint8_t* codes, const void* k,
                          const void* v, hipStream_t st);
 

@@ -366,6 +366,8 @@ def test_decode_phase_by_phase_equals_decode(pqc, n_tokens):
     dict(n_tokens=3000 - 3000 % 8, topk=2000, pq_centroids=7),       # few pairs, big tie classes
     dict(n_tokens=72, topk=1),
     dict(n_tokens=2048, n_local=300, n_init=9, topk=100),            # more window tokens than threads
+    dict(n_tokens=2048, n_local=700, n_init=9, topk=100, pq_centroids=63),
+    dict(n_tokens=8200, topk=500, batch=65, n_q_heads=4, n_kv_heads=4, kmeans_iters=1),  # 16384 tokens per workgroup
 ], ids=lambda kw: ",".join(f"{k}={v}" for k, v in kw.items()) or "scaled")
 def test_indexed_decode_equals_decode(pqc, kw):
     # threshold from code-pair counts: same selection and attention as the general path, and as the oracle

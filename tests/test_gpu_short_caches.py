@@ -51,8 +51,8 @@ def _decode_and_check(pqc, p):
 @pytest.mark.parametrize("kw", [
     dict(n_tokens=513, topk=60),                                                    # a workgroup with one token
     dict(n_tokens=16385, topk=1600, n_q_heads=2, n_kv_heads=1),                     # one chunk beyond a step of the scan
-    dict(n_tokens=16384, topk=1600),                                                # the last short length of a few units, 2 x 64
-    dict(n_tokens=22528, topk=2250, batch=4),                                       # of more units
+    dict(n_tokens=16384, topk=1600),
+    dict(n_tokens=22528, topk=2250, batch=4),
     dict(n_tokens=24576, topk=2400),
     dict(n_tokens=24577, topk=2400),
     dict(n_tokens=11264, topk=1100, pq_m=4, n_q_heads=4),                           # the last short length of a few units, 4 x 64
@@ -73,7 +73,40 @@ def test_short_caches(pqc, kw):
     _decode_and_check(pqc, build_problem(w, seed=3, checked_units=[]))
 
 
-@pytest.mark.parametrize("n_tokens", [6007, 30001])  # without and with a histogram kernel
+# Steps that count the code pairs of their unit (two partitions of up to 64 centroids): units at every alignment of the codes, middle tokens
+# beside whole chunks of eight, none of these, more chunks than are under way at a time (1152 and 3072).
+@pytest.mark.parametrize("kw", [
+    dict(n_tokens=10241, topk=1000, n_init=3, n_local=5, batch=2),
+    dict(n_tokens=10247, topk=1000, n_q_heads=5, n_kv_heads=5, pq_centroids=48, n_init=0, n_local=0),
+    dict(n_tokens=9285, topk=900, n_q_heads=2, n_kv_heads=1, pq_centroids=33),            # a chunk beyond those counted beside the table
+    dict(n_tokens=33861, topk=3000, n_q_heads=2, n_kv_heads=1, pq_centroids=17),          # a chunk beyond those under way
+    dict(n_tokens=49152, topk=9000, n_q_heads=8, n_kv_heads=1),                           # the last length of a few units; G = 8
+    dict(n_tokens=77, topk=2, n_init=30, n_local=40, batch=3),
+    dict(n_tokens=20011, topk=2000, n_q_heads=4, dtype="f32", batch=2),
+    dict(n_tokens=11000, topk=600, n_init=4001, n_local=6003),                            # more window tokens than middle ones
+    dict(n_tokens=10300, topk=3, n_init=5000, n_local=5295, n_q_heads=2, n_kv_heads=1),   # five middle tokens
+    dict(n_tokens=12289, topk=0),
+    dict(n_tokens=11111, topk=11043, n_q_heads=2, n_kv_heads=1),                          # all of them
+    dict(n_tokens=14336, topk=1400, n_q_heads=8, n_kv_heads=8, batch=16),                 # one workgroup per compute unit
+], ids=lambda kw: ",".join(f"{k}={v}" for k, v in kw.items()))
+def test_counted_pairs(pqc, kw):
+    w = _w(**kw)
+    print(f"[case] counted pairs {w}", flush=True)
+    _decode_and_check(pqc, build_problem(w, seed=5, checked_units=[]))
+
+
+@pytest.mark.parametrize("share", [0.3, 0.6, 1.0])
+def test_counted_pairs_of_repeated_codes(pqc, share):
+    # lanes that meet in one address are counted in one go; a fraction of the tokens carries one pair, or all do
+    w = _w(n_tokens=12293, topk=1200, n_init=5)
+    p = build_problem(w, seed=7, checked_units=[])
+    rng = np.random.default_rng(8)
+    codes = np.where(rng.random((1, 2, w.n_tokens, 1)) < share, np.array([13, 60], np.uint8), p.codes)
+    print(f"[case] repeated codes {share} {w}", flush=True)
+    _decode_and_check(pqc, dataclasses.replace(p, codes=np.ascontiguousarray(codes)))
+
+
+@pytest.mark.parametrize("n_tokens", [6007, 30001, 60001])  # without and (the last one) with a histogram kernel
 @pytest.mark.parametrize("where", ["below", "above"])
 def test_threshold_outside_the_window(pqc, n_tokens, where):
     # The sampled tokens (every nmid / 1024-th) all score best or all score worst, so that the K-th largest score lies below or
@@ -128,10 +161,11 @@ def _launches(call):
 
 
 @pytest.mark.parametrize("units, n_tokens, m, c, den, launches", [
-    (1, 16384, 2, 64, 10, 2), (1, 16385, 2, 64, 10, 3), (7, 16385, 2, 48, 10, 3), (8, 16385, 2, 64, 10, 2), (1, 24576, 2, 64, 10, 3),
-    (8, 22528, 2, 64, 10, 2), (8, 22529, 2, 64, 10, 3), (1, 11264, 4, 64, 10, 2), (1, 11265, 4, 64, 10, 3), (8, 12288, 4, 64, 10, 2),
-    (8, 12289, 4, 64, 10, 3), (1, 8192, 4, 256, 10, 2), (1, 8193, 4, 256, 10, 3), (1, 16384, 2, 65, 10, 2), (1, 16385, 2, 256, 10, 3),
-    (8, 2048, 8, 64, 10, 3), (8, 2048, 1, 64, 10, 3), (96, 20000, 2, 64, 20, 3), (80, 20000, 2, 64, 10, 2), (80, 20000, 2, 64, 5, 3),
+    (1, 2048, 2, 64, 10, 2), (7, 49152, 2, 64, 10, 2), (7, 49153, 2, 64, 10, 3), (8, 49153, 2, 48, 10, 2), (15, 53249, 2, 48, 10, 3),
+    (16, 57344, 2, 64, 10, 2), (31, 57345, 2, 64, 10, 3), (32, 65536, 2, 64, 5, 2), (32, 65537, 2, 64, 10, 3), (1, 11264, 4, 64, 10, 2),
+    (1, 11265, 4, 64, 10, 3), (8, 12288, 4, 64, 10, 2), (8, 12289, 4, 64, 10, 3), (1, 8192, 4, 256, 10, 2), (1, 8193, 4, 256, 10, 3),
+    (1, 16384, 2, 65, 10, 2), (1, 16385, 2, 256, 10, 3), (8, 2048, 8, 64, 10, 3), (8, 2048, 1, 64, 10, 3), (96, 20000, 2, 64, 20, 3),
+    (80, 20000, 2, 64, 10, 2), (80, 20000, 2, 64, 5, 2), (128, 12288, 2, 64, 5, 3), (128, 16384, 2, 64, 5, 2),
     (207, 8192, 2, 64, 5, 2), (208, 8192, 2, 64, 5, 3), (208, 8192, 2, 64, 7, 2), (256, 8191, 2, 64, 5, 2)])
 def test_launches_of_a_step(pqc, units, n_tokens, m, c, den, launches):
     w = _w(batch=units, n_q_heads=1, n_kv_heads=1, n_tokens=n_tokens, pq_m=m, pq_centroids=c, topk=n_tokens // den)
