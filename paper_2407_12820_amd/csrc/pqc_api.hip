@@ -187,9 +187,12 @@ int make_plan(const pqc_config* c, Plan* p, For call = For::kOther) {
   s.npart = s.nblkC > s.nblkP ? s.nblkC : s.nblkP;
   p->rec_stride = (int)cand_unit_bytes(G, c->kv_dtype == PQC_F32 ? 4 : 2);
   // finalize kernel: as many workgroups per query head (each with its share of the output dimensions) as keep the
-  // grid within about two workgroups per compute unit
+  // grid within about one workgroup per compute unit (16 units of 8 heads, 4096 tokens, us per layer: two per head, 320 workgroups, 17.8, one
+  // 17.1), and fewer that copy the lists where there are many units (64 of 20000, 4x256: four 47.7, two 46.7; 12 of 20011 fp32: two
+  // 24.2, four 23.6, six 23.1)
+  s.copyWgs = units > 32 ? 2 : units > 16 || units < 4 ? 4 : 6;
   s.slices = 1;
-  while (s.slices < kMaxSlices && units * (2 * s.slices * G + kCopyWgs) <= 512) s.slices *= 2;
+  while (s.slices < kMaxSlices && units * (2 * s.slices * G + 4) <= 256) s.slices *= 2;
   // sample ranks that bracket the K-th largest score by 5 standard errors (+2)
   const int nmid = s.N - s.I - s.L;
   s.sampleN = nmid < 1024 ? (nmid > 0 ? nmid : 1) : 1024;
@@ -318,16 +321,16 @@ void launch_hist(const Shape& s, const Workspace& ws, const T* q, const float* c
 template <typename T, int G>
 void launch_finalize(pqc_ctx* ctx, const Shape& s, const Workspace& ws, const T* qt, const T* kt, const T* vt, int32_t* out_idx,
                      float* out_attn, hipStream_t st) {
-  const dim3 grid(G * s.slices + kCopyWgs + (ctx->append.key ? 1 : 0), (unsigned)(s.B * s.Hkv));
+  const dim3 grid(G * s.slices + s.copyWgs + (ctx->append.key ? 1 : 0), (unsigned)(s.B * s.Hkv));
   // Tokens that share all their codes share a score: with few distinct code words the tie class at the threshold is
   // large (131072 tokens over 64 x 64 code pairs: up to 70 candidates), and the kernel requests more records up front.
   double words = 1.0;
   for (int j = 0; j < s.M; ++j) words *= s.C;
   if (s.slices == kMaxSlices && s.N >= 16.0 * words)
-    hipLaunchKernelGGL((finalize_kernel<T, G, true, true>), grid, dim3(256), finalize_lds_bytes(s, true), st, s, ws, qt, kt, vt,
+    hipLaunchKernelGGL((finalize_kernel<T, G, true, true>), grid, dim3(kFinalThreads), finalize_lds_bytes(s, true), st, s, ws, qt, kt, vt,
                        out_idx, out_attn, ctx->append);
   else
-    hipLaunchKernelGGL((finalize_kernel<T, G, true, false>), grid, dim3(256), finalize_lds_bytes(s, true), st, s, ws, qt, kt, vt,
+    hipLaunchKernelGGL((finalize_kernel<T, G, true, false>), grid, dim3(kFinalThreads), finalize_lds_bytes(s, true), st, s, ws, qt, kt, vt,
                        out_idx, out_attn, ctx->append);
 }
 
@@ -691,7 +694,7 @@ int pqc_topk(pqc_ctx* ctx, const float* scores, int32_t* out_idx, void* stream) 
   launch_hist<float, ScoreChunks>(s, ctx->ws, nof, nof, static_cast<const void*>(scores), 0, st);
   hipLaunchKernelGGL((select_kernel<float, 1, ScoreChunks, false>), dim3(s.nblkC, units), dim3(256), list_bytes<From::kBins>(s.tokC), st,
                      s, ctx->ws, nof, nof, nof, static_cast<const void*>(scores));
-  hipLaunchKernelGGL((finalize_kernel<float, 1, false>), dim3(1 + kCopyWgs, units), dim3(256), finalize_lds_bytes(s, false), st, s,
+  hipLaunchKernelGGL((finalize_kernel<float, 1, false>), dim3(1 + s.copyWgs, units), dim3(kFinalThreads), finalize_lds_bytes(s, false), st, s,
                      ctx->ws, nof, nof, nof, out_idx, static_cast<float*>(nullptr), AppendArgs{nullptr, nullptr, nullptr, 0, nullptr});
   rc = check_launch(ctx);
   if (rc == PQC_OK) {

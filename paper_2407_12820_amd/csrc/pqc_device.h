@@ -36,6 +36,7 @@ struct Shape {
   int rowsP, nblkP; // list-attention kernel: rows per workgroup, workgroups per unit
   int npart;        // partial slots per unit
   int slices;       // finalize kernel: workgroups per query head (1, 2 or 4), each producing kD/slices output dimensions
+  int copyWgs;      // finalize kernel: workgroups per unit that copy the index lists
   int binStride;    // stored bins per unit (nblkC * tokC)
   int stageStride;  // 8-byte words between the staging slots of consecutive select workgroups: tokC plus a pad, so that
                     // the slots do not all start on the same memory channels

@@ -951,7 +951,7 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
 }
 
 // ------------------------------------------------------------- 3. finalize
-// Grid (heads * SL + kCopyWgs, units), 256 threads; heads = the group's query heads, SL = Shape::slices (one
+// Grid (heads * SL + s.copyWgs, units), 512 threads; heads = the group's query heads, SL = Shape::slices (one
 // head, one slice for the stand-alone top-k).
 //   blockIdx.x <  heads * SL  slice blockIdx.x % SL of head blockIdx.x / SL: ranks the candidates and
 //                        folds the admitted ones and all partial softmax states into kD / SL dimensions
@@ -988,21 +988,24 @@ __device__ __forceinline__ float block_sum(float v, float* sm /* [NT/64] */) {
   return r;
 }
 
-constexpr int kHdrPerThread = kCandRec / 256;  // candidate record headers per thread
-constexpr int kAccPer = 8;                     // partial states a thread keeps in flight at once (every eighth state is its own)
-constexpr int kVPer = 12;                      // candidate records per thread whose V values are requested before the ranking knows which are admitted (96 records
-                                               // with eight threads per dimension: tie classes of two-partition tables reach 70 tokens at 128K)
-constexpr int kVPerFew = 8;                    // the same with fewer threads per dimension (many units; there the tie classes are small)
+// 512 threads: a head's work is a chain of short steps, alone on its compute unit with nothing to hide their latency, and what a thread
+// does of each is half of what it is with 256 (from the first workgroup's start to the last one's end, 8 x 131072 tokens, 2x64: 5.4 us, now
+// 4.5; 8 x 32768: 4.7, now 3.9; 64 x 32768, 4x256: 5.0 both, bound by what it reads).
+constexpr int kFinalThreads = 512;
+constexpr int kHdrPerThread = kCandRec / kFinalThreads;  // candidate record headers per thread
+constexpr int kAccPer = 4;                     // partial states a thread keeps in flight at once
+constexpr int kVPer = 6;                       // candidate records per thread whose V values are requested before the ranking knows which are admitted (96 records
+                                               // with sixteen threads per dimension: tie classes of two-partition tables reach 70 tokens at 128K)
+constexpr int kVPerFew = 4;                    // the same with fewer threads per dimension (many units; there the tie classes are small)
 constexpr int kManyCand = 4096;                // candidates whose composites the path for large tie classes keeps in LDS
 constexpr int kRankStep = 8;                    // composites read per step of the ranking loop
 constexpr int kFoldRanks = 96;                 // admitted rows whose terms meet in LDS by rank (beyond: fetched by rank from the records)
 constexpr int kMaxSlices = 4;                  // workgroups per query head, at most (32 output dimensions each)
 constexpr int kIdxLists = 4;                   // staged index lists a wave copies with loads issued up front
-constexpr int kCopyWgs = 4;                    // copy workgroups per unit
 
 // dynamic LDS of finalize_kernel
 inline size_t finalize_lds_bytes(const Shape& s, bool attn) {
-  const size_t terms = attn ? (size_t)kFoldRanks * (kD / s.slices) * sizeof(float) : 0;
+  const size_t terms = attn ? (size_t)(kFoldRanks + 1) * (kD / s.slices) * sizeof(float) : 0;  // and a spare row
   const size_t many = (size_t)kManyCand * (sizeof(unsigned long long) + sizeof(int));  // the same region, when a unit has more than kCandRec candidates
   return (size_t)(4 * s.nblkC + 2) * sizeof(int) + (terms > many ? terms : many);
 }
@@ -1017,16 +1020,35 @@ struct AppendArgs {
   unsigned* pair_counts;  // two partitions: [units][C*C] counts that gain the token's code pair, or null
 };
 
+// acc += sum_x w_j a_x, l += sum_x w_j l_j over the states j = first, first + step, ... below n, with w_j = exp2(m_j - m*).
+template <int U>
+__device__ __forceinline__ void fold_states(const float* pm, const float* pl, float mstar, int first, int step, int n, const float (&a)[U], float& acc,
+                                            float& lsum) {
+  float m[U], l[U];
+#pragma unroll
+  for (int x = 0; x < U; ++x) {
+    const int j = min(first + step * x, n - 1);
+    m[x] = pm[j];
+    l[x] = pl[j];
+  }
+#pragma unroll
+  for (int x = 0; x < U; ++x) {
+    const float w = __builtin_amdgcn_exp2f(m[x] - mstar), na = fmaf(w, a[x], acc), nl = fmaf(w, l[x], lsum);
+    acc = first + step * x < n ? na : acc;  // (a state that is not there may hold infinities)
+    lsum = first + step * x < n ? nl : lsum;
+  }
+}
+
 // WIDE: four workgroups per head (eight threads per output dimension); they request more candidate records up front.
 template <typename T, int G, bool ATTN, bool WIDE = false>
-__global__ __launch_bounds__(256) void finalize_kernel(Shape s, Workspace ws, const T* __restrict__ q,
+__global__ __launch_bounds__(kFinalThreads) void finalize_kernel(Shape s, Workspace ws, const T* __restrict__ q,
                                                        const T* __restrict__ kc, const T* __restrict__ vc,
                                                        int* __restrict__ out_idx, float* __restrict__ out_attn, AppendArgs ap) {
-  constexpr int NT = 256, NW = 4;
+  constexpr int NT = kFinalThreads, NW = NT / 64;
   constexpr int heads = ATTN ? G : 1;
   constexpr int VPER = WIDE ? kVPer : kVPerFew;
   const int SL = ATTN ? s.slices : 1;  // head workgroups per head
-  if ((int)blockIdx.x == heads * SL + kCopyWgs) {
+  if ((int)blockIdx.x == heads * SL + s.copyWgs) {
     // -------------------------------------------------------------- append workgroup
     // one thread per centroid, the distance chain of pq_round_vector_kernel, the smallest (distance, centroid) pair
     // of each partition through a 64-bit LDS minimum
@@ -1074,16 +1096,16 @@ __global__ __launch_bounds__(256) void finalize_kernel(Shape s, Workspace ws, co
   __shared__ int digit_sm[2];
   __shared__ int rows_sm[NT];
   __shared__ float red[ATTN ? NW * (kD + 2) : 1];
-  __shared__ float half_acc[ATTN ? kD : 1];
-  __shared__ float slice_sm[ATTN ? 256 : 1];  // [threads per dimension][dimensions of the workgroup]
-  __shared__ float lsm[8];
+  __shared__ float part_acc[ATTN ? NT : 1];
+  __shared__ float slice_sm[ATTN ? NT : 1];  // [threads per dimension][dimensions of the workgroup]
+  __shared__ float lsm[NW];
   const int u = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int b = u / s.Hkv, g = u % s.Hkv;
   int* pre_sel = dyn;
   int* pre_cand = dyn + (s.nblkC + 1);
   float* pm = reinterpret_cast<float*>(dyn + 2 * (s.nblkC + 1));
   float* pl = pm + s.nblkC;
-  float* terms = pl + s.nblkC;  // [kFoldRanks][dimensions of the workgroup]: weighted V values of the admitted rows, by rank
+  float* terms = pl + s.nblkC;  // [kFoldRanks + 1][dimensions of the workgroup]: weighted V values of the admitted rows, by rank
   const int2* cnt = ws.stage_cnt + (size_t)u * s.nblkC;
   const unsigned long long* stage_u = ws.stage + (size_t)u * s.nblkC * s.stageStride;
   int* out = out_idx + (size_t)u * s.Ktot;
@@ -1116,16 +1138,21 @@ __global__ __launch_bounds__(256) void finalize_kernel(Shape s, Workspace ws, co
 
   if ((int)blockIdx.x >= heads * SL) {
     // ---------------------------------------------------------------- copy workgroup
-    // one wave per list, coalesced; the local window moves behind the admitted candidates
-    const int cw = blockIdx.x - heads * SL, ncw = kCopyWgs;
+    // a wave copies 256 entries of a list at a time, coalesced; with fewer lists than waves several waves share a list, with more a wave
+    // takes every so manieth list as a whole.  The local window moves behind the admitted candidates.
+    const int cw = blockIdx.x - heads * SL, waves = s.copyWgs * NW, wid = cw * NW + w;
+    const int shares = max(1, waves / s.nblkC);              // waves per list
+    const int j_first = wid / shares, share = wid % shares;  // this wave's (first) list, and which of its waves it is
+    const int j_step = shares > 1 ? s.nblkC : waves;
     const int2 cnt0 = cnt[min(tid, s.nblkC - 1)];
-    int ix[kIdxLists][4];  // first 256 entries of this wave's first kIdxLists lists
+    int ix[kIdxLists][4];  // its first 256 * kIdxLists entries, or those 256 of its first kIdxLists lists
+    auto list_at = [&](int j) { return reinterpret_cast<const int*>(stage_u + (size_t)min(j, s.nblkC - 1) * s.stageStride); };
 #pragma unroll
     for (int x = 0; x < kIdxLists; ++x) {
-      const int j = min(cw * NW + w + x * ncw * NW, s.nblkC - 1);
-      const int* src = reinterpret_cast<const int*>(stage_u + (size_t)j * s.stageStride);
+      const int* src = list_at(shares > 1 ? j_first : j_first + x * j_step);
+      const int p0 = shares > 1 ? (share + x * shares) * 256 : 0;
 #pragma unroll
-      for (int y = 0; y < 4; ++y) ix[x][y] = src[min(y * 64 + lane, 2 * s.tokC - 1)];
+      for (int y = 0; y < 4; ++y) ix[x][y] = src[min(p0 + y * 64 + lane, 2 * s.tokC - 1)];
     }
     PQC_LOADS_ISSUED();
     int n_list, n_cand;
@@ -1133,13 +1160,13 @@ __global__ __launch_bounds__(256) void finalize_kernel(Shape s, Workspace ws, co
     const int n_above = max(0, n_list - s.I - s.L);
     const int need = max(0, min(s.K - n_above, n_cand));
     PQC_MARK(ws, 2, 1);
-    int x = 0;
-    for (int j = cw * NW + w; j < s.nblkC; j += ncw * NW, ++x) {
+    int x = 0;  // of the pieces requested above
+    for (int j = j_first; j < s.nblkC; j += j_step) {
       const int base = pre_sel[j], n = pre_sel[j + 1] - base;
-      const int* src = reinterpret_cast<const int*>(stage_u + (size_t)j * s.stageStride);
-      for (int p0 = 0; p0 < n; p0 += 256) {
+      const int* src = list_at(j);
+      for (int p0 = share * 256; p0 < n; p0 += shares * 256) {
         int v[4];
-        if (x < kIdxLists && p0 == 0) {
+        if (x < kIdxLists && (shares > 1 || p0 == 0)) {
 #pragma unroll
           for (int y = 0; y < 4; ++y) v[y] = x == 0 ? ix[0][y] : x == 1 ? ix[1][y] : x == 2 ? ix[2][y] : ix[3][y];
         } else {
@@ -1147,6 +1174,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(Shape s, Workspace ws, co
           for (int y = 0; y < 4; ++y)
             if (p0 + y * 64 + lane < n) v[y] = src[p0 + y * 64 + lane];
         }
+        if (shares > 1) ++x;
 #pragma unroll
         for (int y = 0; y < 4; ++y) {
           const int pos = base + p0 + y * 64 + lane;
@@ -1155,6 +1183,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(Shape s, Workspace ws, co
           if (p0 + y * 64 + lane < n && dst < s.Ktot) out[dst] = v[y];
         }
       }
+      if (shares == 1) ++x;
     }
     PQC_MARK(ws, 2, 4);
     if (cw == 0) {  // the select kernel was their last reader: zero histogram and record counter for the next call
@@ -1172,16 +1201,16 @@ __global__ __launch_bounds__(256) void finalize_kernel(Shape s, Workspace ws, co
   // cache lines per microsecond), so with few units the partial states of a head are spread over several workgroups,
   // each reading only its dimensions of every state, and everything a workgroup reads of the candidates is dense.
   const int hq = (int)blockIdx.x / SL, sl = (int)blockIdx.x % SL;
-  const int dims = kD / SL, nps = NT / dims;   // output dimensions of this workgroup; threads per dimension (2, 4 or 8)
+  const int dims = kD / SL, nps = NT / dims;   // output dimensions of this workgroup; threads per dimension (4, 8 or 16)
   const int dl = tid & (dims - 1), ps = tid / dims;  // dimension inside the slice; which share of the states and admitted rows
   const int d = dims * sl + dl;
   const int units = s.B * s.Hkv;
   // ---- everything whose address is known up front is requested first
   const CandView cv = cand_view(ws.cand_rec + (size_t)u * ws.rec_stride, heads);
-  unsigned long long rc[kHdrPerThread];  // candidate x*NT + tid; the first NT are requested up front
+  unsigned long long rc[kHdrPerThread];  // candidate x*NT + tid; the first 256 are requested up front
   float rl[kHdrPerThread];
-  rc[0] = cv.composite[tid];
-  rl[0] = ATTN ? cv.logit[hq * kCandRec + tid] : 0.0f;
+  rc[0] = cv.composite[tid & 255];
+  rl[0] = ATTN ? cv.logit[hq * kCandRec + (tid & 255)] : 0.0f;
   const float* pacc = ws.partials + (size_t)u * s.npart * G * kD;                                   // [j][h][kD]
   const float2* pml = reinterpret_cast<const float2*>(ws.partials + (size_t)units * s.npart * G * kD) +
                       ((size_t)u * G + hq) * s.npart;                                                // [j] of this head
@@ -1252,10 +1281,12 @@ __global__ __launch_bounds__(256) void finalize_kernel(Shape s, Workspace ws, co
     const bool meet = ATTN && need <= kFoldRanks;  // the admitted rows' terms meet in LDS, by rank
     if (need > 0) {
 #pragma unroll
-      for (int x = 1; x < kHdrPerThread; ++x) {
-        rc[x] = 0ull;
-        rl[x] = 0.0f;
-        if (x * NT + tid < n_cand) {  // rare: more than NT candidates
+      for (int x = 0; x < kHdrPerThread; ++x) {
+        if (x > 0) {
+          rc[x] = 0ull;
+          rl[x] = 0.0f;
+        }
+        if (x * NT + tid < n_cand && (x > 0 || tid >= 256)) {  // rare: more than 256 candidates
           rc[x] = cv.composite[x * NT + tid];
           rl[x] = ATTN ? cv.logit[hq * kCandRec + x * NT + tid] : 0.0f;
         }
@@ -1308,39 +1339,33 @@ __global__ __launch_bounds__(256) void finalize_kernel(Shape s, Workspace ws, co
             for (int x = 0; x < VPER; ++x)
               vv0[x] = load_as_float<T>(reinterpret_cast<const T*>(cv.v) + (size_t)min(k0 + ps + nps * x, kCandRec - 1) * kD, d);
           }
+          // (half of them at a time, all look-ups of a kind before the first of the next: one after the other they are a chain of LDS
+          // latencies; records that are not admitted go to a spare row)
+          constexpr int H = VPER / 2;
 #pragma unroll
-          for (int x = 0; x < VPER; ++x) {
-            const int k = k0 + ps + nps * x;
-            if (k < n_cand) {
-              const int r = rankv[k];
-              if (r < need) terms[r * dims + dl] = __builtin_amdgcn_exp2f(lgk[r] - mstar) * vv0[x];
+          for (int x0 = 0; x0 < VPER; x0 += H) {
+            if (k0 + nps * x0 >= n_cand) break;  // uniform
+            int r[H];
+            float lg[H];
+#pragma unroll
+            for (int x = 0; x < H; ++x) r[x] = rankv[min(k0 + ps + nps * (x0 + x), kCandRec - 1)];
+#pragma unroll
+            for (int x = 0; x < H; ++x) {
+              r[x] = k0 + ps + nps * (x0 + x) < n_cand && r[x] < need ? r[x] : kFoldRanks;
+              lg[x] = lgk[min(r[x], need - 1)];
             }
+#pragma unroll
+            for (int x = 0; x < H; ++x) terms[r[x] * dims + dl] = __builtin_amdgcn_exp2f(lg[x] - mstar) * vv0[x0 + x];
           }
         }
       }
       float acc = 0.0f, lsum = 0.0f;
-#pragma unroll
-      for (int x = 0; x < kAccPer; ++x) {
-        const int j = ps + nps * x;
-        if (j < s.nblkC) {
-          const float wj = __builtin_amdgcn_exp2f(pm[j] - mstar);
-          acc = fmaf(wj, a0[x], acc);
-          lsum = fmaf(wj, pl[j], lsum);
-        }
-      }
+      fold_states<kAccPer>(pm, pl, mstar, ps, nps, s.nblkC, a0, acc, lsum);
       for (int j0 = nps * kAccPer + ps; j0 < s.nblkC; j0 += nps * kAccPer) {
         float a[kAccPer];
 #pragma unroll
         for (int x = 0; x < kAccPer; ++x) a[x] = pacc[((size_t)min(j0 + nps * x, s.nblkC - 1) * G + hq) * kD + d];
-#pragma unroll
-        for (int x = 0; x < kAccPer; ++x) {
-          const int j = j0 + nps * x;
-          if (j < s.nblkC) {
-            const float wj = __builtin_amdgcn_exp2f(pm[j] - mstar);
-            acc = fmaf(wj, a[x], acc);
-            lsum = fmaf(wj, pl[j], lsum);
-          }
-        }
+        fold_states<kAccPer>(pm, pl, mstar, j0, nps, s.nblkC, a, acc, lsum);
       }
       if (meet) {
         if (need > 0) __syncthreads();  // (need is uniform over the workgroup)
@@ -1376,21 +1401,27 @@ __global__ __launch_bounds__(256) void finalize_kernel(Shape s, Workspace ws, co
           }
         }
       }
-      slice_sm[ps * dims + dl] = acc;
-      if (dl == 0) lsm[ps] = lsum;
+      // waves that hold two shares of 32 dimensions add them up first: then there are eight shares, or four of 128 dimensions
+      if (dims == 32) {  // uniform
+        acc += __shfl_xor(acc, 32);
+        lsum += __shfl_xor(lsum, 32);
+      }
+      const int shares = dims == kD ? NT / kD : NW, share = dims == kD ? ps : w;
+      if (dims > 32 || lane < 32) slice_sm[share * dims + dl] = acc;
+      if (dl == 0) lsm[share] = lsum;
       __syncthreads();
       PQC_MARK(ws, 2, 2);
       if (tid < dims) {
-        float ts[8], ls[8];  // nps <= 8
+        float ts[NW], ls[NW];
 #pragma unroll
-        for (int x = 0; x < 8; ++x) {
-          ts[x] = slice_sm[min(x, nps - 1) * dims + tid];
-          ls[x] = lsm[min(x, nps - 1)];
+        for (int x = 0; x < NW; ++x) {
+          ts[x] = slice_sm[min(x, shares - 1) * dims + tid];
+          ls[x] = lsm[min(x, shares - 1)];
         }
         float tot = ts[0], lstar = ls[0];
 #pragma unroll
-        for (int x = 1; x < 8; ++x)
-          if (x < nps) {
+        for (int x = 1; x < NW; ++x)
+          if (x < shares) {
             tot += ts[x];
             lstar += ls[x];
           }
@@ -1401,7 +1432,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(Shape s, Workspace ws, co
   } else if (sl == 0) {
     // generic path (one workgroup per head does all 128 dimensions): radix select of the need-th largest staged
     // composite, 8 bits per pass
-    const int d128 = tid & (kD - 1), half = tid >> 7;
+    const int d128 = tid & (kD - 1), part = tid / kD;
     {
       int nl, nc;
       scan_counts(cnt0, nl, nc);
@@ -1462,7 +1493,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(Shape s, Workspace ws, co
           prefix |= common & (0xffull << shift);
           continue;
         }
-        rhist[tid] = 0u;
+        if (tid < 256) rhist[tid] = 0u;
         __syncthreads();
         for (int i = tid; i < n_cand; i += NT) {
           const unsigned long long c = cand_at(i);
@@ -1536,11 +1567,15 @@ __global__ __launch_bounds__(256) void finalize_kernel(Shape s, Workspace ws, co
       }
       const float f_own = __builtin_amdgcn_exp2f(m_own - mstar);
       const float lstar = block_sum<NT>(lsum, fsm) + l_own * f_own;
-      acc = half == 0 ? acc * f_own : 0.0f;
-      for (int j = half; j < s.nblkC; j += 2) acc = fmaf(pm[j], pacc[((size_t)j * G + hq) * kD + d128], acc);
-      if (half == 1) half_acc[d128] = acc;
+      acc = part == 0 ? acc * f_own : 0.0f;
+      for (int j = part; j < s.nblkC; j += NT / kD) acc = fmaf(pm[j], pacc[((size_t)j * G + hq) * kD + d128], acc);
+      part_acc[tid] = acc;
       __syncthreads();
-      if (half == 0) out_attn[((size_t)b * s.Hq + (size_t)g * G + hq) * kD + d128] = (acc + half_acc[d128]) / lstar;
+      if (part == 0) {
+#pragma unroll
+        for (int x = 1; x < NT / kD; ++x) acc += part_acc[x * kD + d128];
+        out_attn[((size_t)b * s.Hq + (size_t)g * G + hq) * kD + d128] = acc / lstar;
+      }
     }
   }
   PQC_NOTE(ws, 2, 13, n_above);

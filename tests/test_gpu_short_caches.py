@@ -145,6 +145,16 @@ def test_topk_of_infinite_scores(pqc, low, high):
     np.testing.assert_array_equal(np.sort(idx, -1), np.sort(oracle.select(s32, w.topk, w.n_init, w.n_local), -1))
 
 
+@pytest.mark.parametrize("units, n_tokens, topk", [(64, 32768, 30000), (33, 4100, 4000), (3, 60001, 59000), (70, 600, 500)])
+def test_lists_copied_by_several_waves(pqc, units, n_tokens, topk):
+    # few, long lists per unit: waves share one, beyond what they request up front; and lists of which a wave takes several
+    w = _w(batch=units, n_q_heads=1, n_kv_heads=1, n_tokens=n_tokens, topk=topk, n_local=33)
+    s32 = np.random.default_rng(units).standard_normal((units, 1, n_tokens)).astype(np.float32)
+    print(f"[case] long lists {units} {n_tokens}", flush=True)
+    idx = pqc.PQCache(w, DEV).topk(torch.from_numpy(s32).to(DEV)).cpu().numpy()
+    np.testing.assert_array_equal(np.sort(idx, -1), np.sort(oracle.select(s32, w.topk, w.n_init, w.n_local), -1))
+
+
 def _launches(call):
     """Kernel launches that `call` makes, counted in a recorded graph (which is not run)."""
     from paper_2407_12820_amd import binding
