@@ -1,7 +1,7 @@
 // Kernels of libpqcache (gfx950).  Grid layout: blockIdx.y = unit (sequence b, KV
 // head g); blockIdx.x = workgroup inside the unit (query head for finalize_kernel).
 //
-// Decode path (pqc_decode), three launches, two for short caches (From::kShort), every dependency at a kernel boundary:
+// Decode path (pqc_decode), three launches, two for short caches (From::kCount, From::kShort), every dependency at a kernel boundary:
 //   hist_kernel      table -> scan codes -> histogram of scores over kNB bins, and every
 //                    token's bin number left behind for the next kernel
 //   select_kernel    threshold bin from the histogram -> tokens whose stored bin lies
