@@ -746,7 +746,9 @@ __device__ __forceinline__ void pair_slots(unsigned word, unsigned& s0, unsigned
   s0 = __builtin_amdgcn_udot4(w, 0x00004001u, 0u, false);
   s1 = __builtin_amdgcn_udot4(w, 0x40010000u, 0u, false);
 }
-// One partition's table of two, up to 64 centroids, by one wave: a lane has one entry.  lo, hi: the smallest and the largest one.
+// One partition's table of two, up to 64 centroids, by one wave: a lane has one entry.  lo, hi: the smallest and the largest one; BY_KEY:
+// in the order of score keys, in which an entry that is not a number is an end of the range like an infinite one (else it is left out).
+template <bool BY_KEY>
 __device__ __forceinline__ void pair_table(const float* tile, const float* qs, int C, int j, float* lut, float& lo, float& hi) {
   constexpr int Dm = kD / 2, RS = lut_row_stride(2), kStages = Dm / 16;
   const int lane = threadIdx.x & 63;
@@ -774,7 +776,7 @@ __device__ __forceinline__ void pair_table(const float* tile, const float* qs, i
     if (st + 2 < kStages) read(st + 2);
   }
   if (lane < C) lut[j * kLutRow + lane] = p;
-  if (C == 64) {  // uniform
+  if (!BY_KEY && C == 64) {  // uniform
     lo = key_score(score_key(wave_min(p)));
     hi = key_score(score_key(wave_max(p)));
   } else {
@@ -798,7 +800,8 @@ __device__ __forceinline__ void store_classes(unsigned short* cls, const unsigne
 // The classes of all pairs by exact score keys: 0 below the K-th largest score, 1 at it, 2 above; visible behind a barrier of the
 // caller's.  `count`: middle tokens of this thread's slots; `hist` is zero on entry.
 // The pair scores, weighted by their counts, are counted into uniform bins; the few pairs of the bin that holds the K-th largest
-// are then ranked.  Scores use the same fp32 order as everywhere.
+// are then ranked.  Scores use the same fp32 order as everywhere.  lo and hi bound them in the order of keys: where one is infinite or
+// not a number there is a single bin, and the keys decide.
 template <int NT>
 __device__ __forceinline__ void pair_classes(const Shape& s, const float* lut, float lo, float hi, const unsigned (&count)[kPairPer], PairLds& L,
                                              unsigned* hist, int* scan_sm) {

@@ -602,7 +602,7 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
         if (v < gpw) own_codes.fix(src, u, s.cap, own_token(v), raw[v]);
       if (w < 2) {
         float lo, hi;
-        pair_table(tile, qs, s.C, w, lut, lo, hi);
+        pair_table<PAIRS>(tile, qs, s.C, w, lut, lo, hi);
         if (lane == 0) {
           pl.bounds[2 * w] = lo;
           pl.bounds[2 * w + 1] = hi;

@@ -410,6 +410,28 @@ def test_indexed_decode_zero_query_and_unsupported(pqc):
         pqc.pair_counts(w4, torch.zeros((1, 2, 3000, 4), dtype=torch.uint8, device=DEV))
 
 
+@pytest.mark.parametrize("c", [64, 48])
+@pytest.mark.parametrize("topk, hit", [(300, 40), (300, 900)])  # more and fewer tokens retrieved than carry the centroid
+def test_indexed_decode_of_a_centroid_that_is_not_a_number(pqc, c, topk, hit):
+    # A centroid that overflowed (NaN) gives its tokens a score that is not a number: their keys rank above all others, equal ones by
+    # index, and exactly K tokens are retrieved.  (Keys and values are finite, and so is the attention.)
+    w = _small(pq_m=2, pq_centroids=c, n_tokens=3000, topk=topk)
+    p = build_problem(w, seed=18, checked_units=[])
+    codes, cent = p.codes.copy(), p.centroids.copy()
+    codes[..., 0][codes[..., 0] == 5] = 6
+    codes[:, :, w.n_init + 7:w.n_init + 7 + hit, 0] = 5
+    cent[:, :, 0, 5] = np.nan
+    dev = upload(pqc, dataclasses.replace(p, codes=codes, centroids=cent))
+    idx, out = pqc.PQCache(w, DEV).decode_indexed(dev["q"], dev["centroids"], dev["codes"], pqc.pair_counts(w, dev["codes"]), dev["k"], dev["v"])
+    torch.cuda.synchronize()
+    idx, out = idx.cpu().numpy(), out.cpu().numpy()
+    finite = dataclasses.replace(p, codes=codes)
+    s32, _ = oracle.scores(p.q, w.dtype, p.centroids, codes)
+    s32[codes[..., 0] == 5] = np.inf
+    np.testing.assert_array_equal(np.sort(idx, -1), np.sort(oracle.select(s32, w.topk, w.n_init, w.n_local), -1))
+    assert attn_error(finite, idx, out, units=range(w.n_kv_heads)) <= ATTN_TOL[w.dtype]
+
+
 def test_pair_counts_follow_an_appended_code(pqc):
     w = _small(pq_m=2, pq_centroids=16, n_tokens=1000)
     rng = np.random.default_rng(3)
