@@ -95,6 +95,16 @@ def test_counted_pairs(pqc, kw):
     _decode_and_check(pqc, build_problem(w, seed=5, checked_units=[]))
 
 
+# Code tensors whose bytes are no multiple of 16, or fewer than 16: the last bytes reach the last unit's last tokens on every form.
+@pytest.mark.parametrize("m, c, n_tokens", [(2, 64, 5), (2, 64, 1003), (2, 64, 4099), (2, 200, 1005), (2, 200, 17003), (4, 64, 3), (4, 64, 1001), (4, 64, 1002),
+                                            (4, 64, 12291), (8, 16, 1), (8, 16, 515), (1, 64, 1001), (1, 64, 1014), (1, 64, 13)])
+@pytest.mark.parametrize("heads", [1, 3])
+def test_ragged_end_of_the_codes(pqc, m, c, n_tokens, heads):
+    w = _w(n_tokens=n_tokens, topk=max(1, n_tokens // 3), n_q_heads=heads, n_kv_heads=heads, pq_m=m, pq_centroids=c, n_init=0, n_local=0)
+    print(f"[case] ragged end {w}", flush=True)
+    _decode_and_check(pqc, build_problem(w, seed=9, checked_units=[]))
+
+
 @pytest.mark.parametrize("share", [0.3, 0.6, 1.0])
 def test_counted_pairs_of_repeated_codes(pqc, share):
     # lanes that meet in one address are counted in one go; a fraction of the tokens carries one pair, or all do
