@@ -1063,8 +1063,10 @@ __device__ __forceinline__ void fold_states(const float* pm, const float* pl, fl
 }
 
 // WIDE: four workgroups per head (eight threads per output dimension); they request more candidate records up front.
+// (Four waves per SIMD, so that two workgroups share a compute unit: fp32 would take 129 to 131 registers instead of 128, and then a
+// compute unit holds one.  200 units of 2056 tokens, 2x64, fp32, two query heads: 13.5 us, now 9.1.)
 template <typename T, int G, bool ATTN, bool WIDE = false>
-__global__ __launch_bounds__(kFinalThreads) void finalize_kernel(Shape s, Workspace ws, const T* __restrict__ q,
+__global__ __launch_bounds__(kFinalThreads, ATTN && sizeof(T) == 4 ? 4 : 2) void finalize_kernel(Shape s, Workspace ws, const T* __restrict__ q,
                                                        const T* __restrict__ kc, const T* __restrict__ vc,
                                                        int* __restrict__ out_idx, float* __restrict__ out_attn, AppendArgs ap) {
   constexpr int NT = kFinalThreads, NW = NT / 64;

@@ -1,0 +1,73 @@
+"""Launch shapes of a decode step, read from a recorded graph: which select kernel runs and on how many tokens per workgroup, how many
+workgroups finish a step, and how many of them share a compute unit.  Results do not depend on any of it (the other tests compare
+those); speed does."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2407_12820_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+class _Dim3(ctypes.Structure):
+    _fields_ = [("x", ctypes.c_uint32), ("y", ctypes.c_uint32), ("z", ctypes.c_uint32)]
+
+
+class _NodeParams(ctypes.Structure):  # hipKernelNodeParams
+    _fields_ = [("block", _Dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", _Dim3),
+                ("args", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
+@pytest.fixture(scope="module")
+def pqc():
+    from paper_2407_12820_amd import binding
+    binding.load()
+    return binding
+
+
+def _kernels(pqc, call):
+    """Launches of `call`, in order: (workgroups per unit, units, threads, dynamic LDS, workgroups resident per compute unit)."""
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream(device=DEV)):
+        call()
+    hip, raw = pqc.load(), ctypes.c_void_p(graph.raw_cuda_graph())  # (the library is linked to the HIP runtime)
+    n = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        p, resident = _NodeParams(), ctypes.c_int(0)
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        assert hip.hipOccupancyMaxActiveBlocksPerMultiprocessor(ctypes.byref(resident), ctypes.c_void_p(p.func), ctypes.c_int(p.block.x),
+                                                                ctypes.c_size_t(p.lds)) == 0
+        out.append((p.grid.x, p.grid.y, p.block.x, p.lds, resident.value))
+    return out
+
+
+def _step(pqc, units, group, n_tokens, m, c, den, dtype, indexed):
+    w = wl.Workload(name="launches", batch=units, n_q_heads=group, n_kv_heads=1, head_dim=128, n_tokens=n_tokens, pq_m=m, pq_centroids=c,
+                    topk=n_tokens // den, n_init=4, n_local=64, dtype=dtype, kmeans_iters=1, recipe="plain")
+    print(f"[case] {w} indexed={indexed}", flush=True)
+    kv = torch.bfloat16 if dtype == "bf16" else torch.float32
+    new = lambda shape, t: torch.zeros(shape, dtype=t, device=DEV)
+    k = new((units, 1, n_tokens, 128), kv)
+    q, cent, codes = new((units, group, 128), kv), new((units, 1, m, c, 128 // m), torch.float32), new((units, 1, n_tokens, m), torch.uint8)
+    ctx = pqc.PQCache(w, DEV)
+    outs = ctx.empty_outputs()
+    if indexed:
+        counts = pqc.pair_counts(w, codes)
+        return _kernels(pqc, lambda: ctx.decode_indexed(q, cent, codes, counts, k, k, *outs))
+    return _kernels(pqc, lambda: ctx.decode(q, cent, codes, k, k, *outs))
+
+
+@pytest.mark.parametrize("units, group, n_tokens, m, c", [(64, 4, 2048, 2, 64), (200, 2, 2056, 2, 64), (8, 8, 8000, 1, 64), (40, 1, 20011, 4, 64)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_workgroups_that_finish_a_step_share_a_compute_unit(pqc, units, group, n_tokens, m, c, dtype):
+    assert _step(pqc, units, group, n_tokens, m, c, 10, dtype, False)[-1][4] >= 2
