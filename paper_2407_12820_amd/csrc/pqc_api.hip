@@ -125,6 +125,24 @@ bool short_cache(const Shape& s) {
   return (long long)s.N * s.M <= (s.C > 64 ? 32768 : units < 8 ? 45056 : 49152) && roomy;
 }
 
+// Tokens that share all their codes share a score: with few distinct code words the tie class at the threshold is large (131072 tokens
+// over 64 x 64 code pairs: up to 70 candidates), and the finalize kernel requests more records up front.
+bool large_tie_classes(const Shape& s) {
+  double words = 1.0;
+  for (int j = 0; j < s.M; ++j) words *= s.C;
+  return s.N >= 16.0 * words;
+}
+
+// Workgroups per unit of the finalize kernel that copy the lists, beside `heads` others: fewer where there are many units (64 of 20000,
+// 4x256: four 47.7, two 46.7; 12 of 20011 fp32: two 24.2, four 23.6, six 23.1), and where more than one workgroup per compute unit would
+// come of it (20011 tokens, 4x64, a tenth retrieved: 12 units of 4 heads six 22.7, four 22.3, 24 units of 8 heads four 26.6, two 25.7; with large tie
+// classes there is more to copy, 2x64, 131072 tokens, a fifth retrieved: 8 units of 8 heads two 45.6, four 41.8).
+int copy_workgroups(long long units, int heads, bool large_ties) {
+  int n = units > 32 ? 2 : units > 16 || units < 4 ? 4 : 6;
+  while (n > (large_ties ? 4 : 2) && units * (heads + n) > 256) n -= 2;
+  return n;
+}
+
 // What a launch plan is for: the decode step, the step with given pair counts, or any other call.
 enum class For { kOther, kDecode, kPairs };
 int make_plan(const pqc_config* c, Plan* p, For call = For::kOther) {
@@ -188,11 +206,12 @@ int make_plan(const pqc_config* c, Plan* p, For call = For::kOther) {
   p->rec_stride = (int)cand_unit_bytes(G, c->kv_dtype == PQC_F32 ? 4 : 2);
   // finalize kernel: as many workgroups per query head (each with its share of the output dimensions) as keep the
   // grid within about one workgroup per compute unit (16 units of 8 heads, 4096 tokens, us per layer: two per head, 320 workgroups, 17.8, one
-  // 17.1), and fewer that copy the lists where there are many units (64 of 20000, 4x256: four 47.7, two 46.7; 12 of 20011 fp32: two
-  // 24.2, four 23.6, six 23.1)
-  s.copyWgs = units > 32 ? 2 : units > 16 || units < 4 ? 4 : 6;
+  // 17.1), or two with large tie classes, whose many admitted rows are spread over them (one partition of 256 centroids, 40000 tokens: 24 units of 4
+  // heads 47.3, two 39.4, 14 of 8 heads 45.7, 39.0; 2x64, 131072 tokens: 24 units of 4 heads 60.7, 58.7)
+  const bool ties = large_tie_classes(s);
   s.slices = 1;
-  while (s.slices < kMaxSlices && units * (2 * s.slices * G + 4) <= 256) s.slices *= 2;
+  while (s.slices < kMaxSlices && units * (2 * s.slices * G + 4) <= (ties ? 512 : 256)) s.slices *= 2;
+  s.copyWgs = copy_workgroups(units, s.slices * G, ties);
   // sample ranks that bracket the K-th largest score by 5 standard errors (+2)
   const int nmid = s.N - s.I - s.L;
   s.sampleN = nmid < 1024 ? (nmid > 0 ? nmid : 1) : 1024;
@@ -322,11 +341,7 @@ template <typename T, int G>
 void launch_finalize(pqc_ctx* ctx, const Shape& s, const Workspace& ws, const T* qt, const T* kt, const T* vt, int32_t* out_idx,
                      float* out_attn, hipStream_t st) {
   const dim3 grid(G * s.slices + s.copyWgs + (ctx->append.key ? 1 : 0), (unsigned)(s.B * s.Hkv));
-  // Tokens that share all their codes share a score: with few distinct code words the tie class at the threshold is
-  // large (131072 tokens over 64 x 64 code pairs: up to 70 candidates), and the kernel requests more records up front.
-  double words = 1.0;
-  for (int j = 0; j < s.M; ++j) words *= s.C;
-  if (s.slices == kMaxSlices && s.N >= 16.0 * words)
+  if (s.slices == kMaxSlices && large_tie_classes(s))
     hipLaunchKernelGGL((finalize_kernel<T, G, true, true>), grid, dim3(kFinalThreads), finalize_lds_bytes(s, true), st, s, ws, qt, kt, vt,
                        out_idx, out_attn, ctx->append);
   else
@@ -683,12 +698,13 @@ int pqc_scan(pqc_ctx* ctx, const float* table, const uint8_t* codes, float* scor
 int pqc_topk(pqc_ctx* ctx, const float* scores, int32_t* out_idx, void* stream) {
   if (!ctx || !scores || !out_idx) return PQC_EINVAL;
   if (!aligned16(scores) || !aligned16(out_idx)) return PQC_EINVAL;
-  const Shape& s = ctx->plan.s;
+  Shape s = ctx->plan.s;
   hipStream_t st = static_cast<hipStream_t>(stream);
   int rc = ensure_clean_hist(ctx, st);
   if (rc != PQC_OK) return rc;
   ctx->hist_clean = false;
   const unsigned units = (unsigned)(s.B * s.Hkv);
+  s.copyWgs = copy_workgroups(units, 1, false);
   const float* nof = nullptr;
   hipLaunchKernelGGL(score_range_kernel, dim3(1, units), dim3(1024), 0, st, s, scores, ctx->ws.range);
   launch_hist<float, ScoreChunks>(s, ctx->ws, nof, nof, static_cast<const void*>(scores), 0, st);
