@@ -125,6 +125,17 @@ bool short_cache(const Shape& s) {
   return (long long)s.N * s.M <= (s.C > 64 ? 32768 : units < 8 ? 45056 : 49152) && roomy;
 }
 
+// Tokens per workgroup of the select kernel: twice as many until `resident` workgroups per compute unit hold all of them, or a unit is one
+// workgroup's.  (Without the second condition more than `resident` * 256 units always took the largest, of which one wave then held every token
+// of a short unit: 264 units of 2048 tokens, 2x64, 4 query heads, a tenth retrieved, us per layer, given pair counts 54.3, now 45.7, without
+// 48.3, now 45.4.)
+int select_tokens(const Shape& s, int resident, int most) {
+  const long long units = (long long)s.B * s.Hkv;
+  int tok = 512;
+  while (tok < most && tok < s.N && units * ((s.N + tok - 1) / tok) > 256ll * resident) tok *= 2;
+  return tok;
+}
+
 // Tokens that share all their codes share a score: with few distinct code words the tie class at the threshold is large (131072 tokens
 // over 64 x 64 code pairs: up to 70 candidates), and the finalize kernel requests more records up front.
 bool large_tie_classes(const Shape& s) {
@@ -187,15 +198,11 @@ int make_plan(const pqc_config* c, Plan* p, For call = For::kOther) {
   if (tokA % 1024 || tokA > maxA) return PQC_EINVAL;
   s.tokA = tokA; s.nblkA = (s.N + lead + tokA - 1) / tokA;
   s.histCopies = s.nblkA <= 32 ? 1 : s.nblkA <= 64 ? 2 : kHistCopies;
-  // select kernel: 256-thread workgroups, two resident per compute unit
-  int tokC = env_int("PQC_TOK_C", 0);
+  // select kernel: two workgroups of 256 threads per compute unit, or one of 512 where there is no histogram kernel
   p->short_form = call == For::kDecode && short_cache(s);
   const From form = call == For::kPairs ? From::kPairs : p->short_form ? From::kShort : From::kBins;
-  if (!tokC) {
-    tokC = 512;
-    const int most = form == From::kBins ? 512 : 256;  // one workgroup per compute unit, of twice the size, where there is no histogram kernel
-    while (tokC < max_tokens_per_select(form) && units * ((s.N + tokC - 1) / tokC) > most) tokC *= 2;
-  }
+  int tokC = env_int("PQC_TOK_C", 0);
+  if (!tokC) tokC = select_tokens(s, form == From::kBins ? 2 : 1, max_tokens_per_select(form));
   if (tokC < 512 || tokC > max_tokens_per_select(form) || (tokC & (tokC - 1))) return PQC_EINVAL;
   s.tokC = tokC; s.nblkC = (s.N + tokC - 1) / tokC;
   s.binStride = s.nblkC * s.tokC;

@@ -81,3 +81,13 @@ def test_workgroups_that_finish_a_step_share_a_compute_unit(pqc, units, group, n
 def test_workgroups_that_finish_a_unit(pqc, units, group, n_tokens, m, c, workgroups):
     grid, y, threads, _, _ = _step(pqc, units, group, n_tokens, m, c, 10, "bf16", False)[-1]
     assert (grid, y, threads) == (workgroups, units, 512)
+
+
+def test_tokens_of_a_workgroup_end_with_the_unit(pqc):
+    # more units than workgroups fit at once: a select workgroup's list (two bytes per token, and one entry per thread behind it) is that of the next
+    # power of two, not of the largest workgroup
+    for units, n_tokens, tokens in ((520, 600, 1024), (520, 1024, 1024), (520, 1025, 2048), (8, 600, 512)):
+        grid, _, threads, lds, _ = _step(pqc, units, 1, n_tokens, 8, 16, 10, "bf16", False)[1]
+        assert (grid, threads, lds) == (-(-n_tokens // tokens), 256, 2 * (tokens + 256))
+    lists = [_step(pqc, units, 4, n_tokens, 2, 64, 10, "bf16", False)[0][3] for units, n_tokens in ((264, 600), (264, 2048), (264, 4097))]
+    assert (lists[1] - lists[0], lists[2] - lists[0]) == (2 * 1024, 2 * 7168)
