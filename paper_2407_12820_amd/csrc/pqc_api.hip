@@ -136,6 +136,29 @@ int select_tokens(const Shape& s, int resident, int most) {
   return tok;
 }
 
+// The select kernel of a step with given pair counts.  One workgroup of 512 threads per compute unit and up to 16384 tokens is the
+// quickest while a unit's tokens divide well among the compute units; where they don't (more units than compute units, or a round of
+// workgroups that is nearly empty), two smaller workgroups per compute unit are: of 256 threads (From::kPairsMany), or of 512 where their
+// registers leave room for two (fp32, up to two query heads).  Compared by the tokens that the busiest compute unit goes through and what its
+// workgroups pay for their start, in tokens: 2400 for one, 1600 for each of two.  us per layer, 2x64, a tenth retrieved, bf16, one and two:
+//   8 units of 4096 tokens, 4 query heads 16.1, 17.4; 64 of 16384, one 24.6, 26.5; 100 of 9000, one 30.0, 26.1; 100 of 28000, one 46.7, 49.4;
+//   130 of 20000, two 83.1, 51.6; 256 of 17000, two 94.1, 88.0; 264 of 2048, four 45.7, 38.8; 1024 of 2048, two 99.5, 81.8.
+// fp32, one workgroup of 512 threads, two of them, and two of 256: 100 of 20000, one query head 62.2, 53.4, 55.6; 130 of 28000, two 125.7, 104.9,
+// 122.3; 400 of 9000, two 112.7, 123.3, 132.1; two of 512 and two of 256, 600 of 2048, two query heads 68.9, 75.7.
+struct PairsForm {
+  From from;
+  int tokens;
+};
+PairsForm pairs_form(const Shape& s, bool f32) {
+  const long long units = (long long)s.B * s.Hkv;
+  auto rounds = [&](int tok) { return (units * ((s.N + tok - 1) / tok) + 255) / 256; };
+  const int one = select_tokens(s, 1, max_tokens_per_select(From::kPairs)), two = select_tokens(s, 2, max_tokens_per_select(From::kPairsMany));
+  const long long cost_one = rounds(one) * (std::min(one, s.N) + 2400);
+  const long long cost_two = rounds(two) * std::min(two, s.N) + std::max(rounds(two), 2ll) * 1600;
+  if (cost_one <= cost_two) return {From::kPairs, one};
+  return {f32 && s.G <= 2 ? From::kPairs : From::kPairsMany, two};
+}
+
 // Tokens that share all their codes share a score: with few distinct code words the tie class at the threshold is large (131072 tokens
 // over 64 x 64 code pairs: up to 70 candidates), and the finalize kernel requests more records up front.
 bool large_tie_classes(const Shape& s) {
@@ -200,9 +223,11 @@ int make_plan(const pqc_config* c, Plan* p, For call = For::kOther) {
   s.histCopies = s.nblkA <= 32 ? 1 : s.nblkA <= 64 ? 2 : kHistCopies;
   // select kernel: two workgroups of 256 threads per compute unit, or one of 512 where there is no histogram kernel
   p->short_form = call == For::kDecode && short_cache(s);
-  const From form = call == For::kPairs ? From::kPairs : p->short_form ? From::kShort : From::kBins;
+  const PairsForm pairs = call == For::kPairs ? pairs_form(s, c->kv_dtype == PQC_F32) : PairsForm{From::kBins, 0};
+  const From form = p->short_form ? From::kShort : pairs.from;
+  s.pairsMany = form == From::kPairsMany;
   int tokC = env_int("PQC_TOK_C", 0);
-  if (!tokC) tokC = select_tokens(s, form == From::kBins ? 2 : 1, max_tokens_per_select(form));
+  if (!tokC) tokC = call == For::kPairs ? pairs.tokens : select_tokens(s, p->short_form ? 1 : 2, max_tokens_per_select(form));
   if (tokC < 512 || tokC > max_tokens_per_select(form) || (tokC & (tokC - 1))) return PQC_EINVAL;
   s.tokC = tokC; s.nblkC = (s.N + tokC - 1) / tokC;
   s.binStride = s.nblkC * s.tokC;

@@ -36,6 +36,7 @@ struct Shape {
   int rowsP, nblkP; // list-attention kernel: rows per workgroup, workgroups per unit
   int npart;        // partial slots per unit
   int slices;       // finalize kernel: workgroups per query head (1, 2 or 4), each producing kD/slices output dimensions
+  bool pairsMany;   // step with given pair counts: in two workgroups of 256 threads per compute unit (From::kPairsMany)
   int copyWgs;      // finalize kernel: workgroups per unit that copy the index lists
   int binStride;    // stored bins per unit (nblkC * tokC)
   int stageStride;  // 8-byte words between the staging slots of consecutive select workgroups: tokC plus a pad, so that
@@ -726,14 +727,16 @@ struct ThresholdSearch {
 // ------------------------------------------------- threshold from code-pair counts
 // With M = 2 and C <= 64 a token's score takes one of C*C values, one per pair of codes: given how many middle tokens carry each
 // pair, the threshold follows from the table without a pass over the tokens, and a token is classified by one look-up.  A pair has
-// the slot c0 + 64 * c1 whatever C is, and a thread of 512 the eight slots 8 * thread + i: they share c1, and have one 16-byte
-// piece of every array of 16-bit entries to themselves.
+// the slot c0 + 64 * c1 whatever C is, and a thread of NT the kPairPer<NT> slots from kPairPer<NT> * thread on: they share c1, and have
+// whole 16-byte pieces of every array to themselves.
 constexpr int kPairSlots = 4096;
 constexpr int kPairC = 64;        // largest C
-constexpr int kPairPer = 8;       // slots per thread
+template <int NT>
+constexpr int kPairPer = kPairSlots / NT;  // slots per thread: eight or sixteen
 constexpr int kPairList = 256;    // pairs resolved by direct ranking; more fall back to a radix search
 struct PairLds {
-  unsigned cnt[kPairSlots];                  // tokens per pair: the middle tokens, or the window tokens that the given counts hold besides
+  unsigned cnt[kPairSlots + 128];            // tokens per pair: the middle tokens, or the window tokens that the given counts hold besides
+                                             // (kPairsMany: afterwards the list of up to 8192 tokens, and 256 places behind it)
   unsigned short cls[kPairSlots];            // what a token of the pair is, in stored form
   unsigned long long lst[kPairList];         // (key << 32) | count of the pairs in the threshold bin
   int res[4];
@@ -786,15 +789,22 @@ __device__ __forceinline__ void pair_table(const float* tile, const float* qs, i
   }
 }
 // The scores of this thread's slots (entries of centroids that do not exist hold anything).
-__device__ __forceinline__ void pair_scores(const float* lut, float (&sc)[kPairPer]) {
-  const int c0 = (threadIdx.x & 7) * 8, c1 = threadIdx.x >> 3;
-  const f32x4_t a = *reinterpret_cast<const f32x4_t*>(&lut[c0]), b = *reinterpret_cast<const f32x4_t*>(&lut[c0 + 4]);
+template <int PER>
+__device__ __forceinline__ void pair_scores(const float* lut, float (&sc)[PER]) {
+  const int c0 = (int)(threadIdx.x * PER) & 63, c1 = (int)(threadIdx.x * PER) >> 6;
+  f32x4_t a[PER / 4];
+#pragma unroll
+  for (int i = 0; i < PER / 4; ++i) a[i] = *reinterpret_cast<const f32x4_t*>(&lut[c0 + 4 * i]);
   const float y = lut[kLutRow + c1];
 #pragma unroll
-  for (int i = 0; i < kPairPer; ++i) sc[i] = __fadd_rn(i < 4 ? a[i & 3] : b[i & 3], y);
+  for (int i = 0; i < PER; ++i) sc[i] = __fadd_rn(a[i / 4][i % 4], y);
 }
-__device__ __forceinline__ void store_classes(unsigned short* cls, const unsigned (&v)[kPairPer]) {
-  *reinterpret_cast<uint4*>(&cls[threadIdx.x * kPairPer]) = make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
+template <int PER>
+__device__ __forceinline__ void store_classes(unsigned short* cls, const unsigned (&v)[PER]) {
+#pragma unroll
+  for (int i = 0; i < PER; i += 8)
+    *reinterpret_cast<uint4*>(&cls[threadIdx.x * PER + i]) =
+        make_uint4(v[i] | (v[i + 1] << 16), v[i + 2] | (v[i + 3] << 16), v[i + 4] | (v[i + 5] << 16), v[i + 6] | (v[i + 7] << 16));
 }
 
 // The classes of all pairs by exact score keys: 0 below the K-th largest score, 1 at it, 2 above; visible behind a barrier of the
@@ -803,19 +813,20 @@ __device__ __forceinline__ void store_classes(unsigned short* cls, const unsigne
 // are then ranked.  Scores use the same fp32 order as everywhere.  lo and hi bound them in the order of keys: where one is infinite or
 // not a number there is a single bin, and the keys decide.
 template <int NT>
-__device__ __forceinline__ void pair_classes(const Shape& s, const float* lut, float lo, float hi, const unsigned (&count)[kPairPer], PairLds& L,
+__device__ __forceinline__ void pair_classes(const Shape& s, const float* lut, float lo, float hi, const unsigned (&count)[kPairPer<NT>], PairLds& L,
                                              unsigned* hist, int* scan_sm) {
-  static_assert(NT * kPairPer == kPairSlots, "one thread per eight slots");
+  constexpr int PER = kPairPer<NT>;
+  static_assert(PER == 8 || PER == 16, "512 or 256 threads");
   const int tid = threadIdx.x;
   const float width = hi - lo;
   const float inv = (width > 1e-30f && width < 3e38f) ? (float)kNB / width : 0.0f;
-  float sc[kPairPer];
-  unsigned key[kPairPer];
-  int bin[kPairPer];
+  float sc[PER];
+  unsigned key[PER];
+  int bin[PER];
   pair_scores(lut, sc);
   if (tid == 0) L.res[0] = L.res[1] = 0;
 #pragma unroll
-  for (int i = 0; i < kPairPer; ++i) {
+  for (int i = 0; i < PER; ++i) {
     key[i] = score_key(sc[i]);
     bin[i] = max(0, min(kNB - 1, __float2int_rz((sc[i] - lo) * inv)));
     if (count[i]) atomicAdd(&hist[bin[i]], count[i]);
@@ -827,7 +838,7 @@ __device__ __forceinline__ void pair_classes(const Shape& s, const float* lut, f
   unsigned kth = 0u;
   if (th.bstar < kNB) {  // uniform
 #pragma unroll
-    for (int i = 0; i < kPairPer; ++i)
+    for (int i = 0; i < PER; ++i)
       if (count[i] && bin[i] == th.bstar) {
         const int slot = atomicAdd(&L.res[0], 1);
         if (slot < kPairList) L.lst[slot] = ((unsigned long long)key[i] << 32) | count[i];
@@ -873,7 +884,7 @@ __device__ __forceinline__ void pair_classes(const Shape& s, const float* lut, f
         if (tid < 256) hist[tid] = 0u;  // digits
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < kPairPer; ++i)
+        for (int i = 0; i < PER; ++i)
           if (count[i] && bin[i] == th.bstar && (shift == 24 || (key[i] >> (shift + 8)) == (kth >> (shift + 8))))
             atomicAdd(&hist[(key[i] >> shift) & 255u], count[i]);
         __syncthreads();
@@ -896,9 +907,9 @@ __device__ __forceinline__ void pair_classes(const Shape& s, const float* lut, f
   }
   // No score has the lowest key, so that the K-th largest's is at least 1; nothing lies above the highest.
   const unsigned base = th.bstar < kNB ? max(kth, 1u) - 1u : 0xffffffffu;
-  unsigned c[kPairPer];
+  unsigned c[PER];
 #pragma unroll
-  for (int i = 0; i < kPairPer; ++i) c[i] = min(__builtin_elementwise_sub_sat(key[i], base), 2u);
+  for (int i = 0; i < PER; ++i) c[i] = min(__builtin_elementwise_sub_sat(key[i], base), 2u);
   store_classes(L.cls, c);
 }
 

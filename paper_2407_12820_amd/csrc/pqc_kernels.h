@@ -306,17 +306,18 @@ __global__ __launch_bounds__(1024) void hist_kernel(Shape s, Workspace ws, const
 // Where the threshold comes from.  kBins: from the histogram kernel in front.  The other forms have no histogram kernel: every workgroup
 // builds the table itself and finds the threshold without the others.
 //   kPairs  (M = 2, up to 64 centroids) from code-pair counts of the caller's (pair_classes); tokens above it are those with a higher
-//           exact score, its own are the candidates.
+//           exact score, its own are the candidates.  kPairsMany: the same in workgroups of 256 threads, two of them per compute unit (the
+//           list lies over the counts, so that both fit its LDS), for grids that one workgroup per compute unit leaves uneven.
 //   kCount  (M = 2, up to 64 centroids) from code-pair counts that the workgroup takes of all tokens of its unit while the table is built:
 //           the pairs' scores go to the bins that the histogram kernel would have put the tokens into.
 //   kShort  (M = 2 or 4) scores all tokens of its unit.
 // In the last two the launch of the histogram kernel, its table and what it leaves in memory are saved, against work in each workgroup that
-// grows with the unit: one LDS addition per token (kCount), or M look-ups and a bin (kShort); see short_cache().  A workgroup of 512
+// grows with the unit: one LDS addition per token (kCount), or M look-ups and a bin (kShort); see short_cache(), and pairs_form().  A workgroup of 512
 // threads per compute unit (the table and the waves' tiles share its LDS) keeps as many rows in flight as two of 256, and does
 // what does not depend on its own tokens once instead of twice.
-enum class From { kBins, kPairs, kCount, kShort };
+enum class From { kBins, kPairs, kPairsMany, kCount, kShort };
 template <From FROM>
-constexpr int select_threads() { return FROM == From::kBins ? 256 : 512; }
+constexpr int select_threads() { return FROM == From::kBins || FROM == From::kPairsMany ? 256 : 512; }
 constexpr int kShortChunks = 4;  // 16-byte code chunks per thread and step, the next step's in flight
 // kCount: while two waves build the table the other six count, kCountEarly chunks per thread (about as long as the table takes), requested
 // in front of the wait for the centroids; then all count the rest, kCountChunks per thread under way (together 33792 tokens).
@@ -336,8 +337,8 @@ constexpr int states_bytes(int G) { return select_threads<FROM>() / 64 * G * (kD
 // own tokens' bins (kShort).
 template <From FROM>
 constexpr size_t table_form_lds_bytes(const Shape& s, bool mfma) {
-  const size_t tile = (size_t)lut_tile_floats(select_threads<FROM>(), s.M, s.C) * sizeof(float);
-  const size_t work = tiles_bytes<FROM>(mfma) + states_bytes<FROM>(s.G) + list_bytes<FROM>(s.tokC) + (FROM == From::kShort ? (size_t)s.tokC * 2 : 0);
+  const size_t tile = (size_t)lut_tile_floats(512 /* the whole table */, s.M, s.C) * sizeof(float);
+  const size_t work = tiles_bytes<FROM>(mfma) + states_bytes<FROM>(s.G) + (FROM == From::kPairsMany ? 0 : list_bytes<FROM>(s.tokC)) + (FROM == From::kShort ? (size_t)s.tokC * 2 : 0);
   return tile > work ? tile : work;
 }
 
@@ -502,7 +503,7 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
                                                      const float* __restrict__ cent = nullptr,
                                                      const unsigned* __restrict__ pair_counts = nullptr,
                                                      int uncounted = -1 /* kPairs: a window token not in the counts yet */) {
-  constexpr bool PAIRS = FROM == From::kPairs, COUNT = FROM == From::kCount, SHORT = FROM == From::kShort;
+  constexpr bool PAIRS = FROM == From::kPairs || FROM == From::kPairsMany, COUNT = FROM == From::kCount, SHORT = FROM == From::kShort;
   constexpr bool TABLE = FROM != From::kBins;
   constexpr int NT = select_threads<FROM>(), NW = NT / 64;
   constexpr bool kMfma = ATTN && sizeof(T) == 2 && kMatrixCoreAttention;
@@ -512,8 +513,12 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
   constexpr int GV = max_tokens_per_select(FROM) / (8 * NT);  // 8-token groups per lane, at most
   extern __shared__ __attribute__((aligned(16))) unsigned char select_lds[];
   constexpr int kList = TABLE ? tiles_bytes<FROM>(kMfma) + states_bytes<FROM>(G) : 0;
-  unsigned short* list = reinterpret_cast<unsigned short*>(select_lds + kList);  // [tokC] token offsets from the workgroup's first token, [NT] see below
   __shared__ std::conditional_t<PAIRS || COUNT, PairLds, int> pl;
+  unsigned short* list = reinterpret_cast<unsigned short*>(select_lds + kList);  // [tokC] token offsets from the workgroup's first token, [NT] see below
+  if constexpr (FROM == From::kPairsMany) {
+    static_assert(sizeof(pl.cnt) >= list_bytes<FROM>(max_tokens_per_select(FROM)), "the list lies over the counts");
+    list = reinterpret_cast<unsigned short*>(pl.cnt);
+  }
   __shared__ int scan_sm[2 * NW + 1 + 4];
   __shared__ int wcnt[NW];
   __shared__ float red_own[ATTN && !TABLE ? states_bytes<FROM>(G) / 4 : 1];
@@ -552,7 +557,8 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
     [[maybe_unused]] u32x4_t early[kCountEarly];
     constexpr int PS = 1024 / NT, QN = (G * kD + NT - 1) / NT;
     typename SRC::One sample[PS];
-    u32x4_t given[kPairPer / 4];  // kPairs: the counts of this thread's slots
+    constexpr int PER = kPairPer<NT>;
+    u32x4_t given[PER / 4];  // kPairs: the counts of this thread's slots
     unsigned short wcode = 0;  // kPairs: this thread's first window token (the usual case: I + L <= NT)
     [[maybe_unused]] const std::conditional_t<PAIRS || COUNT, OwnCodes, Absent> own_codes(src, u, s.cap);
     auto own_token = [&](int v) -> int { return min(wave_t0 + min((v * 64 + lane) * 8, tpw - 8), s.N - 1); };
@@ -564,21 +570,22 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
       PQC_LOADS_ISSUED();
       if constexpr (PAIRS || COUNT) {
 #pragma unroll
-        for (int i = 0; i < kPairPer / 4; ++i) reinterpret_cast<uint4*>(pl.cnt)[i * NT + tid] = make_uint4(0u, 0u, 0u, 0u);
+        for (int i = 0; i < PER / 4; ++i) reinterpret_cast<uint4*>(pl.cnt)[i * NT + tid] = make_uint4(0u, 0u, 0u, 0u);
         if (tid < kSampleBins / 4) reinterpret_cast<uint4*>(pl.samples)[tid] = make_uint4(0u, 0u, 0u, 0u);
       }
-      reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+      for (int i = 0; i < kNB / (4 * NT); ++i) reinterpret_cast<uint4*>(hist)[i * NT + tid] = make_uint4(0u, 0u, 0u, 0u);
     };
     auto issue_loads = [&]() {
       if constexpr (PAIRS) {
         const unsigned* pc = pair_counts + (size_t)u * s.C * s.C;
-        const int c0 = (tid & 7) * 8, c1 = tid >> 3;
+        const int c0 = (tid * PER) & 63, c1 = (tid * PER) >> 6;
         if (s.C == kPairC) {  // uniform
-          given[0] = reinterpret_cast<const u32x4_t*>(pc)[2 * tid];
-          given[1] = reinterpret_cast<const u32x4_t*>(pc)[2 * tid + 1];
+#pragma unroll
+          for (int i = 0; i < PER / 4; ++i) given[i] = reinterpret_cast<const u32x4_t*>(pc)[PER / 4 * tid + i];
         } else {
 #pragma unroll
-          for (int i = 0; i < kPairPer; ++i) given[i / 4][i % 4] = pc[min(c1, s.C - 1) * s.C + min(c0 + i, s.C - 1)];
+          for (int i = 0; i < PER; ++i) given[i / 4][i % 4] = pc[min(c1, s.C - 1) * s.C + min(c0 + i, s.C - 1)];
         }
         const int wt = min(max(tid - 128, 0), max(s.I + s.L - 1, 0)), t = wt < s.I ? wt : s.N - s.L + (wt - s.I);
         wcode = src.load_one(min(max(t, 0), s.N - 1), u, s.cap);
@@ -602,7 +609,7 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
           if (v < gpw) raw[v] = own_codes.load(own_token(v));  // uniform
       }
     };
-    static_assert(kNB == 4 * NT, "one 16-byte piece per thread");
+    static_assert(kNB % (4 * NT) == 0 && (FROM != From::kShort || kNB == 4 * NT), "whole 16-byte pieces per thread; one in kShort");
     const T* qu = q + ((size_t)b * s.Hq + (size_t)g * G) * kD;
     const float* cu = cent + (size_t)u * LM * s.C * (kD / LM);
     float* tile = reinterpret_cast<float*>(select_lds);
@@ -658,12 +665,16 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
         __syncthreads();
       }
       PQC_MARK(ws, 1, 9);
-      const uint4 x = reinterpret_cast<const uint4*>(pl.cnt)[2 * tid], y = reinterpret_cast<const uint4*>(pl.cnt)[2 * tid + 1];
-      unsigned count[kPairPer] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-      if constexpr (PAIRS) {
-        const int c0 = (tid & 7) * 8, c1 = tid >> 3;
+      unsigned count[PER];
 #pragma unroll
-        for (int i = 0; i < kPairPer; ++i) count[i] = c1 < s.C && c0 + i < s.C ? given[i / 4][i % 4] - count[i] : 0u;
+      for (int i = 0; i < PER; i += 4) {
+        const uint4 x = *reinterpret_cast<const uint4*>(&pl.cnt[tid * PER + i]);
+        count[i] = x.x; count[i + 1] = x.y; count[i + 2] = x.z; count[i + 3] = x.w;
+      }
+      if constexpr (PAIRS) {
+        const int c0 = (tid * PER) & 63, c1 = (tid * PER) >> 6;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) count[i] = c1 < s.C && c0 + i < s.C ? given[i / 4][i % 4] - count[i] : 0u;
         pair_classes<NT>(s, lut, lo, hi, count, pl, hist, scan_sm);
         th.bstar = 1;
         __syncthreads();
@@ -671,14 +682,14 @@ __global__ __launch_bounds__(select_threads<FROM>(), 2) void select_kernel(Shape
         int b_hi, b_lo;  // (every wave walks the samples by itself)
         walk_samples<false>(pl.samples, s.rankHi, s.rankLo, b_hi, b_lo);
         const BinMap map = window_bins(lo, hi, b_hi, b_lo);
-        float sc[kPairPer];
-        unsigned bin[kPairPer];
+        float sc[PER];
+        unsigned bin[PER];
         pair_scores(lut, sc);
 #pragma unroll
-        for (int i = 0; i < kPairPer; ++i) bin[i] = score_bin(sc[i], map);
+        for (int i = 0; i < PER; ++i) bin[i] = score_bin(sc[i], map);
         store_classes(pl.cls, bin);
 #pragma unroll
-        for (int i = 0; i < kPairPer; ++i)
+        for (int i = 0; i < PER; ++i)
           if (bin[i] && count[i]) atomicAdd(&hist[bin[i]], count[i]);
       }
     } else {

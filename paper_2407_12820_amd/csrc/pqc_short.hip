@@ -26,7 +26,9 @@ void launch(const Args& a) {
 
 template <typename T, int G>
 void launch_form(const Args& a) {
-  if (a.pair_counts)
+  if (a.pair_counts && a.s.pairsMany)
+    launch<T, G, 2, From::kPairsMany, 8>(a);
+  else if (a.pair_counts)
     launch<T, G, 2, From::kPairs, 4>(a);
   else if (counts_pairs(a.s))
     launch<T, G, 2, From::kCount, 4>(a);

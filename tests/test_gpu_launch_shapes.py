@@ -91,3 +91,12 @@ def test_tokens_of_a_workgroup_end_with_the_unit(pqc):
         assert (grid, threads, lds) == (-(-n_tokens // tokens), 256, 2 * (tokens + 256))
     lists = [_step(pqc, units, 4, n_tokens, 2, 64, 10, "bf16", False)[0][3] for units, n_tokens in ((264, 600), (264, 2048), (264, 4097))]
     assert (lists[1] - lists[0], lists[2] - lists[0]) == (2 * 1024, 2 * 7168)
+
+
+@pytest.mark.parametrize("units, group, n_tokens, dtype, grid, threads, resident", [
+    (8, 4, 4096, "bf16", 8, 512, 1), (64, 1, 16384, "bf16", 4, 512, 1), (100, 1, 16384, "bf16", 2, 512, 1), (256, 2, 2048, "bf16", 1, 512, 1),
+    (264, 4, 2048, "bf16", 1, 256, 2), (264, 8, 8192, "bf16", 1, 256, 2), (130, 2, 20000, "bf16", 3, 256, 2), (100, 1, 9000, "bf16", 5, 256, 2),
+    (8, 2, 4096, "f32", 8, 512, 2), (100, 1, 20000, "f32", 5, 512, 2), (600, 2, 600, "f32", 1, 512, 2), (300, 4, 2048, "f32", 1, 256, 2)])
+def test_select_kernel_of_a_step_with_given_pair_counts(pqc, units, group, n_tokens, dtype, grid, threads, resident):
+    x, y, t, _, r = _step(pqc, units, group, n_tokens, 2, 64, 10, dtype, True)[0]
+    assert (x, y, t) == (grid, units, threads) and r >= resident

@@ -368,6 +368,11 @@ def test_decode_phase_by_phase_equals_decode(pqc, n_tokens):
     dict(n_tokens=2048, n_local=300, n_init=9, topk=100),            # more window tokens than threads
     dict(n_tokens=2048, n_local=700, n_init=9, topk=100, pq_centroids=63),
     dict(n_tokens=8200, topk=500, batch=65, n_q_heads=4, n_kv_heads=4, kmeans_iters=1),  # 16384 tokens per workgroup
+    # two workgroups of 256 threads per compute unit: more window tokens than threads, G = 8, fp32, two workgroups per unit
+    dict(n_tokens=2048, topk=200, batch=66, n_q_heads=4, n_kv_heads=4, pq_centroids=64, n_local=300, kmeans_iters=1),
+    dict(n_tokens=600, topk=100, batch=65, n_q_heads=32, n_kv_heads=4, pq_centroids=63, kmeans_iters=1),
+    dict(n_tokens=520, topk=77, batch=65, n_q_heads=16, n_kv_heads=4, dtype="f32", pq_centroids=64, kmeans_iters=1),
+    dict(n_tokens=16392, topk=500, batch=33, n_q_heads=4, n_kv_heads=4, kmeans_iters=1),
 ], ids=lambda kw: ",".join(f"{k}={v}" for k, v in kw.items()) or "scaled")
 def test_indexed_decode_equals_decode(pqc, kw):
     # threshold from code-pair counts: same selection and attention as the general path, and as the oracle
