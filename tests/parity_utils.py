@@ -12,6 +12,7 @@ Comparison rules (per unit = (sequence, KV head)):
 """
 from __future__ import annotations
 
+import ctypes
 import dataclasses
 from typing import Dict, Optional, Sequence
 
@@ -135,3 +136,20 @@ def attn_error(p: Problem, idx_gpu: np.ndarray, out_gpu: np.ndarray, units: Opti
         err = np.abs(got - ref).max(axis=1) / np.maximum(np.abs(ref).max(axis=1), 1e-30)
         worst = max(worst, float(err.max()))
     return worst
+
+
+def count_launches(call) -> int:
+    """Kernel launches that `call` makes, counted in a recorded graph (which is not run)."""
+    import torch
+
+    from paper_2407_12820_amd import binding
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream(device="cuda:0")):
+        call()
+    n = ctypes.c_size_t(0)
+    get = binding.load().hipGraphGetNodes  # of the HIP runtime that the library is linked to
+    get.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
+    assert get(graph.raw_cuda_graph(), None, ctypes.byref(n)) == 0
+    return n.value

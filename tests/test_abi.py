@@ -141,6 +141,18 @@ def test_workspace_for_a_capacity_covers_every_length():
                 assert need_cap == (need if n == cap else bound)
 
 
+@pytest.mark.parametrize("heads, kv_dtype", [(132, "bf16"), (264, "bf16"), (264, "f32"), (600, "f32"), (1000, "bf16")])
+def test_workspace_of_many_units_covers_every_length(heads, kv_dtype):
+    # the same with more units than compute units, where the step with given pair counts changes its kernel with the length
+    lib = binding.load()
+    cap = 24000
+    w = dataclasses.replace(wl.get("llama8b_128k"), n_q_heads=heads, n_kv_heads=heads, n_tokens=200, topk=8, dtype=kv_dtype)
+    bound = lib.pqc_workspace_bytes(C.byref(binding.make_config(w, capacity=cap)))
+    for n in sorted({200, 511, 512, 513, 600, 1024, 1025, 4096, 4097, 8191, 8192, 8200, 12288, 16384, 16392, 16400, 20000, cap}):
+        need = lib.pqc_workspace_bytes(C.byref(binding.make_config(dataclasses.replace(w, n_tokens=n, topk=n // 10))))
+        assert 0 < need <= bound, (heads, n, need, bound)
+
+
 def test_set_length_checks():
     lib = binding.load()
     w = wl.get("llama8b_32k")

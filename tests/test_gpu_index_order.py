@@ -109,7 +109,8 @@ def test_scores_at_the_edges_of_bins(pqc, n_tokens, topk):
 @pytest.mark.parametrize("kw", [dict(n_tokens=60001, topk=6000, n_kv_heads=16), dict(n_tokens=12289, topk=1200, pq_centroids=64, n_kv_heads=16),
                                 dict(n_tokens=7001, topk=1400, pq_centroids=64, n_kv_heads=32), dict(n_tokens=30001, topk=3000, pq_m=2, n_kv_heads=8),
                                 dict(n_tokens=9003, topk=900, pq_m=2, pq_centroids=48, n_kv_heads=8), dict(n_tokens=30001, topk=6000, pq_m=2, pq_centroids=64, n_kv_heads=8),
-                                dict(n_tokens=11003, topk=1100, pq_m=2, pq_centroids=48, n_kv_heads=8), dict(n_tokens=20002, topk=2000, pq_m=8)],
+                                dict(n_tokens=11003, topk=1100, pq_m=2, pq_centroids=48, n_kv_heads=8), dict(n_tokens=20002, topk=2000, pq_m=8),
+                                dict(n_tokens=60001, topk=6000, pq_m=2, pq_centroids=64, n_kv_heads=8)],
                          ids=lambda kw: ",".join(f"{k}={v}" for k, v in kw.items()))
 def test_decode(pqc, kw):
     w = _w(n_q_heads=kw.get("n_kv_heads", 2), **kw)

@@ -13,7 +13,7 @@ import torch
 import oracle
 from paper_2407_12820_amd import workloads as wl
 
-from parity_utils import ATTN_TOL, attn_error, build_problem, check_indices, check_structure, unit_slice
+from parity_utils import ATTN_TOL, attn_error, build_problem, check_indices, check_structure, count_launches, unit_slice
 
 pytestmark = pytest.mark.gpu
 
@@ -174,7 +174,7 @@ def _small(**kw):
     # many units: more than the 256 compute units, a multiple of 8 and not (the last ones are not interleaved over the XCDs)
     dict(batch=40, n_q_heads=16, n_kv_heads=8, n_tokens=600, topk=60),
     dict(batch=37, n_q_heads=6, n_kv_heads=3, n_tokens=777, topk=99, pq_m=4),
-    # with a histogram kernel whatever the number of partitions: windows only, every token, no windows, big tie classes
+    # two partitions, pairs counted, and four with a histogram kernel: windows only, every token, no windows, big tie classes
     dict(n_tokens=16401, topk=0),
     dict(n_tokens=16402, topk=16402 - 68, pq_centroids=64),
     dict(n_tokens=16403, n_init=0, n_local=0, topk=17),
@@ -192,6 +192,33 @@ def test_edge_shapes(pqc, kw):
     p = build_problem(w, seed=3)
     idx, out = run_decode(pqc, p)
     full_check(p, idx, out)
+
+
+def _launches_of(ctx, dev):
+    outs = ctx.empty_outputs()
+    return count_launches(lambda: ctx.decode(dev["q"], dev["centroids"], dev["codes"], dev["k"], dev["v"], *outs))
+
+
+@pytest.mark.parametrize("kw", [
+    dict(n_tokens=49201, topk=0),
+    dict(n_tokens=49202, topk=49202 - 68, pq_centroids=64),
+    dict(n_tokens=49203, n_init=0, n_local=0, topk=17),
+    dict(n_tokens=49300, n_init=500, n_local=9000, topk=100, pq_centroids=3),
+    dict(n_tokens=49210, topk=5000, dtype="f32", n_q_heads=8, n_kv_heads=1, pq_centroids=64),
+    dict(n_tokens=53250, topk=5000, batch=3, n_q_heads=24, n_kv_heads=3, pq_centroids=64),  # nine units, misaligned
+], ids=lambda kw: ",".join(f"{k}={v}" for k, v in kw.items()))
+def test_two_partitions_with_a_histogram_kernel(pqc, kw):
+    w = _small(**{**dict(pq_m=2, pq_centroids=16, kmeans_iters=1), **kw})
+    print(f"[case] two partitions, histogram {kw}", flush=True)
+    p = build_problem(w, seed=3, checked_units=[])
+    dev, ctx = upload(pqc, p), pqc.PQCache(w, DEV)
+    assert _launches_of(ctx, dev) == 3
+    idx, out = run_decode(pqc, p, ctx, dev)
+    every = range(w.batch * w.n_kv_heads)
+    assert check_indices(p, idx, units=every) == 0
+    err = attn_error(p, idx, out, units=every)
+    assert err <= ATTN_TOL[w.dtype], f"attention error {err:.3e}"
+    check_structure(p, idx, out)
 
 
 @pytest.mark.timeout(600)
@@ -238,11 +265,27 @@ def test_random_shapes(pqc, kw):
 
 @pytest.mark.parametrize("kw", _random_shapes(16, seed=2025, tokens=(16385, 26000)), ids=lambda kw: "-".join(str(v) for v in kw.values()))
 def test_random_shapes_with_a_histogram_kernel(pqc, kw):
-    # the same where two and four partitions have a histogram kernel too; codes need no clustering here
+    # the same where four partitions, and two of more than 64 centroids, have a histogram kernel too; codes need no clustering here
     w = _small(**kw)
     print(f"[case] random shape {kw}", flush=True)
     p = build_problem(w, seed=22, checked_units=[])
     idx, out = run_decode(pqc, p)
+    every = range(w.batch * w.n_kv_heads)
+    assert check_indices(p, idx, units=every) == 0
+    err = attn_error(p, idx, out, units=every)
+    assert err <= ATTN_TOL[w.dtype], f"attention error {err:.3e}"
+    check_structure(p, idx, out)
+
+
+@pytest.mark.parametrize("kw", [kw for kw in _random_shapes(60, seed=2026, tokens=(49153, 56000)) if kw["pq_m"] == 2 and kw["pq_centroids"] <= 64],
+                         ids=lambda kw: "-".join(str(v) for v in kw.values()))
+def test_random_shapes_of_two_partitions_with_a_histogram_kernel(pqc, kw):
+    w = _small(**kw)
+    print(f"[case] random shape {kw}", flush=True)
+    p = build_problem(w, seed=22, checked_units=[])
+    dev, ctx = upload(pqc, p), pqc.PQCache(w, DEV)
+    assert _launches_of(ctx, dev) == 3
+    idx, out = run_decode(pqc, p, ctx, dev)
     every = range(w.batch * w.n_kv_heads)
     assert check_indices(p, idx, units=every) == 0
     err = attn_error(p, idx, out, units=every)
@@ -310,12 +353,14 @@ def test_topk_when_the_sample_misleads(pqc, sample_value):
     np.testing.assert_array_equal(np.sort(got.cpu().numpy(), -1), np.sort(want, -1))
 
 
-@pytest.mark.parametrize("na,nb", [(3000, 5000), (17001, 12001), (17001, 5000)])  # without, with, and one each with a histogram kernel
+@pytest.mark.parametrize("na,nb", [(3000, 5000), (17001, 12001), (17001, 5000), (50001, 12001), (50001, 5000)])
 def test_context_reuse_and_two_contexts(pqc, na, nb):
-    # Calls on one context leave the workspace ready for the next call; contexts do not interfere.
+    # Calls on one context leave the workspace ready for the next call; contexts do not interfere.  With and without a histogram kernel
+    # on either side.
     wa, wb = _small(n_tokens=na, topk=123), _small(n_tokens=nb, topk=900, pq_m=4)
     pa1, pa2, pb = build_problem(wa, 5), build_problem(wa, 6), build_problem(wb, 7)
     ca, cb = pqc.PQCache(wa, DEV), pqc.PQCache(wb, DEV)
+    assert _launches_of(ca, upload(pqc, pa1)) == (3 if na > 49152 else 2) and _launches_of(cb, upload(pqc, pb)) == (3 if nb > 11264 else 2)
     for _ in range(2):
         for p, c in ((pa1, ca), (pb, cb), (pa2, ca), (pa1, ca)):
             idx, out = run_decode(pqc, p, ctx=c)
@@ -328,12 +373,13 @@ def test_context_reuse_and_two_contexts(pqc, na, nb):
     full_check(pa2, idx, out)
 
 
-@pytest.mark.parametrize("n_tokens", [9000, 13001])  # phase 0 has nothing to launch, and leaves a histogram behind
-def test_decode_phase_by_phase_equals_decode(pqc, n_tokens):
-    # the profiling entry point launches the same kernels one at a time
-    w = _small(n_tokens=n_tokens, topk=1200, pq_m=4)
+@pytest.mark.parametrize("n_tokens, m", [pytest.param(9000, 4, id="9000"), pytest.param(13001, 4, id="13001"), (9000, 2), (50001, 2)])
+def test_decode_phase_by_phase_equals_decode(pqc, n_tokens, m):
+    # the profiling entry point launches the same kernels one at a time; phase 0 has nothing to launch, or leaves a histogram behind
+    w = _small(n_tokens=n_tokens, topk=1200, pq_m=m)
     p = build_problem(w, seed=9)
     dev, ctx = upload(pqc, p), pqc.PQCache(w, DEV)
+    assert _launches_of(ctx, dev) == (2 if n_tokens == 9000 else 3)
     a = run_decode(pqc, p, ctx, dev)
     idx, out = ctx.empty_outputs()
     for _ in range(2):  # twice: a complete pass leaves the workspace ready for the next
@@ -451,22 +497,24 @@ def test_pair_counts_follow_an_appended_code(pqc):
     np.testing.assert_array_equal(full.cpu().numpy(), part.cpu().numpy())
 
 
-@pytest.mark.parametrize("n_tokens", [20011, 24011])  # without and with a histogram kernel
+@pytest.mark.parametrize("n_tokens", [20011, 24011, 53251])  # without, and (the last one) with a histogram kernel
 def test_decode_is_deterministic(pqc, n_tokens):
     w = wl.get("llama8b_128k", n_tokens=n_tokens)
-    p = build_problem(w, seed=1)
+    p = build_problem(w, seed=1, checked_units=None if n_tokens < 50000 else [])
     dev, ctx = upload(pqc, p), pqc.PQCache(w, DEV)
+    assert _launches_of(ctx, dev) == (3 if n_tokens > 53248 else 2)
     a = run_decode(pqc, p, ctx, dev)
     b = run_decode(pqc, p, ctx, dev)
     np.testing.assert_array_equal(a[0], b[0])
     np.testing.assert_array_equal(a[1].view(np.uint32), b[1].view(np.uint32))
 
 
-@pytest.mark.parametrize("n_tokens", [3000, 17001])  # without and with a histogram kernel
+@pytest.mark.parametrize("n_tokens", [3000, 17001, 50001])  # without, and (the last one) with a histogram kernel
 def test_runs_on_a_side_stream(pqc, n_tokens):
     w = _small(n_tokens=n_tokens, topk=200)
     p = build_problem(w, seed=8)
     dev, ctx = upload(pqc, p), pqc.PQCache(w, DEV)
+    assert _launches_of(ctx, dev) == (3 if n_tokens > 49152 else 2)
     torch.cuda.synchronize()
     st = torch.cuda.Stream(device=DEV)
     idx, out = ctx.decode(dev["q"], dev["centroids"], dev["codes"], dev["k"], dev["v"], stream=st)
@@ -474,7 +522,7 @@ def test_runs_on_a_side_stream(pqc, n_tokens):
     full_check(p, idx.cpu().numpy(), out.cpu().numpy())
 
 
-@pytest.mark.parametrize("n_tokens", [9000, 17000])  # without and with a histogram kernel in the general step
+@pytest.mark.parametrize("n_tokens", [9000, 17000, 50000])  # without, and (the last one) with a histogram kernel in the general step
 @pytest.mark.parametrize("indexed", [False, True])
 def test_layers_recorded_into_a_hip_graph_replay_correctly(pqc, indexed, n_tokens):
     # Algorithm 2 loops over the layers: one call per layer on a shared context, recorded once by stream
@@ -499,6 +547,7 @@ def test_layers_recorded_into_a_hip_graph_replay_correctly(pqc, indexed, n_token
         eager.append((oi.cpu().numpy().copy(), oa.cpu().numpy().copy()))
         bufs.append(ctx.empty_outputs())
     torch.cuda.synchronize()
+    assert count_launches(lambda: call(devs[0], pcs[0], *bufs[0])) == (3 if n_tokens > 49152 and not indexed else 2)
     graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream(device=DEV)
     with torch.cuda.graph(graph, stream=side):
         for d, pc, (oi, oa) in zip(devs, pcs, bufs):

@@ -11,7 +11,7 @@ import torch
 import oracle
 from paper_2407_12820_amd import workloads as wl
 
-from parity_utils import ATTN_TOL, attn_error, build_problem, check_indices, check_structure
+from parity_utils import ATTN_TOL, attn_error, build_problem, check_indices, check_structure, count_launches
 
 pytestmark = pytest.mark.gpu
 
@@ -74,12 +74,12 @@ def test_short_caches(pqc, kw):
 
 
 # Steps that count the code pairs of their unit (two partitions of up to 64 centroids): units at every alignment of the codes, middle tokens
-# beside whole chunks of eight, none of these, more chunks than are under way at a time (1152 and 3072).
+# beside whole chunks of eight, none of these.
 @pytest.mark.parametrize("kw", [
     dict(n_tokens=10241, topk=1000, n_init=3, n_local=5, batch=2),
     dict(n_tokens=10247, topk=1000, n_q_heads=5, n_kv_heads=5, pq_centroids=48, n_init=0, n_local=0),
-    dict(n_tokens=9285, topk=900, n_q_heads=2, n_kv_heads=1, pq_centroids=33),            # a chunk beyond those counted beside the table
-    dict(n_tokens=33861, topk=3000, n_q_heads=2, n_kv_heads=1, pq_centroids=17),          # a chunk beyond those under way
+    dict(n_tokens=9285, topk=900, n_q_heads=2, n_kv_heads=1, pq_centroids=33),
+    dict(n_tokens=33861, topk=3000, n_q_heads=2, n_kv_heads=1, pq_centroids=17),
     dict(n_tokens=49152, topk=9000, n_q_heads=8, n_kv_heads=1),                           # the last length of a few units; G = 8
     dict(n_tokens=77, topk=2, n_init=30, n_local=40, batch=3),
     dict(n_tokens=20011, topk=2000, n_q_heads=4, dtype="f32", batch=2),
@@ -92,6 +92,16 @@ def test_short_caches(pqc, kw):
 def test_counted_pairs(pqc, kw):
     w = _w(**kw)
     print(f"[case] counted pairs {w}", flush=True)
+    _decode_and_check(pqc, build_problem(w, seed=5, checked_units=[]))
+
+
+# Whole chunks of middle tokens at both sides of what is counted beside the table (1152), and of that and one turn of what is under way
+# afterwards (3072 more).
+@pytest.mark.parametrize("n_tokens, chunks", [(9293, 1152), (9301, 1153), (33869, 4224), (33877, 4225)])
+def test_counted_pairs_at_the_hand_overs(pqc, n_tokens, chunks):
+    w = _w(n_tokens=n_tokens, topk=n_tokens // 10, n_q_heads=2, n_kv_heads=1, pq_centroids=33)
+    assert (n_tokens - w.n_local) // 8 - -(-w.n_init // 8) == chunks  # (one unit: its chunks start at token 0)
+    print(f"[case] hand-over {w}", flush=True)
     _decode_and_check(pqc, build_problem(w, seed=5, checked_units=[]))
 
 
@@ -165,28 +175,16 @@ def test_lists_copied_by_several_waves(pqc, units, n_tokens, topk):
     np.testing.assert_array_equal(np.sort(idx, -1), np.sort(oracle.select(s32, w.topk, w.n_init, w.n_local), -1))
 
 
-def _launches(call):
-    """Kernel launches that `call` makes, counted in a recorded graph (which is not run)."""
-    from paper_2407_12820_amd import binding
-    call()
-    torch.cuda.synchronize()
-    graph = torch.cuda.CUDAGraph(keep_graph=True)
-    with torch.cuda.graph(graph, stream=torch.cuda.Stream(device=DEV)):
-        call()
-    n = ctypes.c_size_t(0)
-    get = binding.load().hipGraphGetNodes  # of the HIP runtime that the library is linked to
-    get.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
-    assert get(graph.raw_cuda_graph(), None, ctypes.byref(n)) == 0
-    return n.value
-
-
 @pytest.mark.parametrize("units, n_tokens, m, c, den, launches", [
     (1, 2048, 2, 64, 10, 2), (7, 49152, 2, 64, 10, 2), (7, 49153, 2, 64, 10, 3), (8, 49153, 2, 48, 10, 2), (15, 53249, 2, 48, 10, 3),
     (16, 57344, 2, 64, 10, 2), (31, 57345, 2, 64, 10, 3), (32, 65536, 2, 64, 5, 2), (32, 65537, 2, 64, 10, 3), (1, 11264, 4, 64, 10, 2),
     (1, 11265, 4, 64, 10, 3), (8, 12288, 4, 64, 10, 2), (8, 12289, 4, 64, 10, 3), (1, 8192, 4, 256, 10, 2), (1, 8193, 4, 256, 10, 3),
     (1, 16384, 2, 65, 10, 2), (1, 16385, 2, 256, 10, 3), (8, 2048, 8, 64, 10, 3), (8, 2048, 1, 64, 10, 3), (96, 20000, 2, 64, 20, 3),
     (80, 20000, 2, 64, 10, 2), (80, 20000, 2, 64, 5, 2), (128, 12288, 2, 64, 5, 3), (128, 16384, 2, 64, 5, 2),
-    (207, 8192, 2, 64, 5, 2), (208, 8192, 2, 64, 5, 3), (208, 8192, 2, 64, 7, 2), (256, 8191, 2, 64, 5, 2)])
+    (207, 8192, 2, 64, 5, 2), (208, 8192, 2, 64, 5, 3), (208, 8192, 2, 64, 7, 2), (256, 8191, 2, 64, 5, 2),
+    # lengths around which steps that score every token (not its code pair) give way to the histogram kernel
+    (1, 16384, 2, 64, 10, 2), (1, 16385, 2, 64, 10, 2), (7, 16385, 2, 48, 10, 2), (8, 16385, 2, 64, 10, 2), (1, 24576, 2, 64, 10, 2),
+    (8, 22528, 2, 64, 10, 2), (8, 22529, 2, 64, 10, 2)])
 def test_launches_of_a_step(pqc, units, n_tokens, m, c, den, launches):
     w = _w(batch=units, n_q_heads=1, n_kv_heads=1, n_tokens=n_tokens, pq_m=m, pq_centroids=c, topk=n_tokens // den)
     print(f"[case] launches {w}", flush=True)
@@ -196,7 +194,7 @@ def test_launches_of_a_step(pqc, units, n_tokens, m, c, den, launches):
     args = [new((units, 1, 128), kv), new((units, 1, m, c, 128 // m), torch.float32), new((units, 1, n_tokens, m), torch.uint8), k, k]
     ctx = pqc.PQCache(w, DEV)
     outs = ctx.empty_outputs()
-    assert _launches(lambda: ctx.decode(*args, *outs)) == launches
+    assert count_launches(lambda: ctx.decode(*args, *outs)) == launches
 
 
 # A workspace that holds the plan of every other call but not that of the step without a histogram kernel: the step takes the
@@ -231,7 +229,7 @@ def test_smallest_workspace(pqc, kw):
         def call():
             assert lib.pqc_decode(h, *[t.data_ptr() for t in dev], idx.data_ptr(), out.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
 
-        launches.append(_launches(call))
+        launches.append(count_launches(call))
         call()
         torch.cuda.synchronize()
         lib.pqc_destroy(h)
