@@ -168,13 +168,15 @@ bool large_tie_classes(const Shape& s) {
 }
 
 // Workgroups per unit of the finalize kernel that copy the lists, beside `heads` others: fewer where there are many units (64 of 20000,
-// 4x256: four 47.7, two 46.7; 12 of 20011 fp32: two 24.2, four 23.6, six 23.1), and where more than one workgroup per compute unit would
-// come of it (20011 tokens, 4x64, a tenth retrieved: 12 units of 4 heads six 22.7, four 22.3, 24 units of 8 heads four 26.6, two 25.7; with large tie
-// classes there is more to copy, 2x64, 131072 tokens, a fifth retrieved: 8 units of 8 heads two 45.6, four 41.8).
+// 4x256: four 47.7, two 46.7; 12 of 20011 fp32: two 24.2, four 23.6, six 23.1), and where fewer keep the grid within one workgroup per compute
+// unit (20011 tokens, 4x64, a tenth retrieved: 12 units of 4 heads six 22.7, four 22.3, 24 units of 8 heads four 26.6, two 25.7; a grid that is
+// beyond it either way takes four, 32 units of 8 heads, 4x256, 131072 tokens: two 76.6, four 75.7; and with large tie classes there is more to copy,
+// 2x64, 131072 tokens, a fifth retrieved: 8 units of 8 heads two 45.6, four 41.8).
 int copy_workgroups(long long units, int heads, bool large_ties) {
-  int n = units > 32 ? 2 : units > 16 || units < 4 ? 4 : 6;
-  while (n > (large_ties ? 4 : 2) && units * (heads + n) > 256) n -= 2;
-  return n;
+  const int n = units > 32 ? 2 : units > 16 || units < 4 ? 4 : 6;
+  auto fits = [&](int m) { return units * (heads + m) <= 256; };
+  if (n == 2 || fits(n)) return n;
+  return !fits(4) && fits(2) && !large_ties ? 2 : 4;
 }
 
 // What a launch plan is for: the decode step, the step with given pair counts, or any other call.

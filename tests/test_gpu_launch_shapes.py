@@ -75,7 +75,7 @@ def test_workgroups_that_finish_a_step_share_a_compute_unit(pqc, units, group, n
 
 @pytest.mark.parametrize("units, group, n_tokens, m, c, workgroups", [
     (8, 4, 32768, 2, 64, 16 + 6), (12, 4, 20011, 4, 64, 16 + 4), (7, 8, 4096, 4, 64, 32 + 4), (24, 8, 20011, 4, 64, 8 + 2), (16, 8, 4096, 2, 64, 8 + 6),
-    (64, 1, 20000, 4, 256, 1 + 2), (2, 1, 3000, 2, 64, 4 + 4),
+    (64, 1, 20000, 4, 256, 1 + 2), (2, 1, 3000, 2, 64, 4 + 4), (32, 8, 4096, 4, 256, 8 + 4),
     # large tie classes: four workgroups per head up to two per compute unit
     (24, 4, 40000, 1, 256, 16 + 4), (14, 8, 8000, 1, 64, 32 + 4), (8, 8, 131072, 2, 64, 32 + 4), (64, 1, 8000, 1, 64, 4 + 2)])
 def test_workgroups_that_finish_a_unit(pqc, units, group, n_tokens, m, c, workgroups):
