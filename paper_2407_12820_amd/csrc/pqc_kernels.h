@@ -76,6 +76,8 @@ struct CodeChunks {
     __builtin_memcpy(&r, total_bytes < 16 ? spare : all + off, 16);
     return r;
   }
+  // Whether the last of a unit's chunks is that one (uniform).
+  __device__ __forceinline__ bool ragged(int chunks) const { return unit_byte0 + 16ll * chunks > total_bytes; }
   __device__ __forceinline__ void fix_tail(Raw& r, int chunk) const {
     const long long off = unit_byte0 + 16ll * chunk;
     if (off + 16 > total_bytes && off < total_bytes) {  // at most one chunk in the whole tensor
@@ -126,7 +128,6 @@ struct ScoreChunks {
     }
     return r;
   }
-  __device__ __forceinline__ void fix_tail(Raw&, int) const {}
   __device__ __forceinline__ float score(const Raw& r, int i) const { return r.f[i]; }
   using One = float;
   __device__ __forceinline__ One load_one(int t, int, int) const { return scores[t]; }
@@ -237,10 +238,16 @@ __global__ __launch_bounds__(1024) void hist_kernel(Shape s, Workspace ws, const
     __syncthreads();
   }
   PQC_MARK(ws, 0, 1);
-#pragma unroll
-  for (int v = 0; v < VA; ++v) src.fix_tail(raw[v], chunk0 + min(v * NT + tid, chunks - 1));
   const float sample_score[1] = {src.score_one(sample)};
   const BinMap map = sample_window<NT, 1>(bounds.x, bounds.y, sample_score, s.sampleN, s.rankHi, s.rankLo, hist, scan_sm);
+  if constexpr (SRC::kFromCodes) {
+    const int all = (s.N + src.lead + P - 1) / P;  // chunks of the unit
+    if (src.ragged(all) && chunk0 + chunks >= all) {  // uniform (behind the window: in front of it every step takes 0.2 us longer)
+#pragma unroll
+      for (int v = 0; v < VA; ++v)
+        if (chunk0 + v * NT + tid == all - 1) src.fix_tail(raw[v], all - 1);
+    }
+  }
   PQC_MARK(ws, 0, 2);
   // most tokens score below the window and are not counted, the rest go to their LDS bin (an LDS atomic costs in proportion
   // to the lanes that take part)
@@ -469,12 +476,17 @@ __device__ __forceinline__ void bin_scores(const SRC& src, typename SRC::Raw (&c
                                            const BinMap& map, unsigned* hist /* [kNB + 64] */) {
   constexpr int P = SRC::P;
   const int tid = threadIdx.x, lane = tid & 63;
+  const bool ragged = src.ragged(chunks);
   for (int c0 = 0; c0 < chunks; c0 += U * NT) {
+    if (ragged && c0 + U * NT >= chunks) {  // uniform, and apart from the loop below, whose code is kept short
+#pragma unroll
+      for (int v = 0; v < U; ++v)
+        if (c0 + v * NT + tid == chunks - 1) src.fix_tail(code[v], chunks - 1);
+    }
 #pragma unroll
     for (int v = 0; v < U; ++v) {
       const int c = c0 + v * NT + tid;
       if (c < chunks) {
-        src.fix_tail(code[v], c);
         const int t0 = c * P - src.lead;
         unsigned st[P], hb[P];
 #pragma unroll
