@@ -304,18 +304,23 @@ __host__ __device__ constexpr int lut_row_stride(int M) { return M <= 2 ? kD / M
 __host__ __device__ constexpr int lut_tile_floats(int nt, int M, int C) {
   return nt >= 512 ? M * C * lut_row_stride(M) : kLutTileFloats + kLutTileFloats / (kD / M);
 }
-// The group's query heads: all loads first (clamped, straight-line), then the sum in head order.
-template <typename T, class IssueFn>
-__device__ __forceinline__ void sum_query(const T* __restrict__ q, int G, float* qs, IssueFn issue_more) {
+// The group's query heads: all loads first (clamped, straight-line), the caller's `issue_first` behind them, then the sum in head order.
+template <typename T, class FirstFn, class IssueFn>
+__device__ __forceinline__ void sum_query(const T* __restrict__ q, int G, float* qs, FirstFn issue_first, IssueFn issue_more) {
   const int dq = threadIdx.x & (kD - 1);
-  float qv[8];
+  T qr[8];  // (as they are in memory: a conversion here would be waited for in front of the loads that follow)
 #pragma unroll
-  for (int h = 0; h < 8; ++h) qv[h] = load_as_float<T>(q, min(h, G - 1) * kD + dq);
+  for (int h = 0; h < 8; ++h) qr[h] = q[min(h, G - 1) * kD + dq];
+  PQC_LOADS_ISSUED();
+  issue_first();
   // Loads return in issue order: whatever the caller streams from HBM goes behind the table's
   // (mostly L2-resident) centroids, so that the table is built while that stream arrives.
   PQC_LOADS_ISSUED();
   issue_more();
   PQC_LOADS_ISSUED();
+  float qv[8];
+#pragma unroll
+  for (int h = 0; h < 8; ++h) qv[h] = load_as_float<T>(&qr[h], 0);
   float a = qv[0];
 #pragma unroll
   for (int h = 1; h < 8; ++h) {
@@ -340,9 +345,17 @@ __device__ __forceinline__ void lut_stage(const T* __restrict__ q /* [G][kD] of 
   // the place of the store, which puts every load behind the waits in front of it, one round trip after the other)
   const f32x4_t* centv = reinterpret_cast<const f32x4_t*>(cent);
   f32x4_t vw[VWP];
+  auto load_centroids = [&]() {
 #pragma unroll
-  for (int x = 0; x < VWP; ++x) vw[x] = centv[min(x * NT + tid, total / 4 - 1)];
-  sum_query<T>(q, G, qs, issue_early);
+    for (int x = 0; x < VWP; ++x) vw[x] = centv[min(x * NT + tid, total / 4 - 1)];
+  };
+  // With 512 threads the query goes in front of the centroids, many per thread: behind them its sum waits for nearly all of them, and
+  // left alone the compiler takes either order (8 units of 1000 tokens, two query heads, us per layer: 4x256 17.7 and 17.4, 2x256 17.4, 17.1; the
+  // histogram kernel's 1024 threads have few: 1 of 106444, 4x64, 23.2 behind them, 23.4 in front).
+  if constexpr (NT >= 1024) load_centroids();
+  sum_query<T>(q, G, qs, [&]() {
+    if constexpr (NT < 1024) load_centroids();
+  }, issue_early);
   mark(8);
 #pragma unroll
   for (int x = 0; x < VWP; ++x) {
@@ -449,7 +462,7 @@ __device__ __forceinline__ float2 build_lut(const T* __restrict__ q, const float
     }
     mark(9);
   } else {
-    sum_query<T>(q, G, qs, issue_more);
+    sum_query<T>(q, G, qs, []() {}, issue_more);
     mark(8);
     float4 v[VPG];
 #pragma unroll
