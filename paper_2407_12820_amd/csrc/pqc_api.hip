@@ -161,10 +161,10 @@ PairsForm pairs_form(const Shape& s, bool f32) {
 
 // Tokens that share all their codes share a score: with few distinct code words the tie class at the threshold is large (131072 tokens
 // over 64 x 64 code pairs: up to 70 candidates), and the finalize kernel requests more records up front.
-bool large_tie_classes(const Shape& s) {
+bool large_tie_classes(const Shape& s, double tokens_per_word = 16.0) {
   double words = 1.0;
   for (int j = 0; j < s.M; ++j) words *= s.C;
-  return s.N >= 16.0 * words;
+  return s.N >= tokens_per_word * words;
 }
 
 // Workgroups per unit of the finalize kernel that copy the lists, beside `heads` others: fewer where there are many units (64 of 20000,
@@ -241,8 +241,10 @@ int make_plan(const pqc_config* c, Plan* p, For call = For::kOther) {
   // finalize kernel: as many workgroups per query head (each with its share of the output dimensions) as keep the
   // grid within about one workgroup per compute unit (16 units of 8 heads, 4096 tokens, us per layer: two per head, 320 workgroups, 17.8, one
   // 17.1), or two with large tie classes, whose many admitted rows are spread over them (one partition of 256 centroids, 40000 tokens: 24 units of 4
-  // heads 47.3, two 39.4, 14 of 8 heads 45.7, 39.0; 2x64, 131072 tokens: 24 units of 4 heads 60.7, 58.7)
-  const bool ties = large_tie_classes(s);
+  // heads 47.3, two 39.4, 14 of 8 heads 45.7, 39.0; 2x64, 131072 tokens: 24 units of 4 heads 60.7, 58.7).  With given pair counts only one pair's
+  // tokens are candidates, not those of all pairs in a bin (24 units of 4 heads: 2x16, 20000 tokens 29.7, 27.4, fp32; 8 units of 8 heads, 2x64, 72000
+  // tokens 51.0, 52.9).
+  const bool ties = large_tie_classes(s, call == For::kPairs ? 64.0 : 16.0);
   s.slices = 1;
   while (s.slices < kMaxSlices && units * (2 * s.slices * G + 4) <= (ties ? 512 : 256)) s.slices *= 2;
   s.copyWgs = copy_workgroups(units, s.slices * G, ties);
