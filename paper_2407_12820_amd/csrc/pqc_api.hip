@@ -170,7 +170,7 @@ bool large_tie_classes(const Shape& s, double tokens_per_word = 16.0) {
 // Workgroups per unit of the finalize kernel that copy the lists, beside `heads` others: fewer where there are many units (64 of 20000,
 // 4x256: four 47.7, two 46.7; 12 of 20011 fp32: two 24.2, four 23.6, six 23.1), and where fewer keep the grid within one workgroup per compute
 // unit (20011 tokens, 4x64, a tenth retrieved: 12 units of 4 heads six 22.7, four 22.3, 24 units of 8 heads four 26.6, two 25.7; a grid that is
-// beyond it either way takes four, 32 units of 8 heads, 4x256, 131072 tokens: two 76.6, four 75.7; and with large tie classes there is more to copy,
+// beyond it either way takes four, 32 units of 8 heads, 4x256, 131072 tokens: two 76.7, four 75.7; and with large tie classes there is more to copy,
 // 2x64, 131072 tokens, a fifth retrieved: 8 units of 8 heads two 45.6, four 41.8).
 int copy_workgroups(long long units, int heads, bool large_ties) {
   const int n = units > 32 ? 2 : units > 16 || units < 4 ? 4 : 6;
@@ -308,8 +308,8 @@ struct pqc_ctx {
   Plan decode_plan;    // of the decode step: `plan`, or its short form
   Plan pairs_plan;     // of the step with given pair counts
   Workspace ws;        // views of `plan`
-  Workspace decode_ws; // views of `decode_plan` and of `pairs_plan`; histograms and record counters lie in the same place
-  Workspace pairs_ws;
+  Workspace decode_ws; // views of `decode_plan`; histograms and record counters lie in the same place in all three
+  Workspace pairs_ws;  // views of `pairs_plan`
   AppendArgs append;       // set for the duration of a pqc_decode_append call
   char* workspace;         // the caller's device memory
   size_t workspace_bytes;

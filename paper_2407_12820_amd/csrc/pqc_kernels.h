@@ -8,7 +8,7 @@
 //                    above it (and the two windows) are listed in ascending order
 //                    without atomics and attended at once; tokens inside the bin
 //                    ("candidates") are recorded with their logits and V row
-//   finalize_kernel  one workgroup per query head ranks the candidates and folds the
+//   finalize_kernel  one to four workgroups per query head rank the candidates and fold the
 //                    admitted ones and all partial softmax states into the output;
 //                    copy workgroups beside them write the indices and zero the unit's
 //                    histogram and record counter again, which nothing reads after the
@@ -316,7 +316,8 @@ __global__ __launch_bounds__(1024) void hist_kernel(Shape s, Workspace ws, const
 //           exact score, its own are the candidates.  kPairsMany: the same in workgroups of 256 threads, two of them per compute unit (the
 //           list lies over the counts, so that both fit its LDS), for grids that one workgroup per compute unit leaves uneven.
 //   kCount  (M = 2, up to 64 centroids) from code-pair counts that the workgroup takes of all tokens of its unit while the table is built:
-//           the pairs' scores go to the bins that the histogram kernel would have put the tokens into.
+//           the pairs' scores go to the bins that the histogram kernel would have put the tokens into, and the tokens of the threshold's
+//           bin are the candidates, whichever of its pairs they carry.
 //   kShort  (M = 2 or 4) scores all tokens of its unit.
 // In the last two the launch of the histogram kernel, its table and what it leaves in memory are saved, against work in each workgroup that
 // grows with the unit: one LDS addition per token (kCount), or M look-ups and a bin (kShort); see short_cache(), and pairs_form().  A workgroup of 512
@@ -1042,7 +1043,7 @@ constexpr int kHdrPerThread = kCandRec / kFinalThreads;  // candidate record hea
 constexpr int kAccPer = 4;                     // partial states a thread keeps in flight at once
 constexpr int kVPer = 6;                       // candidate records per thread whose V values are requested before the ranking knows which are admitted (96 records
                                                // with sixteen threads per dimension: tie classes of two-partition tables reach 70 tokens at 128K)
-constexpr int kVPerFew = 4;                    // the same with fewer threads per dimension (many units; there the tie classes are small)
+constexpr int kVPerFew = 4;                    // the same without large tie classes, or with fewer threads per dimension (many units)
 constexpr int kManyCand = 4096;                // candidates whose composites the path for large tie classes keeps in LDS
 constexpr int kRankStep = 8;                    // composites read per step of the ranking loop
 constexpr int kFoldRanks = 96;                 // admitted rows whose terms meet in LDS by rank (beyond: fetched by rank from the records)
@@ -1085,7 +1086,7 @@ __device__ __forceinline__ void fold_states(const float* pm, const float* pl, fl
   }
 }
 
-// WIDE: four workgroups per head (eight threads per output dimension); they request more candidate records up front.
+// WIDE: four workgroups per head (sixteen threads per output dimension) and large tie classes; they request more candidate records up front.
 // (Four waves per SIMD, so that two workgroups share a compute unit: fp32 would take 129 to 131 registers instead of 128, and then a
 // compute unit holds one.  200 units of 2056 tokens, 2x64, fp32, two query heads: 13.5 us, now 9.1.)
 template <typename T, int G, bool ATTN, bool WIDE = false>

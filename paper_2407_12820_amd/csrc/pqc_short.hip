@@ -1,4 +1,4 @@
-// The select kernels that have no histogram kernel in front (From::kCount, kShort and kPairs), instantiated in a file of their own: it
+// The select kernels that have no histogram kernel in front (From::kCount, kShort, kPairs and kPairsMany), instantiated in a file of their own: it
 // compiles beside pqc_api.hip.
 #include "pqc_kernels.h"
 
